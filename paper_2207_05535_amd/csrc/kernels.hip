@@ -153,12 +153,10 @@ constexpr int VB = 6;   // counts up to 63 per lane
 // The site index t (the same on every lane) decides which carries pair up;
 // every block takes exactly the 16 sites t = 0 .. 15 in order (zero inputs
 // for missing ones).
-constexpr int LUT_MAJ3 = lut3((LUT_A & LUT_B) | (LUT_A & LUT_C) | (LUT_B & LUT_C));
-
 __device__ __forceinline__ void csa(uint64_t &carry, uint64_t &sum, uint64_t a, uint64_t b, uint64_t c)
 {
     const uint64_t s = bop3<LUT_XOR3>(a, b, c);
-    carry = bop3<LUT_MAJ3>(a, b, c);
+    carry = bop3<LUT_MAJ>(a, b, c);
     sum = s;
 }
 
@@ -991,8 +989,8 @@ __device__ __forceinline__ void sweep_int8_tile(const RunInfo &R, const PopState
         const int ru = halo ? rc - 1 : (rc == 0 ? L - 1 : rc - 1);
         const uint64_t w = packed[rc * L + x];
         const uint8_t jn = jbits[n];
-        fm[idx] = flip_mask(w, packed[rc * L + xr], packed[rc * L + xl], packed[rd * L + x], packed[ru * L + x],
-                            jmask(jn, 0), jmask(jbits[y * L + xl], 0), jmask(jn, 1), jmask(jbits[yu * L + x], 1),
+        fm[idx] = flip_mask(w, packed[rc * L + xr] ^ jmask(jn, 0), packed[rc * L + xl] ^ jmask(jbits[y * L + xl], 0),
+                            packed[rd * L + x] ^ jmask(jn, 1), packed[ru * L + x] ^ jmask(jbits[yu * L + x], 1),
                             Th, valid, (uint32_t)n, (uint32_t)g, (uint32_t)i, c3, key0, key1, ncalls);
         ++nwords;
     }
@@ -1095,27 +1093,27 @@ __device__ __forceinline__ int wrap_once(int x, int m)
     return (int)min((uint32_t)x, (uint32_t)x - (uint32_t)m);
 }
 
-// A list entry's undecided lanes of the two classes (dE = +4, dE = +8), kept
+// A list entry's undecided replicas and their class (set: dE = +4), kept
 // side by side so that one LDS address serves both.  Reads are one 16-byte
 // access (ds_read_b128).  Writes go out as two 8-byte halves of one
 // instruction (ds_write2_b64): with 16-byte writes the wavefronts waited
 // longer for LDS issue and the sweep was slower.
 struct alignas(16) UndPair {
-    uint64_t u4, u8;
+    uint64_t und, one;
 };
 
-__device__ __forceinline__ void und_load(const UndPair *p, uint64_t &u4, uint64_t &u8)
+__device__ __forceinline__ void und_load(const UndPair *p, uint64_t &und, uint64_t &one)
 {
     const UndPair v = *p;
-    u4 = v.u4;
-    u8 = v.u8;
+    und = v.und;
+    one = v.one;
 }
 
-__device__ __forceinline__ void und_store(UndPair *p, uint64_t u4, uint64_t u8)
+__device__ __forceinline__ void und_store(UndPair *p, uint64_t und, uint64_t one)
 {
     uint64_t *w = (uint64_t *)(void *)p;   // 8-byte alignment: two 8-byte halves
-    w[0] = u4;
-    w[1] = u8;
+    w[0] = und;
+    w[1] = one;
 }
 
 // Sparse rounds of one wavefront over its own compacted list of `cnt`
@@ -1130,43 +1128,51 @@ __device__ __forceinline__ void sweep_sparse_wave(uint64_t *lat, UndPair *eu, ui
     const int lane = threadIdx.x & 63;
     for (int c = c_first; c < 16 && cnt > 0; ++c) {
         if (cnt <= 64) {
-            uint64_t und4 = 0, und8 = 0, acc = 0;
+            uint64_t und = 0, one = 0, acc = 0;
             int addr = 0;
             uint32_t n = 0, g = 0;
             if (lane < cnt) {
-                und_load(&eu[lane], und4, und8);
+                und_load(&eu[lane], und, one);
                 const uint32_t pk = en[lane];
                 addr = (int)(pk >> 16);
                 n = pk & 0xFFFFu;
                 g = (uint32_t)(group0 + addr / N);
             }
+            const uint64_t drew = und;
             for (; c < 16; ++c) {
-                const uint64_t live = wave_ballot((und4 | und8) != 0);
+                const uint64_t live = wave_ballot(und != 0);
                 if (live == 0) break;
                 wcalls += (uint32_t)__popcll(live);
-                if ((und4 | und8) != 0) draw_call((uint32_t)c, Th.t4, Th.t8, und4, und8, acc, n, g, i, c3, key0, key1);
+                if (und != 0) {
+                    const uint64_t was = und;
+                    const uint64_t less = draw_call((uint32_t)c, call_masks(Th.t4, Th.t8, (uint32_t)c), one, und, n, g,
+                                                    i, c3, key0, key1);
+                    acc = bop3<LUT_SEL>(was, less, acc);
+                }
             }
-            flip_word(&lat[addr], acc);
+            flip_word(&lat[addr], bop3<LUT_ANDN2>(acc, drew, und));
             return;
         }
         int wcnt = 0;
         for (int e0 = 0; e0 < cnt; e0 += 64) {
             const int e = e0 + lane;
-            uint64_t und4 = 0, und8 = 0, acc = 0;
+            uint64_t und = 0, one = 0;
             uint32_t pk = 0;
             wcalls += (uint32_t)min(64, cnt - e0);
             if (e < cnt) {
-                und_load(&eu[e], und4, und8);
+                und_load(&eu[e], und, one);
                 pk = en[e];
                 const int addr = (int)(pk >> 16);
                 const uint32_t g = (uint32_t)(group0 + addr / N);
-                draw_call((uint32_t)c, Th.t4, Th.t8, und4, und8, acc, pk & 0xFFFFu, g, i, c3, key0, key1);
-                flip_word(&lat[addr], acc);
+                const uint64_t was = und;
+                const uint64_t less = draw_call((uint32_t)c, call_masks(Th.t4, Th.t8, (uint32_t)c), one, und,
+                                                pk & 0xFFFFu, g, i, c3, key0, key1);
+                flip_word(&lat[addr], bop3<LUT_ANDN2>(less, was, und));
             }
-            const uint64_t need = wave_ballot((und4 | und8) != 0);
-            if ((und4 | und8) != 0) {
+            const uint64_t need = wave_ballot(und != 0);
+            if (und != 0) {
                 const int slot = rank_below(need, wcnt);
-                und_store(&eu[slot], und4, und8);
+                und_store(&eu[slot], und, one);
                 en[slot] = pk;
             }
             wcnt += __popcll(need);
@@ -1196,7 +1202,7 @@ struct Ring {
 // Full rounds while the ring holds more than `limit` (>= 64) entries.
 template <bool ONE_GROUP>
 __device__ __forceinline__ void stream_rounds(Ring &q, int limit, uint64_t *lat, UndPair *eu,
-                                              uint32_t *en, int cap, int N, int group0, const uint4 *tmask,
+                                              uint32_t *en, int cap, int N, int group0, const PlaneMasks *tmask,
                                               uint32_t i, uint32_t c3, uint32_t key0, uint32_t key1,
                                               uint32_t &wcalls)
 {
@@ -1205,20 +1211,21 @@ __device__ __forceinline__ void stream_rounds(Ring &q, int limit, uint64_t *lat,
     int left = q.left, hs = q.hs, ts = q.ts;
     while (left > limit) {
         const int slot = wrap_once(hs + lane, cap);
-        uint64_t und4, und8, acc = 0;
-        und_load(&eu[slot], und4, und8);
+        uint64_t und, one;
+        und_load(&eu[slot], und, one);
         const uint32_t pk = en[slot];
         const int addr = (int)(pk >> 16);
         const uint32_t c = (pk >> 12) & 15u;
-        draw_call_masks(c, tmask[c], und4, und8, acc, pk & 0xFFFu, group_of(addr), i, c3, key0, key1);
+        const uint64_t was = und;
+        const uint64_t less = draw_call(c, tmask[c], one, und, pk & 0xFFFu, group_of(addr), i, c3, key0, key1);
         wcalls += 64;
-        flip_word(&lat[addr], acc);
-        const bool more = (und4 | und8) != 0 && c < 15u;
+        flip_word(&lat[addr], bop3<LUT_ANDN2>(less, was, und));
+        const bool more = und != 0 && c < 15u;
         // the two compares' masks, combined on the scalar unit
-        const uint64_t need = wave_ballot((und4 | und8) != 0) & wave_ballot(c < 15u);
+        const uint64_t need = wave_ballot(und != 0) & wave_ballot(c < 15u);
         if (more) {
             const int out = wrap_once(rank_below(need, ts), cap);
-            und_store(&eu[out], und4, und8);
+            und_store(&eu[out], und, one);
             en[out] = (pk & 0xFFFF0FFFu) | ((c + 1u) << 12);
         }
         const int nn = __popcll(need);
@@ -1237,34 +1244,37 @@ __device__ __forceinline__ void stream_rounds(Ring &q, int limit, uint64_t *lat,
 // its own entry.
 template <bool ONE_GROUP>
 __device__ __forceinline__ void stream_tail(const Ring &q, uint64_t *lat, const UndPair *eu,
-                                            const uint32_t *en, int cap, int N, int group0, const uint4 *tmask,
+                                            const uint32_t *en, int cap, int N, int group0, const PlaneMasks *tmask,
                                             uint32_t i, uint32_t c3, uint32_t key0, uint32_t key1,
                                             uint32_t &wcalls)
 {
     const int lane = threadIdx.x & 63;
-    uint64_t und4 = 0, und8 = 0, acc = 0;
+    uint64_t und = 0, one = 0, acc = 0;
     int addr = 0;
     uint32_t n = 0, c = 16;
     if (lane < q.left) {
         const int slot = wrap_once(q.hs + lane, cap);
-        und_load(&eu[slot], und4, und8);
+        und_load(&eu[slot], und, one);
         const uint32_t pk = en[slot];
         addr = (int)(pk >> 16);
         c = (pk >> 12) & 15u;
         n = pk & 0xFFFu;
     }
     const uint32_t g = (uint32_t)(ONE_GROUP ? group0 : group0 + addr / N);
+    const uint64_t drew = und;
     for (;;) {
-        const bool live = (und4 | und8) != 0 && c < 16u;
-        const uint64_t lv = wave_ballot((und4 | und8) != 0) & wave_ballot(c < 16u);
+        const bool live = und != 0 && c < 16u;
+        const uint64_t lv = wave_ballot(und != 0) & wave_ballot(c < 16u);
         if (lv == 0) break;
         wcalls += (uint32_t)__popcll(lv);
         if (live) {
-            draw_call_masks(c, tmask[c], und4, und8, acc, n, g, i, c3, key0, key1);
+            const uint64_t was = und;
+            const uint64_t less = draw_call(c, tmask[c], one, und, n, g, i, c3, key0, key1);
+            acc = bop3<LUT_SEL>(was, less, acc);
             ++c;
         }
     }
-    flip_word(&lat[addr], acc);
+    flip_word(&lat[addr], bop3<LUT_ANDN2>(acc, drew, und));
 }
 
 // Sparse rounds over one list shared by the workgroup (ctl[h & 1] entries,
@@ -1290,42 +1300,49 @@ __device__ __forceinline__ void sweep_sparse_pooled(uint64_t *lat, UndPair *eu, 
         if (cnt <= 64 * tailw) {
             if (wv < tailw) {
                 const int e = wv * 64 + lane;
-                uint64_t und4 = 0, und8 = 0, acc = 0;
+                uint64_t und = 0, one = 0, acc = 0;
                 int addr = 0;
                 uint32_t n = 0, g = 0;
                 if (e < cnt) {
-                    und_load(&eu[e], und4, und8);
+                    und_load(&eu[e], und, one);
                     const uint32_t pk = en[e];
                     addr = (int)(pk >> 16);
                     n = pk & 0xFFFFu;
                     g = (uint32_t)(group0 + addr / N);
                 }
+                const uint64_t drew = und;
                 for (; c < 16; ++c) {
-                    const uint64_t live = wave_ballot((und4 | und8) != 0);
+                    const uint64_t live = wave_ballot(und != 0);
                     if (live == 0) break;
                     wcalls += (uint32_t)__popcll(live);
-                    if ((und4 | und8) != 0)
-                        draw_call((uint32_t)c, Th.t4, Th.t8, und4, und8, acc, n, g, i, c3, key0, key1);
+                    if (und != 0) {
+                        const uint64_t was = und;
+                        const uint64_t less = draw_call((uint32_t)c, call_masks(Th.t4, Th.t8, (uint32_t)c), one, und,
+                                                        n, g, i, c3, key0, key1);
+                        acc = bop3<LUT_SEL>(was, less, acc);
+                    }
                 }
-                flip_word(&lat[addr], acc);
+                flip_word(&lat[addr], bop3<LUT_ANDN2>(acc, drew, und));
             }
             return;
         }
         int out = 0;
         for (int s0 = 0; s0 < cnt; s0 += 64 * nw) {
             const int e = s0 + wv * 64 + lane;
-            uint64_t und4 = 0, und8 = 0, acc = 0;
+            uint64_t und = 0, one = 0;
             uint32_t pk = 0;
             wcalls += (uint32_t)max(0, min(64, cnt - (s0 + wv * 64)));
             if (e < cnt) {
-                und_load(&eu[e], und4, und8);
+                und_load(&eu[e], und, one);
                 pk = en[e];
                 const int addr = (int)(pk >> 16);
                 const uint32_t g = (uint32_t)(group0 + addr / N);
-                draw_call((uint32_t)c, Th.t4, Th.t8, und4, und8, acc, pk & 0xFFFFu, g, i, c3, key0, key1);
-                flip_word(&lat[addr], acc);
+                const uint64_t was = und;
+                const uint64_t less = draw_call((uint32_t)c, call_masks(Th.t4, Th.t8, (uint32_t)c), one, und,
+                                                pk & 0xFFFFu, g, i, c3, key0, key1);
+                flip_word(&lat[addr], bop3<LUT_ANDN2>(less, was, und));
             }
-            const uint64_t need = wave_ballot((und4 | und8) != 0);
+            const uint64_t need = wave_ballot(und != 0);
             int *cw = ctl + 2 + 16 * par;
             if (lane == 0) cw[wv] = __popcll(need);
             __syncthreads();
@@ -1335,9 +1352,9 @@ __device__ __forceinline__ void sweep_sparse_pooled(uint64_t *lat, UndPair *eu, 
                 off += w < wv ? v : 0;
                 tot += v;
             }
-            if ((und4 | und8) != 0) {
+            if (und != 0) {
                 const int slot = rank_below(need, off);
-                und_store(&eu[slot], und4, und8);
+                und_store(&eu[slot], und, one);
                 en[slot] = pk;
             }
             out += tot;
@@ -1396,7 +1413,7 @@ __device__ __forceinline__ void sweep_item(const SweepItem &item, const RunInfo 
     uint32_t *en = (uint32_t *)(eu + ents);               // [ents] (LDS word << 16) | site
     uint8_t *jb = (uint8_t *)(en + ents);                 // [2][nh] bond signs of each site (spin glass)
     int *ctl = (int *)(jb + (EA ? N : 0));                // pooled list counts [2], pass counts [2][16]
-    uint4 *tmask = (uint4 *)(lds + msc_lds_tmask_off(N, G, EA, nw, lmode) / 8);   // [16] T's bits per call
+    PlaneMasks *tmask = (PlaneMasks *)(lds + msc_lds_tmask_off(N, G, EA, nw, lmode) / 8);   // [16] T's bits per call
     uint64_t *base = (uint64_t *)R.spins[pop][S.cur] + (size_t)group0 * N;
     for (int u = tid; u < G * N; u += T) {
         const int gs = u / N, n = u - gs * N;
@@ -1444,51 +1461,52 @@ __device__ __forceinline__ void sweep_item(const SweepItem &item, const RunInfo 
             Ring q = {0, 0, 0};
             // dense rounds, 64 units per pass; one unit (lane) per site word
             auto chunk = [&](bool live_unit, int gs, int k, int kh, int ku, int kd, int addr, uint32_t n) {
-                uint64_t und4 = 0, und8 = 0, acc = 0;
+                uint64_t und = 0, one = 0, acc = 0;
                 const uint32_t g = (uint32_t)(group0 + gs);
                 if (live_unit) {
                     const uint64_t *oth = lat + (size_t)gs * N + (colour ^ 1) * nh;
                     const uint64_t w = lat[addr];
-                    uint64_t j0 = 0, j1 = 0, j2 = 0, j3 = 0;
+                    uint64_t n0 = oth[k], n1 = oth[kh], n2 = oth[ku], n3 = oth[kd];
                     if (EA) {
                         const uint32_t jm = jb[colour * nh + k];
-                        j0 = jmask((uint8_t)jm, 0);
-                        j1 = jmask((uint8_t)jm, 1);
-                        j2 = jmask((uint8_t)jm, 2);
-                        j3 = jmask((uint8_t)jm, 3);
+                        n0 ^= jmask((uint8_t)jm, 0);
+                        n1 ^= jmask((uint8_t)jm, 1);
+                        n2 ^= jmask((uint8_t)jm, 2);
+                        n3 ^= jmask((uint8_t)jm, 3);
                     }
-                    SiteClass sc = classify<EA>(w, oth[k], oth[kh], oth[ku], oth[kd], j0, j1, j2, j3);
-                    if (saturated) {   // uniform, only where a threshold is 2^32 (beta_i = 0)
-                        if (Th.all4) { sc.flip |= sc.one; sc.one = 0; }
-                        if (Th.all8) { sc.flip |= sc.zero; sc.zero = 0; }
-                    }
-                    acc = sc.flip;
-                    und4 = sc.one;
-                    und8 = sc.zero;
-                    if (group0 + gs == lastg) {   // only its valid replicas draw
-                        und4 &= vlast;
-                        und8 &= vlast;
+                    SiteClass sc = classify(w, n0, n1, n2, n3);
+                    if (saturated) accept_saturated(sc, Th);   // uniform, only where a threshold is 2^32
+                    und = sc.und;
+                    one = sc.one;
+                    acc = ~0ull;   // flips unless a draw says otherwise
+                    if (group0 + gs == lastg) {   // only its valid replicas draw and flip
+                        und &= vlast;
+                        acc = vlast;
                     }
                 }
                 for (int c = 0; c < dense; ++c) {
-                    const uint64_t live = wave_ballot((und4 | und8) != 0);
+                    const uint64_t live = wave_ballot(und != 0);
                     if (live == 0) break;
                     wcalls += (uint32_t)__popcll(live);
-                    if ((und4 | und8) != 0)
-                        draw_call((uint32_t)c, Th.t4, Th.t8, und4, und8, acc, n, g, (uint32_t)i, c3, key0, key1);
+                    if (und != 0) {
+                        const uint64_t was = und;
+                        const uint64_t less = draw_call((uint32_t)c, call_masks(Th.t4, Th.t8, (uint32_t)c), one, und,
+                                                        n, g, (uint32_t)i, c3, key0, key1);
+                        acc = bop3<LUT_SEL>(was, less, acc);
+                    }
                 }
-                flip_word(&lat[addr], acc);
-                const uint64_t need = wave_ballot((und4 | und8) != 0);
+                flip_word(&lat[addr], acc & ~und);
+                const uint64_t need = wave_ballot(und != 0);
                 int base_slot = ub + cnt;
                 if (pool && need) {
                     int b0 = 0;
                     if (lane == 0) b0 = atomicAdd(&ctl[h & 1], __popcll(need));
                     base_slot = __builtin_amdgcn_readlane(b0, 0);
                 }
-                if ((und4 | und8) != 0) {
+                if (und != 0) {
                     const int slot =
                         stream ? rb + wrap_once(rank_below(need, q.ts), rcap) : rank_below(need, base_slot);
-                    und_store(&eu[slot], und4, und8);
+                    und_store(&eu[slot], und, one);
                     en[slot] = ((uint32_t)addr << 16) | (stream ? (uint32_t)dense << 12 : 0u) | n;
                 }
                 cnt += __popcll(need);
