@@ -1045,20 +1045,20 @@ __global__ void __launch_bounds__(THREADS) k_sweep_int8(const RunInfo *runs, con
 //
 // Draw scheduling.  A site needs as many Philox calls as its slowest
 // undecided replica (about 3-4 on average, up to 16).  Each wavefront owns a
-// contiguous range of a colour's sites and works in rounds with one call
-// index per round, uniform across the wavefront:
-//  - dense rounds: chunks of 64 sites are classified (always flip / dE = +4 /
-//    dE = +8) and make calls 0 .. dense-1 in lockstep; nearly every site
-//    needs that many, so few lanes idle;
+// contiguous range of a colour's sites, whole chunks of 64, and works in
+// rounds:
+//  - dense rounds: chunks of 64 sites are classified and make calls
+//    0 .. dense-1 in lockstep; nearly every site needs that many, so few
+//    lanes idle;
 //  - sparse rounds: the sites still undecided are kept in a wave-private LDS
-//    list.  For lattices of at most 4096 sites the list is a queue (a ring
-//    of at most MSC_QUEUE_SLOTS entries in the kernels compiled for one
-//    size) whose entries carry their next call index, and every round takes
-//    the next 64 entries whatever call each is at (stream_rounds,
-//    stream_tail); otherwise the list is compacted in place after every
-//    call index (sweep_sparse_wave), or pooled over the workgroup
-//    (sweep_sparse_pooled).  Either way each round's calls run on full
-//    wavefronts until the last entries.
+//    list.  For lattices of at most 4096 sites the list is a queue
+//    (stream_item): a ring whose entries are the site's next Philox counter
+//    word itself (site, replica group within the workgroup, call index), and
+//    every round takes the next 64 entries whatever call each is at.
+//    Otherwise (general_item: larger lattices, 16 lockstep calls, or lists
+//    pooled over the workgroup) the list is compacted in place after every
+//    call index.  Either way the calls run on full wavefronts until the last
+//    entries.
 // Every site's result is still the plain most-significant-first comparison
 // of its own bit planes; only the order of the work changes.
 
@@ -1086,12 +1086,10 @@ __device__ __forceinline__ int rank_below(uint64_t m, int b)
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)b));
 }
 
-// x mod m for 0 <= x < 2m: an unsigned minimum instead of a compare and a
-// select.
-__device__ __forceinline__ int wrap_once(int x, int m)
-{
-    return (int)min((uint32_t)x, (uint32_t)x - (uint32_t)m);
-}
+// x / d for 0 <= x < 2^21 and a divisor known only at run time, from
+// inv = 1 / d: the error of the product (below 2^-23 of it) is less than the
+// distance 1 / (2d) of (x + 1/2) / d from the next integer.
+__device__ __forceinline__ int div_small(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
 
 // A list entry's undecided replicas and their class (set: dE = +4), kept
 // side by side so that one LDS address serves both.  Reads are one 16-byte
@@ -1122,7 +1120,7 @@ __device__ __forceinline__ void und_store(UndPair *p, uint64_t und, uint64_t one
 // every remaining entry it runs all their remaining calls without writing
 // the list back.
 __device__ __forceinline__ void sweep_sparse_wave(uint64_t *lat, UndPair *eu, uint32_t *en, int cnt,
-                                                  int c_first, int N, int group0, const Thresholds &Th, uint32_t i,
+                                                  int c_first, float invN, int group0, const Thresholds &Th, uint32_t i,
                                                   uint32_t c3, uint32_t key0, uint32_t key1, uint32_t &wcalls)
 {
     const int lane = threadIdx.x & 63;
@@ -1136,7 +1134,7 @@ __device__ __forceinline__ void sweep_sparse_wave(uint64_t *lat, UndPair *eu, ui
                 const uint32_t pk = en[lane];
                 addr = (int)(pk >> 16);
                 n = pk & 0xFFFFu;
-                g = (uint32_t)(group0 + addr / N);
+                g = (uint32_t)(group0 + div_small(addr, invN));
             }
             const uint64_t drew = und;
             for (; c < 16; ++c) {
@@ -1163,7 +1161,7 @@ __device__ __forceinline__ void sweep_sparse_wave(uint64_t *lat, UndPair *eu, ui
                 und_load(&eu[e], und, one);
                 pk = en[e];
                 const int addr = (int)(pk >> 16);
-                const uint32_t g = (uint32_t)(group0 + addr / N);
+                const uint32_t g = (uint32_t)(group0 + div_small(addr, invN));
                 const uint64_t was = und;
                 const uint64_t less = draw_call((uint32_t)c, call_masks(Th.t4, Th.t8, (uint32_t)c), one, und,
                                                 pk & 0xFFFFu, g, i, c3, key0, key1);
@@ -1181,102 +1179,6 @@ __device__ __forceinline__ void sweep_sparse_wave(uint64_t *lat, UndPair *eu, ui
     }
 }
 
-// Sparse rounds of one wavefront as a stream (lattices of at most 4096
-// sites): its undecided sites form a queue in a ring of `cap` slots (an
-// entry is LDS word << 16 | its next call << 12 | site).  Every round takes
-// the next 64 entries, whatever call each is at, makes that call, and
-// appends the sites still undecided at the tail with their next call, so
-// rounds stay full until fewer than 64 entries remain; those then run all
-// their remaining calls without being written back (stream_tail).  The
-// dense chunks append to the same ring; when it is smaller than the
-// wavefront's range, full rounds run between chunks whenever it holds more
-// than 64 entries, so the next chunk's entries always fit.  Each site keeps
-// the plain most-significant-first comparison of its own bit planes; only
-// the order of the work changes.  tmask[c] holds T's bits at the planes of
-// call c (call_masks); with ONE_GROUP (the workgroup holds one replica
-// group) every entry's group is group0, a uniform value.
-struct Ring {
-    int hs, ts, left;   // slot of the head, slot of the tail, entries
-};
-
-// Full rounds while the ring holds more than `limit` (>= 64) entries.
-template <bool ONE_GROUP>
-__device__ __forceinline__ void stream_rounds(Ring &q, int limit, uint64_t *lat, UndPair *eu,
-                                              uint32_t *en, int cap, int N, int group0, const PlaneMasks *tmask,
-                                              uint32_t i, uint32_t c3, uint32_t key0, uint32_t key1,
-                                              uint32_t &wcalls)
-{
-    const int lane = threadIdx.x & 63;
-    auto group_of = [&](int addr) { return (uint32_t)(ONE_GROUP ? group0 : group0 + addr / N); };
-    int left = q.left, hs = q.hs, ts = q.ts;
-    while (left > limit) {
-        const int slot = wrap_once(hs + lane, cap);
-        uint64_t und, one;
-        und_load(&eu[slot], und, one);
-        const uint32_t pk = en[slot];
-        const int addr = (int)(pk >> 16);
-        const uint32_t c = (pk >> 12) & 15u;
-        const uint64_t was = und;
-        const uint64_t less = draw_call(c, tmask[c], one, und, pk & 0xFFFu, group_of(addr), i, c3, key0, key1);
-        wcalls += 64;
-        flip_word(&lat[addr], bop3<LUT_ANDN2>(less, was, und));
-        const bool more = und != 0 && c < 15u;
-        // the two compares' masks, combined on the scalar unit
-        const uint64_t need = wave_ballot(und != 0) & wave_ballot(c < 15u);
-        if (more) {
-            const int out = wrap_once(rank_below(need, ts), cap);
-            und_store(&eu[out], und, one);
-            en[out] = (pk & 0xFFFF0FFFu) | ((c + 1u) << 12);
-        }
-        const int nn = __popcll(need);
-        ts += nn;
-        if (ts >= cap) ts -= cap;
-        hs += 64;
-        if (hs >= cap) hs -= cap;
-        left += nn - 64;
-    }
-    q.left = left;
-    q.hs = hs;
-    q.ts = ts;
-}
-
-// The last (at most 64) entries: each lane runs all the remaining calls of
-// its own entry.
-template <bool ONE_GROUP>
-__device__ __forceinline__ void stream_tail(const Ring &q, uint64_t *lat, const UndPair *eu,
-                                            const uint32_t *en, int cap, int N, int group0, const PlaneMasks *tmask,
-                                            uint32_t i, uint32_t c3, uint32_t key0, uint32_t key1,
-                                            uint32_t &wcalls)
-{
-    const int lane = threadIdx.x & 63;
-    uint64_t und = 0, one = 0, acc = 0;
-    int addr = 0;
-    uint32_t n = 0, c = 16;
-    if (lane < q.left) {
-        const int slot = wrap_once(q.hs + lane, cap);
-        und_load(&eu[slot], und, one);
-        const uint32_t pk = en[slot];
-        addr = (int)(pk >> 16);
-        c = (pk >> 12) & 15u;
-        n = pk & 0xFFFu;
-    }
-    const uint32_t g = (uint32_t)(ONE_GROUP ? group0 : group0 + addr / N);
-    const uint64_t drew = und;
-    for (;;) {
-        const bool live = und != 0 && c < 16u;
-        const uint64_t lv = wave_ballot(und != 0) & wave_ballot(c < 16u);
-        if (lv == 0) break;
-        wcalls += (uint32_t)__popcll(lv);
-        if (live) {
-            const uint64_t was = und;
-            const uint64_t less = draw_call(c, tmask[c], one, und, n, g, i, c3, key0, key1);
-            acc = bop3<LUT_SEL>(was, less, acc);
-            ++c;
-        }
-    }
-    flip_word(&lat[addr], bop3<LUT_ANDN2>(acc, drew, und));
-}
-
 // Sparse rounds over one list shared by the workgroup (ctl[h & 1] entries,
 // appended by every wavefront in the dense rounds): each round takes the
 // list in passes of one wavefront-load per wavefront; after a pass the
@@ -1287,7 +1189,7 @@ __device__ __forceinline__ void stream_tail(const Ring &q, uint64_t *lat, const 
 // workgroup has only one) run all their remaining calls without writing the
 // list back.
 __device__ __forceinline__ void sweep_sparse_pooled(uint64_t *lat, UndPair *eu, uint32_t *en,
-                                                    int *ctl, int h, int c_first, int N, int group0,
+                                                    int *ctl, int h, int c_first, float invN, int group0,
                                                     const Thresholds &Th, uint32_t i, uint32_t c3, uint32_t key0,
                                                     uint32_t key1, uint32_t &wcalls)
 {
@@ -1308,7 +1210,7 @@ __device__ __forceinline__ void sweep_sparse_pooled(uint64_t *lat, UndPair *eu, 
                     const uint32_t pk = en[e];
                     addr = (int)(pk >> 16);
                     n = pk & 0xFFFFu;
-                    g = (uint32_t)(group0 + addr / N);
+                    g = (uint32_t)(group0 + div_small(addr, invN));
                 }
                 const uint64_t drew = und;
                 for (; c < 16; ++c) {
@@ -1336,7 +1238,7 @@ __device__ __forceinline__ void sweep_sparse_pooled(uint64_t *lat, UndPair *eu, 
                 und_load(&eu[e], und, one);
                 pk = en[e];
                 const int addr = (int)(pk >> 16);
-                const uint32_t g = (uint32_t)(group0 + addr / N);
+                const uint32_t g = (uint32_t)(group0 + div_small(addr, invN));
                 const uint64_t was = und;
                 const uint64_t less = draw_call((uint32_t)c, call_masks(Th.t4, Th.t8, (uint32_t)c), one, und,
                                                 pk & 0xFFFFu, g, i, c3, key0, key1);
@@ -1365,123 +1267,447 @@ __device__ __forceinline__ void sweep_sparse_pooled(uint64_t *lat, UndPair *eu, 
     }
 }
 
-template <int LT, bool EA, bool RING>
-__device__ __forceinline__ void sweep_item(const SweepItem &item, const RunInfo &R, const PopState &S,
-                                           uint64_t *lds, int mode, unsigned long long *stats)
+// One item of the batched sweep, read into scalar registers before the first
+// barrier: a barrier orders memory, so values left in global memory would be
+// loaded again after every one of them.
+struct SweepJob {
+    int L, N, half, nh;
+    int G, group0, lastg, units;
+    int s_begin, s_end;      // this item's sweeps
+    int ub, ue;              // this wavefront's units (site words of one colour)
+    uint32_t key0, key1, i, c3p;
+    uint64_t vlast;          // valid replicas of the last group
+    Thresholds Th;
+    uint64_t *base;          // the groups' lattices in memory
+};
+
+template <int LT>
+__device__ __forceinline__ bool sweep_job(const SweepItem &item, const RunInfo &R, const PopState &S, SweepJob &J)
 {
-    // Everything the loops need is read into registers before the first
-    // barrier: a barrier orders memory, so values left in global memory
-    // would be loaded again after every one of them.
-    const int L = LT ? LT : __builtin_amdgcn_readfirstlane(R.L);
-    const int N = L * L, half = L >> 1, nh = N >> 1;
-    const int T = blockDim.x, tid = threadIdx.x;
-    const int lane = tid & 63, wv = wave_id(), nw = T >> 6;
+    J.L = LT > 0 ? LT : __builtin_amdgcn_readfirstlane(R.L);
+    J.N = J.L * J.L;
+    J.half = J.L >> 1;
+    J.nh = J.N >> 1;
     const int Rc = __builtin_amdgcn_readfirstlane(S.Rcur);
-    const int group0 = __builtin_amdgcn_readfirstlane(item.group0);
     const int pop = __builtin_amdgcn_readfirstlane(item.pop);
-    const int theta = __builtin_amdgcn_readfirstlane(R.theta);
-    // this item's sweeps: a chunk of them (boundaries chosen by the plan,
+    J.group0 = __builtin_amdgcn_readfirstlane(item.group0);
+    J.G = min(__builtin_amdgcn_readfirstlane(item.ngroups), (Rc + 63) / 64 - J.group0);
+    if (J.G <= 0) return false;
+    // a chunk of the sweeps (boundaries chosen by the plan,
     // expand_sweep_chunks), or all theta
+    const int theta = __builtin_amdgcn_readfirstlane(R.theta);
     const int nchunk = max(1, __builtin_amdgcn_readfirstlane(item.nchunk));
     const int chunk = __builtin_amdgcn_readfirstlane(item.chunk);
-    int s_begin = 0, s_end = theta;
+    J.s_begin = 0;
+    J.s_end = theta;
     if (nchunk == 2) {
         const int cut = min(max(__builtin_amdgcn_readfirstlane(item.cut), 0), theta);
-        s_begin = chunk ? cut : 0;
-        s_end = chunk ? theta : cut;
+        J.s_begin = chunk ? cut : 0;
+        J.s_end = chunk ? theta : cut;
     } else if (nchunk > 2) {
         const int sq = theta / nchunk, sr = theta - sq * nchunk;
-        s_begin = chunk * sq + min(chunk, sr);
-        s_end = s_begin + sq + (chunk < sr ? 1 : 0);
+        J.s_begin = chunk * sq + min(chunk, sr);
+        J.s_end = J.s_begin + sq + (chunk < sr ? 1 : 0);
     }
-    const uint32_t key0 = __builtin_amdgcn_readfirstlane(R.key0), key1 = __builtin_amdgcn_readfirstlane(R.key1);
-    const int G = min(__builtin_amdgcn_readfirstlane(item.ngroups), (Rc + 63) / 64 - group0);
-    if (G <= 0) return;
-    const int units = G * nh;
-    const bool pool = (mode >> 8) & 1;
-    const int dense = mode & 0xFF;
-    // the streamed sparse rounds keep each entry's next call in its site
-    // word's top bits (sites < 4096); calls 0 .. 15 only
-    const bool stream = msc_streamed(N, mode);
-    // one list entry per unit, or (RING: the kernels compiled for one size)
-    // a ring of MSC_QUEUE_SLOTS per wavefront
-    const int lmode = RING ? mode : mode | MSC_WHOLE_LISTS;   // the layout the launch sized
-    const int ents = msc_list_entries(N, G, nw, lmode);
-    const bool bounded = ents < units;
-    uint64_t *lat = lds;                                  // [G][2][nh]
-    UndPair *eu = (UndPair *)(lds + (size_t)G * N);       // [ents] undecided lanes of the two classes
-    uint32_t *en = (uint32_t *)(eu + ents);               // [ents] (LDS word << 16) | site
-    uint8_t *jb = (uint8_t *)(en + ents);                 // [2][nh] bond signs of each site (spin glass)
-    int *ctl = (int *)(jb + (EA ? N : 0));                // pooled list counts [2], pass counts [2][16]
-    PlaneMasks *tmask = (PlaneMasks *)(lds + msc_lds_tmask_off(N, G, EA, nw, lmode) / 8);   // [16] T's bits per call
-    uint64_t *base = (uint64_t *)R.spins[pop][S.cur] + (size_t)group0 * N;
-    for (int u = tid; u < G * N; u += T) {
-        const int gs = u / N, n = u - gs * N;
-        const int y = n / L, x = n - y * L;
-        lat[(size_t)gs * N + ((x + y) & 1) * nh + y * half + (x >> 1)] = base[u];
-    }
-    // Colour-split neighbours of site k = y half + m (x = 2m + p, p = (y +
-    // colour) & 1) in the other colour's array: k itself and kh = k - 1 or
-    // k + 1 within the row (the horizontal pair), k -+ half (up, down).
-    // jb holds the signs of the four bonds in that order (bit set: J = -1).
-    if (EA)
-        for (int v = tid; v < N; v += T) {
-            const int colour = v / nh, k = v - colour * nh;
-            const int y = k / half, m = k - y * half;
-            const int p = (y + colour) & 1, x = 2 * m + p;
-            const int xl = x == 0 ? L - 1 : x - 1, yu = y == 0 ? L - 1 : y - 1;
-            const uint8_t jn = R.jbits[y * L + x];
-            const uint32_t jr = jn & 1u, jd = (jn >> 1) & 1u;
-            const uint32_t jl = R.jbits[y * L + xl] & 1u, ju = (R.jbits[yu * L + x] >> 1) & 1u;
-            // k is the right neighbour when p = 0 and the left one when p = 1
-            const uint32_t jk = p ? jl : jr, jh = p ? jr : jl;
-            jb[v] = (uint8_t)(jk | (jh << 1) | (ju << 2) | (jd << 3));
-        }
+    J.key0 = __builtin_amdgcn_readfirstlane(R.key0);
+    J.key1 = __builtin_amdgcn_readfirstlane(R.key1);
     const int i = __builtin_amdgcn_readfirstlane(S.i);
-    const Thresholds Th = thresholds_of(R.tabT, i);
-    const bool saturated = Th.all4 || Th.all8;
-    if (tid < 16) tmask[tid] = call_masks(Th.t4, Th.t8, (uint32_t)tid);   // read after the next barrier
-    const uint32_t c3p = (TAG_SWEEP << 28) | ((uint32_t)pop << 24);
-    const int lastg = group0 + G - 1;
-    const uint64_t vlast = (Rc - lastg * 64 >= 64) ? ~0ull : ((1ull << (Rc - lastg * 64)) - 1);
-    const int upw = (units + nw - 1) / nw;
-    const int ub = min(units, wv * upw), ue = min(units, ub + upw);
-    // this wavefront's ring of streamed entries: its own range of the lists,
-    // or MSC_QUEUE_SLOTS slots of its own
-    const int rb = bounded ? wv * MSC_QUEUE_SLOTS : ub, rcap = bounded ? MSC_QUEUE_SLOTS : ue - ub;
+    J.i = (uint32_t)i;
+    J.c3p = (TAG_SWEEP << 28) | ((uint32_t)pop << 24);
+    J.Th = thresholds_of(R.tabT, i);
+    J.lastg = J.group0 + J.G - 1;
+    J.vlast = (Rc - J.lastg * 64 >= 64) ? ~0ull : ((1ull << (Rc - J.lastg * 64)) - 1);
+    J.units = J.G * J.nh;
+    const int upw = msc_units_per_wave(J.units, blockDim.x >> 6);
+    J.ub = min(J.units, wave_id() * upw);
+    J.ue = min(J.units, J.ub + upw);
+    J.base = (uint64_t *)R.spins[pop][S.cur] + (size_t)J.group0 * J.N;
+    return true;
+}
+
+// Lattice word of site n of group gs: colour (x + y) & 1, then the site's
+// place n >> 1 among its colour (rows of L/2).
+__device__ __forceinline__ int lattice_word(const SweepJob &J, int gs, int n, int y)
+{
+    return gs * J.N + ((n + y) & 1) * J.nh + (n >> 1);
+}
+
+template <int LT, bool STORE>
+__device__ __forceinline__ void move_lattices(const SweepJob &J, uint64_t *lat)
+{
+    const float invN = 1.0f / (float)J.N, invL = 1.0f / (float)J.L;
+    for (int u = threadIdx.x; u < J.G * J.N; u += blockDim.x) {
+        const int gs = LT > 0 ? u / J.N : div_small(u, invN);
+        const int n = u - gs * J.N;
+        const int y = LT > 0 ? n / J.L : div_small(n, invL);
+        if (STORE) J.base[u] = lat[lattice_word(J, gs, n, y)];
+        else lat[lattice_word(J, gs, n, y)] = J.base[u];
+    }
+}
+
+// Signs of the four bonds of site k of a colour, in the order of its
+// neighbours in the other colour's array: k itself and k - 1 or k + 1 within
+// the row (the horizontal pair), k - L/2 (up), k + L/2 (down).  Bit set: J = -1.
+__device__ __forceinline__ void bond_signs(const SweepJob &J, const uint8_t *jbits, uint8_t *jb)
+{
+    const float invH = 1.0f / (float)J.half;
+    for (int v = threadIdx.x; v < J.N; v += blockDim.x) {
+        const int colour = v >= J.nh ? 1 : 0, k = v - colour * J.nh;
+        const int y = div_small(k, invH), m = k - y * J.half;
+        const int p = (y + colour) & 1, x = 2 * m + p;
+        const int xl = x == 0 ? J.L - 1 : x - 1, yu = y == 0 ? J.L - 1 : y - 1;
+        const uint8_t jn = jbits[y * J.L + x];
+        const uint32_t jr = jn & 1u, jd = (jn >> 1) & 1u;
+        const uint32_t jl = jbits[y * J.L + xl] & 1u, ju = (jbits[yu * J.L + x] >> 1) & 1u;
+        // k is the right neighbour when p = 0 and the left one when p = 1
+        const uint32_t jk = p ? jl : jr, jh = p ? jr : jl;
+        jb[v] = (uint8_t)(jk | (jh << 1) | (ju << 2) | (jd << 3));
+    }
+}
+
+// Classes of one unit: w its word, oth + k (+ offsets) the other colour's.
+template <bool EA>
+__device__ __forceinline__ SiteClass classify_unit(uint64_t w, const uint64_t *o, int dh, int du, int dd, uint32_t jm)
+{
+    uint64_t n0 = o[0], n1 = o[dh], n2 = o[du], n3 = o[dd];
+    if (EA) {
+        n0 ^= jmask((uint8_t)jm, 0);
+        n1 ^= jmask((uint8_t)jm, 1);
+        n2 ^= jmask((uint8_t)jm, 2);
+        n3 ^= jmask((uint8_t)jm, 3);
+    }
+    return classify(w, n0, n1, n2, n3);
+}
+
+// A lane's walk over its wavefront's units in steps of 64: replica group gs
+// within the workgroup, site k = y L/2 + m of the colour, first lattice word
+// a = gs N + k (colour 0).  No division per step: the step's rows, columns
+// and groups are known beforehand and each carries at most once.
+struct UnitWalk {
+    int gs, k, y, m, a;
+    __device__ __forceinline__ void start(const SweepJob &J, int u)
+    {
+        gs = div_small(u, 1.0f / (float)J.nh);
+        k = u - gs * J.nh;
+        y = div_small(k, 1.0f / (float)J.half);
+        m = k - y * J.half;
+        a = gs * J.N + k;
+    }
+    __device__ __forceinline__ void step(const SweepJob &J, int gq, int kr, int yr, int mr)
+    {
+        gs += gq;
+        k += kr;
+        y += yr;
+        m += mr;
+        a += gq * J.N + kr;
+        if (m >= J.half) {
+            m -= J.half;
+            ++y;
+        }
+        if (k >= J.nh) {
+            k -= J.nh;
+            y -= J.L;
+            a += J.N - J.nh;
+            ++gs;
+        }
+    }
+    // offset of the other horizontal neighbour, p = x & 1
+    __device__ __forceinline__ int dh(const SweepJob &J, int p) const
+    {
+        return p ? (m + 1 == J.half ? 1 - J.half : 1) : (m == 0 ? J.half - 1 : -1);
+    }
+    __device__ __forceinline__ int du(const SweepJob &J) const { return y == 0 ? J.nh - J.half : -J.half; }
+    __device__ __forceinline__ int dd(const SweepJob &J) const { return y + 1 == J.L ? J.half - J.nh : J.half; }
+};
+
+// Work counters of an item: word-site updates and attempted flips in closed
+// form (the item's sweeps x 2 colours x its units, 64 replicas each except
+// the valid ones of the last group), the calls as counted.
+__device__ __forceinline__ void item_stats(const SweepJob &J, uint32_t wcalls, unsigned long long *stats)
+{
+    const int mine = max(J.ue - J.ub, 0);
+    const int nlast = max(J.ue - max(J.ub, (J.G - 1) * J.nh), 0);   // its units in the last group
+    const uint64_t nsw = (uint64_t)(J.s_end - J.s_begin);
+    const uint64_t nwords = nsw * 2u * (uint64_t)mine;
+    const uint64_t nflips =
+        nsw * 2u * ((uint64_t)(mine - nlast) * 64u + (uint64_t)nlast * (uint64_t)__popcll(J.vlast));
+    const bool first = (threadIdx.x & 63) == 0;
+    flush_stats(stats, first ? nwords : 0ull, first ? wcalls : 0u, first ? nflips : 0ull);
+}
+
+// The sweeps of a streamed item.  Each wavefront's queue of undecided sites
+// is a ring of `slots` entries of its own; an entry's word is the counter
+// word of its next call, site | call << 20, with the group's index within the
+// workgroup between them (bits 12 .. 19) unless the workgroup holds one
+// group (ONE).  A site's place among its colour is site >> 1, so the lattice
+// word follows from the counter word.
+//
+// Bound by the vector ALU's issue rate (at L = 64 it issues in 97 % of the
+// slots while the CU has work), so everything here is counted in
+// instructions: the lockstep calls run without branches or lane masks (a
+// decided lane's call changes nothing) on masks held in registers, a chunk
+// of whole rows finds its neighbours at constant offsets, the entry word
+// needs no unpacking.  Against a form with a branch and an exec mask per
+// call, divisions per chunk for the sizes without a kernel of their own, and
+// one kernel body per size in the dispatching kernel (100 registers instead
+// of 61, so two workgroups per CU instead of three), per launch: L = 64,
+// R = 1e5 576 -> 531 us (2.76e8 instead of 3.08e8 vector instructions); two
+// populations of 2e5 at L = 32 657 -> 570; 1024 runs of four sizes 1520 ->
+// 1297; ten spin-glass runs of five sizes 1765 -> 1604; R = 1e5 at L = 20
+// 184 -> 144; 3840 runs at L = 10 322 -> 166.
+template <int LT, bool EA, bool ONE>
+__device__ __forceinline__ uint32_t stream_sweeps(const SweepJob &J, uint64_t *lat, UndPair *eu, uint32_t *en,
+                                                  const uint8_t *jb, const PlaneMasks *tmask, int slots, int dense)
+{
+    const int L = LT > 0 ? LT : J.L, N = L * L, half = L >> 1, nh = N >> 1;
+    const int lane = threadIdx.x & 63;
+    const uint32_t i = J.i, key0 = J.key0, key1 = J.key1;
+    const bool saturated = J.Th.all4 || J.Th.all8;
+    const bool partial = J.vlast != ~0ull;
+    // masks of the first calls; one of each pair in a vector register (an
+    // instruction reads one scalar operand), where the compiler would
+    // otherwise copy it again for every call
+    PlaneMasks dm[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        dm[c] = call_masks(J.Th.t4, J.Th.t8, (uint32_t)c);
+        asm volatile("" : "+v"(dm[c].a8), "+v"(dm[c].b8));
+    }
+    // steps of a walk over 64 units
+    const int gq = 64 / nh, kr = 64 - gq * nh, yr = kr / half, mr = kr - yr * half;
+    UnitWalk first;
+    first.start(J, min(J.ub, J.units - 1) + lane);
     uint32_t wcalls = 0;   // Philox calls of this wavefront (uniform)
-    if (tid == 0) ctl[0] = ctl[1] = 0;
-    for (int s = s_begin; s < s_end; ++s) {
-        const uint32_t c3 = c3p | (uint32_t)s;
+    for (int s = J.s_begin; s < J.s_end; ++s) {
+        const uint32_t c3 = J.c3p | (uint32_t)s;
         for (int colour = 0; colour < 2; ++colour) {
-            const int h = 2 * s + colour;   // half-sweep index: its list count is ctl[h & 1]
             __syncthreads();
-            if (tid == 0) ctl[(h + 1) & 1] = 0;   // the next half-sweep's count; last read before this barrier
-            int cnt = 0;
-            Ring q = {0, 0, 0};
-            // dense rounds, 64 units per pass; one unit (lane) per site word
-            auto chunk = [&](bool live_unit, int gs, int k, int kh, int ku, int kd, int addr, uint32_t n) {
-                uint64_t und = 0, one = 0, acc = 0;
-                const uint32_t g = (uint32_t)(group0 + gs);
-                if (live_unit) {
-                    const uint64_t *oth = lat + (size_t)gs * N + (colour ^ 1) * nh;
-                    const uint64_t w = lat[addr];
-                    uint64_t n0 = oth[k], n1 = oth[kh], n2 = oth[ku], n3 = oth[kd];
-                    if (EA) {
-                        const uint32_t jm = jb[colour * nh + k];
-                        n0 ^= jmask((uint8_t)jm, 0);
-                        n1 ^= jmask((uint8_t)jm, 1);
-                        n2 ^= jmask((uint8_t)jm, 2);
-                        n3 ^= jmask((uint8_t)jm, 3);
+            const int cb = colour * nh;            // this colour's words
+            const int od = colour ? -nh : nh;      // from a word to the same place of the other colour
+            int hs = 0, ts = 0, left = 0;          // ring: slot of the head, slot of the tail, entries
+            auto word_of = [&](uint32_t pk) {      // lattice word of an entry
+                const int k = (int)((pk >> 1) & 0x7FFu) + cb;
+                return ONE ? k : k + (int)((pk >> 12) & 0xFFu) * N;
+            };
+            auto group_of = [&](uint32_t pk) {
+                return (uint32_t)(ONE ? J.group0 : J.group0 + (int)((pk >> 12) & 0xFFu));
+            };
+            auto call = [&](uint32_t c0, const PlaneMasks &m, uint64_t one, uint64_t &und, uint32_t g, auto ug) {
+                const u32x4 o = philox10_sweep<decltype(ug)::value>(c0, g, i, c3, key0, key1);
+                return plane_pair((uint64_t)o.x | ((uint64_t)o.y << 32), (uint64_t)o.z | ((uint64_t)o.w << 32), m,
+                                  one, und);
+            };
+            using UG = std::integral_constant<bool, ONE>;
+            // full rounds while more than 64 entries wait
+            auto rounds = [&]() {
+                while (left > 64) {
+                    const int slot = (hs + lane) & (slots - 1);
+                    uint64_t und, one;
+                    und_load(&eu[slot], und, one);
+                    const uint32_t pk = en[slot];
+                    const uint32_t c0 = ONE ? pk : pk & 0xF00FFFu;
+                    const uint64_t was = und;
+                    const uint64_t less = call(c0, tmask[pk >> 20], one, und, group_of(pk), UG{});
+                    flip_word(&lat[word_of(pk)], bop3<LUT_ANDN2>(less, was, und));
+                    wcalls += 64;
+                    const bool more = und != 0 && pk < 0xF00000u;
+                    // the two compares' masks, combined on the scalar unit
+                    const uint64_t need = wave_ballot(und != 0) & wave_ballot(pk < 0xF00000u);
+                    if (more) {
+                        const int out = (rank_below(need, 0) + ts) & (slots - 1);
+                        und_store(&eu[out], und, one);
+                        en[out] = pk + 0x100000u;
                     }
-                    SiteClass sc = classify(w, n0, n1, n2, n3);
-                    if (saturated) accept_saturated(sc, Th);   // uniform, only where a threshold is 2^32
+                    const int nn = __popcll(need);
+                    ts = (ts + nn) & (slots - 1);
+                    hs = (hs + 64) & (slots - 1);
+                    left += nn - 64;
+                }
+            };
+            // one chunk: a unit (site word) per lane.  own: its lattice word;
+            // dh, du, dd: offsets of the neighbours beside the word at the
+            // same place of the other colour
+            auto chunk = [&](bool in, int own, int dh, int du, int dd, uint32_t n, int gs, auto ug) {
+                uint64_t und = 0, one = 0, acc = 0;
+                const uint32_t g = (uint32_t)(J.group0 + gs);
+                if (in) {
+                    uint32_t jm = 0;
+                    if (EA) jm = jb[cb + (int)(n >> 1)];
+                    SiteClass sc = classify_unit<EA>(lat[own], lat + own + od, dh, du, dd, jm);
+                    if (saturated) accept_saturated(sc, J.Th);   // uniform, only where a threshold is 2^32
                     und = sc.und;
                     one = sc.one;
                     acc = ~0ull;   // flips unless a draw says otherwise
-                    if (group0 + gs == lastg) {   // only its valid replicas draw and flip
-                        und &= vlast;
-                        acc = vlast;
+                    if (partial && (int)g == J.lastg) {   // only valid replicas draw and flip
+                        und &= J.vlast;
+                        acc = J.vlast;
+                    }
+                }
+                auto lockstep = [&](uint32_t c, const PlaneMasks &m) {
+                    wcalls += (uint32_t)__popcll(wave_ballot(und != 0));
+                    const uint64_t was = und;
+                    const uint64_t less = call(n | (c << 20), m, one, und, g, ug);
+                    acc = bop3<LUT_SEL>(was, less, acc);
+                };
+                if (dense > 0) lockstep(0, dm[0]);
+                if (dense > 1) lockstep(1, dm[1]);
+                if (dense > 2) lockstep(2, dm[2]);
+                if (dense > 3) lockstep(3, dm[3]);
+                for (int c = 4; c < dense; ++c)
+                    lockstep((uint32_t)c, call_masks(J.Th.t4, J.Th.t8, (uint32_t)c));
+                flip_word(&lat[own], acc & ~und);
+                const uint64_t need = wave_ballot(und != 0);
+                if (und != 0) {
+                    const int out = (rank_below(need, 0) + ts) & (slots - 1);
+                    und_store(&eu[out], und, one);
+                    en[out] = n | ((uint32_t)dense << 20) | (ONE ? 0u : (uint32_t)gs << 12);
+                }
+                const int nn = __popcll(need);
+                ts = (ts + nn) & (slots - 1);
+                left += nn;
+                rounds();   // room for the next chunk's entries
+            };
+            // A chunk of whole rows (64 a multiple of two row halves, the
+            // colour's half-lattice a multiple of 64): every lane keeps its
+            // column, parity and horizontal neighbour for the whole walk,
+            // all lanes are in one replica group, and only the chunks at the
+            // lattice's top and bottom have wrapped neighbours.
+            constexpr bool ROWS = LT > 0 && 64 % LT == 0 && (LT * LT / 2) % 64 == 0;
+            if constexpr (ROWS) {
+                int gs = __builtin_amdgcn_readfirstlane(first.gs);
+                int kb = J.ub - gs * nh;   // lane 0's place among the colour: uniform
+                const int p = (first.y + colour) & 1;
+                const int dh = first.dh(J, p);
+                uint32_t n = 2u * (uint32_t)first.k + (uint32_t)p;
+                int own = first.a + cb;
+                for (int u0 = J.ub; u0 < J.ue; u0 += 64) {
+                    int du = -half, dd = half;
+                    if (kb == 0) du += lane < half ? nh : 0;
+                    if (kb == nh - 64) dd -= lane >= 64 - half ? nh : 0;
+                    chunk(true, own, dh, du, dd, n, ONE ? 0 : gs, std::true_type{});
+                    kb += 64;
+                    own += 64;
+                    n += 128;
+                    if (kb == nh) {   // every lane at once: the next replica group
+                        kb = 0;
+                        own += N - nh;
+                        n -= (uint32_t)N;
+                        ++gs;
+                    }
+                }
+            } else {
+                UnitWalk w = first;
+                for (int u0 = J.ub; u0 < J.ue; u0 += 64) {
+                    const int p = (w.y + colour) & 1;
+                    chunk(u0 + lane < J.ue, w.a + cb, w.dh(J, p), w.du(J), w.dd(J), 2u * (uint32_t)w.k + (uint32_t)p,
+                          ONE ? 0 : w.gs, UG{});
+                    w.step(J, gq, kr, yr, mr);
+                }
+            }
+            // the last (at most 64) entries: each lane runs all the remaining
+            // calls of its own entry
+            uint64_t und = 0, one = 0, acc = 0;
+            uint32_t pk = 0xFFFFFFFFu;
+            if (lane < left) {
+                const int slot = (hs + lane) & (slots - 1);
+                und_load(&eu[slot], und, one);
+                pk = en[slot];
+            }
+            const uint64_t drew = und;
+            const uint32_t g = group_of(pk);
+            const int own = lane < left ? word_of(pk) : 0;
+            for (;;) {
+                const bool live = und != 0 && pk < 0x1000000u;
+                const uint64_t lv = wave_ballot(und != 0) & wave_ballot(pk < 0x1000000u);
+                if (lv == 0) break;
+                wcalls += (uint32_t)__popcll(lv);
+                if (live) {
+                    const uint64_t was = und;
+                    const uint64_t less =
+                        call(ONE ? pk : pk & 0xF00FFFu, tmask[pk >> 20], one, und, g, UG{});
+                    acc = bop3<LUT_SEL>(was, less, acc);
+                    pk += 0x100000u;
+                }
+            }
+            flip_word(&lat[own], bop3<LUT_ANDN2>(acc, drew, und));
+        }
+    }
+    return wcalls;
+}
+
+// LDS layout: msc_stream_lds.
+template <int LT, bool EA>
+__device__ __forceinline__ void stream_item(const SweepItem &item, const RunInfo &R, const PopState &S, uint64_t *lds,
+                                            int mode, unsigned long long *stats)
+{
+    SweepJob J;
+    if (!sweep_job<LT>(item, R, S, J)) return;
+    const int nw = blockDim.x >> 6, slots = msc_ring_slots(J.units, nw);
+    PlaneMasks *tmask = (PlaneMasks *)lds;
+    uint64_t *lat = lds + 32;
+    UndPair *eu = (UndPair *)(lat + (size_t)J.G * J.N);
+    uint32_t *en = (uint32_t *)(eu + nw * slots);
+    uint8_t *jb = (uint8_t *)(en + nw * slots);
+    move_lattices<LT, false>(J, lat);
+    if (EA) bond_signs(J, R.jbits, jb);
+    if (threadIdx.x < 16) tmask[threadIdx.x] = call_masks(J.Th.t4, J.Th.t8, threadIdx.x);   // read after a barrier
+    const int ring = wave_id() * slots;
+    const uint32_t wcalls =
+        J.G == 1 ? stream_sweeps<LT, EA, true>(J, lat, eu + ring, en + ring, jb, tmask, slots, mode & 0xFF)
+                 : stream_sweeps<LT, EA, false>(J, lat, eu + ring, en + ring, jb, tmask, slots, mode & 0xFF);
+    __syncthreads();
+    move_lattices<LT, true>(J, lat);
+    item_stats(J, wcalls, stats);
+}
+
+// Items whose lists are not streamed.  LDS layout: msc_list_lds.
+template <bool EA>
+__device__ __forceinline__ void general_item(const SweepItem &item, const RunInfo &R, const PopState &S, uint64_t *lds,
+                                             int mode, unsigned long long *stats)
+{
+    SweepJob J;
+    if (!sweep_job<0>(item, R, S, J)) return;
+    const int N = J.N, nh = J.nh;
+    const int lane = threadIdx.x & 63;
+    const bool pool = (mode >> 8) & 1;
+    const int dense = mode & 0xFF;
+    uint64_t *lat = lds;                                  // [G][2][nh]
+    UndPair *eu = (UndPair *)(lds + (size_t)J.G * N);     // [units] undecided replicas and classes
+    uint32_t *en = (uint32_t *)(eu + J.units);            // [units] (LDS word << 16) | site
+    uint8_t *jb = (uint8_t *)(en + J.units);              // [2][nh] bond signs of each site (spin glass)
+    int *ctl = (int *)(jb + (EA ? N : 0));                // pooled list counts [2], pass counts [2][16]
+    move_lattices<0, false>(J, lat);
+    if (EA) bond_signs(J, R.jbits, jb);
+    if (threadIdx.x == 0) ctl[0] = ctl[1] = 0;
+    const float invN = 1.0f / (float)N;
+    const int gq = 64 / nh, kr = 64 - gq * nh, yr = kr / J.half, mr = kr - yr * J.half;
+    UnitWalk first;
+    first.start(J, min(J.ub, J.units - 1) + lane);
+    uint32_t wcalls = 0;   // Philox calls of this wavefront (uniform)
+    for (int s = J.s_begin; s < J.s_end; ++s) {
+        const uint32_t c3 = J.c3p | (uint32_t)s;
+        for (int colour = 0; colour < 2; ++colour) {
+            const int h = 2 * s + colour;   // half-sweep index: its list count is ctl[h & 1]
+            __syncthreads();
+            if (threadIdx.x == 0) ctl[(h + 1) & 1] = 0;   // the next half-sweep's count; last read before this barrier
+            const int cb = colour * nh, od = colour ? -nh : nh;
+            int cnt = 0;
+            UnitWalk w = first;
+            for (int u0 = J.ub; u0 < J.ue; u0 += 64) {
+                const int p = (w.y + colour) & 1, own = w.a + cb;
+                const uint32_t n = 2u * (uint32_t)w.k + (uint32_t)p, g = (uint32_t)(J.group0 + w.gs);
+                uint64_t und = 0, one = 0, acc = 0;
+                if (u0 + lane < J.ue) {
+                    uint32_t jm = 0;
+                    if (EA) jm = jb[cb + w.k];
+                    SiteClass sc = classify_unit<EA>(lat[own], lat + own + od, w.dh(J, p), w.du(J), w.dd(J), jm);
+                    accept_saturated(sc, J.Th);
+                    und = sc.und;
+                    one = sc.one;
+                    acc = ~0ull;   // flips unless a draw says otherwise
+                    if ((int)g == J.lastg) {   // only valid replicas draw and flip
+                        und &= J.vlast;
+                        acc = J.vlast;
                     }
                 }
                 for (int c = 0; c < dense; ++c) {
@@ -1490,171 +1716,66 @@ __device__ __forceinline__ void sweep_item(const SweepItem &item, const RunInfo 
                     wcalls += (uint32_t)__popcll(live);
                     if (und != 0) {
                         const uint64_t was = und;
-                        const uint64_t less = draw_call((uint32_t)c, call_masks(Th.t4, Th.t8, (uint32_t)c), one, und,
-                                                        n, g, (uint32_t)i, c3, key0, key1);
+                        const uint64_t less = draw_call((uint32_t)c, call_masks(J.Th.t4, J.Th.t8, (uint32_t)c), one,
+                                                        und, n, g, J.i, c3, J.key0, J.key1);
                         acc = bop3<LUT_SEL>(was, less, acc);
                     }
                 }
-                flip_word(&lat[addr], acc & ~und);
+                if (u0 + lane < J.ue) flip_word(&lat[own], acc & ~und);
                 const uint64_t need = wave_ballot(und != 0);
-                int base_slot = ub + cnt;
+                int base_slot = J.ub + cnt;
                 if (pool && need) {
                     int b0 = 0;
                     if (lane == 0) b0 = atomicAdd(&ctl[h & 1], __popcll(need));
                     base_slot = __builtin_amdgcn_readlane(b0, 0);
                 }
                 if (und != 0) {
-                    const int slot =
-                        stream ? rb + wrap_once(rank_below(need, q.ts), rcap) : rank_below(need, base_slot);
+                    const int slot = rank_below(need, base_slot);
                     und_store(&eu[slot], und, one);
-                    en[slot] = ((uint32_t)addr << 16) | (stream ? (uint32_t)dense << 12 : 0u) | n;
+                    en[slot] = ((uint32_t)own << 16) | n;
                 }
                 cnt += __popcll(need);
-                if (stream) {
-                    q.ts += __popcll(need);
-                    if (q.ts >= rcap) q.ts -= rcap;
-                    q.left += __popcll(need);
-                    if (RING && bounded && q.left > rcap - 64) {   // room for the next chunk's entries
-                        if (G == 1)
-                            stream_rounds<true>(q, rcap - 64, lat, eu + rb, en + rb, rcap, N, group0, tmask,
-                                                (uint32_t)i, c3, key0, key1, wcalls);
-                        else
-                            stream_rounds<false>(q, rcap - 64, lat, eu + rb, en + rb, rcap, N, group0,
-                                                 tmask, (uint32_t)i, c3, key0, key1, wcalls);
-                    }
-                }
-            };
-            // Strength-reduced indices: when a pass starts on a multiple of
-            // 64 units, a row half (L/2 words) divides 64 an even number of
-            // times and a colour's half-lattice (N/2 words) is a multiple of
-            // 64, every lane keeps its column, parity and horizontal
-            // neighbour offset for the whole pass; its row advances by
-            // 64/(L/2) per pass, and all lanes move to the next replica group
-            // together.  Only the up/down wraps are tested per pass.
-            constexpr bool STEP_ROWS = LT > 0 && 64 % (LT / 2) == 0 && (64 / (LT / 2)) % 2 == 0 &&
-                                       (LT * LT / 2) % 64 == 0;
-            if (STEP_ROWS && (ub & 63) == 0 && ub < ue) {
-                constexpr int RS = STEP_ROWS ? 64 / (LT / 2) : 0;   // rows per pass
-                int gs = __builtin_amdgcn_readfirstlane(ub / nh);
-                int kb = ub - gs * nh;   // lane 0's unit in its group: uniform, so the group change is too
-                int k = kb + lane;
-                int y = k / half;
-                const int m = k - y * half;
-                const int p = (y + colour) & 1;   // constant: y advances by an even count
-                int mh = p ? m + 1 : m - 1;
-                mh = mh < 0 ? half - 1 : (mh == half ? 0 : mh);
-                const int dh = mh - m;
-                int addr = gs * N + colour * nh + k;
-                uint32_t n = (uint32_t)(y * L + 2 * m + p);
-                for (int u0 = ub; u0 < ue; u0 += 64) {
-                    const int ku = y == 0 ? k + nh - half : k - half;
-                    const int kd = y + 1 == L ? k - nh + half : k + half;
-                    chunk(u0 + lane < ue, gs, k, k + dh, ku, kd, addr, n);
-                    kb += 64;
-                    k += 64;
-                    y += RS;
-                    n += (uint32_t)(RS * L);
-                    addr += 64;
-                    if (kb >= nh) {   // every lane at once: the next replica group
-                        kb -= nh;
-                        k -= nh;
-                        y -= L;
-                        n -= (uint32_t)N;
-                        addr += N - nh;
-                        ++gs;
-                    }
-                }
-            } else {
-                for (int u0 = ub; u0 < ue; u0 += 64) {
-                    const int u = u0 + lane;
-                    const bool in = u < ue;
-                    const int uu = in ? u : ub;   // any in-range unit; the chunk ignores it
-                    const int gs = uu / nh, k = uu - gs * nh;
-                    const int y = k / half, m = k - y * half;
-                    const int p = (y + colour) & 1;
-                    int mh = p ? m + 1 : m - 1;                  // the other horizontal neighbour
-                    mh = mh < 0 ? half - 1 : (mh == half ? 0 : mh);
-                    const int kh = k - m + mh;
-                    const int ku = y == 0 ? k + nh - half : k - half;
-                    const int kd = y + 1 == L ? k - nh + half : k + half;
-                    chunk(in, gs, k, kh, ku, kd, gs * N + colour * nh + k, (uint32_t)(y * L + 2 * m + p));
-                }
+                w.step(J, gq, kr, yr, mr);
             }
             if (pool)
-                sweep_sparse_pooled(lat, eu, en, ctl, h, dense, N, group0, Th, (uint32_t)i, c3, key0, key1,
+                sweep_sparse_pooled(lat, eu, en, ctl, h, dense, invN, J.group0, J.Th, J.i, c3, J.key0, J.key1,
                                     wcalls);
-            else if (stream && G == 1) {
-                stream_rounds<true>(q, 64, lat, eu + rb, en + rb, rcap, N, group0, tmask, (uint32_t)i, c3,
-                                    key0, key1, wcalls);
-                stream_tail<true>(q, lat, eu + rb, en + rb, rcap, N, group0, tmask, (uint32_t)i, c3, key0,
-                                  key1, wcalls);
-            } else if (stream) {
-                stream_rounds<false>(q, 64, lat, eu + rb, en + rb, rcap, N, group0, tmask, (uint32_t)i, c3,
-                                     key0, key1, wcalls);
-                stream_tail<false>(q, lat, eu + rb, en + rb, rcap, N, group0, tmask, (uint32_t)i, c3, key0,
-                                   key1, wcalls);
-            }
             else
-                sweep_sparse_wave(lat, eu + ub, en + ub, cnt, dense, N, group0, Th, (uint32_t)i, c3, key0,
-                                  key1, wcalls);
+                sweep_sparse_wave(lat, eu + J.ub, en + J.ub, cnt, dense, invN, J.group0, J.Th, J.i, c3, J.key0,
+                                  J.key1, wcalls);
         }
     }
     __syncthreads();
-    for (int u = tid; u < G * N; u += T) {
-        const int gs = u / N, n = u - gs * N;
-        const int y = n / L, x = n - y * L;
-        base[u] = lat[(size_t)gs * N + ((x + y) & 1) * nh + y * half + (x >> 1)];
-    }
-    // word-site updates and attempted flips of this wavefront's range, in
-    // closed form: the item's sweeps x 2 colours x its units, 64 replicas
-    // each except the valid ones of the last group
-    const int mine = max(ue - ub, 0);
-    const int nlast = max(ue - max(ub, (G - 1) * nh), 0);   // its units in the last group
-    const uint64_t nsw = (uint64_t)(s_end - s_begin);
-    const uint64_t nwords = nsw * 2u * (uint64_t)mine;
-    const uint64_t nflips =
-        nsw * 2u * ((uint64_t)(mine - nlast) * 64u + (uint64_t)nlast * (uint64_t)__popcll(vlast));
-    flush_stats(stats, lane == 0 ? nwords : 0ull, lane == 0 ? wcalls : 0u, lane == 0 ? nflips : 0ull);
+    move_lattices<0, true>(J, lat);
+    item_stats(J, wcalls, stats);
 }
 
-template <bool EA>
-__device__ __forceinline__ void sweep_dispatch(const SweepItem &it, const RunInfo &R, const PopState &S,
-                                               uint64_t *lds, int dense, unsigned long long *stats)
-{
-    switch (R.L) {
-    case 8: sweep_item<8, EA, false>(it, R, S, lds, dense, stats); break;
-    case 16: sweep_item<16, EA, false>(it, R, S, lds, dense, stats); break;
-    case 24: sweep_item<24, EA, false>(it, R, S, lds, dense, stats); break;
-    case 32: sweep_item<32, EA, false>(it, R, S, lds, dense, stats); break;
-    case 48: sweep_item<48, EA, false>(it, R, S, lds, dense, stats); break;
-    case 64: sweep_item<64, EA, false>(it, R, S, lds, dense, stats); break;
-    case 128: sweep_item<128, EA, false>(it, R, S, lds, dense, stats); break;
-    default: sweep_item<0, EA, false>(it, R, S, lds, dense, stats); break;
-    }
-}
-
-// LS < 0: any lattice size and model, chosen per item; otherwise every item
-// of the launch has L = LS and the model EA (a kernel of its own allocates
-// only the registers that one size needs).
+// LS >= 0: every item of the launch has the model EA and, for LS > 0, L = LS,
+// and its lists are streamed (a kernel of its own allocates only the
+// registers that one form needs).  LS < 0: any size, model and list scheme,
+// chosen per item.
 template <int LS, bool EA>
 __device__ __forceinline__ void sweep_one(const SweepItem &it, const RunInfo *runs, const PopState *st,
-                                          uint64_t *lds, uint32_t lds_bytes, int dense, unsigned long long *stats)
+                                          uint64_t *lds, uint32_t lds_bytes, int mode, unsigned long long *stats)
 {
     const RunInfo &R = runs[it.run];
     const PopState &S = st[it.run * MAX_POP + it.pop];
     if (!pop_active(S) || R.theta == 0) return;
     // an item that does not fit the LDS of this launch (a list that does not
     // belong to the launch's plan) is skipped and counted, never run
-    if (msc_lds_need(R.N, it.ngroups, R.model == PA_EA_PMJ, (int)(blockDim.x >> 6),
-                     LS >= 0 ? dense : dense | MSC_WHOLE_LISTS) > lds_bytes) {
+    const bool ea = R.model == PA_EA_PMJ;
+    if (msc_lds_need(R.N, it.ngroups, ea, (int)(blockDim.x >> 6), mode) > lds_bytes) {
         if (threadIdx.x == 0) atomicAdd(&stats[ST_STALL], 1ull);
         return;
     }
     if constexpr (LS >= 0) {
-        sweep_item<LS, EA, true>(it, R, S, lds, dense, stats);
+        stream_item<LS, EA>(it, R, S, lds, mode, stats);
+    } else if (msc_streamed(R.N, mode)) {
+        if (ea) stream_item<0, true>(it, R, S, lds, mode, stats);
+        else stream_item<0, false>(it, R, S, lds, mode, stats);
     } else {
-        if (R.model == PA_EA_PMJ) sweep_dispatch<true>(it, R, S, lds, dense, stats);
-        else sweep_dispatch<false>(it, R, S, lds, dense, stats);
+        if (ea) general_item<true>(it, R, S, lds, mode, stats);
+        else general_item<false>(it, R, S, lds, mode, stats);
     }
 }
 
@@ -1682,24 +1803,24 @@ constexpr unsigned int SWEEP_WAIT_SPINS = 1u << 22;
 
 template <int LS, bool EA>
 __global__ void __launch_bounds__(1024) k_sweep_msc(const SweepItem *items, int n_items, const RunInfo *runs,
-                                                    const PopState *st, int dense, unsigned long long *stats,
+                                                    const PopState *st, int mode, unsigned long long *stats,
                                                     unsigned int *queue, unsigned int *flags, uint32_t lds_bytes)
 {
-    extern __shared__ uint64_t lds[];
-    if (queue == nullptr) {
-        sweep_one<LS, EA>(items[blockIdx.x], runs, st, lds, lds_bytes, dense, stats);
-        return;
-    }
+    extern __shared__ __align__(16) uint64_t lds[];
     __shared__ unsigned int ticket, gen;
-    if (threadIdx.x == 0) gen = __hip_atomic_load(&queue[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool persistent = queue != nullptr;
+    unsigned int t = blockIdx.x;
+    if (persistent && threadIdx.x == 0) gen = __hip_atomic_load(&queue[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (;;) {
-        __syncthreads();
-        if (threadIdx.x == 0) ticket = atomicAdd(&queue[0], 1u);
-        __syncthreads();
-        const unsigned int t = ticket;
+        if (persistent) {
+            __syncthreads();
+            if (threadIdx.x == 0) ticket = atomicAdd(&queue[0], 1u);
+            __syncthreads();
+            t = ticket;
+        }
         if (t >= (unsigned int)n_items) break;
         const SweepItem it = items[t];
-        if (it.chunk > 0) {
+        if (persistent && it.chunk > 0) {
             if (threadIdx.x == 0) {
                 const unsigned int want = (gen << 4) | (unsigned int)it.chunk;
                 unsigned int spins = 0;
@@ -1714,7 +1835,8 @@ __global__ void __launch_bounds__(1024) k_sweep_msc(const SweepItem *items, int 
             }
             __syncthreads();
         }
-        sweep_one<LS, EA>(it, runs, st, lds, lds_bytes, dense, stats);
+        sweep_one<LS, EA>(it, runs, st, lds, lds_bytes, mode, stats);
+        if (!persistent) return;
         if (it.chunk + 1 < it.nchunk) {
             // every wavefront waits for its own lattice stores (a barrier
             // alone does not), so that the release by the first thread,
@@ -3119,7 +3241,10 @@ using SweepKernel = void (*)(const SweepItem *, int, const RunInfo *, const PopS
 
 SweepKernel msc_kernel(int L, int ea)
 {
+    if (L < 0) return k_sweep_msc<-1, false>;
     switch (2 * L + (ea ? 1 : 0)) {
+    case 0: return k_sweep_msc<0, false>;
+    case 1: return k_sweep_msc<0, true>;
     case 16: return k_sweep_msc<8, false>;
     case 17: return k_sweep_msc<8, true>;
     case 32: return k_sweep_msc<16, false>;
@@ -3141,7 +3266,7 @@ bool msc_specialised(int L) { return L == 8 || L == 16 || L == 24 || L == 32 || 
 hipError_t prepare_msc_lds(size_t bytes)
 {
     if (bytes <= 65536) return hipSuccess;
-    static const int Ls[] = {8, 16, 24, 32, 48, 64, 0};
+    static const int Ls[] = {8, 16, 24, 32, 48, 64, 0, -1};
     for (int L : Ls)
         for (int ea = 0; ea < 2; ++ea) {
             const hipError_t e = hipFuncSetAttribute((const void *)msc_kernel(L, ea),
@@ -3167,7 +3292,7 @@ hipError_t launch_sweep_msc(const LaunchCtx &c)
         // the persistent grid makes safe
         if (q.nchunk > 1 && !persistent) return hipErrorInvalidConfiguration;
         const int grid = persistent ? q.grid : q.count;
-        const int mode = c.sweep_dense | (c.sweep_pooled << 8) | (q.L > 0 ? 0 : MSC_WHOLE_LISTS);
+        const int mode = c.sweep_dense | (c.sweep_pooled << 8);
         msc_kernel(q.L, q.ea)<<<grid, c.sweep_threads, q.lds, c.stream>>>(
             c.sweep_items + q.first, q.count, c.runs, c.st, mode, c.stats,
             persistent ? c.sweep_queue : nullptr, c.sweep_flags, (uint32_t)q.lds);
@@ -3183,18 +3308,21 @@ int sweep_classes(std::vector<SweepItem> &items, const std::vector<int> &run_L, 
     // kernel of another size must never see them)
     std::vector<SweepItem> out;
     out.reserve(items.size());
-    std::vector<int> keys;   // per kept item: 2 L + ea, 0 if L has no kernel of its own
+    // per kept item: 2 L + ea of the kernel that sweeps it, 0 + ea for a size
+    // without a kernel of its own, -1 where the lists are not streamed
+    std::vector<int> keys;
     for (const SweepItem &it : items) {
         const int L = run_L[it.run];
         if (L == 0) continue;
-        keys.push_back(msc_specialised(L) ? 2 * L + (run_ea[it.run] ? 1 : 0) : 0);
+        const int ea = run_ea[it.run] ? 1 : 0;
+        keys.push_back(!msc_streamed(L * L, mode) ? -1 : (msc_specialised(L) ? 2 * L : 0) + ea);
         out.push_back(it);
     }
     items.swap(out);
     if (items.empty()) return 0;
-    auto lds_of = [&](const SweepItem &it, int cmode) {
+    auto lds_of = [&](const SweepItem &it) {
         const int L = run_L[it.run];
-        return msc_lds_bytes(L * L, it.ngroups, run_ea[it.run] != 0, threads, cmode);
+        return msc_lds_bytes(L * L, it.ngroups, run_ea[it.run] != 0, threads, mode);
     };
     // One launch per (size, model) when every item has a kernel compiled
     // for its size and each class fills at least half of the workgroups
@@ -3206,7 +3334,7 @@ int sweep_classes(std::vector<SweepItem> &items, const std::vector<int> &run_L, 
     std::vector<int> ks(keys);
     std::sort(ks.begin(), ks.end());
     ks.erase(std::unique(ks.begin(), ks.end()), ks.end());
-    bool split = split_ok && ks.size() > 1 && (int)ks.size() <= MAX_SWEEP_CLASSES && ks[0] != 0;
+    bool split = split_ok && ks.size() > 1 && (int)ks.size() <= MAX_SWEEP_CLASSES && ks[0] > 1;
     std::vector<SweepClass> cand(ks.size());
     for (size_t q = 0; split && q < ks.size(); ++q) {
         SweepClass &C = cand[q];
@@ -3218,7 +3346,7 @@ int sweep_classes(std::vector<SweepItem> &items, const std::vector<int> &run_L, 
         for (size_t t = 0; t < items.size(); ++t)
             if (keys[t] == ks[q]) {
                 ++C.count;
-                C.lds = std::max(C.lds, lds_of(items[t], mode));
+                C.lds = std::max(C.lds, lds_of(items[t]));
             }
         const int resident = sweep_msc_resident(threads, C.lds, C.L, C.ea);
         if (resident <= 0 || 2 * C.count < resident) split = false;
@@ -3236,16 +3364,18 @@ int sweep_classes(std::vector<SweepItem> &items, const std::vector<int> &run_L, 
         items.swap(sorted);
         return (int)ks.size();
     }
-    const int key = ks.size() == 1 ? ks[0] : 0;
+    // several sizes of one model share the kernel for any size of that model;
+    // anything else takes the one that chooses per item
+    int key = ks[0];
+    for (int k : ks) key = key < 0 || k < 0 || ((key ^ k) & 1) ? -1 : (key == k ? k : key & 1);
     SweepClass &C = cls[0];
     C.first = 0;
     C.count = (int)items.size();
-    C.L = key / 2;
-    C.ea = key & 1;
+    C.L = key < 0 ? -1 : key / 2;
+    C.ea = key < 0 ? 0 : key & 1;
     C.grid = 0;
     C.lds = 0;
-    const int cmode = C.L > 0 ? mode : mode | MSC_WHOLE_LISTS;
-    for (const SweepItem &it : items) C.lds = std::max(C.lds, lds_of(it, cmode));
+    for (const SweepItem &it : items) C.lds = std::max(C.lds, lds_of(it));
     return 1;
 }
 

@@ -10,8 +10,8 @@
 namespace pa {
 
 // One launch of the batched sweep: the items of one (lattice size, model)
-// class, swept by the kernel compiled for that class (L = 0: the kernel
-// that dispatches per item, for the sizes without one of their own).
+// class, swept by the kernel compiled for that class (L = 0: the kernel for
+// any size of the model ea; L = -1: the one that chooses per item).
 struct SweepClass {
     int first, count;   // items [first, first + count) of the sweep list
     int L, ea;

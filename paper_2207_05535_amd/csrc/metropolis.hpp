@@ -118,7 +118,7 @@ __device__ __forceinline__ uint64_t draw_call(uint32_t c, const PlaneMasks &m, u
                                               uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                               uint32_t k1)
 {
-    const u32x4 o = philox10_sweep(c0 | (c << 20), c1, c2, c3, k0, k1);
+    const u32x4 o = philox10_sweep<false>(c0 | (c << 20), c1, c2, c3, k0, k1);
     const uint64_t pa = (uint64_t)o.x | ((uint64_t)o.y << 32);
     const uint64_t pb = (uint64_t)o.z | ((uint64_t)o.w << 32);
     return plane_pair(pa, pb, m, one, und);

@@ -126,53 +126,57 @@ struct SweepItem {    // groups [group0, group0 + ngroups) of one (run, pop), on
 };
 constexpr int MAX_SWEEP_CHUNKS = 4;
 
-// LDS bytes of a batched-sweep workgroup holding `groups` replica groups of
-// N sites: the colour-split lattices, the lists of undecided sites (two
-// 64-bit masks and a 32-bit entry per unit), the bond signs and the counters.
-// Queue slots per wavefront of the streamed sparse rounds: a wavefront
-// that owns more site words than this keeps its undecided sites in a ring
-// of this many entries, run down by full rounds whenever it holds more than
-// one chunk's worth (a chunk adds at most 64, and full rounds leave at most
-// 64), so the lists take less LDS and more workgroups fit on a CU.
-constexpr int MSC_QUEUE_SLOTS = 128;
-constexpr int MSC_WHOLE_LISTS = 1 << 9;
-
-// mode = lockstep calls | pooled << 8 | whole lists << 9, as the batched
-// sweep is launched (whole lists: one entry per site word even when the
-// rounds are streamed; the kernel that dispatches per item uses them, its
-// many registers leaving no room for more workgroups per CU anyway).  The
-// sparse rounds are streamed for lattices of at most 4096 sites when they
-// are not pooled and there are sparse rounds at all.
+// LDS of a batched-sweep workgroup holding `groups` replica groups of N
+// sites in nw wavefronts.  mode = lockstep calls | pooled << 8, as the sweep
+// is launched: the sparse rounds are streamed for lattices of at most 4096
+// sites when they are not pooled and there are sparse rounds at all.
 __host__ __device__ inline bool msc_streamed(int N, int mode)
 {
     return !((mode >> 8) & 1) && N <= 4096 && (mode & 0xFF) < 16;
 }
 
-// Entries of a workgroup's lists of undecided sites: one per site word of
-// one colour of its groups, or MSC_QUEUE_SLOTS per wavefront when streamed
-// rounds let that be fewer.
-__host__ __device__ inline int msc_list_entries(int N, int groups, int nw, int mode)
+// Site words of one colour that each wavefront owns: whole chunks of 64.
+__host__ __device__ inline int msc_units_per_wave(int units, int nw) { return ((units + nw - 1) / nw + 63) & ~63; }
+
+// Slots of a wavefront's ring of streamed entries (a power of two): a chunk
+// adds at most 64, and a wavefront with several chunks runs full rounds
+// whenever the ring holds more than 64, so the next chunk's always fit.
+__host__ __device__ inline int msc_ring_slots(int units, int nw)
 {
-    const int units = groups * (N / 2);
-    const int upw = (units + nw - 1) / nw;
-    return msc_streamed(N, mode) && !(mode & MSC_WHOLE_LISTS) && upw > MSC_QUEUE_SLOTS ? nw * MSC_QUEUE_SLOTS
-                                                                                        : units;
+    return msc_units_per_wave(units, nw) <= 64 ? 64 : 128;
 }
 
-// Layout: lattices [groups][N] u64, undecided lanes of the two classes
-// [entries] u64 each, list entries [entries] u32, bond signs [N] u8 (spin
-// glass only), list counts [34] int, then (16-byte aligned) T's bits at the
-// planes of each call [16] uint4.  nw: wavefronts of the workgroup.
-__host__ __device__ inline size_t msc_lds_tmask_off(int N, int groups, bool ea, int nw, int mode)
+// Streamed: T's bits at the planes of each call [16] 16 bytes, lattices
+// [groups][N] u64, rings: entries' undecided replicas and classes [nw][slots]
+// 16 bytes and counter words [nw][slots] u32, bond signs [N] u8 (spin glass
+// only).  (At L = 64 one group of 32 KB and eight rings of 2.5 KB: three
+// workgroups of 512 threads per CU.)
+__host__ __device__ inline size_t msc_stream_lds(int N, int groups, bool ea, int nw)
 {
-    const size_t ent = (size_t)msc_list_entries(N, groups, nw, mode);
-    const size_t end = (size_t)groups * N * 8 + ent * 20 + (ea ? (size_t)N : 0) + sizeof(int) * 34;
+    const int slots = msc_ring_slots(groups * (N / 2), nw);
+    return 256 + (size_t)groups * N * 8 + (size_t)nw * slots * 20 + (ea ? (size_t)N : 0);
+}
+
+// Otherwise: lattices [groups][N] u64, one list entry per site word of a
+// colour (16 + 4 bytes), bond signs [N] u8 (spin glass only), list counts
+// [34] int.
+__host__ __device__ inline size_t msc_list_lds(int N, int groups, bool ea)
+{
+    const size_t end = (size_t)groups * N * 8 + (size_t)groups * (N / 2) * 20 + (ea ? (size_t)N : 0) + sizeof(int) * 34;
     return (end + 15) & ~(size_t)15;
 }
 
 __host__ __device__ inline size_t msc_lds_need(int N, int groups, bool ea, int nw, int mode)
 {
-    return msc_lds_tmask_off(N, groups, ea, nw, mode) + 16 * 16;
+    return msc_streamed(N, mode) ? msc_stream_lds(N, groups, ea, nw) : msc_list_lds(N, groups, ea);
+}
+
+// What a shape must fit in to be accepted: the larger of the two layouts
+// and 256 bytes (a bound that does not depend on the mode).
+__host__ __device__ inline size_t msc_lds_bound(int N, int groups, bool ea, int nw)
+{
+    const size_t a = msc_stream_lds(N, groups, ea, nw), b = msc_list_lds(N, groups, ea) + 256;
+    return a > b ? a : b;
 }
 
 struct ChunkItem {    // one chunk of CH replicas of one (run, pop)

@@ -83,25 +83,29 @@ __device__ __forceinline__ u32x4 philox10(uint32_t c0, uint32_t c1, uint32_t c2,
 // of round 0 (the replica group and the tag word) and of round 1 (the low
 // half of the product of the temperature index) are the same for every call
 // of a site and often for the whole workgroup, so they are mixed with the key
-// first, as a separate XOR that the compiler moves out of the call loops;
-// rounds 2-9 are those of philox10.  (A chain of independent calls, as in the
-// calibration, is better served by philox10's three-input XORs.)
+// first, as a separate XOR that the compiler moves out of the call loops.
+// With UNIFORM (the replica group c1 is the same on every lane) that holds
+// for one odd word of round 2 as well: the low half of round 1's product of
+// the group.  The other rounds are those of philox10.  (A chain of
+// independent calls, as in the calibration, is better served by philox10's
+// three-input XORs.)
+template <bool UNIFORM>
 __device__ __forceinline__ u32x4 philox10_sweep(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                                 uint32_t k1)
 {
 #pragma unroll
-    for (int round = 0; round < 2; ++round) {
-        const uint32_t x1 = c1 ^ k0, x3 = c3 ^ k1;
+    for (int round = 0; round < (UNIFORM ? 3 : 2); ++round) {
+        const uint32_t x3 = c3 ^ k1;
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        c0 = (uint32_t)(p1 >> 32) ^ x1;
+        c0 = round == 2 ? bop3<LUT_XOR3>((uint32_t)(p1 >> 32), c1, k0) : (uint32_t)(p1 >> 32) ^ (c1 ^ k0);
         c2 = (uint32_t)(p0 >> 32) ^ x3;
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
-    const u32x4 r = philox10_rounds<2>(c0, c1, c2, c3, k0, k1);
+    const u32x4 r = philox10_rounds<UNIFORM ? 3 : 2>(c0, c1, c2, c3, k0, k1);
     return r;
 }
 

@@ -708,3 +708,29 @@ def test_single_size_kernel(L, model, persistent):
         assert_obs_equal(obs[r, :orc.npop], orc.obs(), f"run {r}")
         assert_state_equal(ctx, orc, r, f"run {r} final")
     ctx.close()
+
+
+@pytest.mark.parametrize("L,model,R,threads,groups,dense", [
+    (4, W.FM, 16_500, 512, 256, 3),      # 258 groups of 8 site words: group indices up to 255
+    (6, W.EA_PMJ, 333, 128, 3, 0),       # no lockstep calls: every site goes through the ring
+    (10, W.FM, 2700, 512, 41, 3),
+    (16, W.FM, 700, 1024, 5, 4),         # 640 units on 16 wavefronts: some have none
+    (20, W.EA_PMJ, 200, 256, 1, 3),      # one chunk per wavefront, the last partial
+    (22, W.FM, 500, 64, 7, 5),           # one wavefront, 27 chunks
+    (62, W.EA_PMJ, 130, 512, 1, 3),
+    (62, W.FM, 130, 64, 2, 15),
+    (64, W.FM, 130, 256, 2, 1)])
+def test_streamed_sweep_shapes(L, model, R, threads, groups, dense):
+    """The streamed sweep at the edges of its indexing: sizes without a
+    kernel of their own, chunks that straddle replica groups, wavefronts
+    with one, many or no chunks, rings of 64 and 128 slots, group indices up
+    to the largest; every record and the final state equal the oracle's."""
+    say(f"streamed sweep L={L} model={model} threads={threads} groups={groups} dense={dense}")
+    d = W.run_desc(L, model, seed=W.RUN_SEED_BASE + 0x7400 + L, disorder_seed=9, R=R, theta=2, K=5, beta_f=1.0)
+    ctx = pa.Context([d], "msc")
+    ctx.set_tuning(L, threads, groups, dense)
+    ctx.run(1, 5)
+    orc = oracle.OracleRun(d).run_all()
+    assert_obs_equal(ctx.obs()[0, :1], orc.obs(), f"L={L}")
+    assert_state_equal(ctx, orc, 0, f"L={L} final")
+    ctx.close()
