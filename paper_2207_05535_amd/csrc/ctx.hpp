@@ -80,7 +80,10 @@ inline int n_meas_items_of(const pa_run_desc &d)
     const int gpw = MEAS_WAVES / meas_waves_per_group(d.L * d.L);
     return (groups_cap_of(d) + gpw - 1) / gpw;
 }
-int default_groups(int L);
+int groups_of_2048(int L);   // replica groups whose colours hold about 2048 site words
+// Launch shape of the batched sweep for these runs where nobody has chosen
+// one: threads per workgroup and replica groups per workgroup of each L.
+void default_shape(const pa_run_desc *const *runs, int n, int *threads, std::map<int, int> &groups);
 // Batched-sweep shape for lattice size L from an autotuner cache file.
 bool tuning_from_cache(const char *path, int L, int *threads, int *groups, int *dense, int *persistent,
                        int *pooled);
@@ -109,7 +112,8 @@ struct pa_ctx {
     bool sweep_persistent = false;      // persistent grid with a ticket queue
     bool sweep_pooled = false;          // sparse rounds over one list per workgroup
     int sweep_chunks = 1;               // chunks of sweeps per item on the persistent grid, 0: chosen per plan
-    std::map<int, int> groups_per_wg;   // L -> replica groups per workgroup of the batched sweep
+    std::map<int, int> groups_per_wg;   // L -> replica groups per workgroup of the batched sweep, as set
+    std::map<int, int> default_groups;  // L -> the same where not set
     bool any_multinomial = false;
     bool any_wang = false;
     bool any_exact_dos = false;

@@ -574,11 +574,55 @@ int wang_lds_ints_of(const pa_run_desc *const *runs, int n, int lds_limit)
     return 2 * best;
 }
 
-int default_groups(int L)
+int groups_of_2048(int L)
 {
     const int nh = L * L / 2;
-    int G = (2048 + nh / 2) / nh;
-    return G < 1 ? 1 : (G > 64 ? 64 : G);
+    return std::max(1, std::min(64, (2048 + nh / 2) / nh));
+}
+
+// A wavefront with c chunks of 64 site words per half-sweep makes about
+// 3 c + c + 4 calls' worth of instructions (lockstep calls, queue, the last
+// entries' serial rounds), so few chunks per wavefront cost more work in all
+// and many make a longer chain.  With fewer chunks than SIMDs to run them the
+// chain is all that counts: one chunk per wavefront, no more groups per
+// workgroup than fill one.  With more chunks per SIMD the work counts: two
+// chunks, then four.  Measured (us per launch of ten sweeps, MI355X), against
+// 512 threads of four chunks throughout: L = 8, R = 1000 41 against 57;
+// L = 16, R = 20000 48-55 / 129; L = 20, R = 5003 51 / 137 (0.01-0.6 chunks
+// per SIMD); L = 32, R = 20000 82 / 132; L = 16, R = 1e5 83 / 131; L = 32,
+// R = 5e4 124 / 134; L = 8, R = 1e6 127 / 134 (2.5-8; one chunk measures 83,
+// 86, 142, 147 there); L = 16, R = 1e6 354 / 374; L = 32, R = 4e5 525 / 561
+// (30-50; two chunks measure 379 and 548).  Above 512 threads only
+// the single-chunk shapes gain (L = 64, R = 2000: 126 against 130).
+void default_shape(const pa_run_desc *const *runs, int n, int *threads, std::map<int, int> &groups)
+{
+    std::map<int, double> chunks;   // L -> chunks of 64 site words per half-sweep
+    double total = 0.0;
+    for (int r = 0; r < n; ++r) {
+        const pa_run_desc &d = *runs[r];
+        const double c = (double)n_pop_of(d.overlap) * groups_cap_of(d) * (d.L * d.L / 2) / 64.0;
+        chunks[d.L] += c;
+        total += c;
+    }
+    constexpr double SIMDS = 1024.0;
+    const int c = total < 2.0 * SIMDS ? 1 : (total < 12.0 * SIMDS ? 2 : 4);
+    const int aim = 64 * c * (c == 1 ? 1 : 4);   // units per workgroup
+    int heavy = 0;
+    double most = -1.0;
+    groups.clear();
+    for (const auto &kv : chunks) {
+        const int nh = kv.first * kv.first / 2;
+        groups[kv.first] = std::max(1, std::min(256, aim / nh));
+        if (kv.second > most) {
+            most = kv.second;
+            heavy = kv.first;
+        }
+    }
+    const int waves = (groups[heavy] * (heavy * heavy / 2) + 64 * c - 1) / (64 * c);   // of the heaviest size
+    int t = 64;
+    while (t < 64 * waves && t < (c == 1 ? 1024 : 512)) t *= 2;
+    if (c > 1 && t > 64 && 3 * t > 4 * 64 * waves) t /= 2;   // nearer the power of two below
+    *threads = t;
 }
 
 pa_status dev_fail(pa_ctx *c, hipError_t e)
@@ -592,7 +636,9 @@ pa_status dev_fail(pa_ctx *c, hipError_t e)
 int groups_for(const pa_ctx *c, int L)
 {
     auto it = c->groups_per_wg.find(L);
-    return it == c->groups_per_wg.end() ? default_groups(L) : it->second;
+    if (it != c->groups_per_wg.end()) return it->second;
+    const auto d = c->default_groups.find(L);
+    return d == c->default_groups.end() ? groups_of_2048(L) : d->second;
 }
 
 // Work list and LDS size of the batched sweep for the current tuning.
@@ -837,6 +883,11 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&c->lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
             return fail(PA_ERR_DEVICE);
+    }
+    {
+        std::vector<const pa_run_desc *> dp(n_runs);
+        for (int r = 0; r < n_runs; ++r) dp[r] = &c->descs[r];
+        default_shape(dp.data(), n_runs, &c->sweep_threads, c->default_groups);
     }
     if (repr == PA_MSC64) {
         std::vector<SweepItem> probe;

@@ -165,7 +165,9 @@ struct pa_server {
     int lds_limit = 65536;
     int threads = 512, dense = 3;
     bool persistent = false, pooled = false;
-    std::map<int, int> groups;
+    std::map<int, int> groups;          // L -> groups per workgroup, from the cache
+    bool shaped = false;                // the shape comes from the cache
+    std::map<int, int> resident_groups; // else: L -> the same for the resident runs
     bool failed = false;
     hipError_t last = hipSuccess;
 };
@@ -216,7 +218,9 @@ int serve_mode(const pa_server *s)
 int groups_of(const pa_server *s, int L)
 {
     auto it = s->groups.find(L);
-    return it == s->groups.end() ? default_groups(L) : it->second;
+    if (it != s->groups.end()) return it->second;
+    it = s->resident_groups.find(L);
+    return it == s->resident_groups.end() ? groups_of_2048(L) : it->second;
 }
 
 // Regrows a work-list region to hold `need` bytes (doubling).  The old
@@ -247,6 +251,12 @@ pa_status rebuild(pa_server *s)
     bool mn = false, wang = false, exact = false, mn_wide = false, ovl = false;
     std::vector<SweepItem> sweep;
     size_t lds = 0;
+    if (!s->shaped && s->repr == PA_MSC64) {
+        std::vector<const pa_run_desc *> dp;
+        for (const Slot &sl : s->slots)
+            if (sl.used) dp.push_back(&sl.d);
+        if (!dp.empty()) default_shape(dp.data(), (int)dp.size(), &s->threads, s->resident_groups);
+    }
     for (int k = 0; k < s->max_slots; ++k) {
         const Slot &sl = s->slots[k];
         if (!sl.used) continue;
@@ -419,6 +429,7 @@ pa_status pa_server_create(pa_repr repr, void *dev_arena, size_t arena_bytes, in
         for (int L = 4; L <= 128; L += 2)
             if (tuning_from_cache(tuning_cache, L, &th, &g, &dn, &pe, &po)) {
                 s->groups[L] = g;
+                s->shaped = true;
                 if (L == 64 || s->groups.size() == 1) {   // shared knobs: from L = 64 when present
                     s->threads = th;
                     s->dense = dn;
@@ -455,9 +466,10 @@ pa_status pa_server_admit(pa_server *s, const pa_run_desc *desc, int32_t *slot)
     if (k == s->max_slots) return PA_ERR_CAPACITY;
     const pa_run_desc &d = *desc;
     if (s->repr == PA_MSC64) {
-        const int N = d.L * d.L, G = groups_of(s, d.L);
+        const auto it = s->groups.find(d.L);
+        const int N = d.L * d.L, G = it != s->groups.end() ? it->second : groups_of_2048(d.L);
         if ((size_t)G * N > 65535 ||
-            msc_lds_bound(N, G, d.model == PA_EA_PMJ, s->threads / 64) > (size_t)s->lds_limit)
+            msc_lds_bound(N, G, d.model == PA_EA_PMJ, (s->shaped ? s->threads : 512) / 64) > (size_t)s->lds_limit)
             return PA_ERR_ARG;
     }
     const int N = d.L * d.L;
