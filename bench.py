@@ -15,8 +15,8 @@ updates, sum over steps of theta * R_i * N.
 Headline value: the batched path (64 replicas bit-packed per word, lattice
 held in LDS for all theta sweeps, every kernel of a step captured in one HIP
 graph and replayed; launch shapes from the autotuner).  Reported beside it:
-the plain path (int8 spins, one colour of one run per launch, host-driven
-steps) on the same workload, whose records must equal the batched path's bit
+the plain path (int8 spins, bytes packed into words for the sweeps and back,
+host-driven steps) on the same workload, whose records must equal the batched path's bit
 for bit; the dominant kernel's ALU roofline; and the CPU oracle on a bounded
 sample.
 
@@ -53,13 +53,12 @@ PEAK_LANE_OPS = 256 * 64 * 2.4e9
 # Algorithmic 32-bit VALU operations of the bit-sliced Metropolis update
 # (each 64-bit word operation counts as two):
 # one Philox4x32-10 call = 10 rounds x (2 v_mad_u64_u32 + 2 three-input XORs)
-# = 40, plus two bit planes of the most-significant-first comparison
-# (select, win, tie, or: 4 per 32-bit half) = 16, so 56 per call; one site
-# update of a 64-replica word (four neighbour XORs, the two bond-count
-# classes, the flip and the undecided mask) = 28.
-OPS_PER_CALL = 56
-OPS_PER_WORD = 28
-HBM_PEAK_GBS = 8000.0
+# = 40, plus two bit planes of the most-significant-first comparison (two
+# thresholds' bits, two ties, verdict, merge: 6 per 32-bit half) = 12, so 52
+# per call; one site update of a 64-replica word (sum and majority of three
+# neighbours, the two classes in three, the flips in two: 7 per half) = 14.
+OPS_PER_CALL = 52
+OPS_PER_WORD = 14
 
 
 def log(msg):
@@ -278,8 +277,7 @@ def roofline_of(b, steps):
 
 
 def run_plain(desc, timed, warmup, obs_ref):
-    """The plain path (int8, one colour of one run per launch, host-driven
-    steps) on the same temperature steps as the batched path: each timed
+    """The plain path (int8 spins, host-driven steps) on the same temperature steps as the batched path: each timed
     step from a checkpoint of an untimed pass (consecutive steps in one
     interval); its records must equal the batched path's bit for bit."""
     import numpy as np
@@ -800,28 +798,16 @@ def headline(desc, steps, warmup, args, only):
     line["roofline"]["philox_calls_per_s"] = cal
     if not args.no_plain and "plain" in only:
         p = run_plain(desc, timed, warmup, b["obs"][0, 0])
-        N = desc["L"] ** 2
-        plain_sweep_avg = sum(p["sweep_ms"]) / len(p["sweep_ms"]) / 1e3 / (2 * desc["theta"])
-        # algorithmic bytes per int8 colour launch: 2 bytes per attempted
-        # flip (read and write the updated spin), N / 2 sites of R replicas
-        bytes_launch = 2.0 * (N // 2) * desc["R"]
-        # what any one-colour launch must move at least: every spin byte of
-        # the run (the colour and its neighbours), then the updated colour
-        floor_launch = 1.5 * N * desc["R"]
-        traffic_int8 = measured_traffic("k_sweep_int8", 1)
+        # step (iv) of a temperature step: bytes to words, the sweeps, back
+        plain_sweep_avg = sum(p["sweep_ms"]) / len(p["sweep_ms"]) / 1e3
         line["plain_int8"] = {
             "flips_per_ns": round(b["flips"] / p["wall_s"] / 1e9, 3),
             "ms_per_step": round(p["wall_s"] * 1e3 / steps, 4),
-            "sweep_launch_avg_ms": round(plain_sweep_avg * 1e3, 4),
-            "sweep_hbm_GBps": round(bytes_launch / plain_sweep_avg / 1e9, 1),
-            "sweep_hbm_frac": round(bytes_launch / plain_sweep_avg / 1e9 / HBM_PEAK_GBS, 4),
-            "one_colour_floor_GBps": round(floor_launch / plain_sweep_avg / 1e9, 1),
-            "traffic": traffic_int8,
-            "traffic_GBps": (round(traffic_int8 / plain_sweep_avg / 1e9, 1) if traffic_int8 else None),
-            # the same Philox and site-update work as the batched sweep, per
-            # colour launch, against the integer-VALU peak
+            "sweep_avg_ms": round(plain_sweep_avg * 1e3, 4),
+            # the same Philox and site-update work as the batched sweep,
+            # against the integer-VALU peak
             "sweep_alu_frac": round((OPS_PER_CALL * p["calls"] + OPS_PER_WORD * p["words"])
-                                    / (steps * 2 * desc["theta"]) / plain_sweep_avg / PEAK_LANE_OPS, 4),
+                                    / steps / plain_sweep_avg / PEAK_LANE_OPS, 4),
             "bit_exact_vs_batched": p["bit_exact"],
         }
         line["batched_over_plain"] = round(p["wall_s"] / b["wall_s"], 3)

@@ -218,9 +218,10 @@ pa_status pa_anneal_step(pa_ctx *ctx, int32_t i);
 pa_status pa_resample(pa_ctx *ctx, int32_t i);
 
 /* Step (iv): theta checkerboard single-spin-flip Metropolis sweeps at beta_i
- * (Sec. V A 1).  PA_INT8 contexts launch one colour of one run at a time;
- * PA_MSC64 contexts update every run in one launch with the lattice held in
- * on-chip memory for all theta sweeps. */
+ * (Sec. V A 1).  Every run is updated in one launch with the lattice held in
+ * on-chip memory for all theta sweeps; PA_INT8 contexts pack their bytes into
+ * words before it and unpack them after it, and sweep lattices too large for
+ * that (or a few large ones) from memory, one colour of one run per launch. */
 pa_status pa_sweep(pa_ctx *ctx, int32_t i);
 
 /* Step (v): energies, magnetisations, overlaps and family sizes at beta_i.

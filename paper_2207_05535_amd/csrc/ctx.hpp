@@ -63,7 +63,7 @@ void compute_tables(const pa_run_desc &d, int N, std::vector<uint64_t> &X, std::
                     std::vector<uint64_t> &T);
 // RunInfo of a run whose buffers start at `base` (offsets o) and tables at
 // `tbase` (offsets T); records through obs with the given stride/offset.
-RunInfo make_runinfo(const pa_run_desc &d, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
+RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
                      pa_obs *obs, int obs_stride, int obs_off);
 PopState initial_popstate(const pa_run_desc &d);
 // LDS ints of the permutation-pairing repair: 2 R_cap of the largest such
@@ -113,7 +113,9 @@ struct pa_ctx {
     bool sweep_pooled = false;          // sparse rounds over one list per workgroup
     int sweep_chunks = 1;               // chunks of sweeps per item on the persistent grid, 0: chosen per plan
     std::map<int, int> groups_per_wg;   // L -> replica groups per workgroup of the batched sweep, as set
+    std::vector<pa::WideRun> wide;      // int8 layout: runs swept one colour per launch
     std::map<int, int> default_groups;  // L -> the same where not set
+    int bytes_threads = 512;            // int8 layout: threads of its sweeps (always the default shape)
     bool any_multinomial = false;
     bool any_wang = false;
     bool any_exact_dos = false;
@@ -140,6 +142,10 @@ pa_status dev_fail(pa_ctx *c, hipError_t e = hipSuccess);
 int groups_for(const pa_ctx *c, int L);
 bool plan_sweep(const pa_ctx *c, std::vector<SweepItem> &items, size_t &lds);
 pa_status upload_sweep_plan(pa_ctx *c);
+// int8 layout: whether a run is swept from memory, one colour per launch,
+// rather than in LDS with `groups` groups per workgroup of `threads`.
+bool sweeps_wide(const pa_run_desc &d, int groups, int threads, int lds_limit);
+hipError_t launch_sweeps(const pa_ctx *c);
 pa_status enqueue_step(pa_ctx *c);
 void drop_graph(pa_ctx *c);
 pa_status read_stats(pa_ctx *c, uint64_t out[3]);   // sums the counter slots; synchronises

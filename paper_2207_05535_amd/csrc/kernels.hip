@@ -5,10 +5,11 @@
 // Step (ii)  k_rw_chunk, k_rw_finish                   (Eqs. (QBoltz), (F))
 // Step (iii) k_cnt_chunk, k_mn_draws, k_cnt_scan_chunk, k_cnt_finish,
 //            k_parent, k_copy                          (Sec. II B, IV D, V A 1)
-// Step (iv)  k_sweep_int8 (one colour of one run per launch),
-//            k_sweep_msc (all runs, lattice in LDS for all theta sweeps;
-//            also compiled per lattice size and model), k_dos_sample (the
-//            theta = infinity limit, Sec. V C)
+// Step (iv)  k_sweep_msc (all runs, lattice in LDS for all theta sweeps;
+//            also compiled per lattice size and model), k_sweep_wide (one
+//            colour of one run per launch, from memory), k_bytes_words (the
+//            int8 layout to words and back), k_dos_sample (the theta =
+//            infinity limit, Sec. V C)
 // Step (v)   k_wang_pairs, k_wang_rows, k_wang_gather (permutation pairing,
 //            Sec. III D), k_measure, k_meas_chunk, k_finalize
 //                                                      (Eqs. (e)-(chi), Sec. III D)
@@ -901,141 +902,61 @@ __device__ __forceinline__ void flush_stats(unsigned long long *stats, uint64_t 
 
 __device__ __forceinline__ uint64_t jmask(uint8_t b, int bit) { return ((b >> bit) & 1u) ? ~0ull : 0ull; }
 
-// Plain path: one colour of one run per launch, int8 spins ([group][site][64
-// replicas] bytes).  A workgroup takes `rows` lattice rows of one replica
-// group, plus one halo row on each side unless it holds the whole lattice.
-// All of its 16-byte chunks are loaded first (consecutive lanes take
-// consecutive chunks, so the loads coalesce and are all in flight at once),
-// their sign bits are packed into an LDS bit-lattice (one 64-bit word per
-// site), the colour's sites are updated from the packed words, and the
-// chunks that change are rebuilt from their signs and stored.
-constexpr int I8_CMAX = 12;   // 16-byte chunks held per thread
-
-// Rows per workgroup of the plain sweep: the whole lattice if its chunks fit
-// in `threads` threads' registers, else the largest divisor T of L whose
-// T + 2 rows (with halos) fit.
-constexpr int int8_rows_for(int L, int threads)
+// Configurations of a population as bit-packed words ([group][site], 64
+// replicas each): the population itself in the bit-packed layout; in the int8
+// layout ([group][site][64 replicas] bytes) a copy in the idle spin buffer
+// that the sweeps work on and the measurement reads (the second eighth of it:
+// the first holds the permutation pairing's partner words).
+__device__ __forceinline__ uint64_t *words_of(const RunInfo &R, const PopState &S, int pop)
 {
-    const int cap = threads * I8_CMAX;
-    if (L * L * 4 <= cap) return L;
-    int best = 1;
-    for (int T = 1; T < L; ++T)
-        if (L % T == 0 && (T + 2) * L * 4 <= cap) best = T;
-    return best;
+    return R.bytes ? (uint64_t *)R.spins[pop][S.cur ^ 1] + (size_t)R.groups_cap * R.N
+                   : (uint64_t *)R.spins[pop][S.cur];
 }
 
-template <int LT, int THREADS>
-__device__ __forceinline__ void sweep_int8_tile(const RunInfo &R, const PopState &S, int pop, int g, int tile,
-                                                int s, int colour, int T, uint64_t *sm, unsigned long long *stats)
+// The words of the int8 layout are current from a step's sweeps until its
+// population is resampled.
+__device__ __forceinline__ bool words_current(const RunInfo &R, const PopState &S)
 {
-    const int L = LT ? LT : R.L;
-    const int N = L * L, half = L >> 1;
-    const int Rc = S.Rcur;
-    const int y0 = tile * T;
-    const int rows = min(T, L - y0);
-    const int halo = rows == L ? 0 : 1;
-    const int nrow = rows + 2 * halo;
-    constexpr int nthr = THREADS;
-    const int tid = threadIdx.x;
-    uint64_t *packed = sm;                              // [nrow][L]
-    uint64_t *fm = sm + (size_t)nrow * L;               // [rows][half]
-    uint16_t *pk16 = (uint16_t *)packed;
-    uint8_t *base = R.spins[pop][S.cur] + (size_t)g * N * 64;
-    const int i = S.i;
-    const Thresholds Th = thresholds_of(R.tabT, i);
-    const uint32_t key0 = R.key0, key1 = R.key1;
-    const uint8_t *jbits = R.jbits;
-    const int chunks = nrow * L * 4;
-    uint4 reg[I8_CMAX];
-    // byte offset of chunk c inside the group's N * 64 bytes
-    auto off_of = [&](int c) {
-        const int site = c >> 2, part = c & 3;
-        const int rr = site / L, x = site - rr * L;
-        int y = y0 - halo + rr;
-        y = y < 0 ? y + L : (y >= L ? y - L : y);
-        return (uint32_t)(y * L + x) * 64u + (uint32_t)part * 16u;
-    };
-    // Every load is issued before the first use, with no branch around any
-    // of them (a branch would make each load wait for its registers at the
-    // join): lanes past the last chunk load that chunk again, in bounds.  For
-    // a lattice size known here the tile and so the number of loads per
-    // thread are compile-time constants.
-    constexpr int QN = LT ? (((LT == int8_rows_for(LT, THREADS) ? LT : int8_rows_for(LT, THREADS) + 2) * LT * 4 +
-                              THREADS - 1) / THREADS)
-                          : I8_CMAX;
-    static_assert(QN <= I8_CMAX, "tile chunks exceed the registers held per thread");
+    return !R.bytes || (R.theta > 0 && S.i > 0);
+}
+
+// int8 layout: a population's bytes to its words and back, around the sweeps.
+// A thread takes 16-byte chunks (16 replicas of one site) at consecutive
+// addresses; a workgroup WORDS_SEG sites of one replica group.  Bound by
+// memory: 72 bytes per site and group of 64 replicas either way.  (The byte
+// layout was swept in place before, one colour per launch: 608 us for ten
+// sweeps at L = 64, R = 2e4, where conversions and sweeps take 219.)
+constexpr int WORDS_SEG = 1024;
+
+template <bool TO_WORDS>
+__global__ void __launch_bounds__(256) k_bytes_words(const Item *items, const RunInfo *runs, const PopState *st)
+{
+    const Item it = items[blockIdx.x];
+    const RunInfo &R = runs[it.run];
+    const PopState &S = st[it.run * MAX_POP + it.pop];
+    const int n0 = blockIdx.y * WORDS_SEG;
+    if (!pop_active(S) || R.theta == 0 || it.group * 64 >= S.Rcur || n0 >= R.N) return;
+    const int chunks = 4 * min(WORDS_SEG, R.N - n0);
+    uint4 *bytes = (uint4 *)(R.spins[it.pop][S.cur] + ((size_t)it.group * R.N + n0) * 64);
+    uint16_t *words = (uint16_t *)(words_of(R, S, it.pop) + (size_t)it.group * R.N + n0);
+    // the chunks of a round in flight together, with no branch around a load
+    constexpr int U = 4;
+    for (int c0 = threadIdx.x; c0 < chunks; c0 += 256 * U) {
+        if constexpr (TO_WORDS) {
+            uint4 v[U];
 #pragma unroll
-    for (int q = 0; q < QN; ++q)
-        reg[q] = *(const uint4 *)(base + off_of(min(tid + q * nthr, chunks - 1)));
+            for (int u = 0; u < U; ++u) v[u] = bytes[min(c0 + 256 * u, chunks - 1)];
 #pragma unroll
-    for (int q = 0; q < I8_CMAX; ++q) {
-        const int c = tid + q * nthr;
-        if (c < chunks) pk16[c] = (uint16_t)signs16(reg[q]);
-    }
-    __syncthreads();
-    const uint32_t c3 = (TAG_SWEEP << 28) | ((uint32_t)pop << 24) | (uint32_t)s;
-    const uint64_t valid = (Rc - g * 64 >= 64) ? ~0ull : ((1ull << (Rc - g * 64)) - 1);
-    const uint32_t lanes = (uint32_t)__popcll(valid);
-    uint32_t nwords = 0, ncalls = 0;
-    for (int idx = tid; idx < rows * half; idx += nthr) {
-        const int yy = idx / half, m = idx - yy * half;
-        const int y = y0 + yy;
-        const int x = 2 * m + ((y + colour) & 1);
-        const int n = y * L + x;
-        const int xr = x + 1 == L ? 0 : x + 1, xl = x == 0 ? L - 1 : x - 1;
-        const int yu = y == 0 ? L - 1 : y - 1;
-        const int rc = yy + halo;
-        const int rd = halo ? rc + 1 : (rc + 1 == L ? 0 : rc + 1);
-        const int ru = halo ? rc - 1 : (rc == 0 ? L - 1 : rc - 1);
-        const uint64_t w = packed[rc * L + x];
-        const uint8_t jn = jbits[n];
-        fm[idx] = flip_mask(w, packed[rc * L + xr] ^ jmask(jn, 0), packed[rc * L + xl] ^ jmask(jbits[y * L + xl], 0),
-                            packed[rd * L + x] ^ jmask(jn, 1), packed[ru * L + x] ^ jmask(jbits[yu * L + x], 1),
-                            Th, valid, (uint32_t)n, (uint32_t)g, (uint32_t)i, c3, key0, key1, ncalls);
-        ++nwords;
-    }
-    __syncthreads();
-    // Store: one 16-byte chunk of a colour site per lane step (idx as in the
-    // update loop).  Spins are the canonical bytes +1 = 0x01, -1 = 0xFF, so a
-    // chunk is rebuilt from its packed sign bits and flips; the registers that
-    // held the loads are free during the update.
-    for (int k = tid; k < rows * half * 4; k += nthr) {
-        const int idx = k >> 2, part = k & 3;
-        const uint32_t f = (uint32_t)(fm[idx] >> (16 * part)) & 0xFFFFu;
-        if (f) {
-            const int yy = idx / half, m = idx - yy * half;
-            const int y = y0 + yy;
-            const int x = 2 * m + ((y + colour) & 1);
-            const uint32_t b = f ^ (uint32_t)pk16[((yy + halo) * L + x) * 4 + part];
-            const uint4 v = spins16(b);
-            *(uint4 *)(base + (uint32_t)(y * L + x) * 64u + (uint32_t)part * 16u) = v;
+            for (int u = 0; u < U; ++u)
+                if (c0 + 256 * u < chunks) words[c0 + 256 * u] = (uint16_t)signs16(v[u]);
+        } else {
+            uint32_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = words[min(c0 + 256 * u, chunks - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (c0 + 256 * u < chunks) bytes[c0 + 256 * u] = spins16(v[u]);
         }
-    }
-    flush_stats(stats, nwords, ncalls, nwords * lanes);
-}
-
-// THREADS: the workgroup size it is launched with (256, or 1024 for very
-// large lattices); the bound lets the 256-thread form keep its chunks and
-// the Philox state in registers instead of spilling them to scratch.
-template <int THREADS>
-__global__ void __launch_bounds__(THREADS) k_sweep_int8(const RunInfo *runs, const PopState *st, int run, int pop,
-                                                        int s, int colour, int T, int ntiles,
-                                                        unsigned long long *stats)
-{
-    extern __shared__ uint64_t sm[];
-    const RunInfo &R = runs[run];
-    const PopState &S = st[run * MAX_POP + pop];
-    if (!pop_active(S)) return;
-    const int g = blockIdx.x / ntiles, tile = blockIdx.x - g * ntiles;
-    if (g * 64 >= S.Rcur) return;
-    switch (R.L) {
-    case 8: sweep_int8_tile<8, THREADS>(R, S, pop, g, tile, s, colour, T, sm, stats); break;
-    case 16: sweep_int8_tile<16, THREADS>(R, S, pop, g, tile, s, colour, T, sm, stats); break;
-    case 24: sweep_int8_tile<24, THREADS>(R, S, pop, g, tile, s, colour, T, sm, stats); break;
-    case 32: sweep_int8_tile<32, THREADS>(R, S, pop, g, tile, s, colour, T, sm, stats); break;
-    case 48: sweep_int8_tile<48, THREADS>(R, S, pop, g, tile, s, colour, T, sm, stats); break;
-    case 64: sweep_int8_tile<64, THREADS>(R, S, pop, g, tile, s, colour, T, sm, stats); break;
-    default: sweep_int8_tile<0, THREADS>(R, S, pop, g, tile, s, colour, T, sm, stats); break;
     }
 }
 
@@ -1051,14 +972,12 @@ __global__ void __launch_bounds__(THREADS) k_sweep_int8(const RunInfo *runs, con
 //    0 .. dense-1 in lockstep; nearly every site needs that many, so few
 //    lanes idle;
 //  - sparse rounds: the sites still undecided are kept in a wave-private LDS
-//    list.  For lattices of at most 4096 sites the list is a queue
-//    (stream_item): a ring whose entries are the site's next Philox counter
-//    word itself (site, replica group within the workgroup, call index), and
-//    every round takes the next 64 entries whatever call each is at.
-//    Otherwise (general_item: larger lattices, 16 lockstep calls, or lists
-//    pooled over the workgroup) the list is compacted in place after every
-//    call index.  Either way the calls run on full wavefronts until the last
-//    entries.
+//    list.  It is a queue (stream_item) whose entries are the site's next
+//    Philox counter word itself, and every round takes the next 64 entries
+//    whatever call each is at; or (general_item: several groups of a lattice
+//    above 4096 sites, 16 lockstep calls, or lists pooled over the workgroup)
+//    the list is compacted in place after every call index.  Either way the
+//    calls run on full wavefronts until the last entries.
 // Every site's result is still the plain most-significant-first comparison
 // of its own bit planes; only the order of the work changes.
 
@@ -1321,7 +1240,7 @@ __device__ __forceinline__ bool sweep_job(const SweepItem &item, const RunInfo &
     const int upw = msc_units_per_wave(J.units, blockDim.x >> 6);
     J.ub = min(J.units, wave_id() * upw);
     J.ue = min(J.units, J.ub + upw);
-    J.base = (uint64_t *)R.spins[pop][S.cur] + (size_t)J.group0 * J.N;
+    J.base = words_of(R, S, pop) + (size_t)J.group0 * J.N;
     return true;
 }
 
@@ -1435,98 +1354,193 @@ __device__ __forceinline__ void item_stats(const SweepJob &J, uint32_t wcalls, u
     flush_stats(stats, first ? nwords : 0ull, first ? wcalls : 0u, first ? nflips : 0ull);
 }
 
-// The sweeps of a streamed item.  Each wavefront's queue of undecided sites
-// is a ring of `slots` entries of its own; an entry's word is the counter
-// word of its next call, site | call << 20, with the group's index within the
-// workgroup between them (bits 12 .. 19) unless the workgroup holds one
-// group (ONE).  A site's place among its colour is site >> 1, so the lattice
-// word follows from the counter word.
+// A wavefront's queue of undecided sites: a ring of `slots` entries (a power
+// of two).  An entry's word is the counter word of its next call, site |
+// call << 20, with the replica group's index within the workgroup between
+// them (bits 12 .. 19, sites below 4096) unless the wavefront's sites are all
+// of one group (ONE).  Every round takes the next 64 entries whatever call
+// each is at, makes that call and appends the sites still undecided, so the
+// rounds run on full wavefronts until at most 64 entries are left.
+struct Stream {
+    UndPair *eu;
+    uint32_t *en;
+    const PlaneMasks *tmask;   // T's bits at the planes of each call
+    int slots;
+    uint32_t i, c3, key0, key1;
+    int hs = 0, ts = 0, left = 0;   // slot of the head, slot of the tail, entries
+};
+
+constexpr uint32_t ENTRY_CALL = 1u << 20;        // the call index's unit
+constexpr uint32_t ENTRY_LAST = 15u << 20;       // last call
+constexpr uint32_t ENTRY_SITE = 0xFFFu;          // site where entries carry a group
+
+template <bool UNIFORM>
+__device__ __forceinline__ uint64_t stream_call(const Stream &q, uint32_t c0, uint32_t g, const PlaneMasks &m,
+                                                uint64_t one, uint64_t &und)
+{
+    const u32x4 o = philox10_sweep<UNIFORM>(c0, g, q.i, q.c3, q.key0, q.key1);
+    return plane_pair((uint64_t)o.x | ((uint64_t)o.y << 32), (uint64_t)o.z | ((uint64_t)o.w << 32), m, one, und);
+}
+
+__device__ __forceinline__ void stream_push(Stream &q, uint64_t und, uint64_t one, uint32_t pk)
+{
+    const uint64_t need = wave_ballot(und != 0);
+    if (und != 0) {
+        const int out = (rank_below(need, 0) + q.ts) & (q.slots - 1);
+        und_store(&q.eu[out], und, one);
+        q.en[out] = pk;
+    }
+    const int nn = __popcll(need);
+    q.ts = (q.ts + nn) & (q.slots - 1);
+    q.left += nn;
+}
+
+// Full rounds while more than 64 entries wait.  word(pk): where an entry's
+// flips go (LDS); group(pk): its replica group.
+template <bool ONE, class Word, class Group>
+__device__ __forceinline__ void stream_rounds(Stream &q, Word word, Group group, uint32_t &wcalls)
+{
+    const int lane = threadIdx.x & 63;
+    while (q.left > 64) {
+        const int slot = (q.hs + lane) & (q.slots - 1);
+        uint64_t und, one;
+        und_load(&q.eu[slot], und, one);
+        const uint32_t pk = q.en[slot];
+        const uint64_t was = und;
+        const uint64_t less = stream_call<ONE>(q, ONE ? pk : pk & (ENTRY_LAST | ENTRY_SITE), group(pk),
+                                               q.tmask[pk >> 20], one, und);
+        flip_word(word(pk), bop3<LUT_ANDN2>(less, was, und));
+        wcalls += 64;
+        const bool more = und != 0 && pk < ENTRY_LAST;
+        // the two compares' masks, combined on the scalar unit
+        const uint64_t need = wave_ballot(und != 0) & wave_ballot(pk < ENTRY_LAST);
+        if (more) {
+            const int out = (rank_below(need, 0) + q.ts) & (q.slots - 1);
+            und_store(&q.eu[out], und, one);
+            q.en[out] = pk + ENTRY_CALL;
+        }
+        const int nn = __popcll(need);
+        q.ts = (q.ts + nn) & (q.slots - 1);
+        q.hs = (q.hs + 64) & (q.slots - 1);
+        q.left += nn - 64;
+    }
+}
+
+// The last (at most 64) entries: each lane runs all the remaining calls of
+// its own entry.
+template <bool ONE, class Word, class Group>
+__device__ __forceinline__ void stream_tail(const Stream &q, uint64_t *any, Word word, Group group, uint32_t &wcalls)
+{
+    const int lane = threadIdx.x & 63;
+    uint64_t und = 0, one = 0, acc = 0;
+    uint32_t pk = ~0u;
+    uint64_t *w = any;   // lanes without an entry flip nothing there
+    if (lane < q.left) {
+        const int slot = (q.hs + lane) & (q.slots - 1);
+        und_load(&q.eu[slot], und, one);
+        pk = q.en[slot];
+        w = word(pk);
+    }
+    const uint64_t drew = und;
+    const uint32_t g = group(pk);
+    for (;;) {
+        const bool live = und != 0 && pk < ENTRY_LAST + ENTRY_CALL;
+        const uint64_t lv = wave_ballot(und != 0) & wave_ballot(pk < ENTRY_LAST + ENTRY_CALL);
+        if (lv == 0) break;
+        wcalls += (uint32_t)__popcll(lv);
+        if (live) {
+            const uint64_t was = und;
+            const uint64_t less =
+                stream_call<ONE>(q, ONE ? pk : pk & (ENTRY_LAST | ENTRY_SITE), g, q.tmask[pk >> 20], one, und);
+            acc = bop3<LUT_SEL>(was, less, acc);
+            pk += ENTRY_CALL;
+        }
+    }
+    flip_word(w, bop3<LUT_ANDN2>(acc, drew, und));
+}
+
+// Masks of the first calls; one of each pair in a vector register (an
+// instruction reads one scalar operand), where the compiler would otherwise
+// copy it again for every call.
+struct LockstepMasks {
+    PlaneMasks m[4];
+    __device__ __forceinline__ LockstepMasks(const Thresholds &Th)
+    {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            m[c] = call_masks(Th.t4, Th.t8, (uint32_t)c);
+            asm volatile("" : "+v"(m[c].a8), "+v"(m[c].b8));
+        }
+    }
+};
+
+// Calls 0 .. dense-1 of one site per lane, without branches or lane masks (a
+// decided lane's call changes nothing): und keeps the undecided, the
+// verdicts of the others go to acc.
+template <bool UNIFORM>
+__device__ __forceinline__ void lockstep_calls(const Stream &q, int dense, const LockstepMasks &dm,
+                                               const Thresholds &Th, uint32_t n, uint32_t g, uint64_t one,
+                                               uint64_t &und, uint64_t &acc, uint32_t &wcalls)
+{
+    auto call = [&](uint32_t c, const PlaneMasks &m) {
+        wcalls += (uint32_t)__popcll(wave_ballot(und != 0));
+        const uint64_t was = und;
+        const uint64_t less = stream_call<UNIFORM>(q, n | (c << 20), g, m, one, und);
+        acc = bop3<LUT_SEL>(was, less, acc);
+    };
+    if (dense > 0) call(0, dm.m[0]);
+    if (dense > 1) call(1, dm.m[1]);
+    if (dense > 2) call(2, dm.m[2]);
+    if (dense > 3) call(3, dm.m[3]);
+    for (int c = 4; c < dense; ++c) call((uint32_t)c, call_masks(Th.t4, Th.t8, (uint32_t)c));
+}
+
+// The sweeps of a streamed item.  A site's place among its colour is
+// site >> 1, so an entry's lattice word follows from its counter word.
 //
 // Bound by the vector ALU's issue rate (at L = 64 it issues in 97 % of the
 // slots while the CU has work), so everything here is counted in
-// instructions: the lockstep calls run without branches or lane masks (a
-// decided lane's call changes nothing) on masks held in registers, a chunk
-// of whole rows finds its neighbours at constant offsets, the entry word
-// needs no unpacking.  Against a form with a branch and an exec mask per
-// call, divisions per chunk for the sizes without a kernel of their own, and
-// one kernel body per size in the dispatching kernel (100 registers instead
-// of 61, so two workgroups per CU instead of three), per launch: L = 64,
-// R = 1e5 576 -> 531 us (2.76e8 instead of 3.08e8 vector instructions); two
-// populations of 2e5 at L = 32 657 -> 570; 1024 runs of four sizes 1520 ->
-// 1297; ten spin-glass runs of five sizes 1765 -> 1604; R = 1e5 at L = 20
-// 184 -> 144; 3840 runs at L = 10 322 -> 166.
+// instructions: the lockstep calls run without branches or lane masks on
+// masks held in registers, a chunk of whole rows finds its neighbours at
+// constant offsets, the entry word needs no unpacking.  Against a form with a
+// branch and an exec mask per call, divisions per chunk for the sizes without
+// a kernel of their own, and one kernel body per size in the dispatching
+// kernel (100 registers instead of 61, so two workgroups per CU instead of
+// three), per launch: L = 64, R = 1e5 576 -> 531 us (2.76e8 instead of 3.08e8
+// vector instructions); two populations of 2e5 at L = 32 657 -> 570; 1024
+// runs of four sizes 1520 -> 1297; ten spin-glass runs of five sizes 1765 ->
+// 1604; R = 1e5 at L = 20 184 -> 144; 3840 runs at L = 10 322 -> 166.
 template <int LT, bool EA, bool ONE>
 __device__ __forceinline__ uint32_t stream_sweeps(const SweepJob &J, uint64_t *lat, UndPair *eu, uint32_t *en,
                                                   const uint8_t *jb, const PlaneMasks *tmask, int slots, int dense)
 {
     const int L = LT > 0 ? LT : J.L, N = L * L, half = L >> 1, nh = N >> 1;
     const int lane = threadIdx.x & 63;
-    const uint32_t i = J.i, key0 = J.key0, key1 = J.key1;
     const bool saturated = J.Th.all4 || J.Th.all8;
     const bool partial = J.vlast != ~0ull;
-    // masks of the first calls; one of each pair in a vector register (an
-    // instruction reads one scalar operand), where the compiler would
-    // otherwise copy it again for every call
-    PlaneMasks dm[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        dm[c] = call_masks(J.Th.t4, J.Th.t8, (uint32_t)c);
-        asm volatile("" : "+v"(dm[c].a8), "+v"(dm[c].b8));
-    }
+    const LockstepMasks dm(J.Th);
     // steps of a walk over 64 units
     const int gq = 64 / nh, kr = 64 - gq * nh, yr = kr / half, mr = kr - yr * half;
     UnitWalk first;
     first.start(J, min(J.ub, J.units - 1) + lane);
     uint32_t wcalls = 0;   // Philox calls of this wavefront (uniform)
     for (int s = J.s_begin; s < J.s_end; ++s) {
-        const uint32_t c3 = J.c3p | (uint32_t)s;
         for (int colour = 0; colour < 2; ++colour) {
             __syncthreads();
             const int cb = colour * nh;            // this colour's words
             const int od = colour ? -nh : nh;      // from a word to the same place of the other colour
-            int hs = 0, ts = 0, left = 0;          // ring: slot of the head, slot of the tail, entries
-            auto word_of = [&](uint32_t pk) {      // lattice word of an entry
-                const int k = (int)((pk >> 1) & 0x7FFu) + cb;
-                return ONE ? k : k + (int)((pk >> 12) & 0xFFu) * N;
+            Stream q = {eu, en, tmask, slots, J.i, J.c3p | (uint32_t)s, J.key0, J.key1};
+            auto word = [&](uint32_t pk) {
+                if constexpr (ONE) return lat + cb + (int)((pk & 0xFFFFFu) >> 1);
+                else return lat + cb + (int)((pk >> 1) & 0x7FFu) + (int)((pk >> 12) & 0xFFu) * N;
             };
-            auto group_of = [&](uint32_t pk) {
+            auto group = [&](uint32_t pk) {
                 return (uint32_t)(ONE ? J.group0 : J.group0 + (int)((pk >> 12) & 0xFFu));
             };
-            auto call = [&](uint32_t c0, const PlaneMasks &m, uint64_t one, uint64_t &und, uint32_t g, auto ug) {
-                const u32x4 o = philox10_sweep<decltype(ug)::value>(c0, g, i, c3, key0, key1);
-                return plane_pair((uint64_t)o.x | ((uint64_t)o.y << 32), (uint64_t)o.z | ((uint64_t)o.w << 32), m,
-                                  one, und);
-            };
             using UG = std::integral_constant<bool, ONE>;
-            // full rounds while more than 64 entries wait
-            auto rounds = [&]() {
-                while (left > 64) {
-                    const int slot = (hs + lane) & (slots - 1);
-                    uint64_t und, one;
-                    und_load(&eu[slot], und, one);
-                    const uint32_t pk = en[slot];
-                    const uint32_t c0 = ONE ? pk : pk & 0xF00FFFu;
-                    const uint64_t was = und;
-                    const uint64_t less = call(c0, tmask[pk >> 20], one, und, group_of(pk), UG{});
-                    flip_word(&lat[word_of(pk)], bop3<LUT_ANDN2>(less, was, und));
-                    wcalls += 64;
-                    const bool more = und != 0 && pk < 0xF00000u;
-                    // the two compares' masks, combined on the scalar unit
-                    const uint64_t need = wave_ballot(und != 0) & wave_ballot(pk < 0xF00000u);
-                    if (more) {
-                        const int out = (rank_below(need, 0) + ts) & (slots - 1);
-                        und_store(&eu[out], und, one);
-                        en[out] = pk + 0x100000u;
-                    }
-                    const int nn = __popcll(need);
-                    ts = (ts + nn) & (slots - 1);
-                    hs = (hs + 64) & (slots - 1);
-                    left += nn - 64;
-                }
-            };
             // one chunk: a unit (site word) per lane.  own: its lattice word;
             // dh, du, dd: offsets of the neighbours beside the word at the
-            // same place of the other colour
+            // same place of the other colour; ug: gs is the same on every lane
             auto chunk = [&](bool in, int own, int dh, int du, int dd, uint32_t n, int gs, auto ug) {
                 uint64_t und = 0, one = 0, acc = 0;
                 const uint32_t g = (uint32_t)(J.group0 + gs);
@@ -1543,29 +1557,10 @@ __device__ __forceinline__ uint32_t stream_sweeps(const SweepJob &J, uint64_t *l
                         acc = J.vlast;
                     }
                 }
-                auto lockstep = [&](uint32_t c, const PlaneMasks &m) {
-                    wcalls += (uint32_t)__popcll(wave_ballot(und != 0));
-                    const uint64_t was = und;
-                    const uint64_t less = call(n | (c << 20), m, one, und, g, ug);
-                    acc = bop3<LUT_SEL>(was, less, acc);
-                };
-                if (dense > 0) lockstep(0, dm[0]);
-                if (dense > 1) lockstep(1, dm[1]);
-                if (dense > 2) lockstep(2, dm[2]);
-                if (dense > 3) lockstep(3, dm[3]);
-                for (int c = 4; c < dense; ++c)
-                    lockstep((uint32_t)c, call_masks(J.Th.t4, J.Th.t8, (uint32_t)c));
+                lockstep_calls<decltype(ug)::value>(q, dense, dm, J.Th, n, g, one, und, acc, wcalls);
                 flip_word(&lat[own], acc & ~und);
-                const uint64_t need = wave_ballot(und != 0);
-                if (und != 0) {
-                    const int out = (rank_below(need, 0) + ts) & (slots - 1);
-                    und_store(&eu[out], und, one);
-                    en[out] = n | ((uint32_t)dense << 20) | (ONE ? 0u : (uint32_t)gs << 12);
-                }
-                const int nn = __popcll(need);
-                ts = (ts + nn) & (slots - 1);
-                left += nn;
-                rounds();   // room for the next chunk's entries
+                stream_push(q, und, one, n | ((uint32_t)dense << 20) | (ONE ? 0u : (uint32_t)gs << 12));
+                stream_rounds<ONE>(q, word, group, wcalls);   // room for the next chunk's entries
             };
             // A chunk of whole rows (64 a multiple of two row halves, the
             // colour's half-lattice a multiple of 64): every lane keeps its
@@ -1604,32 +1599,7 @@ __device__ __forceinline__ uint32_t stream_sweeps(const SweepJob &J, uint64_t *l
                     w.step(J, gq, kr, yr, mr);
                 }
             }
-            // the last (at most 64) entries: each lane runs all the remaining
-            // calls of its own entry
-            uint64_t und = 0, one = 0, acc = 0;
-            uint32_t pk = 0xFFFFFFFFu;
-            if (lane < left) {
-                const int slot = (hs + lane) & (slots - 1);
-                und_load(&eu[slot], und, one);
-                pk = en[slot];
-            }
-            const uint64_t drew = und;
-            const uint32_t g = group_of(pk);
-            const int own = lane < left ? word_of(pk) : 0;
-            for (;;) {
-                const bool live = und != 0 && pk < 0x1000000u;
-                const uint64_t lv = wave_ballot(und != 0) & wave_ballot(pk < 0x1000000u);
-                if (lv == 0) break;
-                wcalls += (uint32_t)__popcll(lv);
-                if (live) {
-                    const uint64_t was = und;
-                    const uint64_t less =
-                        call(ONE ? pk : pk & 0xF00FFFu, tmask[pk >> 20], one, und, g, UG{});
-                    acc = bop3<LUT_SEL>(was, less, acc);
-                    pk += 0x100000u;
-                }
-            }
-            flip_word(&lat[own], bop3<LUT_ANDN2>(acc, drew, und));
+            stream_tail<ONE>(q, lat, word, group, wcalls);
         }
     }
     return wcalls;
@@ -1770,7 +1740,7 @@ __device__ __forceinline__ void sweep_one(const SweepItem &it, const RunInfo *ru
     }
     if constexpr (LS >= 0) {
         stream_item<LS, EA>(it, R, S, lds, mode, stats);
-    } else if (msc_streamed(R.N, mode)) {
+    } else if (msc_streamed(R.N, it.ngroups, mode)) {
         if (ea) stream_item<0, true>(it, R, S, lds, mode, stats);
         else stream_item<0, false>(it, R, S, lds, mode, stats);
     } else {
@@ -1858,6 +1828,98 @@ __global__ void __launch_bounds__(1024) k_sweep_msc(const SweepItem *items, int 
     }
 }
 
+// Lattices swept from memory, one colour per launch: sizes beyond a
+// workgroup's LDS, and few groups of large ones, which a workgroup per group
+// would sweep on few compute units.  A wavefront takes cpw chunks of 64 site
+// words of one replica group through the same lockstep calls and queue as the
+// batched sweep, collecting the flips in LDS, and applies them at the end;
+// the neighbours are the other colour's words, which this launch only reads.
+// In place of one byte per spin read and written per colour (and the halo
+// rows of the tiles that took): 8 bytes per 64 spins, so the working set is
+// an eighth and mostly in L2; bound by launches where the run is small, by
+// the calls' instructions where it is not.  Step (iv) of ten sweeps with the
+// conversions: L = 128, R = 2000 (spin glass) 388 -> 209 us; L = 256, R = 5000
+// 3400 -> 874; L = 512, R = 200 732 -> 335.
+constexpr int WIDE_WAVES = 4;
+constexpr int WIDE_CHUNKS = 4;   // most chunks per wavefront
+
+template <bool EA>
+__global__ void __launch_bounds__(64 * WIDE_WAVES) k_sweep_wide(const RunInfo *runs, const PopState *st, int run,
+                                                                int s, int colour, int cpw, int tiles,
+                                                                unsigned long long *stats)
+{
+    __shared__ PlaneMasks tmask[16];
+    __shared__ UndPair eu[WIDE_WAVES][128];
+    __shared__ uint32_t en[WIDE_WAVES][128];
+    __shared__ uint64_t fm[WIDE_WAVES][64 * WIDE_CHUNKS];
+    const RunInfo &R = runs[run];
+    const int pop = blockIdx.y;
+    const PopState &S = st[run * MAX_POP + pop];
+    const int g = blockIdx.x / tiles, tile = blockIdx.x - g * tiles;
+    const int Rc = S.Rcur;
+    if (!pop_active(S) || g * 64 >= Rc) return;
+    const int L = R.L, N = R.N, half = L >> 1, nh = N >> 1;
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    const Thresholds Th = thresholds_of(R.tabT, S.i);
+    if (threadIdx.x < 16) tmask[threadIdx.x] = call_masks(Th.t4, Th.t8, threadIdx.x);
+    __syncthreads();
+    const int k0 = (tile * WIDE_WAVES + wv) * 64 * cpw, k1 = min(nh, k0 + 64 * cpw);
+    if (k0 >= nh) return;
+    uint64_t *words = words_of(R, S, pop) + (size_t)g * N;
+    const uint8_t *jbits = R.jbits;
+    const uint64_t valid = (Rc - g * 64 >= 64) ? ~0ull : ((1ull << (Rc - g * 64)) - 1);
+    const float invH = 1.0f / (float)half;
+    const LockstepMasks dm(Th);
+    uint32_t wcalls = 0;
+    Stream q = {eu[wv], en[wv], tmask, 128, (uint32_t)S.i, (TAG_SWEEP << 28) | ((uint32_t)pop << 24) | (uint32_t)s,
+                R.key0, R.key1};
+    auto word = [&](uint32_t pk) { return &fm[wv][(int)((pk & 0xFFFFFu) >> 1) - k0]; };
+    auto group = [&](uint32_t) { return (uint32_t)g; };
+    auto site = [&](int k, int &y, int &x) {
+        y = div_small(k, invH);
+        x = 2 * (k - y * half) + ((y + colour) & 1);
+        return y * L + x;
+    };
+    for (int kb = k0; kb < k1; kb += 64) {
+        const int k = kb + lane;
+        uint64_t und = 0, one = 0, acc = 0;
+        int n = 0;
+        if (k < k1) {
+            int y, x;
+            n = site(k, y, x);
+            const int nr = x + 1 == L ? n + 1 - L : n + 1, nl = x == 0 ? n + L - 1 : n - 1;
+            const int nd = y + 1 == L ? n + L - N : n + L, nu = y == 0 ? n + N - L : n - L;
+            uint64_t wr = words[nr], wl = words[nl], wd = words[nd], wu = words[nu];
+            if (EA) {
+                const uint8_t jn = jbits[n];
+                wr ^= jmask(jn, 0);
+                wl ^= jmask(jbits[nl], 0);
+                wd ^= jmask(jn, 1);
+                wu ^= jmask(jbits[nu], 1);
+            }
+            SiteClass sc = classify(words[n], wr, wl, wd, wu);
+            accept_saturated(sc, Th);
+            und = sc.und & valid;
+            one = sc.one;
+            acc = valid;   // flips unless a draw says otherwise
+        }
+        lockstep_calls<true>(q, 3, dm, Th, (uint32_t)n, (uint32_t)g, one, und, acc, wcalls);
+        fm[wv][kb - k0 + lane] = acc & ~und;
+        stream_push(q, und, one, (uint32_t)n | 3u * ENTRY_CALL);
+        stream_rounds<true>(q, word, group, wcalls);
+    }
+    stream_tail<true>(q, &fm[wv][0], word, group, wcalls);
+    for (int kb = k0; kb < k1; kb += 64)
+        if (kb + lane < k1) {
+            int y, x;
+            const int n = site(kb + lane, y, x);
+            words[n] ^= fm[wv][kb - k0 + lane];
+        }
+    const bool first = lane == 0;
+    flush_stats(stats, first ? (uint64_t)(k1 - k0) : 0ull, first ? wcalls : 0u,
+                first ? (uint64_t)(k1 - k0) * (uint64_t)__popcll(valid) : 0ull);
+}
+
 // -------------------------------------------------------------- step (v)
 
 // Partner words of the permutation pairing ([group][site] u64): the spare
@@ -1879,6 +1941,14 @@ __device__ __forceinline__ uint64_t load_word(const uint8_t *buf, int g, int n, 
     return pack64(v);
 }
 
+// Spins that a measurement of layout REPR reads: bytes, or words (in the
+// int8 layout the words that the sweeps left).
+template <int REPR>
+__device__ __forceinline__ const uint8_t *spin_buf(const RunInfo &R, const PopState &S, int pop)
+{
+    return REPR == PA_INT8 ? R.spins[pop][S.cur] : (const uint8_t *)words_of(R, S, pop);
+}
+
 // Measurement of replica groups (64 replicas each).  A workgroup of
 // MEAS_WAVES wavefronts takes a measure item of consecutive groups of one
 // (run, pop); each group gets meas_waves_per_group(N) wavefronts, which
@@ -1897,16 +1967,14 @@ __device__ __forceinline__ void measure_group(const SweepItem &it, int g, int su
                                               const RunInfo &R, const PopState &S, const PopState *st,
                                               uint32_t (*red)[MEAS_WAVES][64], const uint64_t *lw)
 {
+    const uint8_t *buf = spin_buf<REPR>(R, S, it.pop);
     // the group's own words come from LDS when the workgroup staged them
     // (lw != nullptr), else from memory
-    auto own = [&](int gg, int n, int NN) -> uint64_t {
-        return lw ? lw[n] : load_word<REPR>(R.spins[it.pop][S.cur], gg, n, NN);
-    };
+    auto own = [&](int gg, int n, int NN) -> uint64_t { return lw ? lw[n] : load_word<REPR>(buf, gg, n, NN); };
     const int L = LT ? LT : R.L;
     const int N = L * L;
     const int Rc = S.Rcur;
     const int lane = threadIdx.x & 63, wv = wave_id();
-    const uint8_t *buf = R.spins[it.pop][S.cur];
     // overlap partners of this group's replicas
     int mode = 0;                      // 0 none, 1 index shift, 2 two populations, 3 permutation pairs
     uint64_t pairmask = 0;
@@ -1934,7 +2002,7 @@ __device__ __forceinline__ void measure_group(const SweepItem &it, int g, int su
                 mode = 2;
                 const int cntp = min(64, m - lo);
                 pairmask = cntp >= 64 ? ~0ull : ((1ull << cntp) - 1);
-                pbuf = R.spins[1][S1.cur];
+                pbuf = spin_buf<REPR>(R, S1, 1);
                 pg = g;
             }
         }
@@ -2134,7 +2202,7 @@ __global__ void __launch_bounds__(MEAS_THREADS) k_measure(const SweepItem *items
     const SweepItem it = items[blockIdx.x];
     const RunInfo &R = runs[it.run];
     const PopState &S = st[it.run * MAX_POP + it.pop];
-    if (!pop_active(S)) return;
+    if (!pop_active(S) || words_current(R, S) != (REPR == PA_MSC64)) return;
     const int wpg = meas_waves_per_group(R.N);
     const int wv = wave_id();
     const int k = wv / wpg, sub = wv - k * wpg;
@@ -3202,31 +3270,42 @@ hipError_t launch_resample(const LaunchCtx &c)
 }
 
 
-// Threads per workgroup of the plain sweep: 256, or 1024 when three rows of
-// a very large lattice would not fit in 256 threads' chunks.
-int int8_threads(int L) { return 3 * L * 4 <= 256 * I8_CMAX ? 256 : 1024; }
-
-int int8_tile_rows(int L) { return int8_rows_for(L, int8_threads(L)); }
-
-hipError_t launch_sweep_int8_run(const LaunchCtx &c, int run, int L, int groups_cap, int npop, int theta)
+hipError_t launch_words(const LaunchCtx &c, int max_N)
 {
-    const int T = int8_tile_rows(L);
-    const int ntiles = (L + T - 1) / T;
-    const int nrow = T == L ? L : T + 2;
-    const int threads = int8_threads(L);
-    const size_t lds = (size_t)nrow * L * 8 + (size_t)T * (L / 2) * 8;
-    for (int s = 0; s < theta; ++s)
-        for (int colour = 0; colour < 2; ++colour)
-            for (int p = 0; p < npop; ++p) {
-                if (threads == 256)
-                    k_sweep_int8<256><<<groups_cap * ntiles, threads, lds, c.stream>>>(c.runs, c.st, run, p, s,
-                                                                                       colour, T, ntiles, c.stats);
+    k_bytes_words<true><<<dim3(c.n_items, (max_N + WORDS_SEG - 1) / WORDS_SEG), 256, 0, c.stream>>>(c.items, c.runs,
+                                                                                                  c.st);
+    return hipGetLastError();
+}
+
+hipError_t launch_sweep_bytes(const LaunchCtx &c, const WideRun *wide, int n_wide, int max_N)
+{
+    if (!c.any_swept || c.n_items == 0) return hipSuccess;
+    hipError_t e = launch_words(c, max_N);
+    if (e != hipSuccess) return e;
+    if ((e = launch_sweep_msc(c)) != hipSuccess) return e;
+    for (int k = 0; k < n_wide; ++k) {
+        const WideRun &w = wide[k];
+        const int nh = w.L * w.L / 2;
+        // chunks per wavefront by the chunks there are per SIMD (1024), as in
+        // the batched sweep's default shape
+        const double chunks = (double)w.groups_cap * w.npop * nh / 64.0;
+        const int cpw = chunks < 2 * 1024.0 ? 1 : (chunks < 12 * 1024.0 ? 2 : WIDE_CHUNKS);
+        const int tiles = (nh + 64 * WIDE_WAVES * cpw - 1) / (64 * WIDE_WAVES * cpw);
+        const dim3 grid((unsigned)w.groups_cap * tiles, w.npop);
+        for (int s = 0; s < w.theta; ++s)
+            for (int colour = 0; colour < 2; ++colour) {
+                if (w.ea)
+                    k_sweep_wide<true><<<grid, 64 * WIDE_WAVES, 0, c.stream>>>(c.runs, c.st, w.run, s, colour, cpw,
+                                                                              tiles, c.stats);
                 else
-                    k_sweep_int8<1024><<<groups_cap * ntiles, threads, lds, c.stream>>>(c.runs, c.st, run, p, s,
-                                                                                        colour, T, ntiles, c.stats);
+                    k_sweep_wide<false><<<grid, 64 * WIDE_WAVES, 0, c.stream>>>(c.runs, c.st, w.run, s, colour, cpw,
+                                                                               tiles, c.stats);
                 PA_CHECK_LAUNCH();
             }
-    return hipSuccess;
+    }
+    k_bytes_words<false><<<dim3(c.n_items, (max_N + WORDS_SEG - 1) / WORDS_SEG), 256, 0, c.stream>>>(c.items, c.runs,
+                                                                                                   c.st);
+    return hipGetLastError();
 }
 
 size_t msc_lds_bytes(int N, int groups, bool ea, int threads, int mode)
@@ -3315,7 +3394,7 @@ int sweep_classes(std::vector<SweepItem> &items, const std::vector<int> &run_L, 
         const int L = run_L[it.run];
         if (L == 0) continue;
         const int ea = run_ea[it.run] ? 1 : 0;
-        keys.push_back(!msc_streamed(L * L, mode) ? -1 : (msc_specialised(L) ? 2 * L : 0) + ea);
+        keys.push_back(!msc_streamed(L * L, it.ngroups, mode) ? -1 : (msc_specialised(L) ? 2 * L : 0) + ea);
         out.push_back(it);
     }
     items.swap(out);
@@ -3497,7 +3576,7 @@ hipError_t launch_dos_sample(const LaunchCtx &c)
     return hipGetLastError();
 }
 
-hipError_t launch_measure(const LaunchCtx &c)
+hipError_t launch_measure(const LaunchCtx &c, bool first)
 {
     if (c.any_wang && c.n_runs > 0) {
         k_wang_pairs<<<c.n_runs, WANG_THREADS, sizeof(int32_t) * (size_t)c.wang_lds_ints, c.stream>>>(
@@ -3514,14 +3593,18 @@ hipError_t launch_measure(const LaunchCtx &c)
     }
     if (c.n_meas_items > 0) {
         // the variant without overlap counters when no run measures overlaps
-        // (fewer registers live in the site loop)
-        if (c.repr == PA_MSC64 && c.any_overlap)
+        // (fewer registers live in the site loop); in the int8 layout the
+        // swept runs are measured from their words, the others from bytes
+        const bool words = c.repr == PA_MSC64 || (!first && c.any_swept);
+        const bool bytes = c.repr == PA_INT8 && (first || c.any_unswept);
+        if (words && c.any_overlap)
             k_measure<PA_MSC64, true><<<c.n_meas_items, MEAS_THREADS, 0, c.stream>>>(c.meas_items, c.runs, c.st);
-        else if (c.repr == PA_MSC64)
+        else if (words)
             k_measure<PA_MSC64, false><<<c.n_meas_items, MEAS_THREADS, 0, c.stream>>>(c.meas_items, c.runs, c.st);
-        else if (c.any_overlap)
+        PA_CHECK_LAUNCH();
+        if (bytes && c.any_overlap)
             k_measure<PA_INT8, true><<<c.n_meas_items, MEAS_THREADS, MEAS_STAGE_BYTES, c.stream>>>(c.meas_items, c.runs, c.st);
-        else
+        else if (bytes)
             k_measure<PA_INT8, false><<<c.n_meas_items, MEAS_THREADS, MEAS_STAGE_BYTES, c.stream>>>(c.meas_items, c.runs, c.st);
         PA_CHECK_LAUNCH();
     }

@@ -37,6 +37,7 @@ struct LaunchCtx {
     bool any_wang;                 // some run pairs replicas by permutations
     int wang_lds_ints;             // LDS of the pairing repair (2 R_cap of the largest run that fits, or 0)
     bool any_exact_dos;            // some run is at theta = infinity
+    bool any_swept, any_unswept;   // some run makes / does not make Metropolis sweeps (int8 layout)
     unsigned long long *stats;   // device [NSTAT] work counters of the sweeps
     const SweepItem *meas_items;   // device [n_meas_items]: groups per measure workgroup
     int n_meas_items;
@@ -54,9 +55,13 @@ hipError_t launch_fill_u32(void *p, uint32_t v, size_t n, hipStream_t s);
 hipError_t launch_init(const LaunchCtx &c, const uint64_t *dseed);
 hipError_t launch_anneal(const LaunchCtx &c);
 hipError_t launch_resample(const LaunchCtx &c);
-hipError_t launch_sweep_int8_run(const LaunchCtx &c, int run, int L, int groups_cap, int npop, int theta);
 hipError_t launch_sweep_msc(const LaunchCtx &c);
-hipError_t launch_measure(const LaunchCtx &c);
+// int8 layout: the batched sweep on the configurations' words (the items of
+// c.sweep_cls), and the runs of `wide` one colour at a time.
+hipError_t launch_sweep_bytes(const LaunchCtx &c, const WideRun *wide, int n_wide, int max_N);
+// first: the measurement at i = 0 (the int8 layout has no words yet).
+hipError_t launch_measure(const LaunchCtx &c, bool first);
+hipError_t launch_words(const LaunchCtx &c, int max_N);   // int8 layout: bytes -> words
 hipError_t launch_dos_sample(const LaunchCtx &c);   // theta = infinity draws (no-op without such runs)
 hipError_t launch_wavg(const LaunchCtx &c, const pa_obs *obs, int M, int kind, int pop, int K, int i_done,
                        double *logw, double *qw, pa_wavg *out);
@@ -65,7 +70,6 @@ hipError_t launch_qweights(const LaunchCtx &c, const pa_obs *obs, int M, int kin
 hipError_t launch_wqhist(const LaunchCtx &c, const pa_obs *obs, int M, int kind, int pop, int K, int i_done,
                          double *logw, double *qw, double *out);
 hipError_t launch_famstats(const LaunchCtx &c, const pa_obs *obs, int pop, int K, int i_done, pa_famstat *out);
-int int8_tile_rows(int L);
 // LDS bytes of a batched-sweep workgroup of `threads` holding `groups`
 // replica groups of N sites (ea: the spin glass), launched with mode =
 // lockstep calls | pooled << 8.

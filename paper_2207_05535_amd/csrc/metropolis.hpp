@@ -124,28 +124,6 @@ __device__ __forceinline__ uint64_t draw_call(uint32_t c, const PlaneMasks &m, u
     return plane_pair(pa, pb, m, one, und);
 }
 
-// Flip mask of one site, all draws done here (used by the plain path).
-// Replicas that draw start from "flip" and take the verdict of every call
-// they are still undecided in; those still undecided at the end drew u = T
-// and stay.
-__device__ __forceinline__ uint64_t flip_mask(uint64_t w, uint64_t nr, uint64_t nl, uint64_t nd,
-                                              uint64_t nu, const Thresholds &T, uint64_t valid,
-                                              uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                              uint32_t k0, uint32_t k1, uint32_t &calls)
-{
-    SiteClass sc = classify(w, nr, nl, nd, nu);
-    accept_saturated(sc, T);
-    uint64_t acc = ~0ull;
-    uint64_t und = sc.und & valid;
-    for (uint32_t c = 0; und != 0 && c < 16; ++c) {
-        const uint64_t was = und;
-        const uint64_t less = draw_call(c, call_masks(T.t4, T.t8, c), sc.one, und, c0, c1, c2, c3, k0, k1);
-        acc = bop3<LUT_SEL>(was, less, acc);
-        ++calls;
-    }
-    return acc & valid & ~und;
-}
-
 // Thresholds of temperature i, read once per workgroup and kept in scalar
 // registers.
 __device__ __forceinline__ Thresholds thresholds_of(const uint64_t *tabT, int i)

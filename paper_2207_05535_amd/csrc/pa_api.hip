@@ -491,7 +491,7 @@ bool dos_thresholds(const pa_run_desc &d, std::vector<uint64_t> &out)
     return true;
 }
 
-RunInfo make_runinfo(const pa_run_desc &d, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
+RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
                      pa_obs *obs, int obs_stride, int obs_off)
 {
     RunInfo I;
@@ -503,6 +503,7 @@ RunInfo make_runinfo(const pa_run_desc &d, uint8_t *base, const RunOff &o, uint8
     I.R_cap = d.R_cap;
     I.theta = d.theta == PA_THETA_EXACT ? 0 : d.theta;   // no Metropolis sweeps at theta = infinity
     I.exact_dos = d.theta == PA_THETA_EXACT ? 1 : 0;
+    I.bytes = repr == PA_INT8 ? 1 : 0;
     I.K = d.K;
     I.model = d.model;
     I.resampling = d.resampling;
@@ -635,10 +636,26 @@ pa_status dev_fail(pa_ctx *c, hipError_t e)
 
 int groups_for(const pa_ctx *c, int L)
 {
-    auto it = c->groups_per_wg.find(L);
+    const auto it = c->groups_per_wg.find(L);
     if (it != c->groups_per_wg.end()) return it->second;
     const auto d = c->default_groups.find(L);
-    return d == c->default_groups.end() ? groups_of_2048(L) : d->second;
+    return c->repr == PA_INT8 || d == c->default_groups.end() ? groups_of_2048(L) : d->second;
+}
+
+bool sweeps_wide(const pa_run_desc &d, int groups, int threads, int lds_limit)
+{
+    const int N = d.L * d.L;
+    const size_t lds = msc_stream_lds(N, groups, d.model == PA_EA_PMJ, threads / 64);
+    if (lds > (size_t)lds_limit) return true;
+    if (N <= 4096) return false;
+    // A workgroup holds one such lattice.  In LDS it pays where two fit on a
+    // CU and there are enough of them for half the CUs (us per ten sweeps,
+    // LDS / from memory: L = 72, R = 1e4 207 / 255, R = 1e5 1162 / 1267;
+    // L = 100, R = 2000, 32 groups: 183 from memory, more than 300 in LDS),
+    // or where one fits and all of them run at once (L = 100, R = 9000 319 /
+    // 345; R = 2e4 643 / 580; L = 128, R = 2e4 1013 / 821).
+    const int n = n_pop_of(d.overlap) * groups_cap_of(d);
+    return !(n >= 128 && (2 * lds <= (size_t)lds_limit || (n <= 256 && 4 * lds <= 3 * (size_t)lds_limit)));
 }
 
 // Work list and LDS size of the batched sweep for the current tuning.
@@ -647,7 +664,7 @@ bool plan_sweep(const pa_ctx *c, std::vector<SweepItem> &items, size_t &lds)
 {
     items.clear();
     lds = 0;
-    for (int r = 0; r < c->n_runs; ++r) {
+    for (int r = 0; r < c->n_runs && c->repr == PA_MSC64; ++r) {
         const pa_run_desc &d = c->descs[r];
         const int N = d.L * d.L;
         if ((size_t)groups_for(c, d.L) * N > 65535) return false;   // 16-bit LDS word indices
@@ -656,7 +673,12 @@ bool plan_sweep(const pa_ctx *c, std::vector<SweepItem> &items, size_t &lds)
     if (lds > (size_t)c->lds_limit) return false;
     for (int r = 0; r < c->n_runs; ++r) {
         const pa_run_desc &d = c->descs[r];
-        const int G = groups_for(c, d.L);
+        int G = groups_for(c, d.L);
+        if (c->repr == PA_INT8) {
+            G = c->default_groups.at(d.L);
+            if (d.theta <= 0 || sweeps_wide(d, G, c->bytes_threads, c->lds_limit)) continue;
+            lds = std::max(lds, msc_stream_lds(d.L * d.L, G, d.model == PA_EA_PMJ, c->bytes_threads / 64));
+        }
         for (int p = 0; p < n_pop_of(d.overlap); ++p)
             for (int g = 0; g < groups_cap_of(d); g += G)
                 items.push_back({r, p, g, std::min(G, groups_cap_of(d) - g)});
@@ -676,17 +698,26 @@ pa_status upload_sweep_plan(pa_ctx *c)
     std::vector<SweepItem> items;
     size_t lds = 0;
     if (!plan_sweep(c, items, lds)) return PA_ERR_ARG;
+    c->wide.clear();
     std::vector<int> run_L(c->n_runs), run_ea(c->n_runs);
     for (int r = 0; r < c->n_runs; ++r) {
-        run_L[r] = c->descs[r].theta > 0 ? c->descs[r].L : 0;
-        run_ea[r] = c->descs[r].model == PA_EA_PMJ;
+        const pa_run_desc &d = c->descs[r];
+        run_L[r] = d.theta > 0 ? d.L : 0;
+        run_ea[r] = d.model == PA_EA_PMJ;
+        if (c->repr == PA_INT8 && d.theta > 0 &&
+            sweeps_wide(d, c->default_groups.at(d.L), c->bytes_threads, c->lds_limit))
+            c->wide.push_back({r, d.L, groups_cap_of(d), n_pop_of(d.overlap), d.theta, run_ea[r]});
     }
+    // the knobs are the bit-packed layout's; the int8 layout keeps what is
+    // set and sweeps with the defaults
+    const bool packed = c->repr == PA_MSC64;
+    const int threads = packed ? c->sweep_threads : c->bytes_threads, dense = packed ? c->sweep_dense : 3;
+    const bool pooled = packed && c->sweep_pooled;
     SweepClass cls[MAX_SWEEP_CLASSES];
     if (prepare_msc_lds(lds) != hipSuccess) return dev_fail(c);
-    const int ncls = sweep_classes(items, run_L, run_ea, cls, c->sweep_threads,
-                                   c->sweep_dense | (c->sweep_pooled ? 1 << 8 : 0), true);
+    const int ncls = sweep_classes(items, run_L, run_ea, cls, threads, dense | (pooled ? 1 << 8 : 0), true);
     if (ncls < 0) return PA_ERR_ARG;
-    if (!sweep_class_grids(cls, ncls, c->sweep_threads, c->sweep_persistent)) return dev_fail(c);
+    if (!sweep_class_grids(cls, ncls, threads, packed && c->sweep_persistent)) return dev_fail(c);
     if (ncls == 1 && cls[0].grid > 0 && cls[0].grid < cls[0].count) {
         const int K = c->sweep_chunks > 0 ? c->sweep_chunks : sweep_chunks_auto(cls[0].count, cls[0].grid);
         std::vector<int> run_theta(c->n_runs);
@@ -700,30 +731,27 @@ pa_status upload_sweep_plan(pa_ctx *c)
     c->lc.sweep_items = at<SweepItem>(c, c->lo.sweep_items);
     c->lc.sweep_flags = at<unsigned int>(c, c->lo.sweep_flags);
     c->lc.n_sweep_items = (int)items.size();
-    c->lc.sweep_threads = c->sweep_threads;
-    c->lc.sweep_dense = c->sweep_dense;
-    c->lc.sweep_pooled = c->sweep_pooled ? 1 : 0;
+    c->lc.sweep_threads = threads;
+    c->lc.sweep_dense = dense;
+    c->lc.sweep_pooled = pooled ? 1 : 0;
     c->lc.n_sweep_classes = ncls;
     std::copy(cls, cls + ncls, c->lc.sweep_cls);
     return PA_OK;
+}
+
+hipError_t launch_sweeps(const pa_ctx *c)
+{
+    return c->repr == PA_MSC64 ? launch_sweep_msc(c->lc)
+                               : launch_sweep_bytes(c->lc, c->wide.data(), (int)c->wide.size(), c->lo.maxN);
 }
 
 pa_status enqueue_step(pa_ctx *c)
 {
     if (launch_anneal(c->lc) != hipSuccess) return dev_fail(c);
     if (launch_resample(c->lc) != hipSuccess) return dev_fail(c);
-    if (c->repr == PA_MSC64) {
-        if (launch_sweep_msc(c->lc) != hipSuccess) return dev_fail(c);
-    } else {
-        for (int r = 0; r < c->n_runs; ++r) {
-            const pa_run_desc &d = c->descs[r];
-            if (launch_sweep_int8_run(c->lc, r, d.L, groups_cap_of(d), n_pop_of(d.overlap), d.theta) !=
-                hipSuccess)
-                return dev_fail(c);
-        }
-    }
+    if (launch_sweeps(c) != hipSuccess) return dev_fail(c);
     if (launch_dos_sample(c->lc) != hipSuccess) return dev_fail(c);
-    if (launch_measure(c->lc) != hipSuccess) return dev_fail(c);
+    if (launch_measure(c->lc, false) != hipSuccess) return dev_fail(c);
     return PA_OK;
 }
 
@@ -828,7 +856,7 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
         const pa_run_desc &d = c->descs[r];
         const RunOff &o = Lo.runs[r];
         const TableOff &T = Lo.tables[o.table];
-        c->hinfo[r] = make_runinfo(d, c->ws, o, c->ws, T, at<pa_obs>(c, Lo.obs), n_runs * Lo.npop_ctx,
+        c->hinfo[r] = make_runinfo(d, repr, c->ws, o, c->ws, T, at<pa_obs>(c, Lo.obs), n_runs * Lo.npop_ctx,
                                    r * Lo.npop_ctx);
         for (int p = 0; p < n_pop_of(d.overlap); ++p) {
             hst[(size_t)r * MAX_POP + p] = initial_popstate(d);
@@ -854,6 +882,7 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
     c->lc.any_multinomial = c->any_multinomial;
     c->lc.mn_split = 1;
     c->lc.any_overlap = false;
+    c->lc.any_swept = c->lc.any_unswept = false;
     // copy workgroups per item: each wavefront keeps about four 64-site blocks
     // of its group (L = 64: 40 -> 35 us per copy at R = 1e5 against one
     // workgroup per item); set by the smallest lattice of the context
@@ -866,6 +895,8 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
     for (int r = 0; r < n_runs; ++r) {
         if (runs[r].resampling == PA_MULTINOMIAL && runs[r].R > CH) c->lc.mn_split = CH_PER;
         if (runs[r].overlap != PA_Q_NONE) c->lc.any_overlap = true;
+        if (runs[r].theta > 0) c->lc.any_swept = true;
+        else c->lc.any_unswept = true;
     }
     c->lc.any_wang = c->any_wang;
     c->lc.any_exact_dos = c->any_exact_dos;
@@ -887,7 +918,7 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
     {
         std::vector<const pa_run_desc *> dp(n_runs);
         for (int r = 0; r < n_runs; ++r) dp[r] = &c->descs[r];
-        default_shape(dp.data(), n_runs, &c->sweep_threads, c->default_groups);
+        default_shape(dp.data(), n_runs, repr == PA_MSC64 ? &c->sweep_threads : &c->bytes_threads, c->default_groups);
     }
     if (repr == PA_MSC64) {
         std::vector<SweepItem> probe;
@@ -947,9 +978,9 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
                                 hipMemcpyHostToDevice, s) == hipSuccess;
         }
     }
-    ok = ok && (repr != PA_MSC64 || upload_sweep_plan(c) == PA_OK);
+    ok = ok && upload_sweep_plan(c) == PA_OK;
     ok = ok && launch_init(c->lc, at<uint64_t>(c, Lo.dseed)) == hipSuccess;
-    ok = ok && launch_measure(c->lc) == hipSuccess;
+    ok = ok && launch_measure(c->lc, true) == hipSuccess;
     ok = ok && hipStreamSynchronize(s) == hipSuccess;
     if (!ok) return fail(PA_ERR_DEVICE);
     c->i = 0;
@@ -984,15 +1015,7 @@ pa_status pa_sweep(pa_ctx *c, int32_t i)
     if (!c) return PA_ERR_ARG;
     if (c->failed) return PA_ERR_DEVICE;
     if (c->phase != PH_RESAMPLED || i != c->i) return PA_ERR_STATE;
-    if (c->repr == PA_MSC64) {
-        if (launch_sweep_msc(c->lc) != hipSuccess) return dev_fail(c);
-    } else {
-        for (int r = 0; r < c->n_runs; ++r) {
-            const pa_run_desc &d = c->descs[r];
-            if (launch_sweep_int8_run(c->lc, r, d.L, groups_cap_of(d), n_pop_of(d.overlap), d.theta) != hipSuccess)
-                return dev_fail(c);
-        }
-    }
+    if (launch_sweeps(c) != hipSuccess) return dev_fail(c);
     if (launch_dos_sample(c->lc) != hipSuccess) return dev_fail(c);
     c->phase = PH_SWEPT;
     return PA_OK;
@@ -1003,7 +1026,7 @@ pa_status pa_measure(pa_ctx *c, int32_t i, pa_obs *host_out)
     if (!c) return PA_ERR_ARG;
     if (c->failed) return PA_ERR_DEVICE;
     if (c->phase != PH_SWEPT || i != c->i) return PA_ERR_STATE;
-    if (launch_measure(c->lc) != hipSuccess) return dev_fail(c);
+    if (launch_measure(c->lc, false) != hipSuccess) return dev_fail(c);
     c->phase = PH_MEASURED;
     if (host_out) {
         const size_t n = (size_t)c->n_runs * c->lo.npop_ctx;
@@ -1294,8 +1317,12 @@ pa_status pa_restore(pa_ctx *c, const void *host_buf, size_t bytes)
     // the workspace copy brought back the sweep list of the plan at
     // checkpoint time; the launches use the current plan, so its list is
     // written again (the tuning may have changed since)
-    if (c->repr == PA_MSC64) return upload_sweep_plan(c);
-    return PA_OK;
+    const pa_status st = upload_sweep_plan(c);
+    // between a step's sweeps and its measurement the int8 layout's words are
+    // read next: a checkpoint that does not hold them has the bytes
+    if (st == PA_OK && c->repr == PA_INT8 && c->phase == PH_SWEPT && c->lc.any_swept)
+        PA_HIP(c, launch_words(c->lc, c->lo.maxN));
+    return st;
 }
 
 pa_status pa_set_tuning(pa_ctx *c, int32_t L, int32_t threads, int32_t groups_per_wg, int32_t dense_calls)
@@ -1358,7 +1385,7 @@ pa_status pa_get_sweep_launches(pa_ctx *c, int32_t *out)
 {
     if (!c || !out) return PA_ERR_ARG;
     int n = 0;
-    for (int k = 0; k < c->lc.n_sweep_classes; ++k) n += c->lc.sweep_cls[k].count > 0 ? 1 : 0;
+    for (int k = 0; k < c->lc.n_sweep_classes && c->repr == PA_MSC64; ++k) n += c->lc.sweep_cls[k].count > 0 ? 1 : 0;
     *out = n;
     return PA_OK;
 }

@@ -61,6 +61,7 @@ struct RunInfo {
     int32_t obs_stride, obs_off;
     int32_t wang_lb;              // permutation pairing: log2 of the bucket capacity
     int32_t exact_dos;            // 1: theta = infinity (energies drawn; theta is 0 here)
+    int32_t bytes;                // 1: int8 layout
     // device pointers into the caller's workspace
     uint8_t *spins[MAX_POP][2];   // int8: [group][site][64] bytes; MSC: [group][site] u64
     int32_t *E[MAX_POP][2];       // energies [R_cap]
@@ -128,11 +129,12 @@ constexpr int MAX_SWEEP_CHUNKS = 4;
 
 // LDS of a batched-sweep workgroup holding `groups` replica groups of N
 // sites in nw wavefronts.  mode = lockstep calls | pooled << 8, as the sweep
-// is launched: the sparse rounds are streamed for lattices of at most 4096
-// sites when they are not pooled and there are sparse rounds at all.
-__host__ __device__ inline bool msc_streamed(int N, int mode)
+// is launched: the sparse rounds are streamed when they are not pooled, there
+// are sparse rounds at all, and an entry's word has room for its site: below
+// 2^12 beside a group index, 2^20 without.
+__host__ __device__ inline bool msc_streamed(int N, int groups, int mode)
 {
-    return !((mode >> 8) & 1) && N <= 4096 && (mode & 0xFF) < 16;
+    return !((mode >> 8) & 1) && (mode & 0xFF) < 16 && (N <= 4096 || groups == 1);
 }
 
 // Site words of one colour that each wavefront owns: whole chunks of 64.
@@ -168,7 +170,7 @@ __host__ __device__ inline size_t msc_list_lds(int N, int groups, bool ea)
 
 __host__ __device__ inline size_t msc_lds_need(int N, int groups, bool ea, int nw, int mode)
 {
-    return msc_streamed(N, mode) ? msc_stream_lds(N, groups, ea, nw) : msc_list_lds(N, groups, ea);
+    return msc_streamed(N, groups, mode) ? msc_stream_lds(N, groups, ea, nw) : msc_list_lds(N, groups, ea);
 }
 
 // What a shape must fit in to be accepted: the larger of the two layouts
@@ -178,6 +180,12 @@ __host__ __device__ inline size_t msc_lds_bound(int N, int groups, bool ea, int 
     const size_t a = msc_stream_lds(N, groups, ea, nw), b = msc_list_lds(N, groups, ea) + 256;
     return a > b ? a : b;
 }
+
+// A run of the int8 layout whose lattice is swept from memory, one colour per
+// launch (k_sweep_wide).
+struct WideRun {
+    int run, L, groups_cap, npop, theta, ea;
+};
 
 struct ChunkItem {    // one chunk of CH replicas of one (run, pop)
     int32_t run, pop, chunk, pad;

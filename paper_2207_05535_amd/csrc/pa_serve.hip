@@ -167,6 +167,8 @@ struct pa_server {
     bool persistent = false, pooled = false;
     std::map<int, int> groups;          // L -> groups per workgroup, from the cache
     bool shaped = false;                // the shape comes from the cache
+    std::vector<WideRun> wide;          // int8 layout: runs swept one colour per launch
+    int max_N = 0;                      // sites of the largest resident lattice
     std::map<int, int> resident_groups; // else: L -> the same for the resident runs
     bool failed = false;
     hipError_t last = hipSuccess;
@@ -251,7 +253,10 @@ pa_status rebuild(pa_server *s)
     bool mn = false, wang = false, exact = false, mn_wide = false, ovl = false;
     std::vector<SweepItem> sweep;
     size_t lds = 0;
-    if (!s->shaped && s->repr == PA_MSC64) {
+    s->wide.clear();
+    s->max_N = 0;
+    bool swept = false, unswept = false;
+    if (!s->shaped || s->repr == PA_INT8) {
         std::vector<const pa_run_desc *> dp;
         for (const Slot &sl : s->slots)
             if (sl.used) dp.push_back(&sl.d);
@@ -271,11 +276,24 @@ pa_status rebuild(pa_server *s)
         ovl = ovl || sl.d.overlap != PA_Q_NONE;
         wang = wang || is_wang(sl.d.overlap);
         exact = exact || sl.d.theta == PA_THETA_EXACT;
-        if (s->repr == PA_MSC64) {
-            const int G = groups_of(s, sl.d.L);
+        swept = swept || sl.d.theta > 0;
+        unswept = unswept || sl.d.theta <= 0;
+        s->max_N = std::max(s->max_N, sl.d.L * sl.d.L);
+        {
+            const int G = s->repr == PA_INT8 ? s->resident_groups.at(sl.d.L) : groups_of(s, sl.d.L);
             const int N = sl.d.L * sl.d.L;
-            if ((size_t)G * N > 65535) return PA_ERR_ARG;
-            lds = std::max(lds, msc_lds_bound(N, G, sl.d.model == PA_EA_PMJ, s->threads / 64));
+            const bool ea = sl.d.model == PA_EA_PMJ;
+            if (s->repr == PA_MSC64) {
+                if ((size_t)G * N > 65535) return PA_ERR_ARG;
+                lds = std::max(lds, msc_lds_bound(N, G, ea, s->threads / 64));
+            } else {
+                if (sl.d.theta <= 0) continue;
+                if (sweeps_wide(sl.d, G, s->threads, s->lds_limit)) {
+                    s->wide.push_back({k, sl.d.L, groups_cap_of(sl.d), npop, sl.d.theta, ea ? 1 : 0});
+                    continue;
+                }
+                lds = std::max(lds, msc_stream_lds(N, G, ea, s->threads / 64));
+            }
             for (int p = 0; p < npop; ++p)
                 for (int g = 0; g < groups_cap_of(sl.d); g += G)
                     sweep.push_back({k, p, g, std::min(G, groups_cap_of(sl.d) - g)});
@@ -294,11 +312,12 @@ pa_status rebuild(pa_server *s)
             run_L[k] = s->slots[k].d.theta > 0 ? s->slots[k].d.L : 0;
             run_ea[k] = s->slots[k].d.model == PA_EA_PMJ;
         }
-    if (s->repr == PA_MSC64) {
+    const int mode = s->repr == PA_MSC64 ? serve_mode(s) : 3;   // the knobs are the bit-packed layout's
+    {
         SweepClass probe[MAX_SWEEP_CLASSES];
         // orders the list by class; a serving mix keeps one launch for its
         // sizes (their classes are too small to fill the chip one by one)
-        if (sweep_classes(sweep, run_L, run_ea, probe, s->threads, serve_mode(s), false) < 0)
+        if (sweep_classes(sweep, run_L, run_ea, probe, s->threads, mode, false) < 0)
             return PA_ERR_ARG;
     }
     if (!grow(s, s->items_off, s->items_cap, sizeof(Item) * std::max<size_t>(n_items, 1)) ||
@@ -353,14 +372,16 @@ pa_status rebuild(pa_server *s)
     c.sweep_items = (const SweepItem *)(s->base + s->sweep_off);
     c.n_sweep_items = (int)sweep.size();
     c.sweep_threads = s->threads;
-    c.sweep_dense = s->dense;
-    c.sweep_pooled = s->pooled ? 1 : 0;
+    c.sweep_dense = mode & 0xFF;
+    c.sweep_pooled = mode >> 8;
+    c.any_swept = swept;
+    c.any_unswept = unswept;
     c.n_sweep_classes = 0;
-    if (s->repr == PA_MSC64 && !sweep.empty()) {
+    if (!sweep.empty()) {
         if (prepare_msc_lds(lds) != hipSuccess) return sfail(s);
-        const int ncls = sweep_classes(sweep, run_L, run_ea, c.sweep_cls, s->threads, serve_mode(s), false);
+        const int ncls = sweep_classes(sweep, run_L, run_ea, c.sweep_cls, s->threads, mode, false);
         if (ncls < 0) return PA_ERR_ARG;
-        if (!sweep_class_grids(c.sweep_cls, ncls, s->threads, s->persistent)) return sfail(s);
+        if (!sweep_class_grids(c.sweep_cls, ncls, s->threads, s->repr == PA_MSC64 && s->persistent)) return sfail(s);
         c.n_sweep_classes = ncls;
         c.n_sweep_items = (int)sweep.size();
     }
@@ -532,7 +553,7 @@ pa_status pa_server_admit(pa_server *s, const pa_run_desc *desc, int32_t *slot)
             return st;
     }
     const int npop = n_pop_of(d.overlap);
-    const RunInfo I = make_runinfo(sl.d, blk, b.o, tbase, T.T, (pa_obs *)(blk + b.obs), npop, 0);
+    const RunInfo I = make_runinfo(sl.d, s->repr, blk, b.o, tbase, T.T, (pa_obs *)(blk + b.obs), npop, 0);
     PopState hst[MAX_POP];
     std::memset(hst, 0, sizeof(hst));
     for (int p = 0; p < npop; ++p) hst[p] = initial_popstate(sl.d);
@@ -585,7 +606,7 @@ pa_status pa_server_admit(pa_server *s, const pa_run_desc *desc, int32_t *slot)
             return sfail(s);
     }
     c.any_exact_dos = d.theta == PA_THETA_EXACT;
-    if (launch_init(c, (const uint64_t *)(blk + b.dseed)) != hipSuccess || launch_measure(c) != hipSuccess)
+    if (launch_init(c, (const uint64_t *)(blk + b.dseed)) != hipSuccess || launch_measure(c, true) != hipSuccess)
         return sfail(s);
     s->dirty = true;
     *slot = k;
@@ -611,16 +632,13 @@ pa_status pa_server_step(pa_server *s, int32_t *finished, int32_t *n_finished)
     if (s->repr == PA_MSC64) {
         if ((e = launch_sweep_msc(c)) != hipSuccess) return sfail(s, e);
     } else {
-        for (int k = 0; k < s->max_slots; ++k) {
-            const Slot &sl = s->slots[k];
-            if (!sl.used || sl.done >= sl.d.K - 1) continue;
-            if (launch_sweep_int8_run(c, k, sl.d.L, groups_cap_of(sl.d), n_pop_of(sl.d.overlap), sl.d.theta) !=
-                hipSuccess)
-                return sfail(s);
-        }
+        std::vector<WideRun> wide;   // of the runs that advance
+        for (const WideRun &w : s->wide)
+            if (s->slots[w.run].done < s->slots[w.run].d.K - 1) wide.push_back(w);
+        if ((e = launch_sweep_bytes(c, wide.data(), (int)wide.size(), s->max_N)) != hipSuccess) return sfail(s, e);
     }
     if ((e = launch_dos_sample(c)) != hipSuccess) return sfail(s, e);
-    if ((e = launch_measure(c)) != hipSuccess) return sfail(s, e);
+    if ((e = launch_measure(c, false)) != hipSuccess) return sfail(s, e);
     for (int k = 0; k < s->max_slots; ++k) {
         Slot &sl = s->slots[k];
         if (!sl.used || sl.done >= sl.d.K - 1) continue;

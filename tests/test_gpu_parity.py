@@ -734,3 +734,37 @@ def test_streamed_sweep_shapes(L, model, R, threads, groups, dense):
     assert_obs_equal(ctx.obs()[0, :1], orc.obs(), f"L={L}")
     assert_state_equal(ctx, orc, 0, f"L={L} final")
     ctx.close()
+
+
+@pytest.mark.parametrize("L,model,R,theta,overlap", [
+    (64, W.EA_PMJ, 70, 1, W.Q_TWO_POP),       # in LDS, two populations
+    (66, W.FM, 129, 1, W.Q_INDEX_SHIFT),      # few groups above 4096 sites: from memory
+    (72, W.FM, 8200, 1, W.Q_NONE),            # 129 groups: in LDS, one group per workgroup
+    (130, W.EA_PMJ, 65, 2, W.Q_INDEX_SHIFT),  # too large for LDS, ragged last chunk
+    (200, W.FM, 64, 1, W.Q_NONE)])
+def test_int8_large_lattices(L, model, R, theta, overlap):
+    """The int8 layout around its two ways of sweeping (lattice in LDS, or
+    one colour per launch from memory), next to a run without sweeps, whose
+    measurement reads bytes: records and final states equal the oracle's;
+    so does a run continued from a checkpoint taken between a step's sweeps
+    and its measurement."""
+    say(f"int8 L={L} model={model} R={R} overlap={overlap}")
+    d = W.run_desc(L, model, seed=W.RUN_SEED_BASE + 0x7500 + L, disorder_seed=3, R=R, theta=theta, K=4, beta_f=0.6,
+                   overlap=overlap)
+    still = W.run_desc(8, W.FM, seed=W.RUN_SEED_BASE + 0x7600, R=100, theta=0, K=4, beta_f=0.6)
+    orcs = [oracle.OracleRun(x).run_all() for x in (d, still)]
+    ctx = pa.Context([d, still], "int8")
+    ctx.step(1)
+    ctx.anneal_step(2)
+    ctx.resample(2)
+    ctx.sweep(2)
+    ck = ctx.checkpoint()
+    other = pa.Context([d, still], "int8")
+    other.restore(ck)
+    for c in (ctx, other):
+        c.measure(2)
+        c.run(3, 4)
+        for r, orc in enumerate(orcs):
+            assert_obs_equal(c.obs()[r, :orc.npop], orc.obs(), f"run {r}")
+            assert_state_equal(c, orc, r, f"run {r} final")
+        c.close()
