@@ -63,7 +63,10 @@ void compute_tables(const pa_run_desc &d, int N, std::vector<uint64_t> &X, std::
                     std::vector<uint64_t> &T);
 // RunInfo of a run whose buffers start at `base` (offsets o) and tables at
 // `tbase` (offsets T); records through obs with the given stride/offset.
-RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
+// Whether a population of this run is resampled by one workgroup, in a
+// context of n populations.
+bool resampled_alone(const pa_run_desc &d, int n);
+RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, bool fused, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
                      pa_obs *obs, int obs_stride, int obs_off);
 PopState initial_popstate(const pa_run_desc &d);
 // LDS ints of the permutation-pairing repair: 2 R_cap of the largest such

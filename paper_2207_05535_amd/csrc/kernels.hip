@@ -2,24 +2,25 @@
 // for gfx950 (CDNA4, 64-wide wavefronts).
 //
 // Step (i)   k_init_couplings, k_init_spins, k_init_fam (Sec. II B, III A)
-// Step (ii)  k_rw_chunk, k_rw_finish                   (Eqs. (QBoltz), (F))
-// Step (iii) k_cnt_chunk, k_mn_draws, k_cnt_scan_chunk, k_cnt_finish,
-//            k_parent, k_copy                          (Sec. II B, IV D, V A 1)
+// Step (ii)  k_rw_chunk                                (Eqs. (QBoltz), (F))
+// Step (iii) k_resample_run (one workgroup per population), or k_cnt_chunk,
+//            k_mn_draws, k_cnt_scan_chunk, k_parent; k_copy
+//                                                      (Sec. II B, IV D, V A 1)
 // Step (iv)  k_sweep_msc (all runs, lattice in LDS for all theta sweeps;
 //            also compiled per lattice size and model), k_sweep_wide (one
 //            colour of one run per launch, from memory), k_bytes_words (the
 //            int8 layout to words and back), k_dos_sample (the theta =
 //            infinity limit, Sec. V C)
 // Step (v)   k_wang_pairs, k_wang_rows, k_wang_gather (permutation pairing,
-//            Sec. III D), k_measure, k_meas_chunk, k_finalize
+//            Sec. III D), k_measure, k_meas_chunk
 //                                                      (Eqs. (e)-(chi), Sec. III D)
 // Sec. IV    k_logw, k_qweights, k_wavg, k_wavg_cumsum, k_wqhist, k_famstats
 // Diagnostic k_philox_rate (integer-VALU calibration)
 //
 // Population-wide reductions and scans are split into fixed-size chunks of
-// CH replicas (one workgroup each) plus a single-workgroup pass over the
-// chunk totals, so every result is independent of the launch shape and the
-// floating-point sums have one fixed order.
+// CH replicas (one workgroup each) plus a pass over the chunk totals by the
+// workgroup that comes last, so every result is independent of the launch
+// shape and the floating-point sums have one fixed order.
 #include <float.h>
 #include <hip/hip_runtime.h>
 
@@ -49,20 +50,33 @@ __device__ __forceinline__ int wave_id()
 
 __device__ __forceinline__ uint64_t umul64hi(uint64_t a, uint64_t b) { return __umul64hi(a, b); }
 
-// floor(rem * 2^32 / d) for rem < d < 2^63: 32 steps of binary long division.
-__device__ __forceinline__ uint32_t frac32(uint64_t rem, uint64_t d)
+// Quotient and remainder of a / d, and floor(rem 2^32 / d), for d < 2^63 and
+// quotients below 2^32: the FP64 estimates (relative error below 2^-50) are
+// at most one off, which the exact remainder shows.  inv = 1 / (double)d.
+__device__ __forceinline__ uint64_t div_exact(uint64_t a, uint64_t d, double inv, uint64_t &rem)
 {
-    uint32_t q = 0;
-#pragma unroll 4
-    for (int k = 0; k < 32; ++k) {
-        rem <<= 1;
-        q <<= 1;
-        if (rem >= d) {
-            rem -= d;
-            q |= 1u;
-        }
+    uint64_t q = (uint64_t)((double)a * inv);
+    int64_t r = (int64_t)(a - q * d);   // in (-d, 2d): a < 2^63, so no ambiguity
+    if (r < 0) {
+        --q;
+        r += (int64_t)d;
+    } else if ((uint64_t)r >= d) {
+        ++q;
+        r -= (int64_t)d;
     }
+    rem = (uint64_t)r;
     return q;
+}
+
+__device__ __forceinline__ uint32_t frac32(uint64_t rem, uint64_t d, double inv)
+{
+    uint64_t q = (uint64_t)((double)rem * inv * 4294967296.0);
+    // rem 2^32 - q d in 128 bits
+    const uint64_t alo = rem << 32, plo = q * d, lo = alo - plo;
+    const int64_t hi = (int64_t)((rem >> 32) - umul64hi(q, d) - (alo < plo ? 1u : 0u));
+    if (hi < 0) --q;
+    else if (hi > 0 || lo >= d) ++q;
+    return (uint32_t)q;
 }
 
 template <typename T>
@@ -78,6 +92,76 @@ __device__ __forceinline__ int wave_min(int v)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
     return v;
+}
+
+// Values passed between workgroups of one launch: device-coherent stores and
+// loads, ordered by waiting for the stores before the counter that announces
+// them (no write-back of an L2).
+template <typename T>
+__device__ __forceinline__ void put(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T take(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A thread's CH_PER consecutive elements, from index jb (a multiple of CH_PER)
+// of a 256-byte aligned array: 16-byte accesses where all of them are below
+// `end`, one by one in the last, partial block.  (A thread's elements one at
+// a time touch as many lines per instruction as the wavefront has lanes.)
+template <typename T>
+__device__ __forceinline__ void load_block(const T *a, int jb, int end, T fill, T (&v)[CH_PER])
+{
+    constexpr int PER = 16 / sizeof(T);
+    if (jb + CH_PER <= end) {
+#pragma unroll
+        for (int q = 0; q < CH_PER / PER; ++q) {
+            const uint4 w = ((const uint4 *)(a + jb))[q];
+            __builtin_memcpy(&v[q * PER], &w, 16);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < CH_PER; ++q) v[q] = jb + q < end ? a[jb + q] : fill;
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void store_block(T *a, int jb, int end, const T (&v)[CH_PER])
+{
+    constexpr int PER = 16 / sizeof(T);
+    if (jb + CH_PER <= end) {
+#pragma unroll
+        for (int q = 0; q < CH_PER / PER; ++q) {
+            uint4 w;
+            __builtin_memcpy(&w, &v[q * PER], 16);
+            ((uint4 *)(a + jb))[q] = w;
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < CH_PER; ++q)
+            if (jb + q < end) a[jb + q] = v[q];
+    }
+}
+
+// Counts this workgroup in once its first thread's stores and atomics have
+// completed; true in the workgroup that comes last of n.  The counter is zero
+// again when it has come (one kernel of a step uses it after the other).  To
+// be called by the whole workgroup; includes a barrier.
+__device__ __forceinline__ bool last_of(int32_t *done, int n)
+{
+    __shared__ int last;
+    if (n == 1) return true;   // nobody else: what it put is still its own
+    if (threadIdx.x == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const int k = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = k == n - 1;
+        if (last) put(done, 0);
+    }
+    __syncthreads();
+    return last;
 }
 
 __device__ __forceinline__ bool pop_active(const PopState &S) { return S.moved && S.status == PA_OK; }
@@ -339,18 +423,23 @@ __global__ void k_init_fam(const RunInfo *runs)
 // Reweighting, Eq. (tauBoltz)/(QBoltz): per chunk of CH replicas the partial
 // sums of x_j = exp(-dbeta (E_j - E_min)) (FP64) and of X_j = floor(x_j 2^40)
 // (exact); for multinomial resampling also the chunk-local exclusive prefix
-// of X_j.  The temperature index is i = (index of the population) + 1.
-__global__ void __launch_bounds__(CH_THREADS) k_rw_chunk(const ChunkItem *items, const RunInfo *runs,
-                                                          const PopState *st)
+// of X_j and cleared descendant counts.  The temperature index is
+// i = (index of the population) + 1.  The population's last chunk finishes
+// the step: chunk bases of the prefix, ln Q_i and A_i.  (In launches of their
+// own that and the clearing took 2-12 us each, counting in takes 1-4; with
+// 16-byte accesses 256 populations of 2e4 take 30 us, 65 in three launches.)
+__global__ void __launch_bounds__(CH_THREADS) k_rw_chunk(const ChunkItem *items, const RunInfo *runs, PopState *st)
 {
     __shared__ uint64_t lds64[CH_THREADS / 64 + 1];
-    __shared__ double ldsd[CH_THREADS / 64];
+    __shared__ double ldsd[CH_THREADS];
     const ChunkItem it = items[blockIdx.x];
     const RunInfo &R = runs[it.run];
-    const PopState &S = st[it.run * MAX_POP + it.pop];
-    if (S.status != PA_OK) return;
+    PopState &S = st[it.run * MAX_POP + it.pop];
     const int i = S.i + 1;
-    if (i >= R.K) return;
+    if (S.status != PA_OK || i >= R.K) {
+        if (it.chunk == 0 && threadIdx.x == 0) S.moved = 0;
+        return;
+    }
     const int Rp = S.Rcur;
     const int j0 = it.chunk * CH;
     if (j0 >= Rp) return;
@@ -363,13 +452,14 @@ __global__ void __launch_bounds__(CH_THREADS) k_rw_chunk(const ChunkItem *items,
     const int jb = j0 + threadIdx.x * CH_PER;
     double s = 0.0;
     uint64_t sx = 0;
+    int32_t Ej[CH_PER];
+    load_block(E, jb, Rp, Emin, Ej);
     uint64_t loc[CH_PER];
 #pragma unroll
     for (int q = 0; q < CH_PER; ++q) {
-        const int j = jb + q;
         uint64_t Xj = 0;
-        if (j < Rp) {
-            const int k = min(max((E[j] - Emin) >> 2, 0), R.N);
+        if (jb + q < Rp) {
+            const int k = min(max((Ej[q] - Emin) >> 2, 0), R.N);
             Xj = X[k];
             s += x[k];
         }
@@ -379,10 +469,13 @@ __global__ void __launch_bounds__(CH_THREADS) k_rw_chunk(const ChunkItem *items,
     uint64_t tot;
     const uint64_t pre = block_exscan<uint64_t, CH_THREADS>(sx, lds64, &tot);
     if (R.resampling == PA_MULTINOMIAL) {
-        uint64_t *P = R.P[it.pop];
 #pragma unroll
-        for (int q = 0; q < CH_PER; ++q)
-            if (jb + q < Rp) P[jb + q] = pre + loc[q];
+        for (int q = 0; q < CH_PER; ++q) loc[q] += pre;
+        store_block(R.P[it.pop], jb, Rp, loc);
+        if (!R.fused) {
+            const int32_t none[CH_PER] = {};
+            store_block(R.r[it.pop], jb, Rp, none);
+        }
     }
     // fixed-order FP64 tree: wave shuffles then waves in order
     double ws = s;
@@ -390,45 +483,39 @@ __global__ void __launch_bounds__(CH_THREADS) k_rw_chunk(const ChunkItem *items,
     for (int o = 1; o < 64; o <<= 1) ws += __shfl_xor(ws, o, 64);
     if ((threadIdx.x & 63) == 0) ldsd[threadIdx.x >> 6] = ws;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int k = 0; k < CH_THREADS / 64; ++k) t += ldsd[k];
-        R.partS[it.pop][it.chunk] = t;
-        R.tot64[it.pop][it.chunk] = tot;
-    }
-}
-
-// ln Q_i = ln S - ln R_{i-1} - dbeta E_min and A_i = A_{i-1} + ln Q_i,
-// Eqs. (QBoltz), (F); chunk bases of the X prefix for multinomial draws.
-__global__ void k_rw_finish(const RunInfo *runs, PopState *st)
-{
-    __shared__ uint64_t lds64[257];
-    const int run = blockIdx.x, pop = blockIdx.y;
-    const RunInfo &R = runs[run];
-    if (pop >= R.npop) return;
-    PopState &S = st[run * MAX_POP + pop];
-    const int i = S.i + 1;
-    const bool go = S.status == PA_OK && i < R.K;
-    if (!go) {
-        if (threadIdx.x == 0) S.moved = 0;
-        return;
-    }
-    const int Rp = S.Rcur;
     const int nch = (Rp + CH - 1) / CH;
-    uint64_t carry = 0;
-    for (int base = 0; base < nch; base += 256) {
+    double part = 0.0;
+    if (threadIdx.x == 0) {
+        for (int k = 0; k < CH_THREADS / 64; ++k) part += ldsd[k];
+        if (nch > 1) {
+            put(&R.partS[it.pop][it.chunk], part);
+            put(&R.tot64[it.pop][it.chunk], tot);
+        }
+    }
+    if (!last_of(&S.done, nch)) return;
+
+    // ln Q_i = ln S - ln R_{i-1} - dbeta E_min and A_i = A_{i-1} + ln Q_i,
+    // Eqs. (QBoltz), (F); the chunks' sums added in order
+    uint64_t carry = nch > 1 ? 0 : tot;
+    double Ssum = nch > 1 ? 0.0 : part;
+    if (nch == 1 && threadIdx.x == 0) R.base64[it.pop][0] = 0;
+    for (int base = 0; nch > 1 && base < nch; base += CH_THREADS) {
         const int c = base + threadIdx.x;
-        const uint64_t v = c < nch ? R.tot64[pop][c] : 0;
-        uint64_t tot;
-        const uint64_t pre = block_exscan<uint64_t, 256>(v, lds64, &tot);
-        if (c < nch) R.base64[pop][c] = carry + pre;
-        carry += tot;
+        const uint64_t v = c < nch ? take(&R.tot64[it.pop][c]) : 0;
+        ldsd[threadIdx.x] = c < nch ? take(&R.partS[it.pop][c]) : 0.0;
+        uint64_t all;
+        const uint64_t before = block_exscan<uint64_t, CH_THREADS>(v, lds64, &all);
+        if (c < nch) R.base64[it.pop][c] = carry + before;
+        carry += all;
+        if (threadIdx.x == 0) {
+            const int n = min(CH_THREADS, nch - base);
+            for (int k = 0; k < n; ++k) Ssum += ldsd[k];
+        }
+        __syncthreads();
     }
     if (threadIdx.x == 0) {
-        double Ssum = 0.0;
-        for (int c = 0; c < nch; ++c) Ssum += R.partS[pop][c];
         const double db = R.beta[i] - R.beta[i - 1];
-        const double lnQ = log(Ssum) - log((double)Rp) - db * (double)S.Emin;
+        const double lnQ = log(Ssum) - log((double)Rp) - db * (double)Emin;
         S.lnQ = lnQ;
         S.A = S.A + lnQ;
         S.S = Ssum;
@@ -439,79 +526,150 @@ __global__ void k_rw_finish(const RunInfo *runs, PopState *st)
     }
 }
 
-// ------------------------------------------------------------ step (iii)
-
-// Nearest-integer counts r_j = n_j + [u_j < t_j], n_j = floor(R X_j / S_X),
-// t_j = floor((R X_j mod S_X) 2^32 / S_X), u_j = o0 of Philox(seed; j, 0, i,
-// TAG_NI << 28 | pop << 24); then the chunk-local exclusive prefix of r.
-// For multinomial resampling this only clears r.
-__global__ void __launch_bounds__(CH_THREADS) k_cnt_chunk(const ChunkItem *items, const RunInfo *runs,
-                                                           const PopState *st)
+// Clears the descendant counts as k_rw_chunk does, for populations restored
+// between steps (ii) and (iii).
+__global__ void __launch_bounds__(CH_THREADS) k_clear_counts(const ChunkItem *items, const RunInfo *runs,
+                                                              const PopState *st)
 {
-    __shared__ int32_t lds[CH_THREADS / 64 + 1];
     const ChunkItem it = items[blockIdx.x];
     const RunInfo &R = runs[it.run];
     const PopState &S = st[it.run * MAX_POP + it.pop];
-    if (!pop_active(S)) return;
+    if (!pop_active(S) || R.resampling != PA_MULTINOMIAL) return;
+    for (int q = 0; q < CH_PER; ++q) {
+        const int j = it.chunk * CH + q * CH_THREADS + (int)threadIdx.x;
+        if (j < S.Rprev) R.r[it.pop][j] = 0;
+    }
+}
+
+// ------------------------------------------------------------ step (iii)
+
+__device__ __forceinline__ pa_obs &obs_at(const RunInfo &R, int i, int pop)
+{
+    return R.obs[(size_t)i * R.obs_stride + R.obs_off + pop];
+}
+
+__device__ void freeze_run(const RunInfo &R, PopState &S, int i, int pop, int32_t status)
+{
+    for (int k = i + threadIdx.x; k < R.K; k += blockDim.x) {
+        pa_obs o = {};
+        o.status = status;
+        obs_at(R, k, pop) = o;
+    }
+    if (threadIdx.x == 0) {
+        S.status = status;
+        S.moved = 0;
+    }
+}
+
+// R_i = sum r_j: capacity and empty-population checks (the run is frozen
+// with that status); otherwise the new population becomes current: the copy
+// reads buffer src, writes cur.  False if frozen.  By the whole workgroup.
+__device__ __forceinline__ bool accept_counts(const RunInfo &R, PopState &S, int pop, int64_t total)
+{
+    if (total > R.R_cap || total == 0) {
+        freeze_run(R, S, S.i, pop, total ? PA_ERR_CAPACITY : PA_ERR_NUMERIC);
+        return false;
+    }
+    if (threadIdx.x == 0) {
+        S.src = S.cur;
+        S.cur = S.cur ^ 1;
+        S.Rcur = (int32_t)total;
+    }
+    return true;
+}
+
+// Nearest-integer count of replica j with energy E: r_j = n_j + [u_j < t_j],
+// n_j = floor(R X_j / S_X), t_j = floor((R X_j mod S_X) 2^32 / S_X), u_j = o0
+// of Philox(seed; j, 0, i, TAG_NI << 28 | pop << 24).
+__device__ __forceinline__ int nearest_count(const RunInfo &R, const PopState &S, int pop, int j, int E,
+                                             const uint64_t *X, double invSX)
+{
+    const uint64_t RX = (uint64_t)R.R * X[min(max((E - S.Emin) >> 2, 0), R.N)];
+    uint64_t rem;
+    const uint64_t n = div_exact(RX, S.SX, invSX, rem);
+    const uint32_t t = frac32(rem, S.SX, invSX);
+    const u32x4 o = philox10((uint32_t)j, 0, (uint32_t)S.i, (TAG_NI << 28) | ((uint32_t)pop << 24), R.key0, R.key1);
+    return (int)n + (o.x < t ? 1 : 0);
+}
+
+// Chunk bases of the count prefix and the checks, by the population's last
+// chunk (the chunks' totals are in tot32).
+__device__ __forceinline__ void finish_counts(const RunInfo &R, PopState &S, int pop, int tot0, int64_t *lds64)
+{
+    const int nch = (S.Rprev + CH - 1) / CH;
+    int64_t carry = nch > 1 ? 0 : tot0;
+    if (nch == 1 && threadIdx.x == 0) R.base32[pop][0] = 0;
+    for (int base = 0; nch > 1 && base < nch; base += CH_THREADS) {
+        const int c = base + threadIdx.x;
+        const int64_t v = c < nch ? take(&R.tot32[pop][c]) : 0;
+        int64_t tot;
+        const int64_t pre = block_exscan<int64_t, CH_THREADS>(v, lds64, &tot);
+        if (c < nch) R.base32[pop][c] = (int32_t)(carry + pre);
+        carry += tot;
+    }
+    accept_counts(R, S, pop, carry);
+}
+
+// Nearest-integer counts and their chunk-local exclusive prefix.  The counts
+// are taken a replica per thread and round (a thread's own eight in turn
+// would be a chain of eight draws and divisions), then scanned from LDS in
+// order.
+__global__ void __launch_bounds__(CH_THREADS) k_cnt_chunk(const ChunkItem *items, const RunInfo *runs, PopState *st)
+{
+    __shared__ int32_t lds[CH_THREADS / 64 + 1];
+    __shared__ int64_t lds64[CH_THREADS / 64 + 1];
+    __shared__ int32_t cnt[CH];
+    const ChunkItem it = items[blockIdx.x];
+    const RunInfo &R = runs[it.run];
+    PopState &S = st[it.run * MAX_POP + it.pop];
+    if (!pop_active(S) || R.resampling != PA_NEAREST_INT || R.fused) return;
     const int Rp = S.Rprev;
     const int j0 = it.chunk * CH;
     if (j0 >= Rp) return;
-    const int jb = j0 + threadIdx.x * CH_PER;
-    int32_t *r = R.r[it.pop];
-    if (R.resampling == PA_MULTINOMIAL) {
-#pragma unroll
-        for (int q = 0; q < CH_PER; ++q)
-            if (jb + q < Rp) r[jb + q] = 0;
-        return;
-    }
-    const int i = S.i;
     const int32_t *E = R.E[it.pop][S.cur];
-    const uint64_t *X = R.tabX + (size_t)i * (R.N + 1);
-    const uint64_t SX = S.SX;
-    const uint32_t c3 = (TAG_NI << 28) | ((uint32_t)it.pop << 24);
+    const uint64_t *X = R.tabX + (size_t)S.i * (R.N + 1);
+    const double invSX = 1.0 / (double)S.SX;
+    int32_t *r = R.r[it.pop];
+    for (int q = 0; q < CH_PER; ++q) {
+        const int k = q * CH_THREADS + threadIdx.x, j = j0 + k;
+        int rj = 0;
+        if (j < Rp) {
+            rj = nearest_count(R, S, it.pop, j, E[j], X, invSX);
+            r[j] = rj;
+        }
+        cnt[k] = rj;
+    }
+    __syncthreads();
     int32_t loc[CH_PER];
     int32_t sum = 0;
 #pragma unroll
     for (int q = 0; q < CH_PER; ++q) {
-        const int j = jb + q;
-        int32_t rj = 0;
-        if (j < Rp) {
-            const uint64_t RX = (uint64_t)R.R * X[min(max((E[j] - S.Emin) >> 2, 0), R.N)];
-            const uint64_t n = RX / SX;
-            const uint64_t rem = RX - n * SX;
-            const uint32_t t = frac32(rem, SX);
-            const u32x4 o = philox10((uint32_t)j, 0, (uint32_t)i, c3, R.key0, R.key1);
-            rj = (int32_t)n + (o.x < t ? 1 : 0);
-            r[j] = rj;
-        }
         loc[q] = sum;
-        sum += rj;
+        sum += cnt[threadIdx.x * CH_PER + q];
     }
     int32_t tot;
     const int32_t pre = block_exscan<int32_t, CH_THREADS>(sum, lds, &tot);
-    int32_t *C = R.C[it.pop];
 #pragma unroll
-    for (int q = 0; q < CH_PER; ++q)
-        if (jb + q < Rp) C[jb + q] = pre + loc[q];
-    if (threadIdx.x == 0) R.tot32[it.pop][it.chunk] = tot;
+    for (int q = 0; q < CH_PER; ++q) loc[q] += pre;
+    store_block(R.C[it.pop], j0 + threadIdx.x * CH_PER, Rp, loc);
+    if (threadIdx.x == 0) put(&R.tot32[it.pop][it.chunk], tot);
+    if (last_of(&S.done, (Rp + CH - 1) / CH)) finish_counts(R, S, it.pop, tot, lds64);
 }
 
 // Multinomial draws: draw d picks the parent j with P_j <= t < P_j + X_j,
 // t = floor(v S_X / 2^64), v = o0 | o1 << 32 of Philox(seed; d, 0, i,
 // TAG_MN << 28 | pop << 24); P_j = base64[chunk] + chunk-local prefix.
-// `split` workgroups per chunk item (1 or CH_PER): a run that fits one
-// chunk is drawn by the first of them alone; in larger runs each takes
-// CH_PER / split rounds of CH_THREADS draws, one per thread and round (the
-// searches are chains of dependent loads at scattered addresses, so with
-// split = CH_PER they are spread over as many compute units as possible).
+// CH_PER workgroups per chunk item, each one round of CH_THREADS draws: the
+// searches are chains of dependent loads at scattered addresses, so they are
+// spread over as many compute units as possible.
 __global__ void __launch_bounds__(CH_THREADS) k_mn_draws(const ChunkItem *items, const RunInfo *runs,
-                                                          const PopState *st, int split)
+                                                          const PopState *st)
 {
-    const int part = blockIdx.x % split;
-    const ChunkItem it = items[blockIdx.x / split];
+    const int part = blockIdx.x % CH_PER;
+    const ChunkItem it = items[blockIdx.x / CH_PER];
     const RunInfo &R = runs[it.run];
     const PopState &S = st[it.run * MAX_POP + it.pop];
-    if (!pop_active(S) || R.resampling != PA_MULTINOMIAL) return;
+    if (!pop_active(S) || R.resampling != PA_MULTINOMIAL || R.fused) return;
     const int d0 = it.chunk * CH;
     if (d0 >= R.R) return;
     const int Rp = S.Rprev;
@@ -520,48 +678,18 @@ __global__ void __launch_bounds__(CH_THREADS) k_mn_draws(const ChunkItem *items,
     const uint64_t *B = R.base64[it.pop];
     const uint32_t c3 = (TAG_MN << 28) | ((uint32_t)it.pop << 24);
     int32_t *r = R.r[it.pop];
-    __shared__ uint64_t sP[CH];   // one chunk's prefix, or the chunk bases
-    __shared__ int32_t sr[CH];
-    if (R.R <= CH && Rp <= CH) {
-        // the whole run in this workgroup: prefix and counts in LDS, the
-        // counts are written out once (no global atomics)
-        if (part != 0) return;
-        for (int j = threadIdx.x; j < Rp; j += CH_THREADS) {
-            sP[j] = P[j];     // one chunk: base64[0] = 0
-            sr[j] = 0;
-        }
-        __syncthreads();
-        for (int q = 0; q < CH_PER; ++q) {
-            const int d = threadIdx.x + q * CH_THREADS;
-            if (d >= R.R) break;
-            const u32x4 o = philox10((uint32_t)d, 0, (uint32_t)S.i, c3, R.key0, R.key1);
-            const uint64_t v = (uint64_t)o.x | ((uint64_t)o.y << 32);
-            const uint64_t t = umul64hi(v, SX);
-            int lo = 0, hi = Rp - 1;
-            while (lo < hi) {
-                const int mid = lo + ((hi - lo + 1) >> 1);
-                if (sP[mid] <= t) lo = mid;
-                else hi = mid - 1;
-            }
-            atomicAdd(&sr[lo], 1);
-        }
-        __syncthreads();
-        for (int j = threadIdx.x; j < Rp; j += CH_THREADS) r[j] = sr[j];
-        return;
-    }
+    __shared__ uint64_t sB[CH];   // the chunk bases
     // largest j with P_j <= t in two levels: the last chunk whose base is
     // <= t (chunk bases staged in LDS), then inside that chunk
     const int nch = (Rp + CH - 1) / CH;
-    uint64_t *sB = sP;
     const bool staged = nch <= CH;
     if (staged)
         for (int k = threadIdx.x; k < nch; k += CH_THREADS) sB[k] = B[k];
     __syncthreads();
     // Fixed power-of-two steps: the largest index whose key is <= t,
     // starting from index 0, whose key is 0.
-    for (int q = part; q < CH_PER; q += split) {
-        const int d = d0 + q * CH_THREADS + (int)threadIdx.x;
-        if (d >= R.R) break;
+    const int d = d0 + part * CH_THREADS + (int)threadIdx.x;
+    if (d < R.R) {
         const u32x4 o = philox10((uint32_t)d, 0, (uint32_t)S.i, c3, R.key0, R.key1);
         const uint64_t v = (uint64_t)o.x | ((uint64_t)o.y << 32);
         uint64_t t = umul64hi(v, SX);
@@ -584,128 +712,242 @@ __global__ void __launch_bounds__(CH_THREADS) k_mn_draws(const ChunkItem *items,
 
 // Multinomial: chunk-local exclusive prefix of the counts r.
 __global__ void __launch_bounds__(CH_THREADS) k_cnt_scan_chunk(const ChunkItem *items, const RunInfo *runs,
-                                                                const PopState *st)
+                                                                PopState *st)
 {
     __shared__ int32_t lds[CH_THREADS / 64 + 1];
+    __shared__ int64_t lds64[CH_THREADS / 64 + 1];
     const ChunkItem it = items[blockIdx.x];
     const RunInfo &R = runs[it.run];
-    const PopState &S = st[it.run * MAX_POP + it.pop];
-    if (!pop_active(S) || R.resampling != PA_MULTINOMIAL) return;
+    PopState &S = st[it.run * MAX_POP + it.pop];
+    if (!pop_active(S) || R.resampling != PA_MULTINOMIAL || R.fused) return;
     const int Rp = S.Rprev;
     const int j0 = it.chunk * CH;
     if (j0 >= Rp) return;
     const int jb = j0 + threadIdx.x * CH_PER;
     const int32_t *r = R.r[it.pop];
-    int32_t loc[CH_PER];
+    int32_t rj[CH_PER], loc[CH_PER];
+    load_block(r, jb, Rp, 0, rj);
     int32_t sum = 0;
 #pragma unroll
     for (int q = 0; q < CH_PER; ++q) {
         loc[q] = sum;
-        if (jb + q < Rp) sum += r[jb + q];
+        sum += rj[q];
     }
     int32_t tot;
     const int32_t pre = block_exscan<int32_t, CH_THREADS>(sum, lds, &tot);
-    int32_t *C = R.C[it.pop];
 #pragma unroll
-    for (int q = 0; q < CH_PER; ++q)
-        if (jb + q < Rp) C[jb + q] = pre + loc[q];
-    if (threadIdx.x == 0) R.tot32[it.pop][it.chunk] = tot;
-}
-
-__device__ __forceinline__ pa_obs &obs_at(const RunInfo &R, int i, int pop)
-{
-    return R.obs[(size_t)i * R.obs_stride + R.obs_off + pop];
-}
-
-__device__ void freeze_run(const RunInfo &R, PopState &S, int pop, int i, int32_t status)
-{
-    for (int k = i + threadIdx.x; k < R.K; k += blockDim.x) {
-        pa_obs o = {};
-        o.status = status;
-        obs_at(R, k, pop) = o;
-    }
-    if (threadIdx.x == 0) {
-        S.status = status;
-        S.moved = 0;
-    }
-}
-
-// Chunk bases of the count prefix, R_i = sum r_j; capacity and empty-
-// population checks (the run is frozen with that status); otherwise the
-// new population becomes current: the copy reads buffer src, writes cur.
-__global__ void k_cnt_finish(const RunInfo *runs, PopState *st)
-{
-    __shared__ int64_t lds64[257];
-    const int run = blockIdx.x, pop = blockIdx.y;
-    const RunInfo &R = runs[run];
-    if (pop >= R.npop) return;
-    PopState &S = st[run * MAX_POP + pop];
-    if (!pop_active(S)) return;
-    const int Rp = S.Rprev;
-    const int nch = (Rp + CH - 1) / CH;
-    int64_t carry = 0;
-    for (int base = 0; base < nch; base += 256) {
-        const int c = base + threadIdx.x;
-        const int64_t v = c < nch ? R.tot32[pop][c] : 0;
-        int64_t tot;
-        const int64_t pre = block_exscan<int64_t, 256>(v, lds64, &tot);
-        if (c < nch) R.base32[pop][c] = (int32_t)(carry + pre);
-        carry += tot;
-    }
-    __syncthreads();
-    if (carry > R.R_cap) {
-        freeze_run(R, S, pop, S.i, PA_ERR_CAPACITY);
-        return;
-    }
-    if (carry == 0) {
-        freeze_run(R, S, pop, S.i, PA_ERR_NUMERIC);
-        return;
-    }
-    if (threadIdx.x == 0) {
-        S.src = S.cur;
-        S.cur = S.cur ^ 1;
-        S.Rcur = (int32_t)carry;
-    }
+    for (int q = 0; q < CH_PER; ++q) loc[q] += pre;
+    store_block(R.C[it.pop], jb, Rp, loc);
+    if (threadIdx.x == 0) put(&R.tot32[it.pop][it.chunk], tot);
+    if (last_of(&S.done, (Rp + CH - 1) / CH)) finish_counts(R, S, it.pop, tot, lds64);
 }
 
 // Parent of every child slot: parent j's r_j children occupy the slots
-// C_j .. C_j + r_j - 1 (C_j = base32[chunk] + chunk-local prefix), so each
-// parent writes its own.  A lane writes the first few; the slots of larger
-// families are written by the whole wavefront, one family at a time.
+// C_j .. C_j + r_j - 1, so each parent writes its own.  A lane writes the
+// first few; the slots of larger families are written by the whole
+// wavefront, one family at a time.  By the whole wavefront, rj = 0 on lanes
+// without a parent.
 constexpr int PARENT_LANE_MAX = 4;
 
+__device__ __forceinline__ void write_children(int32_t *par, int j, int cj, int rj)
+{
+    const int lane = threadIdx.x & 63;
+    const int mine = min(rj, PARENT_LANE_MAX);
+    for (int m = 0; m < mine; ++m) par[cj + m] = j;
+    uint64_t big = __ballot(rj > PARENT_LANE_MAX);
+    while (big) {
+        const int src = __ffsll((unsigned long long)big) - 1;
+        big &= big - 1;
+        const int bj = __builtin_amdgcn_readlane(j, src), bc = __builtin_amdgcn_readlane(cj, src),
+                  br = __builtin_amdgcn_readlane(rj, src);
+        for (int m = PARENT_LANE_MAX + lane; m < br; m += 64) par[bc + m] = bj;
+    }
+}
+
+// C_j = base32[chunk] + chunk-local prefix.
 __global__ void __launch_bounds__(CH_THREADS) k_parent(const ChunkItem *items, const RunInfo *runs,
                                                         const PopState *st)
 {
     const ChunkItem it = items[blockIdx.x];
     const RunInfo &R = runs[it.run];
     const PopState &S = st[it.run * MAX_POP + it.pop];
-    if (!pop_active(S)) return;
+    if (!pop_active(S) || R.fused) return;
     const int Rp = S.Rprev;
     const int j0 = it.chunk * CH;
     if (j0 >= Rp) return;
-    const int lane = threadIdx.x & 63;
     const int32_t *C = R.C[it.pop];
     const int32_t *r = R.r[it.pop];
     const int32_t base = R.base32[it.pop][it.chunk];
-    int32_t *par = R.parent[it.pop];
 #pragma unroll
     for (int q = 0; q < CH_PER; ++q) {
         const int j = j0 + q * CH_THREADS + (int)threadIdx.x;
-        int rj = 0, cj = 0;
-        if (j < Rp) {
-            rj = r[j];
-            cj = base + C[j];
+        const bool in = j < Rp;
+        write_children(R.parent[it.pop], j, in ? base + C[j] : 0, in ? r[j] : 0);
+    }
+}
+
+// Step (iii) up to the copy for a run that fits one workgroup per population
+// (R.fused): counts in LDS, their prefix, the checks and the parent map, in
+// place of four launches.  The counts are 16 bits wide (a run of at most
+// FUSED_MAX replicas draws no more), two to a word.  Multinomial draws search
+// in LDS alone: a guide (where in the coarse prefix a draw with these high
+// bits must lie), the coarse prefix (every CH_PER-th replica), then the fine
+// one inside the block, kept as the 32 high bits of its offset from the
+// block's first (offsets are below CH_PER 2^40); a draw whose high bits equal
+// the one found reads the exact prefix.  Bound by the latency of a single
+// workgroup's passes where there are few populations, by LDS reads and the
+// generator where every CU has one.  Draws, scan, checks and parent map: 303
+// -> 58 us for 256 populations of 2e4 (eleven dependent reads of memory per
+// draw before), 16 -> 10 us for one of 1000, 18 -> 18 for one of 8000; one of
+// 2e4 takes 38 chunk by chunk and 58 here, so above 8192 it needs 64
+// populations to pay (32 of 2e4: 61 and 58).
+constexpr int FINE_SHIFT = 11;
+static_assert(CH_PER == 8, "40 + 3 bits of offset");
+constexpr int GUIDE_BITS = 11;
+
+__global__ void __launch_bounds__(1024) k_resample_run(const RunInfo *runs, PopState *st)
+{
+    // counts [R] u16, coarse prefix [R/8], fine prefix [R] (fused_lds)
+    extern __shared__ __align__(16) uint64_t lds[];
+    __shared__ uint16_t guide[(1 << GUIDE_BITS) + 2];
+    __shared__ int32_t wsum[17];
+    const int run = blockIdx.x, pop = blockIdx.y;
+    const RunInfo &R = runs[run];
+    if (pop >= R.npop || !R.fused) return;
+    PopState &S = st[run * MAX_POP + pop];
+    if (!pop_active(S)) return;
+    const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wv = wave_id(), nw = T >> 6;
+    const int Rp = S.Rprev, n8 = (Rp + CH_PER - 1) / CH_PER;
+    const bool mn = R.resampling == PA_MULTINOMIAL;
+    uint32_t *cnt = (uint32_t *)lds;
+    uint64_t *T8 = lds + 2 * (size_t)n8;
+    uint32_t *F = (uint32_t *)(T8 + n8);
+    const uint64_t SX = S.SX;
+    for (int k = tid; k < n8 * (CH_PER / 2); k += T) cnt[k] = 0;
+    if (mn) {
+        // a thread takes blocks of CH_PER prefixes with 16-byte loads, all of a
+        // block in flight together
+        const uint64_t *B = R.base64[pop], *P = R.P[pop];
+        for (int k = tid; k < n8; k += T) {
+            uint64_t p[CH_PER];
+            load_block(P, k * CH_PER, Rp, ~(uint64_t)0, p);
+            T8[k] = B[k / (CH / CH_PER)] + p[0];
+            uint32_t f[CH_PER];
+#pragma unroll
+            for (int q = 0; q < CH_PER; ++q) f[q] = k * CH_PER + q < Rp ? (uint32_t)((p[q] - p[0]) >> FINE_SHIFT) : ~0u;
+#pragma unroll
+            for (int q = 0; q < CH_PER; q += 4)
+                ((uint4 *)F)[k * (CH_PER / 4) + q / 4] = make_uint4(f[q], f[q + 1], f[q + 2], f[q + 3]);
         }
-        const int mine = min(rj, PARENT_LANE_MAX);
-        for (int m = 0; m < mine; ++m) par[cj + m] = j;
-        uint64_t big = __ballot(rj > PARENT_LANE_MAX);
-        while (big) {
-            const int src = __ffsll((unsigned long long)big) - 1;
-            big &= big - 1;
-            const int bj = __builtin_amdgcn_readlane(j, src), bc = __builtin_amdgcn_readlane(cj, src),
-                      br = __builtin_amdgcn_readlane(rj, src);
-            for (int m = PARENT_LANE_MAX + lane; m < br; m += 64) par[bc + m] = bj;
+        __syncthreads();
+        // largest b with T8[b] <= t, starting from block b0 (T8[b0] <= t) in
+        // power-of-two steps below span
+        auto search = [&](uint64_t t, int b0, int span) {
+            int b = b0;
+            for (int step = span; step > 0; step >>= 1) {
+                const int m = b + step;
+                if (m < n8 && T8[m] <= t) b = m;
+            }
+            return b;
+        };
+        const int top = n8 > 1 ? 1 << (31 - __builtin_clz(n8 - 1)) : 0;
+        const bool guided = n8 > 128;
+        if (guided) {
+            for (int g = tid; g <= (1 << GUIDE_BITS); g += T)
+                guide[g] = (uint16_t)(g >> GUIDE_BITS ? n8 - 1
+                                                      : search(umul64hi((uint64_t)g << (64 - GUIDE_BITS), SX), 0, top));
+            __syncthreads();
+        }
+        // draw d picks the largest j with P_j <= t (see k_mn_draws)
+        const uint32_t c3 = (TAG_MN << 28) | ((uint32_t)pop << 24);
+        for (int d = tid; d < R.R; d += T) {
+            const u32x4 o = philox10((uint32_t)d, 0, (uint32_t)S.i, c3, R.key0, R.key1);
+            const uint64_t t = umul64hi((uint64_t)o.x | ((uint64_t)o.y << 32), SX);
+            int b = 0, span = top;
+            if (guided) {
+                const int g = (int)(o.y >> (32 - GUIDE_BITS));
+                b = guide[g];
+                const int w = guide[g + 1] - b;   // t is below the next entry's block end
+                span = w > 0 ? 1 << (31 - __builtin_clz(w)) : 0;
+            }
+            b = search(t, b, span);
+            const uint64_t rel = t - T8[b];
+            const uint32_t f = (uint32_t)(rel >> FINE_SHIFT);
+            const uint32_t *Fb = F + b * CH_PER;
+            int j = 0;
+#pragma unroll
+            for (int step = CH_PER / 2; step > 0; step >>= 1)
+                if (Fb[j + step] <= f) j += step;
+            if (j > 0 && Fb[j] == f) {   // the exact prefix decides
+                const uint64_t *P = R.P[pop] + (size_t)b * CH_PER;
+                while (j > 0 && P[j] - P[0] > rel) --j;
+            }
+            j += b * CH_PER;
+            atomicAdd(&cnt[j >> 1], 1u << (16 * (j & 1)));
+        }
+    } else {
+        const int32_t *E = R.E[pop][S.cur];
+        const uint64_t *X = R.tabX + (size_t)S.i * (R.N + 1);
+        const double invSX = 1.0 / (double)SX;
+        for (int j = tid; j < Rp; j += T)
+            ((uint16_t *)cnt)[j] = (uint16_t)nearest_count(R, S, pop, j, E[j], X, invSX);
+    }
+    __syncthreads();
+    // population size first: nothing is written for one that is refused
+    auto block_sum = [&](int v) {
+        const int w = wave_sum<int>(v);
+        if (lane == 0) wsum[wv] = w;
+        __syncthreads();
+        int t = 0;
+        for (int k = 0; k < nw; ++k) t += wsum[k];
+        __syncthreads();
+        return t;
+    };
+    int total = R.R;
+    if (!mn) {
+        int s = 0;
+        for (int k = tid; k < n8 * (CH_PER / 2); k += T) s += (int)(cnt[k] & 0xFFFFu) + (int)(cnt[k] >> 16);
+        total = block_sum(s);
+    }
+    int32_t *r = R.r[pop], *par = R.parent[pop];
+    if (!accept_counts(R, S, pop, total)) {
+        for (int j = tid; j < Rp; j += T) r[j] = ((const uint16_t *)cnt)[j];
+        return;
+    }
+    // exclusive prefix over blocks of CH_PER consecutive replicas per thread,
+    // and each parent's children (slots C_j .. C_j + r_j - 1)
+    int carry = 0;
+    for (int base = 0; base < n8; base += T) {
+        const int b = base + tid;
+        int c[CH_PER], s = 0;
+#pragma unroll
+        for (int q = 0; q < CH_PER / 2; ++q) {
+            const uint32_t w = b < n8 ? cnt[b * (CH_PER / 2) + q] : 0u;
+            c[2 * q] = (int)(w & 0xFFFFu);
+            c[2 * q + 1] = (int)(w >> 16);
+            s += c[2 * q] + c[2 * q + 1];
+        }
+        int incl = s;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += t;
+        }
+        if (lane == 63) wsum[wv] = incl;
+        __syncthreads();
+        int before = carry, all = 0;
+        for (int k = 0; k < nw; ++k) {
+            before += k < wv ? wsum[k] : 0;
+            all += wsum[k];
+        }
+        __syncthreads();
+        carry += all;
+        int slot = before + incl - s;
+        store_block(r, b * CH_PER, Rp, c);
+#pragma unroll
+        for (int q = 0; q < CH_PER; ++q) {
+            write_children(par, b * CH_PER + q, slot, c[q]);
+            slot += c[q];
         }
     }
 }
@@ -2714,6 +2956,55 @@ __global__ void __launch_bounds__(256) k_wang_gather(const Item *items, int n_it
     }
 }
 
+// The record of a population's temperature from its sums (in the order of
+// the accumulators) and the pair sums of population 0 (with two populations
+// both records carry them).
+__device__ __forceinline__ void write_record(const RunInfo &R, PopState &S, int pop, const int64_t *acc,
+                                             const int64_t *acc0, int32_t emin)
+{
+    pa_obs o;
+    o.R_i = S.Rcur;
+    o.lnQ = S.i == 0 ? 0.0 : S.lnQ;
+    o.A = S.A;
+    o.sumE = acc[A_SUME];
+    o.sumE2 = acc[A_SUME2];
+    o.sumAbsM = acc[A_SUMABSM];
+    o.sumM2 = acc[A_SUMM2];
+    o.nPairs = acc0[A_NPAIRS];
+    o.sumQ = acc0[A_SUMQ];
+    o.sumAbsQ = acc0[A_SUMABSQ];
+    o.sumQ2 = acc0[A_SUMQ2];
+    o.sumQl = acc0[A_SUMQL];
+    o.sumQl2 = acc0[A_SUMQL2];
+    o.famSumSq = acc[A_FAMSQ];
+    o.famMax = acc[A_FAMMAX];
+    o.nFam = acc[A_NFAM];
+    o.Emin = emin;
+    o.status = PA_OK;
+    obs_at(R, S.i, pop) = o;
+    S.Emin = emin;
+}
+
+// The records of a run's populations from the accumulators that other
+// workgroups of the launch added to, and the accumulators reset (one thread).
+__device__ __forceinline__ void write_records(const RunInfo &R, PopState *st)
+{
+    int64_t acc0[NACC] = {};
+    for (int p = 0; p < R.npop; ++p) {
+        PopState &S = st[p];
+        if (!pop_active(S)) continue;
+        int64_t acc[NACC];
+#pragma unroll
+        for (int k = 0; k < NACC; ++k) {
+            acc[k] = take(&S.acc[k]);
+            if (p == 0) acc0[k] = acc[k];
+        }
+        write_record(R, S, p, acc, acc0, take(&S.EminAcc));
+        for (int k = 0; k < NACC; ++k) put(&S.acc[k], (int64_t)0);
+        put(&S.EminAcc, (int32_t)INT32_MAX);
+    }
+}
+
 // Per chunk of CH replicas (CH / 64 groups): the groups' partial sums, and
 // the family statistics.  Family labels are non-decreasing in the replica
 // index (they start as f_j = j and every resampling copies parents in
@@ -2738,15 +3029,19 @@ __global__ void __launch_bounds__(CH_THREADS) k_meas_chunk(const ChunkItem *item
     const int j0 = it.chunk * CH;
     if (j0 >= Rc) return;
     const int lane = threadIdx.x & 63, wv = wave_id();
+    int chunks = 0;   // of the run's populations
+    for (int p = 0; p < R.npop; ++p)
+        if (pop_active(st[it.run * MAX_POP + p])) chunks += (st[it.run * MAX_POP + p].Rcur + CH - 1) / CH;
     // group partials: groups [j0/64, j0/64 + CH/64), one per lane of wave 0
-    int64_t part[MEAS_PART];
+    int64_t part[NACC];   // as the accumulators: the first ten, then the families
 #pragma unroll
-    for (int k = 0; k < MEAS_PART; ++k) part[k] = 0;
-    part[10] = INT32_MAX;
+    for (int k = 0; k < NACC; ++k) part[k] = 0;
+    int emin = INT32_MAX;
     const int g = j0 / 64 + lane;
     if (wv == 0 && lane < CH / 64 && g * 64 < Rc) {
 #pragma unroll
-        for (int k = 0; k < MEAS_PART; ++k) part[k] = R.part[it.pop][(size_t)g * MEAS_PART + k];
+        for (int k = 0; k < MEAS_PART - 1; ++k) part[k] = R.part[it.pop][(size_t)g * MEAS_PART + k];
+        emin = (int)R.part[it.pop][(size_t)g * MEAS_PART + MEAS_PART - 1];
     }
     // families
     const int32_t *fam = R.fam[it.pop][S.cur];
@@ -2772,13 +3067,16 @@ __global__ void __launch_bounds__(CH_THREADS) k_meas_chunk(const ChunkItem *item
     }
     const int jb = j0 + threadIdx.x * CH_PER;
     int32_t lab[CH_PER];
+    load_block(fam, jb, Rc, 0, lab);
+    // the label before each of them: the previous lane's last, or memory
+    int32_t prev = __shfl_up(lab[CH_PER - 1], 1, 64);
+    if (lane == 0) prev = jb > 0 && jb < Rc ? fam[jb - 1] : -1;   // labels are not negative
+    bool start[CH_PER];
     int last = -1;
 #pragma unroll
     for (int q = 0; q < CH_PER; ++q) {
-        const int j = jb + q;
-        lab[q] = j < Rc ? fam[j] : 0;
-        if (j < Rc && j > j0 && fam[j - 1] != lab[q]) last = j;
-        if (j == j0 && j < Rc && j0 == 0) last = 0;
+        start[q] = jb + q < Rc && (q ? lab[q - 1] : prev) != lab[q];
+        if (start[q]) last = jb + q;
     }
     // exclusive max-scan of the threads' last starts
     int incl = last;
@@ -2801,12 +3099,11 @@ __global__ void __launch_bounds__(CH_THREADS) k_meas_chunk(const ChunkItem *item
     for (int q = 0; q < CH_PER; ++q) {
         const int j = jb + q;
         if (j < Rc) {
-            const bool start = j == 0 || fam[j - 1] != lab[q];
-            if (start) s = j;
+            if (start[q]) s = j;
             const int64_t r = j - s;
             sq += 2 * r + 1;
             mx = r + 1 > mx ? r + 1 : mx;
-            nf += start ? 1 : 0;
+            nf += start[q] ? 1 : 0;
         }
     }
     sq = wave_sum<int64_t>(sq);
@@ -2818,8 +3115,8 @@ __global__ void __launch_bounds__(CH_THREADS) k_meas_chunk(const ChunkItem *item
     }
     if (wv == 0) {
 #pragma unroll
-        for (int k = 0; k < 10; ++k) part[k] = wave_sum<int64_t>(part[k]);
-        part[10] = wave_min((int)part[10]);
+        for (int k = 0; k < MEAS_PART - 1; ++k) part[k] = wave_sum<int64_t>(part[k]);
+        emin = wave_min(emin);
     }
     if (lane == 0) {
         red[0][wv] = sq;
@@ -2834,65 +3131,25 @@ __global__ void __launch_bounds__(CH_THREADS) k_meas_chunk(const ChunkItem *item
             b = red[1][k] > b ? red[1][k] : b;
             c += red[2][k];
         }
-        unsigned long long *acc = (unsigned long long *)S.acc;
-        atomicAdd(&acc[A_FAMSQ], (unsigned long long)a);
-        atomicMax(&acc[A_FAMMAX], (unsigned long long)b);
-        atomicAdd(&acc[A_NFAM], (unsigned long long)c);
-        atomicAdd(&acc[A_SUME], (unsigned long long)part[0]);
-        atomicAdd(&acc[A_SUME2], (unsigned long long)part[1]);
-        atomicAdd(&acc[A_SUMABSM], (unsigned long long)part[2]);
-        atomicAdd(&acc[A_SUMM2], (unsigned long long)part[3]);
-        if (part[4]) {
-            atomicAdd(&acc[A_NPAIRS], (unsigned long long)part[4]);
-            atomicAdd(&acc[A_SUMQ], (unsigned long long)part[5]);
-            atomicAdd(&acc[A_SUMABSQ], (unsigned long long)part[6]);
-            atomicAdd(&acc[A_SUMQ2], (unsigned long long)part[7]);
-            atomicAdd(&acc[A_SUMQL], (unsigned long long)part[8]);
-            atomicAdd(&acc[A_SUMQL2], (unsigned long long)part[9]);
+        part[A_FAMSQ] = a;
+        part[A_FAMMAX] = b;
+        part[A_NFAM] = c;
+        if (chunks == 1) {   // the run's only chunk: its sums are the record's
+            const int64_t none[A_FAMSQ] = {};
+            write_record(R, S, it.pop, part, it.pop == 0 ? part : none, emin);
+        } else {
+            unsigned long long *acc = (unsigned long long *)S.acc;
+#pragma unroll
+            for (int k = 0; k < NACC; ++k) {
+                if (k == A_FAMMAX) atomicMax(&acc[k], (unsigned long long)part[k]);
+                else if (k < A_NPAIRS || k >= A_FAMSQ || part[A_NPAIRS]) atomicAdd(&acc[k], (unsigned long long)part[k]);
+            }
+            atomicMin(&S.EminAcc, emin);
         }
-        atomicMin(&S.EminAcc, (int)part[10]);
     }
-}
-
-// Per run: the record of temperature i for each population, and the
-// accumulators reset.  With two populations both records carry the pair
-// sums.
-__global__ void k_finalize(const RunInfo *runs, PopState *st, int n_runs)
-{
-    const int run = blockIdx.x * blockDim.x + threadIdx.x;
-    if (run >= n_runs) return;
-    const RunInfo &R = runs[run];
-    int64_t pairs[6] = {0, 0, 0, 0, 0, 0};
-    for (int p = 0; p < R.npop; ++p) {
-        PopState &S = st[run * MAX_POP + p];
-        if (!pop_active(S)) continue;
-        const int i = S.i;
-        pa_obs o;
-        o.R_i = S.Rcur;
-        o.lnQ = i == 0 ? 0.0 : S.lnQ;
-        o.A = S.A;
-        o.sumE = S.acc[A_SUME];
-        o.sumE2 = S.acc[A_SUME2];
-        o.sumAbsM = S.acc[A_SUMABSM];
-        o.sumM2 = S.acc[A_SUMM2];
-        if (p == 0)
-            for (int k = 0; k < 6; ++k) pairs[k] = S.acc[A_NPAIRS + k];
-        o.nPairs = pairs[0];
-        o.sumQ = pairs[1];
-        o.sumAbsQ = pairs[2];
-        o.sumQ2 = pairs[3];
-        o.sumQl = pairs[4];
-        o.sumQl2 = pairs[5];
-        o.famSumSq = S.acc[A_FAMSQ];
-        o.famMax = S.acc[A_FAMMAX];
-        o.nFam = S.acc[A_NFAM];
-        o.Emin = S.EminAcc;
-        o.status = PA_OK;
-        obs_at(R, i, p) = o;
-        S.Emin = S.EminAcc;
-        for (int k = 0; k < NACC; ++k) S.acc[k] = 0;
-        S.EminAcc = INT32_MAX;
-    }
+    // the last chunk of the run's populations writes the records
+    if (chunks > 1 && last_of(&st[it.run * MAX_POP].done, chunks) && threadIdx.x == 0)
+        write_records(R, st + it.run * MAX_POP);
 }
 
 // ---------------------------------------------------------------- Sec. IV
@@ -3235,28 +3492,31 @@ hipError_t launch_init(const LaunchCtx &c, const uint64_t *dseed)
 hipError_t launch_anneal(const LaunchCtx &c)
 {
     k_rw_chunk<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
-    PA_CHECK_LAUNCH();
-    k_rw_finish<<<dim3(c.n_runs, c.npop_ctx), 256, 0, c.stream>>>(c.runs + c.run0,
-                                                                 c.st + (size_t)c.run0 * MAX_POP);
     return hipGetLastError();
 }
 
 hipError_t launch_resample(const LaunchCtx &c)
 {
-    k_cnt_chunk<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
-    PA_CHECK_LAUNCH();
-    if (c.any_multinomial) {
-        k_mn_draws<<<c.n_chunk_items * c.mn_split, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st,
-                                                                              c.mn_split);
-        PA_CHECK_LAUNCH();
-        k_cnt_scan_chunk<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
+    if (c.fused_max > 0) {
+        const int threads = c.fused_max <= 512 ? 64 : (c.fused_max <= CH ? 256 : 1024);
+        k_resample_run<<<dim3(c.n_runs, c.npop_ctx), threads, fused_lds(c.fused_max, c.any_multinomial), c.stream>>>(
+            c.runs + c.run0, c.st + (size_t)c.run0 * MAX_POP);
         PA_CHECK_LAUNCH();
     }
-    k_cnt_finish<<<dim3(c.n_runs, c.npop_ctx), 256, 0, c.stream>>>(c.runs + c.run0,
-                                                                  c.st + (size_t)c.run0 * MAX_POP);
-    PA_CHECK_LAUNCH();
-    k_parent<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
-    PA_CHECK_LAUNCH();
+    if (c.any_chained) {
+        if (c.any_nearest) {
+            k_cnt_chunk<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
+            PA_CHECK_LAUNCH();
+        }
+        if (c.any_multinomial) {
+            k_mn_draws<<<c.n_chunk_items * CH_PER, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
+            PA_CHECK_LAUNCH();
+            k_cnt_scan_chunk<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
+            PA_CHECK_LAUNCH();
+        }
+        k_parent<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
+        PA_CHECK_LAUNCH();
+    }
     if (c.n_meas_items > 0) {
         const int split = c.copy_split > 1 ? c.copy_split : 1;
         if (c.repr == PA_MSC64)
@@ -3269,6 +3529,18 @@ hipError_t launch_resample(const LaunchCtx &c)
     return hipGetLastError();
 }
 
+
+hipError_t launch_clear_counts(const LaunchCtx &c)
+{
+    k_clear_counts<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
+    return hipGetLastError();
+}
+
+hipError_t prepare_fused_lds(size_t bytes)
+{
+    if (bytes <= 65536) return hipSuccess;
+    return hipFuncSetAttribute((const void *)k_resample_run, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
 
 hipError_t launch_words(const LaunchCtx &c, int max_N)
 {
@@ -3609,9 +3881,6 @@ hipError_t launch_measure(const LaunchCtx &c, bool first)
         PA_CHECK_LAUNCH();
     }
     k_meas_chunk<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
-    PA_CHECK_LAUNCH();
-    k_finalize<<<(c.n_runs + 63) / 64, 64, 0, c.stream>>>(c.runs + c.run0, c.st + (size_t)c.run0 * MAX_POP,
-                                                          c.n_runs);
     return hipGetLastError();
 }
 

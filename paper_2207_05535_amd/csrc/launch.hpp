@@ -30,9 +30,10 @@ struct LaunchCtx {
     int n_chunk_items;
     int run0, n_runs, npop_ctx;    // per-run launches cover runs [run0, run0 + n_runs)
     int repr;
-    bool any_multinomial;
+    bool any_multinomial, any_nearest = false;
+    bool any_chained = true;       // some run is resampled chunk by chunk
+    int fused_max = 0;             // largest capacity of the runs resampled by one workgroup, 0 without any
     bool any_overlap = true;       // some run measures overlaps (index shift, two populations, pairing)
-    int mn_split = CH_PER;         // workgroups per chunk of multinomial draws: CH_PER if a run spans chunks, else 1
     int copy_split = 1;            // workgroups per copy item, each taking a share of every group's 64-site blocks
     bool any_wang;                 // some run pairs replicas by permutations
     int wang_lds_ints;             // LDS of the pairing repair (2 R_cap of the largest run that fits, or 0)
@@ -60,6 +61,8 @@ hipError_t launch_sweep_msc(const LaunchCtx &c);
 // c.sweep_cls), and the runs of `wide` one colour at a time.
 hipError_t launch_sweep_bytes(const LaunchCtx &c, const WideRun *wide, int n_wide, int max_N);
 // first: the measurement at i = 0 (the int8 layout has no words yet).
+hipError_t launch_clear_counts(const LaunchCtx &c);   // after a restore between steps (ii) and (iii)
+hipError_t prepare_fused_lds(size_t bytes);
 hipError_t launch_measure(const LaunchCtx &c, bool first);
 hipError_t launch_words(const LaunchCtx &c, int max_N);   // int8 layout: bytes -> words
 hipError_t launch_dos_sample(const LaunchCtx &c);   // theta = infinity draws (no-op without such runs)

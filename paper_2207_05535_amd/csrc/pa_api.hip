@@ -491,7 +491,17 @@ bool dos_thresholds(const pa_run_desc &d, std::vector<uint64_t> &out)
     return true;
 }
 
-RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
+// One workgroup per population is a chain of passes on one CU: up to 8192
+// replicas no longer than the launches it replaces (18 us each way at 8000,
+// 10 against 16 at 1000), above that only with enough populations for the
+// CUs (us of step (iii) without the copy, 2e4 replicas, alone / by chunks:
+// 58 / 38 for 16 populations, 58 / 61 for 32, 58 / 303 for 256).
+bool resampled_alone(const pa_run_desc &d, int n)
+{
+    return d.R_cap <= (n >= 64 ? FUSED_MAX : 8192);
+}
+
+RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, bool fused, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
                      pa_obs *obs, int obs_stride, int obs_off)
 {
     RunInfo I;
@@ -504,6 +514,7 @@ RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, uint8_t *base, const Ru
     I.theta = d.theta == PA_THETA_EXACT ? 0 : d.theta;   // no Metropolis sweeps at theta = infinity
     I.exact_dos = d.theta == PA_THETA_EXACT ? 1 : 0;
     I.bytes = repr == PA_INT8 ? 1 : 0;
+    I.fused = fused ? 1 : 0;
     I.K = d.K;
     I.model = d.model;
     I.resampling = d.resampling;
@@ -844,6 +855,9 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
             }
     }
     const Layout &Lo = c->lo;
+    int n_pops = 0;
+    for (int r = 0; r < n_runs; ++r) n_pops += n_pop_of(runs[r].overlap);
+    c->lc.any_chained = false;
 
     // host images of the device-side records
     c->hinfo.resize(n_runs);
@@ -856,7 +870,10 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
         const pa_run_desc &d = c->descs[r];
         const RunOff &o = Lo.runs[r];
         const TableOff &T = Lo.tables[o.table];
-        c->hinfo[r] = make_runinfo(d, repr, c->ws, o, c->ws, T, at<pa_obs>(c, Lo.obs), n_runs * Lo.npop_ctx,
+        const bool fused = resampled_alone(d, n_pops);
+        if (fused) c->lc.fused_max = std::max(c->lc.fused_max, d.R_cap);
+        else c->lc.any_chained = true;
+        c->hinfo[r] = make_runinfo(d, repr, fused, c->ws, o, c->ws, T, at<pa_obs>(c, Lo.obs), n_runs * Lo.npop_ctx,
                                    r * Lo.npop_ctx);
         for (int p = 0; p < n_pop_of(d.overlap); ++p) {
             hst[(size_t)r * MAX_POP + p] = initial_popstate(d);
@@ -880,7 +897,7 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
     c->lc.npop_ctx = Lo.npop_ctx;
     c->lc.repr = repr;
     c->lc.any_multinomial = c->any_multinomial;
-    c->lc.mn_split = 1;
+    c->lc.any_nearest = false;
     c->lc.any_overlap = false;
     c->lc.any_swept = c->lc.any_unswept = false;
     // copy workgroups per item: each wavefront keeps about four 64-site blocks
@@ -893,7 +910,7 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
         c->lc.copy_split = std::max(1, std::min(4, blocks_per_wave / 4));
     }
     for (int r = 0; r < n_runs; ++r) {
-        if (runs[r].resampling == PA_MULTINOMIAL && runs[r].R > CH) c->lc.mn_split = CH_PER;
+        if (runs[r].resampling == PA_NEAREST_INT) c->lc.any_nearest = true;
         if (runs[r].overlap != PA_Q_NONE) c->lc.any_overlap = true;
         if (runs[r].theta > 0) c->lc.any_swept = true;
         else c->lc.any_unswept = true;
@@ -925,6 +942,7 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
         size_t lds = 0;
         if (!plan_sweep(c, probe, lds)) return fail(PA_ERR_ARG);
     }
+    if (prepare_fused_lds(fused_lds(c->lc.fused_max, c->any_multinomial)) != hipSuccess) return fail(PA_ERR_DEVICE);
     if (c->any_wang) {
         std::vector<const pa_run_desc *> dp(n_runs);
         for (int r = 0; r < n_runs; ++r) dp[r] = &c->descs[r];
@@ -1318,6 +1336,7 @@ pa_status pa_restore(pa_ctx *c, const void *host_buf, size_t bytes)
     // checkpoint time; the launches use the current plan, so its list is
     // written again (the tuning may have changed since)
     const pa_status st = upload_sweep_plan(c);
+    if (st == PA_OK && c->phase == PH_ANNEALED) PA_HIP(c, launch_clear_counts(c->lc));
     // between a step's sweeps and its measurement the int8 layout's words are
     // read next: a checkpoint that does not hold them has the bytes
     if (st == PA_OK && c->repr == PA_INT8 && c->phase == PH_SWEPT && c->lc.any_swept)

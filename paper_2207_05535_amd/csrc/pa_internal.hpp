@@ -34,6 +34,13 @@ constexpr int MAX_POP = 2;
 constexpr int CH_THREADS = 256;
 constexpr int CH_PER = 8;
 constexpr int CH = CH_THREADS * CH_PER;
+// Largest population capacity k_resample_run takes (16-bit counts, and the
+// LDS of a workgroup): counts, coarse and fine prefix in LDS, see there.
+constexpr int FUSED_MAX = 22016;
+__host__ __device__ inline size_t fused_lds(int R_cap, bool multinomial)
+{
+    return (size_t)((R_cap + CH_PER - 1) / CH_PER) * (multinomial ? 2 * CH_PER + 8 + 4 * CH_PER : 2 * CH_PER);
+}
 constexpr int NACC = 13;  // measure accumulators, see Acc
 
 // Measurement: workgroups of MEAS_WAVES wavefronts; a lattice of N sites
@@ -62,6 +69,7 @@ struct RunInfo {
     int32_t wang_lb;              // permutation pairing: log2 of the bucket capacity
     int32_t exact_dos;            // 1: theta = infinity (energies drawn; theta is 0 here)
     int32_t bytes;                // 1: int8 layout
+    int32_t fused;                // 1: resampled by one workgroup per population (k_resample_run)
     // device pointers into the caller's workspace
     uint8_t *spins[MAX_POP][2];   // int8: [group][site][64] bytes; MSC: [group][site] u64
     int32_t *E[MAX_POP][2];       // energies [R_cap]
@@ -100,7 +108,7 @@ struct PopState {
     uint64_t SX;
     int64_t acc[NACC];
     int32_t EminAcc;
-    int32_t pad1;
+    int32_t done;     // workgroups counted in by the current launch (last_of)
 };
 
 // Work counters of the sweep kernels (exact, for the ALU roofline):

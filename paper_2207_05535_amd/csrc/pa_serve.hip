@@ -250,7 +250,8 @@ pa_status rebuild(pa_server *s)
 {
     size_t n_items = 0, n_chunks = 0, n_meas = 0;
     int hi = 0, npop_ctx = 1;
-    bool mn = false, wang = false, exact = false, mn_wide = false, ovl = false;
+    bool mn = false, ni = false, wang = false, exact = false, chained = false, ovl = false;
+    int fused_max = 0;
     std::vector<SweepItem> sweep;
     size_t lds = 0;
     s->wide.clear();
@@ -272,7 +273,9 @@ pa_status rebuild(pa_server *s)
         hi = k + 1;
         npop_ctx = std::max(npop_ctx, npop);
         mn = mn || sl.d.resampling == PA_MULTINOMIAL;
-        mn_wide = mn_wide || (sl.d.resampling == PA_MULTINOMIAL && sl.d.R > CH);
+        ni = ni || sl.d.resampling == PA_NEAREST_INT;
+        if (resampled_alone(sl.d, 1)) fused_max = std::max(fused_max, sl.d.R_cap);
+        else chained = true;
         ovl = ovl || sl.d.overlap != PA_Q_NONE;
         wang = wang || is_wang(sl.d.overlap);
         exact = exact || sl.d.theta == PA_THETA_EXACT;
@@ -356,7 +359,10 @@ pa_status rebuild(pa_server *s)
     c.n_runs = hi;
     c.npop_ctx = npop_ctx;
     c.any_multinomial = mn;
-    c.mn_split = mn_wide ? CH_PER : 1;
+    c.any_nearest = ni;
+    c.any_chained = chained;
+    c.fused_max = fused_max;
+    if (prepare_fused_lds(fused_lds(fused_max, mn)) != hipSuccess) return sfail(s);
     c.copy_split = 1;   // requests of any size share the copy launch
     c.any_overlap = ovl;
     c.any_wang = wang;
@@ -553,7 +559,7 @@ pa_status pa_server_admit(pa_server *s, const pa_run_desc *desc, int32_t *slot)
             return st;
     }
     const int npop = n_pop_of(d.overlap);
-    const RunInfo I = make_runinfo(sl.d, s->repr, blk, b.o, tbase, T.T, (pa_obs *)(blk + b.obs), npop, 0);
+    const RunInfo I = make_runinfo(sl.d, s->repr, resampled_alone(sl.d, 1), blk, b.o, tbase, T.T, (pa_obs *)(blk + b.obs), npop, 0);
     PopState hst[MAX_POP];
     std::memset(hst, 0, sizeof(hst));
     for (int p = 0; p < npop; ++p) hst[p] = initial_popstate(sl.d);
@@ -596,7 +602,6 @@ pa_status pa_server_admit(pa_server *s, const pa_run_desc *desc, int32_t *slot)
     c.n_runs = 1;
     c.npop_ctx = npop;
     c.any_multinomial = d.resampling == PA_MULTINOMIAL;
-    c.mn_split = d.resampling == PA_MULTINOMIAL && d.R > CH ? CH_PER : 1;
     c.any_overlap = d.overlap != PA_Q_NONE;
     c.any_wang = is_wang(d.overlap);
     {

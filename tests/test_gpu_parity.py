@@ -768,3 +768,65 @@ def test_int8_large_lattices(L, model, R, theta, overlap):
             assert_obs_equal(c.obs()[r, :orc.npop], orc.obs(), f"run {r}")
             assert_state_equal(c, orc, r, f"run {r} final")
         c.close()
+
+
+@pytest.mark.parametrize("R", [1, 7, 64, 513, 2048, 2049, 8192, 8193])
+@pytest.mark.parametrize("resampling", [W.MULTINOMIAL, W.NEAREST_INT])
+def test_resampling_sizes(R, resampling):
+    """Resampling at the edges of its blocks of 8, chunks of 2048 and of the
+    capacity up to which one workgroup does it (8192; the nearest-integer
+    capacity is larger than R, so its runs cross it earlier), with families
+    that grow large: records, states and counts equal the oracle's, also
+    continued from checkpoints taken between steps (ii), (iii) and (iv)."""
+    say(f"resampling R={R} mode={resampling}")
+    d = W.run_desc(4, W.EA_PMJ, seed=W.RUN_SEED_BASE + 0x7700 + R, disorder_seed=4, R=R, theta=1, K=7, beta_f=3.0,
+                   resampling=resampling, overlap=W.Q_INDEX_SHIFT)
+    orc = oracle.OracleRun(d).run_all()
+    ctx = pa.Context([d], "msc")
+    other = pa.Context([d], "msc")
+    for i in range(1, 4):
+        ctx.anneal_step(i)
+        if i == 1:
+            other.restore(ctx.checkpoint())
+        ctx.resample(i)
+        if i == 2:
+            other.restore(ctx.checkpoint())
+            other.sweep(i)
+            other.measure(i)
+            other.run(3, 7)
+        if i == 1:
+            other.resample(i)
+            other.sweep(i)
+            other.measure(i)
+            other.run(2, 7)
+            assert_obs_equal(other.obs()[0, :1], orc.obs(), "restored after step (ii)")
+        ctx.sweep(i)
+        ctx.measure(i)
+    ctx.run(4, 7)
+    for c, where in ((ctx, "run"), (other, "restored after step (iii)")):
+        assert_obs_equal(c.obs()[0, :1], orc.obs(), where)
+        assert_state_equal(c, orc, 0, where)
+        c.close()
+
+
+def test_many_populations_resampled_alone():
+    """64 populations of 9000 and more in one context are resampled by a
+    workgroup each, where one alone is resampled chunk by chunk: the same
+    records and states, equal to the oracle's for one of them."""
+    say("64 runs of R = 9000 .. 22016")
+    runs = [W.run_desc(4, W.FM, seed=W.RUN_SEED_BASE + 0x7800 + m, R=22016 if m == 5 else 9000 + m, theta=1, K=5,
+                       beta_f=1.5, resampling=W.NEAREST_INT if m % 3 == 1 else W.MULTINOMIAL) for m in range(64)]
+    ctx = pa.Context(runs, "msc")
+    ctx.run(1, 5)
+    obs = ctx.obs()
+    for m in (0, 1, 5):
+        alone = pa.Context([runs[m]], "msc")
+        alone.run(1, 5)
+        assert alone.obs()[0].tobytes() == obs[m].tobytes(), m
+        for a, b in zip(alone.state(0), ctx.state(m)):
+            assert np.array_equal(a, b), m
+        alone.close()
+    orc = oracle.OracleRun(runs[5]).run_all()
+    assert_obs_equal(obs[5, :1], orc.obs(), "R=22016")
+    assert_state_equal(ctx, orc, 5, "R=22016")
+    ctx.close()
