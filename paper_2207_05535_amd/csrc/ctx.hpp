@@ -69,10 +69,9 @@ bool resampled_alone(const pa_run_desc &d, int n);
 RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, bool fused, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
                      pa_obs *obs, int obs_stride, int obs_off);
 PopState initial_popstate(const pa_run_desc &d);
-// LDS ints of the permutation-pairing repair: 2 R_cap of the largest such
-// run whose labels (8 bytes per replica) fit the workgroup LDS beside the
-// kernel's own, 0 if none does (those runs repair in global memory).
-int wang_lds_ints_of(const pa_run_desc *const *runs, int n, int lds_limit);
+// LDS of the permutation pairing in LDS: that of the largest such run that
+// fits, 0 if none does; *large: some run does not.
+size_t wang_lds_of(const pa_run_desc *const *runs, int n, int lds_limit, bool *large);
 // theta = infinity: energy draw thresholds [K][N+1] of a run (see pa.h);
 // false if the density of states is not available for its L.
 bool dos_thresholds(const pa_run_desc &d, std::vector<uint64_t> &out);

@@ -11,7 +11,7 @@
 //            colour of one run per launch, from memory), k_bytes_words (the
 //            int8 layout to words and back), k_dos_sample (the theta =
 //            infinity limit, Sec. V C)
-// Step (v)   k_wang_pairs, k_wang_rows, k_wang_gather (permutation pairing,
+// Step (v)   k_wang_lds, k_wang_pairs, k_wang_rows, k_wang_gather (permutation pairing,
 //            Sec. III D), k_measure, k_meas_chunk
 //                                                      (Eqs. (e)-(chi), Sec. III D)
 // Sec. IV    k_logw, k_qweights, k_wavg, k_wavg_cumsum, k_wqhist, k_famstats
@@ -2518,7 +2518,8 @@ __global__ void __launch_bounds__(256) k_dos_sample(const Item *items, int n_ite
 //
 // Sec. III D, pairings from permutations (Wang et al.), for runs with
 // PA_Q_WANG / PA_Q_WANG_RDM, before the measurement of every temperature:
-//   k_wang_pairs   one workgroup per run: the permutations and the repair;
+//   k_wang_lds     one workgroup per run: the permutations and the repair
+//   k_wang_pairs   (the same for runs too large for LDS);
 //   k_wang_rows    the population as bit rows, one per replica;
 //   k_wang_gather  the partners' configurations as bit-packed words;
 // then k_measure takes the pairs (j, pi_j) like any other overlap pairs.
@@ -2592,15 +2593,15 @@ __device__ int block_scan_excl(int v, int *sh, int *total)
     return r;
 }
 
+// For runs too large for k_wang_lds: the same in global memory.
 __global__ void __launch_bounds__(WANG_THREADS) k_wang_pairs(const RunInfo *runs, const PopState *st, int run0,
-                                                              int lds_ints)
+                                                              uint32_t lds_bytes)
 {
     __shared__ int sh[17];
     __shared__ int big;
-    extern __shared__ int32_t wlds[];   // lds_ints: labels and partner labels when they fit
     const int run = run0 + blockIdx.x;
     const RunInfo &R = runs[run];
-    if (!is_wang(R.overlap)) return;
+    if (!is_wang(R.overlap) || wang_lds_bytes(R.R_cap) <= lds_bytes) return;
     const PopState &S = st[run * MAX_POP];
     if (!pop_active(S)) return;
     const int Rc = S.Rcur, i = S.i;
@@ -2695,51 +2696,20 @@ __global__ void __launch_bounds__(WANG_THREADS) k_wang_pairs(const RunInfo *runs
         if (ldc(&W.fampi[k]) == fam[k]) stc(&W.list[pos++], t);
     }
     wg_sync_stores();
-    // When 2 R_i ints fit the workgroup's LDS, the repair reads and writes
-    // the family labels and the partners' labels there, and logs its
-    // exchanges (in the bucket arrays, free by now) instead of applying them
-    // to pi in global memory; they are replayed onto pi in LDS at the end.
-    const bool in_lds = 2 * Rc <= lds_ints;
-    int32_t *Lfam = wlds, *Lfpi = wlds + Rc;
-    if (in_lds) {
-        for (int k = tid; k < Rc; k += T) {
-            Lfam[k] = fam[k];
-            Lfpi[k] = ldc(&W.fampi[k]);
-        }
-        __syncthreads();
-    }
-    // The other wavefronts wait for the repair, then load and store pi with
-    // it (the replay of the exchanges itself is one wavefront's, in order).
-    int nsw = 0, status = 0;
-    int32_t *swaps = W.cnt;   // [2 B + 1] ints, B >= R_i: room for R_i exchanges
-    // IN_LDS (a constant in each copy of the repair): the labels are read
-    // with LDS instructions only, not through generic pointers that would
-    // make every probe wait for both memory counters.  Values of one lane
-    // that the whole wavefront needs are read with readlane (the lane index
-    // is uniform), not with a permute through LDS.
-    auto repair = [&](auto in_lds_c) {
-        constexpr bool IN_LDS = decltype(in_lds_c)::value;
-        auto famv = [&](int m) {
-            if constexpr (IN_LDS) return Lfam[m];
-            else return fam[m];
-        };
-        auto fpiv = [&](int m) {
-            if constexpr (IN_LDS) return Lfpi[m];
-            else return ldc(&W.fampi[m]);
-        };
-
-        // The repair, one wavefront, over the list in batches of 64 entries.
-        // What does not change during the repair (position, its place in the
-        // search order, its family, the end of its family's run of labels, its
-        // initial partner) is loaded for a whole batch at once; an entry is
-        // still open unless an earlier exchange in this repair took its
-        // position as the partner (an exchange leaves both of its positions
-        // matched for good), which the lanes track by comparing positions.
-        // With the identity pattern the mismatches of one family come one after
-        // the other, and a candidate that failed for one of them fails for the
-        // next as well (exchanges only hand this family's replicas to
-        // candidates), so the search resumes after the previous partner
-        // (unwrapped candidate index prev_u).
+    // The repair, one wavefront, over the list in batches of 64 entries.
+    // What does not change during the repair (position, its place in the
+    // search order, its family, the end of its family's run of labels, its
+    // initial partner) is loaded for a whole batch at once; an entry is
+    // still open unless an earlier exchange in this repair took its
+    // position as the partner (an exchange leaves both of its positions
+    // matched for good), which the lanes track by comparing positions.
+    // With the identity pattern the mismatches of one family come one after
+    // the other, and a candidate that failed for one of them fails for the
+    // next as well (exchanges only hand this family's replicas to
+    // candidates), so the search resumes after the previous partner
+    // (unwrapped candidate index prev_u).
+    int status = 0;
+    if (tid < 64) {
         const int lane = tid;
         int prev_f = -1;
         int64_t prev_u = 0;
@@ -2750,14 +2720,14 @@ __global__ void __launch_bounds__(WANG_THREADS) k_wang_pairs(const RunInfo *runs
             if (e < nlist) {
                 t_l = ldc(&W.list[e]);
                 k_l = rdm ? ldc(&W.sigma[t_l]) : t_l;
-                f_l = famv(k_l);
-                open_l = fpiv(k_l) == f_l;
-                if (!IN_LDS) p_l = ldc(&W.pi[k_l]);
+                f_l = fam[k_l];
+                open_l = ldc(&W.fampi[k_l]) == f_l;
+                p_l = ldc(&W.pi[k_l]);
                 if (!rdm) {   // the first later index with another label
                     int lo = t_l + 1, hi = Rc;
                     while (lo < hi) {
                         const int m = (lo + hi) >> 1;
-                        if (famv(m) == f_l) lo = m + 1;
+                        if (fam[m] == f_l) lo = m + 1;
                         else hi = m;
                     }
                     hi_l = lo;
@@ -2782,8 +2752,8 @@ __global__ void __launch_bounds__(WANG_THREADS) k_wang_pairs(const RunInfo *runs
                     if (uu < uend) {
                         const int q = (int)(uu >= Rc ? uu - Rc : uu);
                         m = rdm ? ldc(&W.sigma[q]) : q;
-                        fpm = fpiv(m);
-                        ok = famv(m) != fk && fpm != fk;
+                        fpm = ldc(&W.fampi[m]);
+                        ok = fam[m] != fk && fpm != fk;
                     }
                     const uint64_t bal = __ballot(ok);
                     if (bal) {
@@ -2798,71 +2768,284 @@ __global__ void __launch_bounds__(WANG_THREADS) k_wang_pairs(const RunInfo *runs
                     status = 2;
                     break;
                 }
-                if constexpr (IN_LDS) {
-                    if (lane == 0) {
-                        Lfpi[k] = fm;
-                        Lfpi[found] = fk;
-                        swaps[2 * nsw] = k;
-                        swaps[2 * nsw + 1] = found;
-                    }
-                    ++nsw;
-                } else {
-                    if (lane == 0) {
-                        const int pm = ldc(&W.pi[found]);
-                        stc(&W.pi[k], pm);
-                        stc(&W.pi[found], pk);
-                        stc(&W.fampi[k], fm);
-                        stc(&W.fampi[found], fk);
-                    }
-                    __builtin_amdgcn_s_waitcnt(0);
+                if (lane == 0) {
+                    const int pm = ldc(&W.pi[found]);
+                    stc(&W.pi[k], pm);
+                    stc(&W.pi[found], pk);
+                    stc(&W.fampi[k], fm);
+                    stc(&W.fampi[found], fk);
                 }
+                __builtin_amdgcn_s_waitcnt(0);
                 if (k_l == found) open_l = false;
                 prev_f = fk;
             }
         }
-        if (lane == 0) {
-            sh[0] = nsw;
-            sh[1] = status;
-        }
-    };
-    if (tid < 64) {
-        if (in_lds) repair(std::true_type{});
-        else repair(std::false_type{});
-    }
-    __syncthreads();
-    nsw = sh[0];
-    status = sh[1];
-    if (in_lds && status == 0) {   // replay the exchanges onto pi, in LDS
-        int32_t *Lpi = Lfam;       // the family labels are no longer needed
-        for (int k = tid; k < Rc; k += T) Lpi[k] = ldc(&W.pi[k]);
-        __syncthreads();
-        if (tid < 64) {
-            const int lane = tid;
-            __builtin_amdgcn_s_waitcnt(0);   // this wavefront's exchange log is written
-            for (int s0 = 0; s0 < nsw; s0 += 64) {
-                int a = 0, b = 0;
-                if (s0 + lane < nsw) {
-                    a = ldc(&swaps[2 * (s0 + lane)]);
-                    b = ldc(&swaps[2 * (s0 + lane) + 1]);
-                }
-                const int ns = min(64, nsw - s0);
-                for (int j = 0; j < ns; ++j) {
-                    const int x = __builtin_amdgcn_readlane(a, j), y = __builtin_amdgcn_readlane(b, j);
-                    if (lane == 0) {
-                        const int px = Lpi[x], py = Lpi[y];
-                        Lpi[x] = py;
-                        Lpi[y] = px;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        for (int k = tid; k < Rc; k += T) stc(&W.pi[k], Lpi[k]);
     }
     if (tid == 0) {
         stc(&W.hdr[0], status);
         stc(&W.hdr[1], nlist);
     }
+}
+
+// Permutation pairing of a run whose arrays fit a workgroup's LDS
+// (wang_lds_bytes): everything k_wang_pairs does, in LDS with 16-bit indices
+// and family numbers (the labels are runs, so their ranks do), and the repair
+// along the identity pattern a family at a time.  A mismatched position of
+// family f takes the first later position of another family whose partner is
+// not of f either; the mismatches of one family follow one another, a
+// position that fails for one of them fails for the next, and an exchange
+// changes none of the positions still ahead.  So the n-th open mismatch of the
+// family takes the n-th position that qualifies, and a wavefront makes up to
+// 64 exchanges at once instead of one after the other.  The random pattern
+// mixes the families: one exchange at a time, in registers, which hold 128
+// positions of the pattern.  16 runs of 2e4 replicas at L = 32, beta 0 to 2.4,
+// average per launch: 2219 us in global memory, 189 here; random pattern 2734
+// and 781 (1220 with the positions read from LDS for each exchange).
+__global__ void __launch_bounds__(WANG_THREADS) k_wang_lds(const RunInfo *runs, const PopState *st, int run0,
+                                                           uint32_t lds_bytes)
+{
+    extern __shared__ __align__(16) uint16_t w16[];
+    __shared__ int sh[17];
+    __shared__ uint16_t kq[64];
+    const int run = run0 + blockIdx.x;
+    const RunInfo &R = runs[run];
+    if (!is_wang(R.overlap) || wang_lds_bytes(R.R_cap) > lds_bytes) return;
+    const PopState &S = st[run * MAX_POP];
+    if (!pop_active(S)) return;
+    const int Rc = S.Rcur, i = S.i;
+    constexpr int T = WANG_THREADS;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int32_t *fam = R.fam[0][S.cur];
+    const WangBufs W = wang_bufs(R.wang, R.R_cap, R.wang_lb);
+    const bool rdm = R.overlap == PA_Q_WANG_RDM;
+    const uint32_t key0 = R.key0, key1 = R.key1;
+    const int Re = (Rc + 7) & ~7;   // 16-byte steps between the arrays
+    uint16_t *Lpi = w16;
+
+    // The permutations: index orders of the keys.  A key's top bits pick one
+    // of B buckets; counts, their prefix (the fill cursors, which end as the
+    // buckets' ends), members, and an index's rank from its bucket's members.
+    int lbc = 1;
+    while ((1 << lbc) < Rc) ++lbc;
+    const int B = 1 << lbc, shift = 64 - lbc;
+    uint32_t *cnt = (uint32_t *)(w16 + Re);      // B u16, two to a word
+    uint16_t *members = w16 + Re + B;
+    auto bump = [&](int b) { return (int)(atomicAdd(&cnt[b >> 1], 1u << (16 * (b & 1))) >> (16 * (b & 1))) & 0xFFFF; };
+    auto cursor = [&](int b) { return (int)((const uint16_t *)cnt)[b]; };
+    for (int which = rdm ? 1 : 0; which >= 0; --which) {
+        for (int k = tid; k < (B + 1) / 2; k += T) cnt[k] = 0;
+        __syncthreads();
+        for (int k = tid; k < Rc; k += T) bump((int)(perm_key(k, i, which, key0, key1) >> shift));
+        __syncthreads();
+        const int seg = (B + T - 1) / T, b0 = min(B, tid * seg), b1 = min(B, b0 + seg);
+        int sum = 0;
+        for (int b = b0; b < b1; ++b) sum += cursor(b);
+        int total;
+        int acc = block_scan_excl(sum, sh, &total);
+        for (int b = b0; b < b1; ++b) {
+            const int c = cursor(b);
+            ((uint16_t *)cnt)[b] = (uint16_t)acc;
+            acc += c;
+        }
+        __syncthreads();
+        for (int k = tid; k < Rc; k += T)
+            members[bump((int)(perm_key(k, i, which, key0, key1) >> shift))] = (uint16_t)k;
+        __syncthreads();
+        for (int k = tid; k < Rc; k += T) {
+            const uint64_t kk = perm_key(k, i, which, key0, key1);
+            const int b = (int)(kk >> shift);
+            const int lo = b ? cursor(b - 1) : 0, hi = cursor(b);
+            int r = lo;
+            for (int q = lo; q < hi; ++q) {
+                const int m = members[q];
+                if (m == k) continue;
+                const uint64_t km = perm_key(m, i, which, key0, key1);
+                r += (km < kk || (km == kk && m < k)) ? 1 : 0;
+            }
+            if (which) W.sigma[r] = k;
+            else Lpi[r] = (uint16_t)k;
+        }
+        __syncthreads();   // (of the workgroup's global stores, too: sigma is read back below)
+    }
+
+    // Family numbers: the rank of a label among the runs of equal labels.
+    // (Then the labels' space becomes the partners' numbers and the list.)
+    uint16_t *Lfam = w16 + Re, *Lfpi = w16 + 2 * Re, *aux = w16 + 3 * Re;
+    int32_t *lab = (int32_t *)(w16 + 2 * Re);
+    for (int k = tid; k < Rc; k += T) lab[k] = fam[k];
+    __syncthreads();
+    const int seg = (Rc + T - 1) / T, t0 = min(Rc, tid * seg), t1 = min(Rc, t0 + seg);
+    int starts = 0;
+    for (int t = t0; t < t1; ++t) starts += t > 0 && lab[t] != lab[t - 1] ? 1 : 0;
+    int all;
+    int number = block_scan_excl(starts, sh, &all);
+    for (int t = t0; t < t1; ++t) {
+        number += t > 0 && lab[t] != lab[t - 1] ? 1 : 0;
+        Lfam[t] = (uint16_t)number;
+    }
+    __syncthreads();
+    // A family of more than Rc / 2 replicas covers the middle index; then no
+    // valid pairing exists.
+    int mine = 0;
+    for (int t = t0; t < t1; ++t) mine += Lfam[t] == Lfam[Rc >> 1] ? 1 : 0;
+    int most;
+    block_scan_excl(mine, sh, &most);
+    if (2 * most > Rc) {
+        if (tid == 0) W.hdr[0] = 1;
+        return;
+    }
+    for (int k = tid; k < Rc; k += T) Lfpi[k] = Lfam[Lpi[k]];
+    if (rdm)
+        for (int k = tid; k < Rc; k += T) aux[k] = (uint16_t)W.sigma[k];
+    __syncthreads();
+    // the mismatched positions, ascending (what the random pattern needs is
+    // their number)
+    mine = 0;
+    for (int t = t0; t < t1; ++t) mine += Lfpi[t] == Lfam[t] ? 1 : 0;
+    int nlist;
+    int pos = block_scan_excl(mine, sh, &nlist);
+    if (!rdm)
+        for (int t = t0; t < t1; ++t)
+            if (Lfpi[t] == Lfam[t]) aux[pos++] = (uint16_t)t;
+    __syncthreads();
+    int status = 0;
+    if (tid < 64 && !rdm) {
+        int prev_f = -1, u = 0;   // the family of the last exchange, the next candidate (unwrapped)
+        for (int e0 = 0; e0 < nlist && status == 0; e0 += 64) {
+            const bool in = e0 + lane < nlist;
+            const int k_l = in ? (int)aux[e0 + lane] : 0, f_l = in ? (int)Lfam[k_l] : -1;
+            int hi_l = k_l + 1;   // the first later index of another family
+            for (int top = in ? Rc : 0; hi_l < top;) {
+                const int m = (hi_l + top) >> 1;
+                if (Lfam[m] == f_l) hi_l = m + 1;
+                else top = m;
+            }
+            bool todo = in;
+            while (status == 0) {
+                // open: not taken as a partner by an earlier exchange
+                const bool open = todo && Lfpi[k_l] == f_l;
+                const uint64_t bal = __ballot(open);
+                if (bal == 0) break;
+                const int first = __ffsll((unsigned long long)bal) - 1;
+                const int f = __builtin_amdgcn_readlane(f_l, first), hi = __builtin_amdgcn_readlane(hi_l, first);
+                const uint64_t same = __ballot(open && f_l == f);
+                if (open && f_l == f) {
+                    kq[rank_below(same, 0)] = (uint16_t)k_l;
+                    todo = false;
+                }
+                __builtin_amdgcn_wave_barrier();
+                if (f != prev_f) u = hi;
+                prev_f = f;
+                const int end = hi + Rc;   // past every position once
+                int left = __popcll(same), base = 0;
+                while (left > 0 && u < end) {
+                    const int uu = u + lane, m = uu >= 2 * Rc ? uu - 2 * Rc : (uu >= Rc ? uu - Rc : uu);
+                    const int fm = Lfpi[m];
+                    const bool ok = uu < end && Lfam[m] != f && fm != f;
+                    const uint64_t v = __ballot(ok);
+                    const int r = rank_below(v, 0), take = min(__popcll(v), left);
+                    if (ok && r < take) {
+                        const int k = kq[base + r];
+                        const uint16_t a = Lpi[k], b = Lpi[m];
+                        Lpi[k] = b;
+                        Lpi[m] = a;
+                        Lfpi[k] = (uint16_t)fm;
+                        Lfpi[m] = (uint16_t)f;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    const uint64_t lastb = __ballot(ok && r == left - 1);   // the candidate that ends the family
+                    u += lastb ? __ffsll((unsigned long long)lastb) : 64;
+                    left -= take;
+                    base += take;
+                }
+                if (left > 0) status = 2;   // impossible with no family above Rc / 2
+            }
+        }
+    } else if (tid < 64) {
+        // two windows of 64 search positions in registers: (m, pi, family,
+        // partner's family), a position past the end in no family
+        int m0, p0, f0, q0, m1, p1, f1, q1;
+        auto take_in = [&](int base, int &m, int &p, int &f, int &q) {
+            const int t = base + lane;
+            m = t < Rc ? (int)aux[t] : -1;
+            p = m < 0 ? 0 : (int)Lpi[m];
+            f = m < 0 ? -1 : (int)Lfam[m];
+            q = m < 0 ? -2 : (int)Lfpi[m];
+        };
+        auto put_back = [&](int m, int p, int q) {
+            if (m < 0) return;
+            Lpi[m] = (uint16_t)p;
+            Lfpi[m] = (uint16_t)q;
+        };
+        take_in(0, m0, p0, f0, q0);
+        for (int base = 0; base < Rc && status == 0; base += 64) {
+            take_in(base + 64, m1, p1, f1, q1);
+            for (;;) {
+                const uint64_t bal = __ballot(f0 == q0);
+                if (bal == 0) break;
+                const int j = __ffsll((unsigned long long)bal) - 1;
+                const int fk = __builtin_amdgcn_readlane(f0, j), pk = __builtin_amdgcn_readlane(p0, j);
+                const uint64_t v0 = __ballot(m0 >= 0 && f0 != fk && q0 != fk) & (~(uint64_t)0 << j);
+                const uint64_t v1 = __ballot(m1 >= 0 && f1 != fk && q1 != fk);
+                if (v0 | v1) {
+                    const int first = __ffsll((unsigned long long)(v0 ? v0 : v1)) - 1;
+                    const int pm = __builtin_amdgcn_readlane(v0 ? p0 : p1, first);
+                    const int fm = __builtin_amdgcn_readlane(v0 ? q0 : q1, first);
+                    if (v0 && lane == first) {
+                        p0 = pk;
+                        q0 = fk;
+                    }
+                    if (!v0 && lane == first) {
+                        p1 = pk;
+                        q1 = fk;
+                    }
+                    if (lane == j) {
+                        p0 = pm;
+                        q0 = fm;
+                    }
+                    continue;
+                }
+                // further on, round the end up to position base + j again
+                put_back(m0, p0, q0);
+                put_back(m1, p1, q1);
+                __builtin_amdgcn_wave_barrier();
+                const int t = base + j, k = __builtin_amdgcn_readlane(m0, j);
+                bool found = false;
+                for (int u = min(base + 128, Rc); u < t + Rc && !found; u += 64) {
+                    const int uu = u + lane;
+                    const int m = (int)aux[uu < t + Rc ? (uu >= Rc ? uu - Rc : uu) : t];
+                    const int fm = Lfpi[m];
+                    const uint64_t v = __ballot(uu < t + Rc && Lfam[m] != fk && fm != fk);
+                    if (v == 0) continue;
+                    found = true;
+                    if (lane == __ffsll((unsigned long long)v) - 1) {
+                        Lpi[k] = Lpi[m];
+                        Lpi[m] = (uint16_t)pk;
+                        Lfpi[k] = (uint16_t)fm;
+                        Lfpi[m] = (uint16_t)fk;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
+                if (!found) {
+                    status = 2;
+                    break;
+                }
+                take_in(base, m0, p0, f0, q0);
+                take_in(base + 64, m1, p1, f1, q1);
+            }
+            put_back(m0, p0, q0);
+            m0 = m1;
+            p0 = p1;
+            f0 = f1;
+            q0 = q1;
+        }
+    }
+    if (tid == 0) {
+        W.hdr[0] = status;
+        W.hdr[1] = nlist;
+    }
+    __syncthreads();
+    for (int k = tid; k < Rc; k += T) W.pi[k] = Lpi[k];
 }
 
 // Calibration: two independent chains of Philox calls per lane, all in
@@ -2892,7 +3075,7 @@ hipError_t launch_philox_rate(int calls, hipStream_t s, int *blocks, int *thread
 hipError_t prepare_wang_lds(size_t bytes)
 {
     if (bytes <= 65536) return hipSuccess;
-    return hipFuncSetAttribute((const void *)k_wang_pairs, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    return hipFuncSetAttribute((const void *)k_wang_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 __device__ __forceinline__ bool wang_group_live(const Item &it, const RunInfo &R, const PopState &S)
@@ -3851,9 +4034,14 @@ hipError_t launch_dos_sample(const LaunchCtx &c)
 hipError_t launch_measure(const LaunchCtx &c, bool first)
 {
     if (c.any_wang && c.n_runs > 0) {
-        k_wang_pairs<<<c.n_runs, WANG_THREADS, sizeof(int32_t) * (size_t)c.wang_lds_ints, c.stream>>>(
-            c.runs, c.st, c.run0, c.wang_lds_ints);
-        PA_CHECK_LAUNCH();
+        if (c.wang_lds) {
+            k_wang_lds<<<c.n_runs, WANG_THREADS, c.wang_lds, c.stream>>>(c.runs, c.st, c.run0, (uint32_t)c.wang_lds);
+            PA_CHECK_LAUNCH();
+        }
+        if (c.wang_large) {
+            k_wang_pairs<<<c.n_runs, WANG_THREADS, 0, c.stream>>>(c.runs, c.st, c.run0, (uint32_t)c.wang_lds);
+            PA_CHECK_LAUNCH();
+        }
         const int blocks = (c.n_items + 3) / 4;
         if (c.repr == PA_INT8)
             k_wang_rows<PA_INT8><<<blocks, 256, 0, c.stream>>>(c.items, c.n_items, c.runs, c.st);

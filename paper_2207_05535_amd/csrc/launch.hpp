@@ -36,7 +36,8 @@ struct LaunchCtx {
     bool any_overlap = true;       // some run measures overlaps (index shift, two populations, pairing)
     int copy_split = 1;            // workgroups per copy item, each taking a share of every group's 64-site blocks
     bool any_wang;                 // some run pairs replicas by permutations
-    int wang_lds_ints;             // LDS of the pairing repair (2 R_cap of the largest run that fits, or 0)
+    size_t wang_lds;               // LDS of k_wang_lds: the largest such run that fits, or 0
+    bool wang_large;               // some such run does not fit
     bool any_exact_dos;            // some run is at theta = infinity
     bool any_swept, any_unswept;   // some run makes / does not make Metropolis sweeps (int8 layout)
     unsigned long long *stats;   // device [NSTAT] work counters of the sweeps

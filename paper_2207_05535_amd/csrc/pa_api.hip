@@ -577,13 +577,17 @@ void meas_items_of(const pa_run_desc &d, int run, int pop, std::vector<SweepItem
     for (int g = 0; g < groups_cap_of(d); g += gpw) out.push_back({run, pop, g, std::min(gpw, groups_cap_of(d) - g)});
 }
 
-int wang_lds_ints_of(const pa_run_desc *const *runs, int n, int lds_limit)
+size_t wang_lds_of(const pa_run_desc *const *runs, int n, int lds_limit, bool *large)
 {
-    int best = 0;
-    for (int r = 0; r < n; ++r)
-        if (is_wang(runs[r]->overlap) && 8 * (size_t)runs[r]->R_cap + 256 <= (size_t)lds_limit)
-            best = std::max(best, runs[r]->R_cap);
-    return 2 * best;
+    size_t best = 0;
+    *large = false;
+    for (int r = 0; r < n; ++r) {
+        if (!is_wang(runs[r]->overlap)) continue;
+        const size_t need = wang_lds_bytes(runs[r]->R_cap);
+        if (need + 1024 <= (size_t)lds_limit) best = std::max(best, need);   // beside the kernel's own
+        else *large = true;
+    }
+    return best;
 }
 
 int groups_of_2048(int L)
@@ -946,8 +950,8 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
     if (c->any_wang) {
         std::vector<const pa_run_desc *> dp(n_runs);
         for (int r = 0; r < n_runs; ++r) dp[r] = &c->descs[r];
-        c->lc.wang_lds_ints = wang_lds_ints_of(dp.data(), n_runs, c->lds_limit);
-        if (prepare_wang_lds(sizeof(int32_t) * (size_t)c->lc.wang_lds_ints) != hipSuccess) return fail(PA_ERR_DEVICE);
+        c->lc.wang_lds = wang_lds_of(dp.data(), n_runs, c->lds_limit, &c->lc.wang_large);
+        if (prepare_wang_lds(c->lc.wang_lds) != hipSuccess) return fail(PA_ERR_DEVICE);
     }
 
     hipStream_t s = c->stream;

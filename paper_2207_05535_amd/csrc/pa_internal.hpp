@@ -225,6 +225,14 @@ __host__ __device__ inline size_t wang_row_words(int R_cap, int N)
 }
 __host__ __device__ inline size_t wang_ints(int R_cap, int N) { return wang_ints_head(R_cap) + 2 * wang_row_words(R_cap, N); }
 __host__ __device__ inline uint64_t *wang_rows(int32_t *w, int R_cap) { return (uint64_t *)(w + wang_ints_head(R_cap)); }
+// LDS of k_wang_lds for a run: pi beside the bucket counts (2^wang_lb) and
+// members, then pi, family numbers, the partners' and the list or search
+// pattern, 16 bits each.
+__host__ __device__ inline size_t wang_lds_bytes(int R_cap)
+{
+    const size_t re = (R_cap + 7) & ~7, a = 2 * (2 * re + ((size_t)1 << wang_lb_of(R_cap))), b = 8 * re;
+    return R_cap > 65535 ? (size_t)1 << 30 : (a > b ? a : b);
+}
 struct WangBufs {
     int32_t *pi, *sigma, *fampi, *members, *list, *cnt, *start, *hdr;
 };

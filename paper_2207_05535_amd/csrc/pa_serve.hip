@@ -370,9 +370,8 @@ pa_status rebuild(pa_server *s)
         std::vector<const pa_run_desc *> dp;
         for (int k = 0; k < s->max_slots; ++k)
             if (s->slots[k].used) dp.push_back(&s->slots[k].d);
-        c.wang_lds_ints = wang_lds_ints_of(dp.data(), (int)dp.size(), s->lds_limit);
-        if (c.wang_lds_ints && prepare_wang_lds(sizeof(int32_t) * (size_t)c.wang_lds_ints) != hipSuccess)
-            return sfail(s);
+        c.wang_lds = wang_lds_of(dp.data(), (int)dp.size(), s->lds_limit, &c.wang_large);
+        if (prepare_wang_lds(c.wang_lds) != hipSuccess) return sfail(s);
     }
     c.any_exact_dos = exact;
     c.sweep_items = (const SweepItem *)(s->base + s->sweep_off);
@@ -606,9 +605,8 @@ pa_status pa_server_admit(pa_server *s, const pa_run_desc *desc, int32_t *slot)
     c.any_wang = is_wang(d.overlap);
     {
         const pa_run_desc *dp = &sl.d;
-        c.wang_lds_ints = wang_lds_ints_of(&dp, 1, s->lds_limit);
-        if (c.wang_lds_ints && prepare_wang_lds(sizeof(int32_t) * (size_t)c.wang_lds_ints) != hipSuccess)
-            return sfail(s);
+        c.wang_lds = wang_lds_of(&dp, 1, s->lds_limit, &c.wang_large);
+        if (prepare_wang_lds(c.wang_lds) != hipSuccess) return sfail(s);
     }
     c.any_exact_dos = d.theta == PA_THETA_EXACT;
     if (launch_init(c, (const uint64_t *)(blk + b.dseed)) != hipSuccess || launch_measure(c, true) != hipSuccess)

@@ -197,3 +197,32 @@ def test_edge_sizes(repr_, L, R, theta, kind):
     assert np.array_equal(ctx.qhist(0), orc.qhist())
     ctx.close()
 
+
+
+@pytest.mark.parametrize("kind", [W.Q_WANG, W.Q_WANG_RDM])
+def test_pairing_sizes(kind):
+    """Pairings at the edges of the repair's batches and windows of 64 and 128
+    positions, few large families and many small ones, and a run whose pairing
+    does not fit a workgroup's LDS beside runs whose does, in one context."""
+    say(f"permutation pairing sizes kind={kind}")
+    sizes = [(3, 0), (63, 1), (64, 1), (65, 0), (127, 1), (128, 1), (129, 2), (191, 0), (1000, 1), (5003, 0), (20481, 0)]
+    runs = [W.run_desc(8, W.EA_PMJ, seed=W.RUN_SEED_BASE + 0x5500 + R, disorder_seed=12, R=R, theta=theta, K=9,
+                       beta_f=2.0, resampling=W.MULTINOMIAL, overlap=kind) for R, theta in sizes]
+    ctx = pa.Context(runs, "msc")
+    paired = 0
+    for i in range(9):
+        if i:
+            ctx.step(i)
+        for r, d in enumerate(runs):
+            fam = ctx.state(r, 0)[2]
+            st, pairs = ctx.pairing(r)
+            if large_family(fam):
+                assert st == 1, (r, i)
+                continue
+            pi = oracle.random_permutation(d["seed"], i, 0, len(fam), 0)
+            sigma = oracle.random_permutation(d["seed"], i, 0, len(fam), 1) if kind == W.Q_WANG_RDM else None
+            st_o, want = oracle.wang_repair(fam, pi, sigma)
+            assert st == st_o == 0 and np.array_equal(pairs, want), (r, i)
+            paired += 1
+    assert paired > len(runs)
+    ctx.close()
