@@ -36,6 +36,24 @@ def test_record_layouts():
     assert pa.pa_run_desc.beta.offset == 40
 
 
+@pytest.mark.parametrize("change", [{}, {"seed": -1}, {"seed": 2**64 + 5}, {"theta": -1}, {"L": np.int64(6)}, {"R": 2**35 + 9},
+                                    {"beta": np.linspace(0, 2, 9)[::2]}, {"beta": (0, 1, 2)}, {"model": True}])
+def test_descriptor_fields(change):
+    d = dict(W.fm_L8_R1000(), **change)
+    arr, keep = pa.make_descs([W.fm_L8_R1000(), d])
+    want = pa.pa_run_desc(**{f: d.get(f, 0) for f, _ in pa.pa_run_desc._fields_ if f not in ("K", "beta")})
+    for f, _ in pa.pa_run_desc._fields_:
+        if f not in ("K", "beta"):
+            assert getattr(arr[1], f) == getattr(want, f), f
+    assert arr[1].K == len(d["beta"]) and arr[1].beta[:arr[1].K] == [float(b) for b in d["beta"]]
+
+
+def test_descriptor_fields_refused():
+    for bad in ({"L": 8.0}, {"seed": None}, {"R": "1000"}):
+        with pytest.raises(TypeError):
+            pa.make_descs([dict(W.fm_L8_R1000(), **bad)])
+
+
 def test_status_strings():
     for st in range(7):
         assert pa.status_str(st)

@@ -180,3 +180,29 @@ def test_edge_sizes(repr_, L, R):
     assert np.array_equal(Eg, Eo) and np.array_equal(fg, fo)
     ctx.close()
 
+
+
+def test_runs_of_several_tables():
+    """Runs of two sizes and two schedules (one with repeated and with irregular
+    steps), theta = infinity and not, interleaved in one context, and the same
+    after a checkpoint restored into another context."""
+    say("theta = infinity runs that share tables")
+    betas = [[0.0, 0.1, 0.2, 0.2, 0.25, 0.35, 0.36], [0.0, 0.1, 0.2, 0.3, 0.4, 0.5, 0.6]]
+    runs = []
+    for q in range(12):
+        d = W.run_desc((4, 6)[q % 2], W.FM, seed=W.RUN_SEED_BASE + 0x6A00 + q, R=130 + q, theta=(-1, -1, 1)[q % 3], K=7,
+                       beta_f=0.6, resampling=W.MULTINOMIAL)
+        runs.append(dict(d, beta=np.array(betas[(q // 2) % 2])))
+    ctx = pa.Context(runs, "msc")
+    ctx.run(1, 4)
+    saved = ctx.checkpoint()
+    ctx.run(4, 7)
+    other = pa.Context(runs, "msc")
+    other.restore(saved)
+    other.run(4, 7)
+    for r, d in enumerate(runs):
+        orc = oracle.OracleRun(d).run_all()
+        for name, c in (("run", ctx), ("restored", other)):
+            assert_obs_equal(c.obs()[r, 0], orc.obs()[0], f"{name} {r}")
+    ctx.close()
+    other.close()
