@@ -314,17 +314,19 @@ pa_status pa_set_tuning(pa_ctx *ctx, int32_t L, int32_t threads, int32_t groups_
  * the same largest-first order).  Results never depend on it. */
 pa_status pa_set_persistent(pa_ctx *ctx, int32_t on);
 
-/* Sweep chunks on the persistent grid: chunks = K > 1 splits every item of
- * the batched sweep into K items of consecutive sweeps (chunk c takes sweeps
- * c theta / K .. (c + 1) theta / K - 1 of its replica groups), listed all
- * first chunks first; a chunk waits on the device until the previous chunk
- * of its groups has stored their lattices.  With every item taking about the
- * same time, a launch of n items on S resident workgroups lasts about
- * ceil(n / S) item times; chunks bring that down to ceil(n K / S) / K at the
- * cost of loading and storing each lattice K - 1 more times, which for
- * small items can outweigh the gain.  1 <= chunks <= 4 fixes K (default 1;
- * pa_autotune searches it); chunks = 0 chooses K per plan from the estimate
- * above.  Chunks apply only where the persistent grid is used
+/* Sweep chunks on the persistent grid: chunks = K > 1 lets an item of the
+ * batched sweep be carried out as several items of consecutive sweeps of its
+ * replica groups; a chunk waits on the device until the previous chunk of its
+ * groups has stored their lattices.  K = 2 deals the items out to one list
+ * per compute unit, of equal work, and cuts in two only those that go over
+ * from one list into the next, so that all compute units end together.  K = 3
+ * and 4 cut every item into K (chunk c takes sweeps c theta / K ..
+ * (c + 1) theta / K - 1), listed all first chunks first: a launch of n items
+ * on S resident workgroups, with every item taking about the same time, lasts
+ * about ceil(n K / S) / K item times instead of ceil(n / S), at the cost of
+ * loading and storing each lattice K - 1 more times.  1 <= chunks <= 4 fixes K
+ * (default 1; pa_autotune searches it); chunks = 0 chooses K per plan from
+ * that estimate.  Chunks apply only where the persistent grid is used
  * (pa_set_persistent, and more items than resident workgroups).  Results
  * never depend on it.  PA_ERR_ARG outside 0..4, PA_ERR_STATE between the
  * calls of a temperature step. */

@@ -25,7 +25,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <queue>
 #include <type_traits>
 #include <vector>
 #include <math.h>
@@ -1493,16 +1492,19 @@ __device__ __forceinline__ int lattice_word(const SweepJob &J, int gs, int n, in
     return gs * J.N + ((n + y) & 1) * J.nh + (n >> 1);
 }
 
+// handed: the other end is another workgroup of this launch (put, take).
 template <int LT, bool STORE>
-__device__ __forceinline__ void move_lattices(const SweepJob &J, uint64_t *lat)
+__device__ __forceinline__ void move_lattices(const SweepJob &J, uint64_t *lat, bool handed)
 {
     const float invN = 1.0f / (float)J.N, invL = 1.0f / (float)J.L;
     for (int u = threadIdx.x; u < J.G * J.N; u += blockDim.x) {
         const int gs = LT > 0 ? u / J.N : div_small(u, invN);
         const int n = u - gs * J.N;
         const int y = LT > 0 ? n / J.L : div_small(n, invL);
-        if (STORE) J.base[u] = lat[lattice_word(J, gs, n, y)];
-        else lat[lattice_word(J, gs, n, y)] = J.base[u];
+        uint64_t &l = lat[lattice_word(J, gs, n, y)];
+        if (STORE && handed) put(&J.base[u], l);
+        else if (STORE) J.base[u] = l;
+        else l = handed ? take(&J.base[u]) : J.base[u];
     }
 }
 
@@ -1860,7 +1862,7 @@ __device__ __forceinline__ void stream_item(const SweepItem &item, const RunInfo
     UndPair *eu = (UndPair *)(lat + (size_t)J.G * J.N);
     uint32_t *en = (uint32_t *)(eu + nw * slots);
     uint8_t *jb = (uint8_t *)(en + nw * slots);
-    move_lattices<LT, false>(J, lat);
+    move_lattices<LT, false>(J, lat, item.chunk > 0);
     if (EA) bond_signs(J, R.jbits, jb);
     if (threadIdx.x < 16) tmask[threadIdx.x] = call_masks(J.Th.t4, J.Th.t8, threadIdx.x);   // read after a barrier
     const int ring = wave_id() * slots;
@@ -1868,7 +1870,7 @@ __device__ __forceinline__ void stream_item(const SweepItem &item, const RunInfo
         J.G == 1 ? stream_sweeps<LT, EA, true>(J, lat, eu + ring, en + ring, jb, tmask, slots, mode & 0xFF)
                  : stream_sweeps<LT, EA, false>(J, lat, eu + ring, en + ring, jb, tmask, slots, mode & 0xFF);
     __syncthreads();
-    move_lattices<LT, true>(J, lat);
+    move_lattices<LT, true>(J, lat, item.chunk + 1 < item.nchunk);
     item_stats(J, wcalls, stats);
 }
 
@@ -1888,7 +1890,7 @@ __device__ __forceinline__ void general_item(const SweepItem &item, const RunInf
     uint32_t *en = (uint32_t *)(eu + J.units);            // [units] (LDS word << 16) | site
     uint8_t *jb = (uint8_t *)(en + J.units);              // [2][nh] bond signs of each site (spin glass)
     int *ctl = (int *)(jb + (EA ? N : 0));                // pooled list counts [2], pass counts [2][16]
-    move_lattices<0, false>(J, lat);
+    move_lattices<0, false>(J, lat, item.chunk > 0);
     if (EA) bond_signs(J, R.jbits, jb);
     if (threadIdx.x == 0) ctl[0] = ctl[1] = 0;
     const float invN = 1.0f / (float)N;
@@ -1958,7 +1960,7 @@ __device__ __forceinline__ void general_item(const SweepItem &item, const RunInf
         }
     }
     __syncthreads();
-    move_lattices<0, true>(J, lat);
+    move_lattices<0, true>(J, lat, item.chunk + 1 < item.nchunk);
     item_stats(J, wcalls, stats);
 }
 
@@ -1992,81 +1994,140 @@ __device__ __forceinline__ void sweep_one(const SweepItem &it, const RunInfo *ru
 }
 
 // One workgroup per item, or (queue != nullptr) a persistent grid whose
-// workgroups take items in list order from a ticket counter.  The items are
-// listed largest first, so the last tickets are the cheapest.  queue[0] is
-// the next ticket, queue[1] counts workgroups that found the list empty; the
-// last of them resets both, so the next launch (or graph replay) starts
-// from zero without a separate clear.
+// workgroups take items from the front of a list until none is left: of the
+// whole list (n_lists = 0), or of the list of their CU (SweepList), and of
+// the others' when it is empty.  queue[0] is the next item of the whole list,
+// queue[1] counts workgroups that found nothing left; the last of them resets
+// the lists, so the next launch (or graph replay) starts without a separate
+// clear.
+//
+// Lists per CU: the workgroups on a CU do not advance alike (the oldest goes
+// first: 109 / 220 / 395 us for equal items of three of them), so the last
+// items of one list for all leave some CUs with two items to go when others
+// are done, and every workgroup's first item is an atomic on one address,
+// about 10 ns each.  Workgroups whose numbers differ by a multiple of the CU
+// count share a CU (when nothing else runs; if not, only time is lost).
+// Step at L = 64, R = 1e5 (1563 items, three workgroups per CU; the launch
+// ends 11 % after the mean CU with whole items from one list, 2 % with these):
+// one list 635 us, in two chunks each 622, lists 591; two populations at
+// L = 32 716, 735, 699.  (Sizes mixed, where the cost of an item is known less
+// well: no better than one list, 1769 against 1684 for five sizes.)
 //
 // Sweep chunks (persistent grid only): an item may cover a part of its
-// groups' theta sweeps.  The list holds every first chunk before any second
-// one, and so on, so the chunk an item depends on was taken from the queue
-// earlier, by a workgroup that is running or done.  When a chunk has stored
-// its lattices, its workgroup publishes (launch generation << 4 | chunk + 1)
-// in the groups' flag slot; the next chunk waits for that value before it
-// loads them.  queue[2] is the launch generation: every workgroup reads it
-// before taking a ticket, and the last one to leave increments it, so
-// values left by earlier launches or graph replays never match.  The wait
-// ends because the producer holds an earlier ticket; it is bounded all the
-// same, and a wait that runs out is counted in the stall counter (the
-// results of that step are then not trustworthy, and reading the work
-// counters reports it).
+// groups' theta sweeps.  When a chunk has stored its lattices (put), its
+// workgroup publishes (launch generation << 4 | chunk + 1) in the groups'
+// flag slot; the next chunk waits for that value before it loads them.
+// queue[2] is the launch generation: every workgroup reads it before taking
+// an item, and the last one to leave increments it, so values left by earlier
+// launches or graph replays never match.  The wait ends because a workgroup
+// that runs holds the previous chunk: it stands earlier in the whole list,
+// or it is the first item of the CU list after this one, and a workgroup that
+// finds it still there takes it first.  The wait is bounded all the same, and
+// one that runs out is counted in the stall counter (the results of that step
+// are then not trustworthy, and reading the work counters reports it).
 constexpr unsigned int SWEEP_WAIT_SPINS = 1u << 22;
+constexpr unsigned int NO_ITEM = ~0u;
+
+// The next item, of list l if it has one, else of another list (l becomes
+// it); NO_ITEM if all are empty.  Called by the whole workgroup.
+__device__ unsigned int next_item(SweepList *lists, int n_lists, int &l, unsigned int *sh)
+{
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const unsigned int t = atomicAdd(&lists[l].next, 1u);
+            *sh = t < lists[l].end ? t : NO_ITEM;
+        }
+        __syncthreads();
+        const unsigned int t = *sh;
+        if (t != NO_ITEM) return t;
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            unsigned int found = NO_ITEM;
+            for (int base = 1; base < n_lists && found == NO_ITEM; base += 64) {
+                const int q = base + (int)threadIdx.x, j = l + q < n_lists ? l + q : l + q - n_lists;
+                const bool has = q < n_lists && take(&lists[j].next) < lists[j].end;
+                const uint64_t bal = __ballot(has);
+                if (bal) found = (unsigned int)(l + base + __ffsll((unsigned long long)bal) - 1) % (unsigned int)n_lists;
+            }
+            if (threadIdx.x == 0) *sh = found;
+        }
+        __syncthreads();
+        if (*sh == NO_ITEM) return NO_ITEM;
+        l = (int)*sh;
+    }
+}
 
 template <int LS, bool EA>
 __global__ void __launch_bounds__(1024) k_sweep_msc(const SweepItem *items, int n_items, const RunInfo *runs,
                                                     const PopState *st, int mode, unsigned long long *stats,
-                                                    unsigned int *queue, unsigned int *flags, uint32_t lds_bytes)
+                                                    unsigned int *queue, unsigned int *flags, SweepList *lists,
+                                                    int n_lists, uint32_t lds_bytes)
 {
     extern __shared__ __align__(16) uint64_t lds[];
-    __shared__ unsigned int ticket, gen;
+    __shared__ unsigned int sh, gen;
     const bool persistent = queue != nullptr;
-    unsigned int t = blockIdx.x;
-    if (persistent && threadIdx.x == 0) gen = __hip_atomic_load(&queue[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned int t = blockIdx.x, later = NO_ITEM;
+    int l = n_lists ? (int)(blockIdx.x % (unsigned int)n_lists) : 0;
+    if (persistent && threadIdx.x == 0) gen = take(&queue[2]);
     for (;;) {
-        if (persistent) {
+        if (later != NO_ITEM) {
+            t = later;
+            later = NO_ITEM;
+        } else if (persistent && n_lists) {
+            t = next_item(lists, n_lists, l, &sh);
+        } else if (persistent) {
             __syncthreads();
-            if (threadIdx.x == 0) ticket = atomicAdd(&queue[0], 1u);
+            if (threadIdx.x == 0) sh = atomicAdd(&queue[0], 1u);
             __syncthreads();
-            t = ticket;
+            t = sh;
         }
         if (t >= (unsigned int)n_items) break;
-        const SweepItem it = items[t];
+        SweepItem it = items[t];
         if (persistent && it.chunk > 0) {
+            __syncthreads();
             if (threadIdx.x == 0) {
+                // the item's beginning, if nobody has it
+                sh = NO_ITEM;
+                if (n_lists) {
+                    const unsigned int first = lists[l + 1].first;
+                    if (atomicCAS(&lists[l + 1].next, first, first + 1) == first) sh = first;
+                }
                 const unsigned int want = (gen << 4) | (unsigned int)it.chunk;
                 unsigned int spins = 0;
-                while (__hip_atomic_load(&flags[it.base], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != want) {
+                while (sh == NO_ITEM && take(&flags[it.base]) != want) {
                     if (++spins == SWEEP_WAIT_SPINS) {
                         atomicAdd(&stats[ST_STALL], 1ull);
                         break;
                     }
                     __builtin_amdgcn_s_sleep(2);
                 }
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             }
             __syncthreads();
+            if (sh != NO_ITEM) {
+                later = t;
+                it = items[sh];
+            }
         }
         sweep_one<LS, EA>(it, runs, st, lds, lds_bytes, mode, stats);
         if (!persistent) return;
         if (it.chunk + 1 < it.nchunk) {
-            // every wavefront waits for its own lattice stores (a barrier
-            // alone does not), so that the release by the first thread,
-            // which writes this XCD's L2 back, covers all of them
+            // every wavefront waits for its own device-coherent lattice
+            // stores (a barrier alone does not)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            if (threadIdx.x == 0)
-                __hip_atomic_store(&flags[it.base], (gen << 4) | (unsigned int)(it.chunk + 1), __ATOMIC_RELEASE,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+            if (threadIdx.x == 0) put(&flags[it.base], (gen << 4) | (unsigned int)(it.chunk + 1));
         }
     }
+    __syncthreads();
+    if (threadIdx.x == 0) sh = atomicAdd(&queue[1], 1u);
+    __syncthreads();
+    if (sh != gridDim.x - 1) return;
+    for (int j = threadIdx.x; j < n_lists; j += blockDim.x) put(&lists[j].next, lists[j].first);
     if (threadIdx.x == 0) {
-        __threadfence();
-        if (atomicAdd(&queue[1], 1u) == gridDim.x - 1) {
-            atomicExch(&queue[0], 0u);
-            atomicExch(&queue[1], 0u);
-            atomicAdd(&queue[2], 1u);
-        }
+        put(&queue[0], 0u);
+        put(&queue[1], 0u);
+        put(&queue[2], gen + 1);
     }
 }
 
@@ -3771,7 +3832,7 @@ size_t msc_lds_bytes(int N, int groups, bool ea, int threads, int mode)
 // The sweep kernel for a launch: one compiled for a single (L, model) when
 // every run of the context has it, else the one that dispatches per item.
 using SweepKernel = void (*)(const SweepItem *, int, const RunInfo *, const PopState *, int, unsigned long long *,
-                             unsigned int *, unsigned int *, uint32_t);
+                             unsigned int *, unsigned int *, SweepList *, int, uint32_t);
 
 SweepKernel msc_kernel(int L, int ea)
 {
@@ -3829,7 +3890,7 @@ hipError_t launch_sweep_msc(const LaunchCtx &c)
         const int mode = c.sweep_dense | (c.sweep_pooled << 8);
         msc_kernel(q.L, q.ea)<<<grid, c.sweep_threads, q.lds, c.stream>>>(
             c.sweep_items + q.first, q.count, c.runs, c.st, mode, c.stats,
-            persistent ? c.sweep_queue : nullptr, c.sweep_flags, (uint32_t)q.lds);
+            persistent ? c.sweep_queue : nullptr, c.sweep_flags, q.lists, q.n_lists, (uint32_t)q.lds);
         PA_CHECK_LAUNCH();
     }
     return hipSuccess;
@@ -3933,28 +3994,85 @@ int sweep_chunks_auto(int n, int slots)
     return best;
 }
 
-// Makespan, in sweeps, of n equal items of theta sweeps each cut into two
-// chunks of a and theta - a sweeps on S workgroups that take tickets in list
-// order (every first chunk before any second one); a chunk costs its sweeps
-// plus `over` (loading and storing its lattices), and a second chunk starts
-// no earlier than its first one ends.
-static double two_chunk_makespan(int n, int S, int theta, int a, double over)
+// Two chunks: a list of items per CU, and only what has to be cut is.  The
+// items (dealt out so that every list gets its share of each size) are laid
+// end to end over the lists, each of capacity T; one that crosses from a
+// list's end into the next one's beginning is cut there, its first sweeps the
+// beginning of the next.  Taken in the order beginning, whole items (largest
+// first), end, every CU is busy until about T, and an item's beginning is done
+// long before its end is taken (McNaughton's wrap-around rule).  A cut falls
+// between sweeps, so the least T that fits is searched upwards from the mean.
+// A chunk costs its sweeps and about a third of one for moving its lattices.
+struct SweepPlan {
+    std::vector<SweepItem> items;
+    std::vector<SweepList> lists;
+};
+
+static bool wrap_around(const std::vector<SweepItem> &items, int n_lists, double T, const std::vector<double> &cost,
+                        const std::vector<int> &run_theta, SweepPlan &P)
 {
-    std::priority_queue<double, std::vector<double>, std::greater<double>> idle;
-    for (int w = 0; w < S; ++w) idle.push(0.0);
-    std::vector<double> first_end((size_t)n);
-    double end = 0.0;
-    for (int lvl = 0; lvl < 2; ++lvl)
-        for (int b = 0; b < n; ++b) {
-            const double t = idle.top();
-            idle.pop();
-            const double start = lvl ? std::max(t, first_end[b]) : t;
-            const double fin = start + (lvl ? theta - a : a) + over;
-            if (!lvl) first_end[b] = fin;
-            end = std::max(end, fin);
-            idle.push(fin);
+    constexpr double MOVE = 0.3;
+    const int n = (int)items.size();
+    P.items.clear();
+    P.lists.clear();
+    double room = T;
+    unsigned int first = 0;
+    for (int k = 0; k < n; ++k) {
+        const int rows = (n + n_lists - 1) / n_lists, full = n - (rows - 1) * n_lists;   // columns with `rows` items
+        const int b = k < full * rows ? (k % rows) * n_lists + k / rows
+                                      : ((k - full * rows) % (rows - 1)) * n_lists + full + (k - full * rows) / (rows - 1);
+        SweepItem it = items[b];
+        const int theta = run_theta[it.run];
+        it.base = b;
+        it.chunk = 0;
+        it.nchunk = 1;
+        it.cut = 0;
+        if (cost[b] * (theta + MOVE) > room) {
+            const int end = (int)std::floor(room / cost[b] - MOVE);   // sweeps that still fit here
+            if (end >= 1 && end < theta) {
+                it.nchunk = 2;
+                it.cut = theta - end;
+                it.chunk = 1;
+                P.items.push_back(it);
+                it.chunk = 0;
+            }
+            P.lists.push_back({first, first, (unsigned int)P.items.size(), {}});
+            if ((int)P.lists.size() == n_lists) return false;
+            first = (unsigned int)P.items.size();
+            room = T;
         }
-    return end;
+        P.items.push_back(it);
+        room -= cost[b] * ((it.nchunk == 2 ? it.cut : theta) + MOVE);
+    }
+    while ((int)P.lists.size() < n_lists) {
+        P.lists.push_back({first, first, (unsigned int)P.items.size(), {}});
+        first = (unsigned int)P.items.size();
+    }
+    return room >= 0;
+}
+
+bool sweep_lists(std::vector<SweepItem> &items, SweepClass &cls, int n_lists, const std::vector<int> &run_theta,
+                 const std::vector<int> &run_L, std::vector<SweepList> &lists)
+{
+    const int n = (int)items.size();
+    if (cls.first != 0 || cls.count != n || n_lists < 1 || n <= n_lists) return false;
+    std::vector<double> cost(n);
+    double T = 0;
+    for (int b = 0; b < n; ++b) {
+        cost[b] = (double)run_L[items[b].run] * run_L[items[b].run] * items[b].ngroups;
+        T += cost[b] * run_theta[items[b].run] / n_lists;
+    }
+    SweepPlan P;
+    for (int k = 0; k < 100; ++k, T *= 1.003) {
+        if (!wrap_around(items, n_lists, T, cost, run_theta, P)) continue;
+        items.swap(P.items);
+        lists.swap(P.lists);
+        cls.count = (int)items.size();
+        cls.nchunk = 2;
+        cls.n_lists = n_lists;
+        return true;
+    }
+    return false;
 }
 
 int expand_sweep_chunks(std::vector<SweepItem> &items, SweepClass &cls, int K, const std::vector<int> &run_theta)
@@ -3963,35 +4081,14 @@ int expand_sweep_chunks(std::vector<SweepItem> &items, SweepClass &cls, int K, c
     if (K <= 1 || cls.count == 0) return 0;
     if (K > MAX_SWEEP_CHUNKS || cls.first != 0 || cls.count != (int)items.size()) return -1;
     const int n = cls.count;
-    // Two chunks: the cut that the makespan above, at the largest theta of
-    // the list and about 0.6 sweeps per chunk, says ends the launch first
-    // (the first chunk at least half; the even cut on ties).  At L = 64,
-    // R = 1e5 (1563 items, 768 workgroups) that is 7 and 3 sweeps, measured
-    // 1.3 % faster than 5 and 5; for the two populations at L = 32 (3125
-    // items, 1280 workgroups) it is 5 and 5, where 8 and 2 measured 5 %
-    // slower.  More chunks: as even as possible, the larger first.
-    int theta_ref = 0;
-    for (const SweepItem &it : items) theta_ref = std::max(theta_ref, run_theta[it.run]);
-    int cut_ref = (theta_ref + 1) / 2;
-    if (K == 2 && theta_ref >= 2 && cls.grid > 0) {
-        double best = two_chunk_makespan(n, cls.grid, theta_ref, cut_ref, 0.6);
-        for (int a = cut_ref + 1; a < theta_ref; ++a) {
-            const double t = two_chunk_makespan(n, cls.grid, theta_ref, a, 0.6);
-            if (t < best - 1e-9) {
-                best = t;
-                cut_ref = a;
-            }
-        }
-    }
     std::vector<SweepItem> out((size_t)n * K);
     for (int c = 0; c < K; ++c)
         for (int b = 0; b < n; ++b) {
             SweepItem it = items[b];
-            const long theta = run_theta[it.run];
             it.chunk = c;
             it.nchunk = K;
             it.base = b;
-            it.cut = theta_ref > 0 ? (int)((theta * cut_ref + theta_ref / 2) / theta_ref) : 0;
+            it.cut = (run_theta[it.run] + 1) / 2;
             out[(size_t)c * n + b] = it;
         }
     items.swap(out);
@@ -4017,11 +4114,16 @@ int sweep_msc_resident(int threads, size_t lds, int L, int ea)
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, msc_kernel(L, ea), threads, lds) != hipSuccess)
         return 0;
+    return per_cu * device_cus();
+}
+
+int device_cus()
+{
     int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    return per_cu * cus;
+    return hipGetDevice(&dev) == hipSuccess &&
+                   hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess
+               ? cus
+               : 0;
 }
 
 hipError_t launch_dos_sample(const LaunchCtx &c)

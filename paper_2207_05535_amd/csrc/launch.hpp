@@ -18,6 +18,8 @@ struct SweepClass {
     int grid;           // > 0: persistent grid of this many workgroups
     size_t lds;
     int nchunk = 1;     // > 1: items split into this many chunks of sweeps (persistent grid only)
+    SweepList *lists = nullptr;   // persistent grid: a list of items per CU (n_lists of them), or
+    int n_lists = 0;              // one list for all (0)
 };
 constexpr int MAX_SWEEP_CLASSES = 16;
 
@@ -97,10 +99,15 @@ bool sweep_class_grids(SweepClass *cls, int n, int threads, bool persistent);
 // resident workgroups: 1 when every item gets a workgroup at once, else the
 // count that least quantises the launch into rounds.
 int sweep_chunks_auto(int n, int slots);
+int device_cus();   // of the current device, 0 on error
 // Replaces the (single) class's items by K chunks of each, all first chunks
 // first, with the sweeps of each chunk (run_theta[r]: run r's theta); 0 on
 // success, -1 if the class does not cover the whole list.
 int expand_sweep_chunks(std::vector<SweepItem> &items, SweepClass &cls, int K, const std::vector<int> &run_theta);
+// Replaces them by n_lists lists of equal work, items cut in two where one
+// list goes over into the next; false (nothing changed) where that cannot be.
+bool sweep_lists(std::vector<SweepItem> &items, SweepClass &cls, int n_lists, const std::vector<int> &run_theta,
+                 const std::vector<int> &run_L, std::vector<SweepList> &lists);
 hipError_t prepare_wang_lds(size_t bytes);
 hipError_t launch_philox_rate(int calls, hipStream_t s, int *blocks, int *threads);
 

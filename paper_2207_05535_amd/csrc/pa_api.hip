@@ -752,6 +752,7 @@ pa_status upload_sweep_plan(pa_ctx *c)
     const int threads = packed ? c->sweep_threads : c->bytes_threads, dense = packed ? c->sweep_dense : 3;
     const bool pooled = packed && c->sweep_pooled;
     SweepClass cls[MAX_SWEEP_CLASSES];
+    std::vector<SweepList> lists;   // kept until the copies are done
     if (prepare_msc_lds(lds) != hipSuccess) return dev_fail(c);
     const int ncls = sweep_classes(items, run_L, run_ea, cls, threads, dense | (pooled ? 1 << 8 : 0), true);
     if (ncls < 0) return PA_ERR_ARG;
@@ -760,7 +761,18 @@ pa_status upload_sweep_plan(pa_ctx *c)
         const int K = c->sweep_chunks > 0 ? c->sweep_chunks : sweep_chunks_auto(cls[0].count, cls[0].grid);
         std::vector<int> run_theta(c->n_runs);
         for (int r = 0; r < c->n_runs; ++r) run_theta[r] = std::max(0, c->descs[r].theta);
-        if (expand_sweep_chunks(items, cls[0], K, run_theta) != 0) return PA_ERR_ARG;
+        // the lists stand behind the items, in the room of chunks not made
+        const int cus = device_cus();
+        const size_t room = sizeof(SweepItem) * (size_t)c->lo.n_items * MAX_SWEEP_CHUNKS;
+        const size_t behind = (sizeof(SweepItem) * (items.size() + cus) + 255) & ~(size_t)255;
+        if (K == 2 && behind + sizeof(SweepList) * cus <= room &&
+            sweep_lists(items, cls[0], cus, run_theta, run_L, lists)) {
+            cls[0].lists = at<SweepList>(c, c->lo.sweep_items + behind);
+            PA_HIP(c, hipMemcpyAsync(cls[0].lists, lists.data(), sizeof(SweepList) * lists.size(),
+                                     hipMemcpyHostToDevice, c->stream));
+        } else if (expand_sweep_chunks(items, cls[0], K, run_theta) != 0) {
+            return PA_ERR_ARG;
+        }
     }
     if (!items.empty())
         PA_HIP(c, hipMemcpyAsync(at<SweepItem>(c, c->lo.sweep_items), items.data(),

@@ -135,6 +135,11 @@ struct SweepItem {    // groups [group0, group0 + ngroups) of one (run, pop), on
 };
 constexpr int MAX_SWEEP_CHUNKS = 4;
 
+struct SweepList {    // items [first, end) of a CU's workgroups, the next one to be taken
+    uint32_t next, first, end;
+    uint32_t pad[29];   // a list to a cache line
+};
+
 // LDS of a batched-sweep workgroup holding `groups` replica groups of N
 // sites in nw wavefronts.  mode = lockstep calls | pooled << 8, as the sweep
 // is launched: the sparse rounds are streamed when they are not pooled, there

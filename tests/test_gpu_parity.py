@@ -644,6 +644,44 @@ def test_sweep_chunks_bit_exact_at_full_size(workload):
             ctx.close()
 
 
+@pytest.mark.parametrize("name,threads,runs", [
+    # items of several sizes, models and numbers of sweeps in the lists
+    ("mixed", 1024, [(L, m, 14000 + L, th) for L, m, th in
+                     ((8, W.FM, 1), (16, W.FM, 10), (24, W.FM, 3), (10, W.EA_PMJ, 2), (16, W.EA_PMJ, 7))]),
+    # one item more than the resident workgroups of 1024 threads, two per CU
+    ("one more", 1024, [(16, W.FM, 64 * 512 + 1, 3)]),
+    # two items to a list, no sweep to cut, and sweeps of half a list
+    ("no cut", 1024, [(8, W.FM, 64 * 700, 1)]),
+    ("two each", 1024, [(8, W.EA_PMJ, 64 * 515, 2)]),
+    # no room for the lists behind the items: chunks of one list
+    ("no room", 512, [(94, W.FM, 64 * 300, 3)])])
+def test_sweep_lists(name, threads, runs):
+    """The persistent grid's lists of items per CU (two chunks) give the
+    records, states and work counters of one workgroup per item, in graph
+    replays with eager steps between them."""
+    import hashlib
+    say(f"sweep lists: {name}")
+    descs = [W.run_desc(L, m, seed=W.RUN_SEED_BASE + 0x6B00 + L + m, disorder_seed=13, R=R, theta=th, K=7, beta_f=0.6)
+             for L, m, R, th in runs]
+    got = []
+    for lists in (0, 1):
+        ctx = pa.Context(descs, "msc")
+        for d in descs:
+            ctx.set_tuning(d["L"], threads, 1, 3)
+        ctx.set_persistent(lists)
+        ctx.set_sweep_chunks(2 if lists else 1)
+        assert ctx.sweep_chunks() == (2 if lists else 1)
+        ctx.run(1, 3)
+        ctx.step(3)
+        ctx.run(4, 7)
+        h = ctx.obs().tobytes()
+        for r in range(len(descs)):
+            h += b"".join(np.ascontiguousarray(a).tobytes() for a in ctx.state(r, 0))
+        got.append((hashlib.sha256(h).hexdigest(), tuple(int(x) for x in ctx.stats().values())))
+        ctx.close()
+    assert got[0] == got[1]
+
+
 def test_sweep_chunks_whole_schedule():
     """The headline workload over its whole schedule (199 steps, beta up to
     0.6) with the cache's three chunks of sweeps on the persistent grid
