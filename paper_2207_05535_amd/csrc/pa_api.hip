@@ -632,7 +632,12 @@ int groups_of_2048(int L)
 // R = 5e4 124 / 134; L = 8, R = 1e6 127 / 134 (2.5-8; one chunk measures 83,
 // 86, 142, 147 there); L = 16, R = 1e6 354 / 374; L = 32, R = 4e5 525 / 561
 // (30-50; two chunks measure 379 and 548).  Above 512 threads only
-// the single-chunk shapes gain (L = 64, R = 2000: 126 against 130).
+// the single-chunk shapes gain (L = 64, R = 2000: 126 against 130).  Several
+// sizes in one launch, up to a group of L = 64: 256 threads, 2048 units for
+// each size (step, ten +-J runs of five sizes 16 to 64 and R = 5e4: 1720 us
+// against 1952 with the heaviest size's shape for all; 1024 ferromagnets of
+// four sizes 8 to 32 1603
+// against 1617).
 void default_shape(const pa_run_desc *const *runs, int n, int *threads, std::map<int, int> &groups)
 {
     std::map<int, double> chunks;   // L -> chunks of 64 site words per half-sweep
@@ -645,13 +650,15 @@ void default_shape(const pa_run_desc *const *runs, int n, int *threads, std::map
     }
     constexpr double SIMDS = 1024.0;
     const int c = total < 2.0 * SIMDS ? 1 : (total < 12.0 * SIMDS ? 2 : 4);
-    const int aim = 64 * c * (c == 1 ? 1 : 4);   // units per workgroup
+    // several sizes with work for all SIMDs: one shape has to serve them all
+    const bool mixed = c == 4 && chunks.size() > 1 && chunks.rbegin()->first <= 64;
+    const int aim = mixed ? 2048 : 64 * c * (c == 1 ? 1 : 4);   // units per workgroup
     int heavy = 0;
     double most = -1.0;
     groups.clear();
     for (const auto &kv : chunks) {
         const int nh = kv.first * kv.first / 2;
-        groups[kv.first] = std::max(1, std::min(256, aim / nh));
+        groups[kv.first] = std::max(1, std::min(256, (aim + (mixed ? nh / 2 : 0)) / nh));
         if (kv.second > most) {
             most = kv.second;
             heavy = kv.first;
@@ -661,7 +668,7 @@ void default_shape(const pa_run_desc *const *runs, int n, int *threads, std::map
     int t = 64;
     while (t < 64 * waves && t < (c == 1 ? 1024 : 512)) t *= 2;
     if (c > 1 && t > 64 && 3 * t > 4 * 64 * waves) t /= 2;   // nearer the power of two below
-    *threads = t;
+    *threads = mixed ? 256 : t;
 }
 
 pa_status dev_fail(pa_ctx *c, hipError_t e)

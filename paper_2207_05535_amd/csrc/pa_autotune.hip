@@ -345,14 +345,15 @@ extern "C" pa_status pa_autotune(pa_ctx *c, int32_t steps, const char *cache_pat
         }
     }
 
-    // chunks of sweeps on the persistent grid (they take effect only where
-    // the items outnumber the resident workgroups)
-    if (best.persistent)
-        for (int k = 2; k <= MAX_SWEEP_CHUNKS; ++k) {
-            Shape s = best;
-            s.chunks = k;
-            if ((st = consider(s)) != PA_OK) return st;
-        }
+    // chunks of sweeps on the persistent grid, also where whole items are
+    // better off without it (they take effect only where the items outnumber
+    // the resident workgroups)
+    for (int k = 2; k <= MAX_SWEEP_CHUNKS; ++k) {
+        Shape s = best;
+        s.persistent = 1;
+        s.chunks = k;
+        if ((st = consider(s)) != PA_OK) return st;
+    }
 
     // leave the context where it started, with the chosen shape
     (void)apply_shape(c, best);
