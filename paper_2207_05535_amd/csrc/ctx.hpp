@@ -82,6 +82,7 @@ inline int n_meas_items_of(const pa_run_desc &d)
     const int gpw = MEAS_WAVES / meas_waves_per_group(d.L * d.L);
     return (groups_cap_of(d) + gpw - 1) / gpw;
 }
+int copy_split_of(const pa_run_desc *const *runs, int n);   // copy workgroups per measure item
 int groups_of_2048(int L);   // replica groups whose colours hold about 2048 site words
 // Launch shape of the batched sweep for these runs where nobody has chosen
 // one: threads per workgroup and replica groups per workgroup of each L.

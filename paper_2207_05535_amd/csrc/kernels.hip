@@ -2253,9 +2253,10 @@ __device__ __forceinline__ const uint8_t *spin_buf(const RunInfo &R, const PopSt
 }
 
 // Measurement of replica groups (64 replicas each).  A workgroup of
-// MEAS_WAVES wavefronts takes a measure item of consecutive groups of one
-// (run, pop); each group gets meas_waves_per_group(N) wavefronts, which
-// split its sites 64 at a time.  A lane accumulates, in bit-sliced
+// W (MEAS_WAVES or four times as many) wavefronts takes a measure item of
+// consecutive groups of one (run, pop); each group gets
+// meas_waves_per_group(N) wavefronts (or four times that), which split its
+// sites 64 at a time.  A lane accumulates, in bit-sliced
 // counters over its sites, the per-replica numbers of unsatisfied bonds
 // (E = 2 #unsat - 2N), down spins (M = N - 2 #down), and for overlap pairs
 // the Hamming distance (Q = N - 2 d) and the number of bonds whose product
@@ -2265,10 +2266,10 @@ __device__ __forceinline__ const uint8_t *spin_buf(const RunInfo &R, const PopSt
 // transposes, the wavefronts of a group are summed in LDS, the energies are
 // stored, and the group's integer sums go to its slot of the partial-sum
 // array; k_meas_chunk reduces those per chunk.
-template <int REPR, int LT, bool WITH_Q>
+template <int REPR, int LT, bool WITH_Q, int W>
 __device__ __forceinline__ void measure_group(const SweepItem &it, int g, int sub, int wpg, bool live,
                                               const RunInfo &R, const PopState &S, const PopState *st,
-                                              uint32_t (*red)[MEAS_WAVES][64], const uint64_t *lw)
+                                              uint32_t (*red)[W][64], const uint64_t *lw)
 {
     const uint8_t *buf = spin_buf<REPR>(R, S, it.pop);
     // the group's own words come from LDS when the workgroup staged them
@@ -2496,17 +2497,16 @@ __device__ __forceinline__ void measure_group(const SweepItem &it, int g, int su
     }
 }
 
-template <int REPR, bool WITH_Q>
-__global__ void __launch_bounds__(MEAS_THREADS) k_measure(const SweepItem *items, const RunInfo *runs,
-                                                          const PopState *st)
+template <int REPR, bool WITH_Q, int W>
+__global__ void __launch_bounds__(64 * W) k_measure(const SweepItem *items, const RunInfo *runs, const PopState *st)
 {
-    __shared__ uint32_t red[4][MEAS_WAVES][64];
+    __shared__ uint32_t red[4][W][64];
     extern __shared__ uint64_t words[];   // [groups of the item][N] when staged
     const SweepItem it = items[blockIdx.x];
     const RunInfo &R = runs[it.run];
     const PopState &S = st[it.run * MAX_POP + it.pop];
     if (!pop_active(S) || words_current(R, S) != (REPR == PA_MSC64)) return;
-    const int wpg = meas_waves_per_group(R.N);
+    const int wpg = meas_waves_per_group(R.N) * (W / MEAS_WAVES);
     const int wv = wave_id();
     const int k = wv / wpg, sub = wv - k * wpg;
     const int g = it.group0 + k;
@@ -2532,13 +2532,13 @@ __global__ void __launch_bounds__(MEAS_THREADS) k_measure(const SweepItem *items
         lw = mine;
     }
     switch (R.L) {
-    case 8: measure_group<REPR, 8, WITH_Q>(it, g, sub, wpg, live, R, S, st, red, lw); break;
-    case 16: measure_group<REPR, 16, WITH_Q>(it, g, sub, wpg, live, R, S, st, red, lw); break;
-    case 24: measure_group<REPR, 24, WITH_Q>(it, g, sub, wpg, live, R, S, st, red, lw); break;
-    case 32: measure_group<REPR, 32, WITH_Q>(it, g, sub, wpg, live, R, S, st, red, lw); break;
-    case 48: measure_group<REPR, 48, WITH_Q>(it, g, sub, wpg, live, R, S, st, red, lw); break;
-    case 64: measure_group<REPR, 64, WITH_Q>(it, g, sub, wpg, live, R, S, st, red, lw); break;
-    default: measure_group<REPR, 0, WITH_Q>(it, g, sub, wpg, live, R, S, st, red, lw); break;
+    case 8: measure_group<REPR, 8, WITH_Q, W>(it, g, sub, wpg, live, R, S, st, red, lw); break;
+    case 16: measure_group<REPR, 16, WITH_Q, W>(it, g, sub, wpg, live, R, S, st, red, lw); break;
+    case 24: measure_group<REPR, 24, WITH_Q, W>(it, g, sub, wpg, live, R, S, st, red, lw); break;
+    case 32: measure_group<REPR, 32, WITH_Q, W>(it, g, sub, wpg, live, R, S, st, red, lw); break;
+    case 48: measure_group<REPR, 48, WITH_Q, W>(it, g, sub, wpg, live, R, S, st, red, lw); break;
+    case 64: measure_group<REPR, 64, WITH_Q, W>(it, g, sub, wpg, live, R, S, st, red, lw); break;
+    default: measure_group<REPR, 0, WITH_Q, W>(it, g, sub, wpg, live, R, S, st, red, lw); break;
     }
 }
 
@@ -4159,15 +4159,24 @@ hipError_t launch_measure(const LaunchCtx &c, bool first)
         // swept runs are measured from their words, the others from bytes
         const bool words = c.repr == PA_MSC64 || (!first && c.any_swept);
         const bool bytes = c.repr == PA_INT8 && (first || c.any_unswept);
-        if (words && c.any_overlap)
-            k_measure<PA_MSC64, true><<<c.n_meas_items, MEAS_THREADS, 0, c.stream>>>(c.meas_items, c.runs, c.st);
+        // With overlaps four times the wavefronts per group where a wavefront
+        // per SIMD would be left over (us, L = 128, R = 2000 97 / 41; L = 20,
+        // R = 5003 18.7 / 14.9; L = 16, R = 2000 13.1 / 10.5).  Without, the
+        // larger workgroups' start costs more (L = 8, R = 1000 7.3 / 10.8;
+        // L = 16, R = 2e4 8.7 / 12.4), and on bytes they spill registers.
+        constexpr int W = MEAS_WAVES;
+        const bool few = c.n_meas_items * W <= 1024;
+        if (words && c.any_overlap && few)
+            k_measure<PA_MSC64, true, 4 * W><<<c.n_meas_items, 256 * W, 0, c.stream>>>(c.meas_items, c.runs, c.st);
+        else if (words && c.any_overlap)
+            k_measure<PA_MSC64, true, W><<<c.n_meas_items, 64 * W, 0, c.stream>>>(c.meas_items, c.runs, c.st);
         else if (words)
-            k_measure<PA_MSC64, false><<<c.n_meas_items, MEAS_THREADS, 0, c.stream>>>(c.meas_items, c.runs, c.st);
+            k_measure<PA_MSC64, false, W><<<c.n_meas_items, 64 * W, 0, c.stream>>>(c.meas_items, c.runs, c.st);
         PA_CHECK_LAUNCH();
         if (bytes && c.any_overlap)
-            k_measure<PA_INT8, true><<<c.n_meas_items, MEAS_THREADS, MEAS_STAGE_BYTES, c.stream>>>(c.meas_items, c.runs, c.st);
+            k_measure<PA_INT8, true, W><<<c.n_meas_items, 64 * W, MEAS_STAGE_BYTES, c.stream>>>(c.meas_items, c.runs, c.st);
         else if (bytes)
-            k_measure<PA_INT8, false><<<c.n_meas_items, MEAS_THREADS, MEAS_STAGE_BYTES, c.stream>>>(c.meas_items, c.runs, c.st);
+            k_measure<PA_INT8, false, W><<<c.n_meas_items, 64 * W, MEAS_STAGE_BYTES, c.stream>>>(c.meas_items, c.runs, c.st);
         PA_CHECK_LAUNCH();
     }
     k_meas_chunk<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);

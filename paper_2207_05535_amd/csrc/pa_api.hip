@@ -600,6 +600,24 @@ void meas_items_of(const pa_run_desc &d, int run, int pop, std::vector<SweepItem
     for (int g = 0; g < groups_cap_of(d); g += gpw) out.push_back({run, pop, g, std::min(gpw, groups_cap_of(d) - g)});
 }
 
+// About four 64-site blocks per copy wavefront, set by the smallest lattice
+// (L = 64: 40 -> 35 us per copy at R = 1e5 against one workgroup per item);
+// fewer, down to one, where that leaves the chip without wavefronts: up to
+// 16384 (int8, unsplit / 4096 / 16384 / 32768: L = 128, R = 2000 82 / 22 / 21 /
+// 21 us, L = 64, R = 2e4 49 / 49 / 38 / 39; L = 20, R = 5003, bit-packed
+// 9.6 / 4.9 / 4.9 / 4.9; 3840 runs of L = 10, R = 100 11 / 11 / 11 / 16).
+int copy_split_of(const pa_run_desc *const *runs, int n)
+{
+    long waves = 0, blocks = 1 << 20;   // wavefronts unsplit; blocks of the one with fewest
+    for (int r = 0; r < n; ++r) {
+        const int N = runs[r]->L * runs[r]->L;
+        waves += (long)n_pop_of(runs[r]->overlap) * n_meas_items_of(*runs[r]) * MEAS_WAVES;
+        blocks = std::min(blocks, (long)((N + 63) / 64) / meas_waves_per_group(N));
+    }
+    if (waves == 0) return 1;
+    return (int)std::max(1l, std::max(std::min(4l, blocks / 4), std::min(blocks, 16384 / waves)));
+}
+
 size_t wang_lds_of(const pa_run_desc *const *runs, int n, int lds_limit, bool *large)
 {
     size_t best = 0;
@@ -951,14 +969,10 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
     c->lc.any_nearest = false;
     c->lc.any_overlap = false;
     c->lc.any_swept = c->lc.any_unswept = false;
-    // copy workgroups per item: each wavefront keeps about four 64-site blocks
-    // of its group (L = 64: 40 -> 35 us per copy at R = 1e5 against one
-    // workgroup per item); set by the smallest lattice of the context
-    int min_n = 1 << 30;
-    for (int r = 0; r < n_runs; ++r) min_n = std::min(min_n, runs[r].L * runs[r].L);
     {
-        const int blocks_per_wave = (min_n / 64) / meas_waves_per_group(min_n);
-        c->lc.copy_split = std::max(1, std::min(4, blocks_per_wave / 4));
+        std::vector<const pa_run_desc *> dp(n_runs);
+        for (int r = 0; r < n_runs; ++r) dp[r] = &runs[r];
+        c->lc.copy_split = copy_split_of(dp.data(), n_runs);
     }
     for (int r = 0; r < n_runs; ++r) {
         if (runs[r].resampling == PA_NEAREST_INT) c->lc.any_nearest = true;

@@ -363,13 +363,13 @@ pa_status rebuild(pa_server *s)
     c.any_chained = chained;
     c.fused_max = fused_max;
     if (prepare_fused_lds(fused_lds(fused_max, mn)) != hipSuccess) return sfail(s);
-    c.copy_split = 1;   // requests of any size share the copy launch
     c.any_overlap = ovl;
     c.any_wang = wang;
     {
         std::vector<const pa_run_desc *> dp;
         for (int k = 0; k < s->max_slots; ++k)
             if (s->slots[k].used) dp.push_back(&s->slots[k].d);
+        c.copy_split = copy_split_of(dp.data(), (int)dp.size());
         c.wang_lds = wang_lds_of(dp.data(), (int)dp.size(), s->lds_limit, &c.wang_large);
         if (prepare_wang_lds(c.wang_lds) != hipSuccess) return sfail(s);
     }

@@ -644,6 +644,26 @@ def test_sweep_chunks_bit_exact_at_full_size(workload):
             ctx.close()
 
 
+@pytest.mark.parametrize("repr_", REPRS)
+@pytest.mark.parametrize("L,R,overlap", [(4, 70, W.Q_INDEX_SHIFT), (18, 1000, W.Q_TWO_POP), (32, 129, W.Q_INDEX_SHIFT),
+                                         (34, 65, W.Q_TWO_POP), (46, 130, W.Q_INDEX_SHIFT), (66, 200, W.Q_TWO_POP)])
+def test_few_groups(repr_, L, R, overlap):
+    """Few replica groups of small and large lattices: copies split over more
+    workgroups and overlaps measured by more wavefronts per group, with group
+    and wavefront remainders, equal the oracle's records and states."""
+    say(f"few groups {repr_} L={L} R={R} overlap={overlap}")
+    d = W.run_desc(L, W.EA_PMJ, seed=W.RUN_SEED_BASE + 0x6C00 + L, disorder_seed=14, R=R, theta=1, K=5, beta_f=1.0,
+                   resampling=W.NEAREST_INT, overlap=overlap, qhist=1)
+    orc = oracle.OracleRun(d).run_all()
+    ctx = pa.Context([d], repr_)
+    ctx.run(1, 5)
+    assert_obs_equal(ctx.obs()[0, :orc.npop], orc.obs(), "records")
+    assert np.array_equal(ctx.qhist(0), orc.qhist())
+    for p in range(orc.npop):
+        assert np.array_equal(ctx.state(0, p)[0], orc.state(p)[0]), p
+    ctx.close()
+
+
 @pytest.mark.parametrize("name,threads,runs", [
     # items of several sizes, models and numbers of sweeps in the lists
     ("mixed", 1024, [(L, m, 14000 + L, th) for L, m, th in
