@@ -3487,122 +3487,197 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_logw(const RunInfo *runs, cons
     }
 }
 
-// One thread per (group of M runs, temperature i): weights w = softmax of
+// Per (group of M runs, temperature i): weights w = softmax of
 // the log weights over the included runs; configurational averages; the
 // weighted variance estimators through the Eq. (Wvar_bound) identity; the
 // sample variance of w and its log-normal prediction; and ln W[Q_i] with
 // the weights of temperature i-1 renormalised over the runs included at i
 // (stored in minus_beta_WF, summed over i by k_wavg_cumsum).
-__global__ void k_wavg(const RunInfo *runs, const pa_obs *obs, const double *logw, const double *qw, int n_runs,
-                       int npop_ctx, int pop, int M, int K, pa_wavg *out)
-{
-    const int gi = blockIdx.x * blockDim.x + threadIdx.x;
-    const int ngroups = n_runs / M;
-    if (gi >= ngroups * K) return;
-    const int grp = gi / K, i = gi - grp * K;
-    const int N = runs[grp * M].N;
-    const double b = runs[grp * M].beta[i];
-    pa_wavg w = {};
-    double amax = -INFINITY;
-    int n = 0;
-    for (int m = 0; m < M; ++m) {
-        const double a = logw[(size_t)(grp * M + m) * K + i];
-        if (!isnan(a)) {
-            amax = fmax(amax, a);
-            ++n;
+// T = 1: a thread per (group, temperature) goes through the group's M runs;
+// T = 64: a wavefront does, a run to a lane, and adds the runs' terms in the
+// same order, one sum to a lane, from LDS (in one thread a long group is a
+// chain of loads and divisions: a weighted average of 256 runs at 89
+// temperatures 867 -> 82 us with the copy of its result).
+template <int T>
+struct GroupSums {
+    static constexpr int MOST = 10;
+    double *lds;   // T = 64: MOST rows of 65 of this wavefront
+
+    // out[s] = the sum of t[s] over the runs m for which f(m, t) is true
+    template <int NS, typename F>
+    __device__ __forceinline__ void add(int M, double (&out)[NS], F f) const
+    {
+        static_assert(NS <= MOST, "");
+        const int lane = threadIdx.x & (T - 1);
+        double acc = 0.0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) out[s] = 0.0;
+        for (int m0 = 0; m0 < M; m0 += T) {
+            double t[NS] = {};
+            const bool in = m0 + lane < M && f(m0 + lane, t);
+            if (T == 1) {
+#pragma unroll
+                for (int s = 0; s < NS; ++s) out[s] = in ? out[s] + t[s] : out[s];
+                continue;
+            }
+            // a run left out adds zero, which changes no sum (none is -0)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) lds[s * 65 + lane] = in ? t[s] : 0.0;
+            sync();
+            if (lane < NS)
+                for (int q = 0; q < min(T, M - m0); ++q) acc += lds[lane * 65 + q];
+            sync();
+        }
+        if (T > 1) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) out[s] = __shfl(acc, s, 64);
         }
     }
+    // the largest f(m), NaN left out, and how many there are
+    template <typename F>
+    __device__ __forceinline__ double largest(int M, int *count, F f) const
+    {
+        const int lane = threadIdx.x & (T - 1);
+        double mx = -INFINITY;
+        int n = 0;
+        for (int m = lane; m < M; m += T) {
+            const double a = f(m);
+            if (isnan(a)) continue;
+            mx = fmax(mx, a);
+            ++n;
+        }
+        if (T > 1) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                mx = fmax(mx, __shfl_xor(mx, o, 64));
+                n += __shfl_xor(n, o, 64);
+            }
+        }
+        *count = n;
+        return mx;
+    }
+
+private:
+    static __device__ __forceinline__ void sync()
+    {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+};
+constexpr int GROUP_THREADS = 128;
+
+template <int T>
+__global__ void __launch_bounds__(GROUP_THREADS) k_wavg(const RunInfo *runs, const pa_obs *obs, const double *logw,
+                                                        const double *qw, int n_runs, int npop_ctx, int pop, int M,
+                                                        int K, pa_wavg *out)
+{
+    __shared__ double lds[T > 1 ? GROUP_THREADS / 64 : 1][T > 1 ? GroupSums<T>::MOST * 65 : 1];
+    const int gi = (blockIdx.x * blockDim.x + threadIdx.x) / T;
+    const int ngroups = n_runs / M;
+    if (gi >= ngroups * K) return;
+    const GroupSums<T> sums = {lds[T > 1 ? threadIdx.x >> 6 : 0]};
+    const bool writes = (threadIdx.x & (T - 1)) == 0;
+    const int grp = gi / K, i = gi - grp * K, run0 = grp * M;
+    const int N = runs[run0].N;
+    const double b = runs[run0].beta[i];
+    auto lw = [&](int m) { return logw[(size_t)(run0 + m) * K + i]; };
+    auto rec = [&](int m) -> const pa_obs & { return obs[((size_t)i * n_runs + run0 + m) * npop_ctx + pop]; };
+    pa_wavg w = {};
+    int n = 0;
+    const double amax = sums.largest(M, &n, lw);
     w.n_included = n;
     if (n == 0) {
         const double nan = NAN;
         w.W_e = w.W_e2 = w.Wvar_c = w.Wconf_c = w.W_m = w.W_m2 = nan;
         w.Wvar_chi = w.Wconf_chi = w.W_absq = w.W_q2 = w.W_ql = nan;
         w.minus_beta_WF = w.var_w = w.var_w_pred = nan;
-        out[(size_t)grp * K + i] = w;
+        if (writes) out[(size_t)grp * K + i] = w;
         return;
     }
-    double Z = 0.0;
-    for (int m = 0; m < M; ++m) {
-        const double a = logw[(size_t)(grp * M + m) * K + i];
-        if (!isnan(a)) Z += exp(a - amax);
-    }
+    double z[1];
+    sums.add(M, z, [&](int m, double *t) {
+        const double a = lw(m);
+        t[0] = exp(a - amax);
+        return !isnan(a);
+    });
+    const double Z = z[0];
     const double dN = (double)N;
-    double sumA = 0.0;
-    for (int m = 0; m < M; ++m) {
-        const int run = grp * M + m;
-        const double a = logw[(size_t)run * K + i];
-        if (isnan(a)) continue;
-        const pa_obs &o = obs[((size_t)i * n_runs + run) * npop_ctx + pop];
+    double f[10];
+    sums.add(M, f, [&](int m, double *t) {
+        const double a = lw(m);
+        if (isnan(a)) return false;
+        const pa_obs &o = rec(m);
         const double wm = exp(a - amax) / Z;
         const double Ri = (double)o.R_i;
         const __int128 vE = (__int128)o.R_i * o.sumE2 - (__int128)o.sumE * o.sumE;
         const __int128 vM = (__int128)o.R_i * o.sumM2 - (__int128)o.sumAbsM * o.sumAbsM;
-        w.W_e += wm * ((double)o.sumE / (dN * Ri));
-        w.W_e2 += wm * ((double)o.sumE2 / (dN * dN * Ri));
-        w.Wconf_c += wm * (b * b * (double)vE / (dN * Ri * Ri));
-        w.W_m += wm * ((double)o.sumAbsM / (dN * Ri));
-        w.W_m2 += wm * ((double)o.sumM2 / (dN * dN * Ri));
-        w.Wconf_chi += wm * (b * (double)vM / (dN * Ri * Ri));
-        const double wq = qw[(size_t)run * K + i];   // overlap weights (exclusion applied)
+        t[0] = wm * ((double)o.sumE / (dN * Ri));
+        t[1] = wm * ((double)o.sumE2 / (dN * dN * Ri));
+        t[2] = wm * (b * b * (double)vE / (dN * Ri * Ri));
+        t[3] = wm * ((double)o.sumAbsM / (dN * Ri));
+        t[4] = wm * ((double)o.sumM2 / (dN * dN * Ri));
+        t[5] = wm * (b * (double)vM / (dN * Ri * Ri));
+        const double wq = qw[(size_t)(run0 + m) * K + i];   // overlap weights (exclusion applied)
         if (o.nPairs > 0 && !isnan(wq)) {
             const double np = (double)o.nPairs;
-            w.W_absq += wq * ((double)o.sumAbsQ / (dN * np));
-            w.W_q2 += wq * ((double)o.sumQ2 / (dN * dN * np));
-            w.W_ql += wq * ((double)o.sumQl / (2.0 * dN * np));
+            t[6] = wq * ((double)o.sumAbsQ / (dN * np));
+            t[7] = wq * ((double)o.sumQ2 / (dN * dN * np));
+            t[8] = wq * ((double)o.sumQl / (2.0 * dN * np));
         }
-        sumA += o.A;
-    }
-    if (isnan(qw[(size_t)(grp * M) * K + i])) w.W_absq = w.W_q2 = w.W_ql = NAN;
-    const double meanA = sumA / n;
-    double se = 0.0, sm = 0.0, vw = 0.0, va = 0.0;
-    for (int m = 0; m < M; ++m) {
-        const int run = grp * M + m;
-        const double a = logw[(size_t)run * K + i];
-        if (isnan(a)) continue;
-        const pa_obs &o = obs[((size_t)i * n_runs + run) * npop_ctx + pop];
+        t[9] = o.A;
+        return true;
+    });
+    w.W_e = f[0];
+    w.W_e2 = f[1];
+    w.Wconf_c = f[2];
+    w.W_m = f[3];
+    w.W_m2 = f[4];
+    w.Wconf_chi = f[5];
+    w.W_absq = f[6];
+    w.W_q2 = f[7];
+    w.W_ql = f[8];
+    if (isnan(qw[(size_t)run0 * K + i])) w.W_absq = w.W_q2 = w.W_ql = NAN;
+    const double meanA = f[9] / n;
+    double v[4];
+    sums.add(M, v, [&](int m, double *t) {
+        const double a = lw(m);
+        if (isnan(a)) return false;
+        const pa_obs &o = rec(m);
         const double wm = exp(a - amax) / Z;
         const double Ri = (double)o.R_i;
         const double e = (double)o.sumE / (dN * Ri), mm = (double)o.sumAbsM / (dN * Ri);
-        se += wm * (e - w.W_e) * (e - w.W_e);
-        sm += wm * (mm - w.W_m) * (mm - w.W_m);
-        vw += (wm - 1.0 / n) * (wm - 1.0 / n);
-        va += (o.A - meanA) * (o.A - meanA);
-    }
-    w.Wvar_c = w.Wconf_c + b * b * dN * se;
-    w.Wvar_chi = w.Wconf_chi + b * dN * sm;
-    w.var_w = vw / n;
-    w.var_w_pred = (exp(va / n) - 1.0) / ((double)n * n);
+        t[0] = wm * (e - w.W_e) * (e - w.W_e);
+        t[1] = wm * (mm - w.W_m) * (mm - w.W_m);
+        t[2] = (wm - 1.0 / n) * (wm - 1.0 / n);
+        t[3] = (o.A - meanA) * (o.A - meanA);
+        return true;
+    });
+    w.Wvar_c = w.Wconf_c + b * b * dN * v[0];
+    w.Wvar_chi = w.Wconf_chi + b * dN * v[1];
+    w.var_w = v[2] / n;
+    w.var_w_pred = (exp(v[3] / n) - 1.0) / ((double)n * n);
     if (i == 0) {
         w.minus_beta_WF = NAN;
-        for (int m = 0; m < M; ++m) {
-            const int run = grp * M + m;
-            if (!isnan(logw[(size_t)run * K])) {
-                w.minus_beta_WF = obs[((size_t)0 * n_runs + run) * npop_ctx + pop].A;
+        for (int m = 0; m < M; ++m)
+            if (!isnan(lw(m))) {
+                w.minus_beta_WF = rec(m).A;
                 break;
             }
-        }
     } else {
-        double mx = -INFINITY, mx0 = -INFINITY;
-        for (int m = 0; m < M; ++m) {
-            const int run = grp * M + m;
-            if (isnan(logw[(size_t)run * K + i])) continue;
-            const double ap = logw[(size_t)run * K + i - 1];
-            const double lq = obs[((size_t)i * n_runs + run) * npop_ctx + pop].lnQ;
-            mx = fmax(mx, ap + lq);
-            mx0 = fmax(mx0, ap);
-        }
-        double s1 = 0.0, s0 = 0.0;
-        for (int m = 0; m < M; ++m) {
-            const int run = grp * M + m;
-            if (isnan(logw[(size_t)run * K + i])) continue;
-            const double ap = logw[(size_t)run * K + i - 1];
-            const double lq = obs[((size_t)i * n_runs + run) * npop_ctx + pop].lnQ;
-            s1 += exp(ap + lq - mx);
-            s0 += exp(ap - mx0);
-        }
-        w.minus_beta_WF = (mx + log(s1)) - (mx0 + log(s0));
+        auto before = [&](int m) { return logw[(size_t)(run0 + m) * K + i - 1]; };
+        int any;
+        const double mx = sums.largest(M, &any, [&](int m) { return isnan(lw(m)) ? NAN : before(m) + rec(m).lnQ; });
+        const double mx0 = sums.largest(M, &any, [&](int m) { return isnan(lw(m)) ? NAN : before(m); });
+        double s[2];
+        sums.add(M, s, [&](int m, double *t) {
+            if (isnan(lw(m))) return false;
+            t[0] = exp(before(m) + rec(m).lnQ - mx);
+            t[1] = exp(before(m) - mx0);
+            return true;
+        });
+        w.minus_beta_WF = (mx + log(s[0])) - (mx0 + log(s[1]));
     }
-    out[(size_t)grp * K + i] = w;
+    if (writes) out[(size_t)grp * K + i] = w;
 }
 
 // A family holds more than R_i / 2 replicas in run `run` at temperature i
@@ -3622,38 +3697,34 @@ __device__ __forceinline__ bool large_family(const RunInfo &R, const pa_obs *obs
 // normalised over the included runs of the group (with
 // PA_W_EXCLUDE_LARGE_FAMILY also leaving out runs with a family above
 // R_i / 2); 0 for a run left out, NaN for every run if none is left.
-__global__ void k_qweights(const RunInfo *runs, const pa_obs *obs, const double *logw, int n_runs, int npop_ctx,
-                           int pop, int M, int K, int flags, double *qw)
+template <int T>
+__global__ void __launch_bounds__(GROUP_THREADS) k_qweights(const RunInfo *runs, const pa_obs *obs,
+                                                            const double *logw, int n_runs, int npop_ctx, int pop,
+                                                            int M, int K, int flags, double *qw)
 {
-    const int gi = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ double lds[T > 1 ? GROUP_THREADS / 64 : 1][T > 1 ? GroupSums<T>::MOST * 65 : 1];
+    const int gi = (blockIdx.x * blockDim.x + threadIdx.x) / T;
     const int ngroups = n_runs / M;
     if (gi >= ngroups * K) return;
-    const int grp = gi / K, i = gi - grp * K;
+    const GroupSums<T> sums = {lds[T > 1 ? threadIdx.x >> 6 : 0]};
+    const int grp = gi / K, i = gi - grp * K, run0 = grp * M;
     const bool excl = flags & PA_W_EXCLUDE_LARGE_FAMILY;
-    double amax = -INFINITY;
+    auto lw = [&](int m) {
+        return excl && large_family(runs[run0 + m], obs, i, run0 + m, n_runs, npop_ctx, pop)
+                   ? NAN
+                   : logw[(size_t)(run0 + m) * K + i];
+    };
     int n = 0;
-    for (int m = 0; m < M; ++m) {
-        const int run = grp * M + m;
-        const double a = logw[(size_t)run * K + i];
-        if (isnan(a) || (excl && large_family(runs[run], obs, i, run, n_runs, npop_ctx, pop))) continue;
-        amax = fmax(amax, a);
-        ++n;
-    }
-    double Z = 0.0;
-    for (int m = 0; m < M; ++m) {
-        const int run = grp * M + m;
-        const double a = logw[(size_t)run * K + i];
-        if (isnan(a) || (excl && large_family(runs[run], obs, i, run, n_runs, npop_ctx, pop))) continue;
-        Z += exp(a - amax);
-    }
-    for (int m = 0; m < M; ++m) {
-        const int run = grp * M + m;
-        const double a = logw[(size_t)run * K + i];
-        double w = 0.0;
-        if (n == 0) w = NAN;
-        else if (!isnan(a) && !(excl && large_family(runs[run], obs, i, run, n_runs, npop_ctx, pop)))
-            w = exp(a - amax) / Z;
-        qw[(size_t)run * K + i] = w;
+    const double amax = sums.largest(M, &n, lw);
+    double Z[1];
+    sums.add(M, Z, [&](int m, double *t) {
+        const double a = lw(m);
+        t[0] = exp(a - amax);
+        return !isnan(a);
+    });
+    for (int m = threadIdx.x & (T - 1); m < M; m += T) {
+        const double a = lw(m);
+        qw[(size_t)(run0 + m) * K + i] = n == 0 ? NAN : (isnan(a) ? 0.0 : exp(a - amax) / Z[0]);
     }
 }
 
@@ -4226,14 +4297,25 @@ hipError_t launch_measure(const LaunchCtx &c, bool first)
     return hipGetLastError();
 }
 
+// A wavefront per (group, temperature) from this many runs a group (whole
+// calls, thread / wavefront: 16 groups of 16, 89 temperatures 172 / 121 us; 240
+// of 16, 61 temperatures 269 / 241; one of 16 92 / 48).
+constexpr int WIDE_GROUP = 16;
+static int group_blocks(int n, int M)
+{
+    const int per = M >= WIDE_GROUP ? GROUP_THREADS / 64 : GROUP_THREADS;
+    return (n + per - 1) / per;
+}
+
 hipError_t launch_qweights(const LaunchCtx &c, const pa_obs *obs, int M, int kind, int pop, int K, int i_done,
                            double *logw, double *qw)
 {
     k_logw<<<c.n_runs, SCAN_THREADS, 0, c.stream>>>(c.runs, obs, c.n_runs, c.npop_ctx, pop, kind, i_done, logw);
     PA_CHECK_LAUNCH();
     const int ng = c.n_runs / M;
-    k_qweights<<<(ng * K + 127) / 128, 128, 0, c.stream>>>(c.runs, obs, logw, c.n_runs, c.npop_ctx, pop, M, K,
-                                                          kind & ~1, qw);
+    auto kernel = M >= WIDE_GROUP ? k_qweights<64> : k_qweights<1>;
+    kernel<<<group_blocks(ng * K, M), GROUP_THREADS, 0, c.stream>>>(c.runs, obs, logw, c.n_runs, c.npop_ctx, pop, M,
+                                                                    K, kind & ~1, qw);
     return hipGetLastError();
 }
 
@@ -4258,8 +4340,9 @@ hipError_t launch_wavg(const LaunchCtx &c, const pa_obs *obs, int M, int kind, i
 {
     if (launch_qweights(c, obs, M, kind, pop, K, i_done, logw, qw) != hipSuccess) return hipGetLastError();
     const int ng = c.n_runs / M;
-    k_wavg<<<(ng * K + 127) / 128, 128, 0, c.stream>>>(c.runs, obs, logw, qw, c.n_runs, c.npop_ctx, pop, M, K,
-                                                      out);
+    auto kernel = M >= WIDE_GROUP ? k_wavg<64> : k_wavg<1>;
+    kernel<<<group_blocks(ng * K, M), GROUP_THREADS, 0, c.stream>>>(c.runs, obs, logw, qw, c.n_runs, c.npop_ctx, pop,
+                                                                    M, K, out);
     PA_CHECK_LAUNCH();
     k_wavg_cumsum<<<ng, SCAN_THREADS, 0, c.stream>>>(out, ng, K);
     return hipGetLastError();

@@ -347,6 +347,34 @@ def test_weighted_average_parity_at_benchmark_groupings(M):
     ctx.close()
 
 
+@pytest.mark.parametrize("M", [1, 15, 16, 63, 65])
+def test_weighted_average_group_sizes(M):
+    """Groups at the edges of a thread and a wavefront per group, with runs
+    that leave the averages (their populations outgrow the capacity) and, at
+    low temperatures, overlap weights without runs of a large family: versus
+    the oracle, every weight kind."""
+    say(f"weighted averages, groups of {M}")
+    runs = [W.run_desc(4, W.EA_PMJ, seed=0x3B00 + m, disorder_seed=3, R=60, theta=1, K=8, beta_f=1.6,
+                       R_cap=64 if m % 5 == 1 else 150, resampling=W.NEAREST_INT, overlap=W.Q_INDEX_SHIFT)
+            for m in range(2 * M)]
+    ctx = pa.Context(runs, "msc")
+    ctx.run(1, 8)
+    obs = ctx.obs()[:, 0, :]
+    Rs = np.array([d["R"] for d in runs], np.int32)
+    for kind in range(4):
+        got = ctx.weighted_average(M, kind, 0)
+        for grp in range(2):
+            sl = slice(grp * M, (grp + 1) * M)
+            ref = oracle.weighted_average(obs[sl], runs[0]["beta"], 16, Rs[sl], kind)
+            assert np.array_equal(got[grp]["n_included"], ref["n_included"])
+            for f in pa.PA_WAVG_DTYPE.names:
+                if f not in ("n_included", "_pad"):
+                    a, b = got[grp][f], ref[f]
+                    assert np.array_equal(np.isnan(a), np.isnan(b)), (kind, grp, f)
+                    assert close(np.nan_to_num(a), np.nan_to_num(b)), (kind, grp, f, a, b)
+    ctx.close()
+
+
 @pytest.mark.parametrize("overlap", [W.Q_INDEX_SHIFT, W.Q_TWO_POP])
 def test_weighted_overlap_distribution_and_family_stats_parity(overlap):
     """Eq. (W_conf_q) on the device, with every weight kind and the
