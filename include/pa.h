@@ -325,8 +325,8 @@ pa_status pa_set_persistent(pa_ctx *ctx, int32_t on);
  * on S resident workgroups, with every item taking about the same time, lasts
  * about ceil(n K / S) / K item times instead of ceil(n / S), at the cost of
  * loading and storing each lattice K - 1 more times.  1 <= chunks <= 4 fixes K
- * (default 1; pa_autotune searches it); chunks = 0 chooses K per plan from
- * that estimate.  Chunks apply only where the persistent grid is used
+ * (default 1; pa_autotune searches it); chunks = 0 leaves it to the library
+ * (2).  Chunks apply only where the persistent grid is used
  * (pa_set_persistent, and more items than resident workgroups).  Results
  * never depend on it.  PA_ERR_ARG outside 0..4, PA_ERR_STATE between the
  * calls of a temperature step. */

@@ -3997,7 +3997,7 @@ hipError_t launch_sweep_msc(const LaunchCtx &c)
         const SweepClass &q = c.sweep_cls[k];
         if (q.count == 0) continue;
         const bool persistent = q.grid > 0 && q.grid < q.count;
-        // chunked items wait on one another, which only the ticket order of
+        // chunked items wait on one another, which only the list order of
         // the persistent grid makes safe
         if (q.nchunk > 1 && !persistent) return hipErrorInvalidConfiguration;
         const int grid = persistent ? q.grid : q.count;
@@ -4086,26 +4086,6 @@ int sweep_classes(std::vector<SweepItem> &items, const std::vector<int> &run_L, 
     C.lds = 0;
     for (const SweepItem &it : items) C.lds = std::max(C.lds, lds_of(it));
     return 1;
-}
-
-int sweep_chunks_auto(int n, int slots)
-{
-    // makespan in units of one whole item when every item takes the same
-    // time: ceil(n K / slots) rounds of 1/K each, plus a cost per extra
-    // chunk (loading and storing the lattices once more, a wait on the
-    // previous chunk, the chunk's own partial last rounds), measured at
-    // about a fifth of an item at L = 64 with three workgroups per CU
-    if (slots <= 0 || n <= slots) return 1;
-    int best = 1;
-    double best_t = 1e300;
-    for (int K = 1; K <= MAX_SWEEP_CHUNKS; ++K) {
-        const double t = (double)((n * (long)K + slots - 1) / slots) / K + 0.2 * (K - 1);
-        if (t < best_t - 1e-9) {
-            best_t = t;
-            best = K;
-        }
-    }
-    return best;
 }
 
 // Two chunks: a list of items per CU, and only what has to be cut is.  The

@@ -95,10 +95,6 @@ int sweep_classes(std::vector<SweepItem> &items, const std::vector<int> &run_L, 
                   SweepClass *cls, int threads, int mode, bool split_ok);
 // Persistent grids of the classes (threads per workgroup as launched).
 bool sweep_class_grids(SweepClass *cls, int n, int threads, bool persistent);
-// Chunks of sweeps per item for a persistent launch of n items on `slots`
-// resident workgroups: 1 when every item gets a workgroup at once, else the
-// count that least quantises the launch into rounds.
-int sweep_chunks_auto(int n, int slots);
 int device_cus();   // of the current device, 0 on error
 // Replaces the (single) class's items by K chunks of each, all first chunks
 // first, with the sweeps of each chunk (run_theta[r]: run r's theta); 0 on

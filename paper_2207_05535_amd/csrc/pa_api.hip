@@ -783,7 +783,7 @@ pa_status upload_sweep_plan(pa_ctx *c)
     if (ncls < 0) return PA_ERR_ARG;
     if (!sweep_class_grids(cls, ncls, threads, packed && c->sweep_persistent)) return dev_fail(c);
     if (ncls == 1 && cls[0].grid > 0 && cls[0].grid < cls[0].count) {
-        const int K = c->sweep_chunks > 0 ? c->sweep_chunks : sweep_chunks_auto(cls[0].count, cls[0].grid);
+        const int K = c->sweep_chunks > 0 ? c->sweep_chunks : 2;
         std::vector<int> run_theta(c->n_runs);
         for (int r = 0; r < c->n_runs; ++r) run_theta[r] = std::max(0, c->descs[r].theta);
         // the lists stand behind the items, in the room of chunks not made
