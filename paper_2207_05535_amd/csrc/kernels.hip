@@ -2526,10 +2526,27 @@ __device__ __forceinline__ void measure_group(const SweepItem &it, int g, int su
     part[8] = wave_sum<int64_t>(pv * Ql);
     part[9] = wave_sum<int64_t>(pv * Ql * Ql);
     part[10] = wave_min(valid ? (int)E : INT32_MAX);
-    if (pair && R.qhist) {
+    if (R.qhist) {
         const size_t Np1 = (size_t)N + 1;
-        atomicAdd(&R.qh[((size_t)it.pop * R.K + S.i) * Np1 + H], 1);
-        if (R.overlap == PA_Q_TWO_POP) atomicAdd(&R.qh[((size_t)1 * R.K + S.i) * Np1 + H], 1);
+        int32_t *h0 = &R.qh[((size_t)it.pop * R.K + S.i) * Np1];
+        auto add = [&](uint32_t bin, int n) {
+            atomicAdd(&h0[bin], n);
+            if (R.overlap == PA_Q_TWO_POP) atomicAdd(&R.qh[((size_t)1 * R.K + S.i) * Np1 + bin], n);
+        };
+        // Few bins: all pairs of a wavefront with one distance at once (atomics
+        // on one address follow one another: L = 4, R = 58348 128 -> 42 us per
+        // launch; step at L = 6, R = 2e4 93 -> 89, but L = 8 86 -> 91)
+        if (N <= 36) {
+            for (uint64_t left = wave_ballot(pair); left != 0;) {
+                const int lead = __ffsll((unsigned long long)left) - 1;
+                const uint32_t bin = (uint32_t)__builtin_amdgcn_readlane((int)H, lead);
+                const uint64_t same = wave_ballot(pair && H == bin);
+                if (lane == lead) add(bin, __popcll(same));
+                left &= ~same;
+            }
+        } else if (pair) {
+            add(H, 1);
+        }
     }
     if (lane < MEAS_PART) {
         int64_t mine = 0;

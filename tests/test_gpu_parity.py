@@ -672,6 +672,21 @@ def test_sweep_chunks_bit_exact_at_full_size(workload):
             ctx.close()
 
 
+@pytest.mark.parametrize("L,R,overlap", [(4, 3, W.Q_INDEX_SHIFT), (4, 4500, W.Q_TWO_POP), (6, 1000, W.Q_INDEX_SHIFT),
+                                         (8, 1000, W.Q_TWO_POP)])
+def test_overlap_histograms_of_small_lattices(L, R, overlap):
+    """Histograms of few bins (a wavefront adds all pairs of one distance at
+    once) and of the first size with more, equal the oracle's."""
+    say(f"overlap histograms L={L} R={R} overlap={overlap}")
+    d = W.run_desc(L, W.FM, seed=W.RUN_SEED_BASE + 0x6D00 + L, R=R, theta=1, K=6, beta_f=0.5,
+                   resampling=W.NEAREST_INT, overlap=overlap, qhist=1)
+    orc = oracle.OracleRun(d).run_all()
+    ctx = pa.Context([d], "msc")
+    ctx.run(1, 6)
+    assert np.array_equal(ctx.qhist(0), orc.qhist())
+    ctx.close()
+
+
 @pytest.mark.parametrize("repr_", REPRS)
 @pytest.mark.parametrize("L,R,overlap", [(4, 70, W.Q_INDEX_SHIFT), (18, 1000, W.Q_TWO_POP), (32, 129, W.Q_INDEX_SHIFT),
                                          (34, 65, W.Q_TWO_POP), (46, 130, W.Q_INDEX_SHIFT), (66, 200, W.Q_TWO_POP)])
