@@ -865,8 +865,8 @@ __global__ void __launch_bounds__(1024) k_resample_run(const RunInfo *runs, PopS
     uint64_t *T8 = lds + 2 * (size_t)n8;
     uint32_t *F = (uint32_t *)(T8 + n8);
     const uint64_t SX = S.SX;
-    for (int k = tid; k < n8 * (CH_PER / 2); k += T) cnt[k] = 0;
     if (mn) {
+        for (int k = tid; k < n8 * (CH_PER / 2); k += T) cnt[k] = 0;
         // a thread takes blocks of CH_PER prefixes with 16-byte loads, all of a
         // block in flight together
         const uint64_t *B = R.base64[pop], *P = R.P[pop];
@@ -931,8 +931,11 @@ __global__ void __launch_bounds__(1024) k_resample_run(const RunInfo *runs, PopS
         const int32_t *E = R.E[pop][S.cur];
         const uint64_t *X = R.tabX + (size_t)S.i * (R.N + 1);
         const double invSX = 1.0 / (double)SX;
-        for (int j = tid; j < Rp; j += T)
-            ((uint16_t *)cnt)[j] = (uint16_t)nearest_count(R, S, pop, j, E[j], X, invSX);
+        // every count is stored here, those past the population as zeros: a
+        // clearing pass before this one would be other wavefronts' stores to
+        // the same words
+        for (int j = tid; j < n8 * CH_PER; j += T)
+            ((uint16_t *)cnt)[j] = j < Rp ? (uint16_t)nearest_count(R, S, pop, j, E[j], X, invSX) : (uint16_t)0;
     }
     __syncthreads();
     // population size first: nothing is written for one that is refused

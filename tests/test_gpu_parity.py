@@ -931,3 +931,29 @@ def test_many_populations_resampled_alone():
     assert_obs_equal(obs[5, :1], orc.obs(), "R=22016")
     assert_state_equal(ctx, orc, 5, "R=22016")
     ctx.close()
+
+
+def test_nearest_integer_counts_of_many_populations():
+    """Nearest-integer resampling in one workgroup per population, with more
+    populations than compute units so that wavefronts start at uneven times:
+    capacities around a wavefront's and a workgroup's share of the counts and
+    populations that end inside a block of 8.  Every record repeats in a second
+    context, and records, states and counts equal the oracle's for one run of
+    each capacity."""
+    caps = (513, 520, 1000, 1025, 2049, 4100, 8191, 8192)
+    say(f"nearest-integer counts of {64 * len(caps)} populations")
+    runs = [W.run_desc(16, W.EA_PMJ, seed=W.RUN_SEED_BASE + 0x7900 + m, disorder_seed=6, R=int(0.8 * caps[m % 8]),
+                       R_cap=caps[m % 8], theta=1, K=6, beta_f=2.0, resampling=W.NEAREST_INT)
+            for m in range(64 * len(caps))]
+    records = []
+    for _ in range(2):
+        ctx = pa.Context(runs, "msc")
+        ctx.run(1, 6)
+        obs = ctx.obs()
+        records.append(obs.tobytes())
+        for r in range(len(caps)):
+            orc = oracle.OracleRun(runs[r]).run_all()
+            assert_obs_equal(obs[r, :1], orc.obs(), f"R_cap={caps[r]}")
+            assert_state_equal(ctx, orc, r, f"R_cap={caps[r]}")
+        ctx.close()
+    assert records[0] == records[1]
