@@ -34,6 +34,7 @@
 #include "metropolis.hpp"
 #include "pa_internal.hpp"
 #include "philox.hpp"
+#include "unit_walk.hpp"
 
 namespace pa {
 
@@ -1292,11 +1293,6 @@ __device__ __forceinline__ int rank_below(uint64_t m, int b)
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)b));
 }
 
-// x / d for 0 <= x < 2^21 and a divisor known only at run time, from
-// inv = 1 / d: the error of the product (below 2^-23 of it) is less than the
-// distance 1 / (2d) of (x + 1/2) / d from the next integer.
-__device__ __forceinline__ int div_small(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
-
 // A list entry's undecided replicas and their class (set: dE = +4), kept
 // side by side so that one LDS address serves both.  Reads are one 16-byte
 // access (ds_read_b128).  Writes go out as two 8-byte halves of one
@@ -1476,8 +1472,7 @@ __device__ __forceinline__ void sweep_sparse_pooled(uint64_t *lat, UndPair *eu, 
 // One item of the batched sweep, read into scalar registers before the first
 // barrier: a barrier orders memory, so values left in global memory would be
 // loaded again after every one of them.
-struct SweepJob {
-    int L, N, half, nh;
+struct SweepJob : LatticeShape {
     int G, group0, lastg, units;
     int s_begin, s_end;      // this item's sweeps
     int ub, ue;              // this wavefront's units (site words of one colour)
@@ -1587,47 +1582,6 @@ __device__ __forceinline__ SiteClass classify_unit(uint64_t w, const uint64_t *o
     }
     return classify(w, n0, n1, n2, n3);
 }
-
-// A lane's walk over its wavefront's units in steps of 64: replica group gs
-// within the workgroup, site k = y L/2 + m of the colour, first lattice word
-// a = gs N + k (colour 0).  No division per step: the step's rows, columns
-// and groups are known beforehand and each carries at most once.
-struct UnitWalk {
-    int gs, k, y, m, a;
-    __device__ __forceinline__ void start(const SweepJob &J, int u)
-    {
-        gs = div_small(u, 1.0f / (float)J.nh);
-        k = u - gs * J.nh;
-        y = div_small(k, 1.0f / (float)J.half);
-        m = k - y * J.half;
-        a = gs * J.N + k;
-    }
-    __device__ __forceinline__ void step(const SweepJob &J, int gq, int kr, int yr, int mr)
-    {
-        gs += gq;
-        k += kr;
-        y += yr;
-        m += mr;
-        a += gq * J.N + kr;
-        if (m >= J.half) {
-            m -= J.half;
-            ++y;
-        }
-        if (k >= J.nh) {
-            k -= J.nh;
-            y -= J.L;
-            a += J.N - J.nh;
-            ++gs;
-        }
-    }
-    // offset of the other horizontal neighbour, p = x & 1
-    __device__ __forceinline__ int dh(const SweepJob &J, int p) const
-    {
-        return p ? (m + 1 == J.half ? 1 - J.half : 1) : (m == 0 ? J.half - 1 : -1);
-    }
-    __device__ __forceinline__ int du(const SweepJob &J) const { return y == 0 ? J.nh - J.half : -J.half; }
-    __device__ __forceinline__ int dd(const SweepJob &J) const { return y + 1 == J.L ? J.half - J.nh : J.half; }
-};
 
 // Work counters of an item: word-site updates and attempted flips in closed
 // form (the item's sweeps x 2 colours x its units, 64 replicas each except
@@ -1828,7 +1782,8 @@ __device__ __forceinline__ uint32_t stream_sweeps(const SweepJob &J, uint64_t *l
                 return (uint32_t)(ONE ? J.group0 : J.group0 + (int)((pk >> 12) & 0xFFu));
             };
             using UG = std::integral_constant<bool, ONE>;
-            // one chunk: a unit (site word) per lane.  own: its lattice word;
+            // one chunk: a unit (site word) per lane.  own: its lattice word (of
+            // the workgroup's, also on lanes with no unit);
             // dh, du, dd: offsets of the neighbours beside the word at the
             // same place of the other colour; ug: gs is the same on every lane
             auto chunk = [&](bool in, int own, int dh, int du, int dd, uint32_t n, int gs, auto ug) {
@@ -1884,8 +1839,9 @@ __device__ __forceinline__ uint32_t stream_sweeps(const SweepJob &J, uint64_t *l
                 UnitWalk w = first;
                 for (int u0 = J.ub; u0 < J.ue; u0 += 64) {
                     const int p = (w.y + colour) & 1;
-                    chunk(u0 + lane < J.ue, w.a + cb, w.dh(J, p), w.du(J), w.dd(J), 2u * (uint32_t)w.k + (uint32_t)p,
-                          ONE ? 0 : w.gs, UG{});
+                    const bool in = u0 + lane < J.ue;
+                    chunk(in, w.word(J, colour, in, lane), w.dh(J, p), w.du(J), w.dd(J),
+                          2u * (uint32_t)w.k + (uint32_t)p, ONE ? 0 : w.gs, UG{});
                     w.step(J, gq, kr, yr, mr);
                 }
             }
@@ -1954,10 +1910,11 @@ __device__ __forceinline__ void general_item(const SweepItem &item, const RunInf
             int cnt = 0;
             UnitWalk w = first;
             for (int u0 = J.ub; u0 < J.ue; u0 += 64) {
-                const int p = (w.y + colour) & 1, own = w.a + cb;
+                const bool in = u0 + lane < J.ue;
+                const int p = (w.y + colour) & 1, own = w.word(J, colour, in, lane);
                 const uint32_t n = 2u * (uint32_t)w.k + (uint32_t)p, g = (uint32_t)(J.group0 + w.gs);
                 uint64_t und = 0, one = 0, acc = 0;
-                if (u0 + lane < J.ue) {
+                if (in) {
                     uint32_t jm = 0;
                     if (EA) jm = jb[cb + w.k];
                     SiteClass sc = classify_unit<EA>(lat[own], lat + own + od, w.dh(J, p), w.du(J), w.dd(J), jm);
@@ -1981,7 +1938,7 @@ __device__ __forceinline__ void general_item(const SweepItem &item, const RunInf
                         acc = bop3<LUT_SEL>(was, less, acc);
                     }
                 }
-                if (u0 + lane < J.ue) flip_word(&lat[own], acc & ~und);
+                flip_word(&lat[own], acc & ~und);
                 const uint64_t need = wave_ballot(und != 0);
                 int base_slot = J.ub + cnt;
                 if (pool && need) {

@@ -957,3 +957,21 @@ def test_nearest_integer_counts_of_many_populations():
             assert_state_equal(ctx, orc, r, f"R_cap={caps[r]}")
         ctx.close()
     assert records[0] == records[1]
+
+
+@pytest.mark.parametrize("L,model", [(74, W.EA_PMJ), (78, W.FM), (82, W.FM), (86, W.EA_PMJ), (90, W.FM), (94, W.FM)])
+@pytest.mark.parametrize("threads", [0, 512])
+def test_largest_streamed_lattices(L, model, threads):
+    """One group to a workgroup of the largest bit-packed lattices, whose last
+    chunk of site words is partial, with the default shape and 512 threads:
+    every record and the final state equal the oracle's."""
+    say(f"streamed sweep L={L} model={model} threads={threads}")
+    d = W.run_desc(L, model, seed=W.RUN_SEED_BASE + 0x7A00 + L, disorder_seed=9, R=144, theta=2, K=4, beta_f=1.0)
+    ctx = pa.Context([d], "msc")
+    if threads:
+        ctx.set_tuning(L, threads, 1, 3)
+    ctx.run(1, 4)
+    orc = oracle.OracleRun(d).run_all()
+    assert_obs_equal(ctx.obs()[0, :1], orc.obs(), f"L={L}")
+    assert_state_equal(ctx, orc, 0, f"L={L} final")
+    ctx.close()

@@ -1,0 +1,44 @@
+"""LDS layouts and addresses of the kernels, enumerated on the CPU from the
+headers the kernels are built from."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2207_05535_amd", "csrc")
+LDS = 160 * 1024
+
+
+@pytest.fixture(scope="module")
+def layout(tmp_path_factory):
+    if shutil.which("g++") is None or not os.path.exists("/opt/rocm/include/hip"):
+        pytest.skip("HIP headers or g++ not available")
+    out = tmp_path_factory.mktemp("layout") / "layout.so"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-I" + CSRC, os.path.join(HERE, "sweep_layout.cpp"), "-o", str(out)], check=True)
+    lib = C.CDLL(str(out))
+    lib.sweep_lds.restype = C.c_int64
+    return lib
+
+
+@pytest.mark.parametrize("threads", [64, 128, 256, 512, 1024])
+def test_sweep_addresses_stay_in_the_lattices(layout, threads):
+    """Every word a lane of the streamed sweep addresses, also one past its
+    wavefront's last unit, lies in the workgroup's lattices, for every lattice
+    size and the numbers of groups that fit; every unit is visited once."""
+    idle = 0
+    for L in list(range(4, 95, 2)) + [100, 110, 126, 128]:
+        for groups in (1, 2, 3, 4, 5, 7, 16, 41, 64, 255, 256):
+            if groups > 1 and (L > 64 or groups * L * L > 16384) or layout.sweep_lds(L, threads, groups, 1) > LDS:
+                continue
+            out = (C.c_int64 * 6)()
+            layout.sweep_walk(L, threads, groups, out)
+            words = groups * L * L
+            assert 0 <= out[0] and out[1] < words, (L, groups, list(out))
+            assert 0 <= out[2] and out[3] < words, (L, groups, list(out))
+            assert out[4] == 0, (L, groups)
+            idle += out[5]
+    assert idle > 0
