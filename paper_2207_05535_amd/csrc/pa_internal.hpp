@@ -238,6 +238,13 @@ __host__ __device__ inline size_t wang_lds_bytes(int R_cap)
     const size_t re = (R_cap + 7) & ~7, a = 2 * (2 * re + ((size_t)1 << wang_lb_of(R_cap))), b = 8 * re;
     return R_cap > 65535 ? (size_t)1 << 30 : (a > b ? a : b);
 }
+// Position of the repair's candidate uu, counted on past the population's end
+// (Rc replicas; the search ends before `end` <= 2 Rc).  Lanes past the search's
+// end read position 0, which they do not use.
+__host__ __device__ inline int wang_candidate(int uu, int end, int Rc)
+{
+    return uu < end ? (uu >= Rc ? uu - Rc : uu) : 0;
+}
 struct WangBufs {
     int32_t *pi, *sigma, *fampi, *members, *list, *cnt, *start, *hdr;
 };

@@ -1,5 +1,5 @@
-// The batched sweep's LDS addresses, from the headers the kernels are built
-// from, for test_sweep_layout.py.
+// LDS addresses of the kernels, from the headers they are built from, for
+// test_sweep_layout.py.
 #include <algorithm>
 #include <vector>
 
@@ -52,4 +52,18 @@ extern "C" void sweep_walk(int L, int threads, int groups, int64_t *out)
 extern "C" int64_t sweep_lds(int L, int threads, int groups, int ea)
 {
     return (int64_t)msc_stream_lds(L * L, groups, ea != 0, threads / 64);
+}
+
+// The pairing repair's candidates for a population of Rc: how many are not the
+// position they stand for, or (past the search's end) no position at all.
+extern "C" int64_t wrong_candidates(int Rc)
+{
+    int64_t wrong = 0;
+    for (int hi = 1; hi <= Rc; ++hi)
+        for (int u = hi; u < hi + Rc; ++u)
+            for (int lane = 0; lane < 64; ++lane) {
+                const int m = wang_candidate(u + lane, hi + Rc, Rc);
+                wrong += m < 0 || m >= Rc || (u + lane < hi + Rc && m != (u + lane) % Rc);
+            }
+    return wrong;
 }

@@ -226,3 +226,30 @@ def test_pairing_sizes(kind):
             paired += 1
     assert paired > len(runs)
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", [W.Q_WANG, W.Q_WANG_RDM])
+def test_pairing_of_tiny_runs_alone(kind):
+    """A context whose only runs are smaller than a wavefront, so that the
+    launch's LDS is no larger than they need."""
+    say(f"permutation pairing of tiny runs kind={kind}")
+    runs = [W.run_desc(8, W.EA_PMJ, seed=W.RUN_SEED_BASE + 0x5600 + R, disorder_seed=12, R=R, theta=1, K=6, beta_f=1.0,
+                       resampling=W.MULTINOMIAL, overlap=kind) for R in (3, 5, 31, 48, 62)]
+    ctx = pa.Context(runs, "msc")
+    paired = 0
+    for i in range(6):
+        if i:
+            ctx.step(i)
+        for r, d in enumerate(runs):
+            fam = ctx.state(r, 0)[2]
+            st, pairs = ctx.pairing(r)
+            if large_family(fam):
+                assert st == 1, (r, i)
+                continue
+            pi = oracle.random_permutation(d["seed"], i, 0, len(fam), 0)
+            sigma = oracle.random_permutation(d["seed"], i, 0, len(fam), 1) if kind == W.Q_WANG_RDM else None
+            st_o, want = oracle.wang_repair(fam, pi, sigma)
+            assert st == st_o == 0 and np.array_equal(pairs, want), (r, i)
+            paired += 1
+    assert paired > len(runs)
+    ctx.close()

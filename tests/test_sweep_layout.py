@@ -20,7 +20,7 @@ def layout(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
                     "-I/opt/rocm/include", "-I" + CSRC, os.path.join(HERE, "sweep_layout.cpp"), "-o", str(out)], check=True)
     lib = C.CDLL(str(out))
-    lib.sweep_lds.restype = C.c_int64
+    lib.sweep_lds.restype = lib.wrong_candidates.restype = C.c_int64
     return lib
 
 
@@ -42,3 +42,10 @@ def test_sweep_addresses_stay_in_the_lattices(layout, threads):
             assert out[4] == 0, (L, groups)
             idle += out[5]
     assert idle > 0
+
+
+@pytest.mark.parametrize("Rc", [1, 2, 3, 31, 62, 63, 64, 65, 130])
+def test_pairing_candidates_are_positions(layout, Rc):
+    """Lanes of the pairing repair read positions of the population alone, at
+    sizes below a wavefront too."""
+    assert layout.wrong_candidates(Rc) == 0
