@@ -850,7 +850,7 @@ constexpr int GUIDE_BITS = 11;
 
 __global__ void __launch_bounds__(1024) k_resample_run(const RunInfo *runs, PopState *st)
 {
-    // counts [R] u16, coarse prefix [R/8], fine prefix [R] (fused_lds)
+    // counts, coarse prefix, fine prefix (fused_lds)
     extern __shared__ __align__(16) uint64_t lds[];
     __shared__ uint16_t guide[(1 << GUIDE_BITS) + 2];
     __shared__ int32_t wsum[17];
@@ -864,7 +864,7 @@ __global__ void __launch_bounds__(1024) k_resample_run(const RunInfo *runs, PopS
     const bool mn = R.resampling == PA_MULTINOMIAL;
     uint32_t *cnt = (uint32_t *)lds;
     uint64_t *T8 = lds + 2 * (size_t)n8;
-    uint32_t *F = (uint32_t *)(T8 + n8);
+    uint32_t *F = (uint32_t *)((uint8_t *)lds + fused_fine_at(n8));
     const uint64_t SX = S.SX;
     if (mn) {
         for (int k = tid; k < n8 * (CH_PER / 2); k += T) cnt[k] = 0;

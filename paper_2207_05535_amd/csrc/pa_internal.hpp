@@ -37,9 +37,14 @@ constexpr int CH = CH_THREADS * CH_PER;
 // Largest population capacity k_resample_run takes (16-bit counts, and the
 // LDS of a workgroup): counts, coarse and fine prefix in LDS, see there.
 constexpr int FUSED_MAX = 22016;
+// Its LDS: counts [n8] of CH_PER u16, coarse prefix [n8] u64 and, 16-byte
+// aligned, fine prefix [n8] of CH_PER u32, n8 = the blocks of CH_PER replicas
+// (the prefixes for multinomial draws only).
+__host__ __device__ inline size_t fused_fine_at(int n8) { return (size_t)n8 * 2 * CH_PER + (((size_t)n8 + 1) & ~(size_t)1) * 8; }
 __host__ __device__ inline size_t fused_lds(int R_cap, bool multinomial)
 {
-    return (size_t)((R_cap + CH_PER - 1) / CH_PER) * (multinomial ? 2 * CH_PER + 8 + 4 * CH_PER : 2 * CH_PER);
+    const int n8 = (R_cap + CH_PER - 1) / CH_PER;
+    return multinomial ? fused_fine_at(n8) + (size_t)n8 * 4 * CH_PER : (size_t)n8 * 2 * CH_PER;
 }
 constexpr int NACC = 13;  // measure accumulators, see Acc
 

@@ -67,3 +67,16 @@ extern "C" int64_t wrong_candidates(int Rc)
             }
     return wrong;
 }
+
+// Layout of the one-workgroup resampling: the end of the coarse prefix, the
+// start of the fine one, its end, and the LDS asked for.
+extern "C" void fused_layout(int R_cap, int64_t *out)
+{
+    const int n8 = (R_cap + CH_PER - 1) / CH_PER;
+    out[0] = (int64_t)n8 * (2 * CH_PER + 8);
+    out[1] = (int64_t)fused_fine_at(n8);
+    out[2] = out[1] + (int64_t)n8 * 4 * CH_PER;
+    out[3] = (int64_t)fused_lds(R_cap, true);
+}
+
+extern "C" int fused_max() { return FUSED_MAX; }

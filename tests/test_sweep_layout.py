@@ -49,3 +49,15 @@ def test_pairing_candidates_are_positions(layout, Rc):
     """Lanes of the pairing repair read positions of the population alone, at
     sizes below a wavefront too."""
     assert layout.wrong_candidates(Rc) == 0
+
+
+def test_fused_resampling_layout(layout):
+    """The fine prefix of the one-workgroup resampling, which is stored 16
+    bytes at a time, is aligned to them behind the coarse one at every
+    population size, and the largest population fits a workgroup's LDS beside
+    the kernel's own 4.3 KB."""
+    out = (C.c_int64 * 4)()
+    for R in range(1, layout.fused_max() + 1):
+        layout.fused_layout(R, out)
+        assert out[1] % 16 == 0 and out[0] <= out[1] < out[2] <= out[3], R
+    assert out[3] + 4400 <= LDS
