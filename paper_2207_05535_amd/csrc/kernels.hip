@@ -25,7 +25,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <map>
+#include <mutex>
 #include <type_traits>
+#include <utility>
 #include <vector>
 #include <math.h>
 #include <stdint.h>
@@ -3153,11 +3156,6 @@ hipError_t launch_philox_rate(int calls, hipStream_t s, int *blocks, int *thread
     return hipGetLastError();
 }
 
-hipError_t prepare_wang_lds(size_t bytes)
-{
-    if (bytes <= 65536) return hipSuccess;
-    return hipFuncSetAttribute((const void *)k_wang_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
 
 __device__ __forceinline__ bool wang_group_live(const Item &it, const RunInfo &R, const PopState &S)
 {
@@ -3871,11 +3869,29 @@ hipError_t launch_clear_counts(const LaunchCtx &c)
     return hipGetLastError();
 }
 
-hipError_t prepare_fused_lds(size_t bytes)
+// Allows launches of a kernel on this device with `bytes` of dynamic LDS.  The
+// permission is the kernel's, not a context's, so it is only ever raised:
+// contexts and servers that live beside each other launch with what each of
+// them needs.  Up to 64 KB, the kernel's own arrays included, needs none.
+static hipError_t allow_lds(const void *kernel, size_t bytes)
 {
-    if (bytes <= 65536) return hipSuccess;
-    return hipFuncSetAttribute((const void *)k_resample_run, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    constexpr size_t OWN = 8192;   // no kernel has more of its own
+    if (bytes + OWN <= 65536) return hipSuccess;
+    static std::mutex mu;
+    static std::map<std::pair<int, const void *>, size_t> allowed;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mu);
+    size_t &have = allowed[{dev, kernel}];
+    if (bytes <= have) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) have = bytes;
+    return e;
 }
+
+hipError_t prepare_fused_lds(size_t bytes) { return allow_lds((const void *)k_resample_run, bytes); }
+hipError_t prepare_wang_lds(size_t bytes) { return allow_lds((const void *)k_wang_lds, bytes); }
 
 hipError_t launch_words(const LaunchCtx &c, int max_N)
 {
@@ -3951,12 +3967,10 @@ bool msc_specialised(int L) { return L == 8 || L == 16 || L == 24 || L == 32 || 
 
 hipError_t prepare_msc_lds(size_t bytes)
 {
-    if (bytes <= 65536) return hipSuccess;
     static const int Ls[] = {8, 16, 24, 32, 48, 64, 0, -1};
     for (int L : Ls)
         for (int ea = 0; ea < 2; ++ea) {
-            const hipError_t e = hipFuncSetAttribute((const void *)msc_kernel(L, ea),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+            const hipError_t e = allow_lds((const void *)msc_kernel(L, ea), bytes);
             if (e != hipSuccess) return e;
         }
     return hipSuccess;

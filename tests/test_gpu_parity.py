@@ -975,3 +975,36 @@ def test_largest_streamed_lattices(L, model, threads):
     assert_obs_equal(ctx.obs()[0, :1], orc.obs(), f"L={L}")
     assert_state_equal(ctx, orc, 0, f"L={L} final")
     ctx.close()
+
+
+def test_contexts_of_different_lds_needs_side_by_side():
+    """Contexts that live beside each other launch the same kernels with their
+    own amounts of LDS (from a little under 64 KB, where the kernel's own
+    arrays decide, to nearly all), the largest created first and stepped again
+    after each of the others: the records of each equal those of the same
+    context alone."""
+    def runs(seed, n, R, L, overlap):
+        return [W.run_desc(L, W.EA_PMJ, seed=W.RUN_SEED_BASE + seed + m, disorder_seed=15, R=R, theta=1, K=7,
+                           beta_f=1.0, overlap=overlap) for m in range(n)]
+    sets = [runs(0x7B00, 64, 22016, 4, W.Q_NONE), runs(0x7B80, 64, 9300, 4, W.Q_NONE), runs(0x7BC0, 64, 10100, 4, W.Q_NONE),
+            runs(0x7C00, 1, 20000, 4, W.Q_WANG), runs(0x7C10, 1, 9000, 4, W.Q_WANG), runs(0x7C20, 1, 70, 92, W.Q_NONE),
+            runs(0x7C30, 1, 70, 62, W.Q_NONE)]
+    sets[5][0]["model"] = W.FM   # a spin glass of that size does not fit
+    alone = []
+    for r in sets:
+        ctx = pa.Context(r, "msc")
+        ctx.run(1, 7)
+        alone.append(ctx.obs().tobytes())
+        ctx.close()
+    live = []
+    for k, r in enumerate(sets):
+        say(f"context {k} of {len(sets)}")
+        live.append(pa.Context(r, "msc"))
+        for ctx in live:
+            if ctx.i < 6:
+                ctx.step(ctx.i + 1)
+    for ctx, want in zip(live, alone):
+        if ctx.i < 6:
+            ctx.run(ctx.i + 1, 7)
+        assert ctx.obs().tobytes() == want
+        ctx.close()
