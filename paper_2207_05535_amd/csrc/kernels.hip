@@ -426,11 +426,11 @@ __global__ void k_init_fam(const RunInfo *runs)
 // Reweighting, Eq. (tauBoltz)/(QBoltz): per chunk of CH replicas the partial
 // sums of x_j = exp(-dbeta (E_j - E_min)) (FP64) and of X_j = floor(x_j 2^40)
 // (exact); for multinomial resampling also the chunk-local exclusive prefix
-// of X_j and cleared descendant counts.  The temperature index is
-// i = (index of the population) + 1.  The population's last chunk finishes
-// the step: chunk bases of the prefix, ln Q_i and A_i.  (In launches of their
-// own that and the clearing took 2-12 us each, counting in takes 1-4; with
-// 16-byte accesses 256 populations of 2e4 take 30 us, 65 in three launches.)
+// of X_j.  The temperature index is i = (index of the population) + 1.  The
+// population's last chunk finishes the step: chunk bases of the prefix, ln Q_i
+// and A_i.  (In a launch of its own that took 2-12 us, counting in takes 1-4;
+// with 16-byte accesses 256 populations of 2e4 take 30 us, 65 in three
+// launches.)
 __global__ void __launch_bounds__(CH_THREADS) k_rw_chunk(const ChunkItem *items, const RunInfo *runs, PopState *st)
 {
     __shared__ uint64_t lds64[CH_THREADS / 64 + 1];
@@ -475,10 +475,6 @@ __global__ void __launch_bounds__(CH_THREADS) k_rw_chunk(const ChunkItem *items,
 #pragma unroll
         for (int q = 0; q < CH_PER; ++q) loc[q] += pre;
         store_block(R.P[it.pop], jb, Rp, loc);
-        if (!R.fused) {
-            const int32_t none[CH_PER] = {};
-            store_block(R.r[it.pop], jb, Rp, none);
-        }
     }
     // fixed-order FP64 tree: wave shuffles then waves in order
     double ws = s;
@@ -529,18 +525,16 @@ __global__ void __launch_bounds__(CH_THREADS) k_rw_chunk(const ChunkItem *items,
     }
 }
 
-// Clears the descendant counts as k_rw_chunk does, for populations restored
-// between steps (ii) and (iii).
-__global__ void __launch_bounds__(CH_THREADS) k_clear_counts(const ChunkItem *items, const RunInfo *runs,
-                                                              const PopState *st)
+// Clears what k_mn_draws adds to, for restored populations (k_parent leaves it
+// clear, a checkpoint of an earlier build may not).
+__global__ void __launch_bounds__(CH_THREADS) k_clear_draws(const ChunkItem *items, const RunInfo *runs)
 {
     const ChunkItem it = items[blockIdx.x];
     const RunInfo &R = runs[it.run];
-    const PopState &S = st[it.run * MAX_POP + it.pop];
-    if (!pop_active(S) || R.resampling != PA_MULTINOMIAL) return;
+    if (R.resampling != PA_MULTINOMIAL || R.fused) return;
     for (int q = 0; q < CH_PER; ++q) {
         const int j = it.chunk * CH + q * CH_THREADS + (int)threadIdx.x;
-        if (j < S.Rprev) R.r[it.pop][j] = 0;
+        if (j < R.R_cap) R.C[it.pop][j] = 0;
     }
 }
 
@@ -713,7 +707,9 @@ __device__ __forceinline__ int last_not_above(const uint64_t *P, int n, uint64_t
 // CH_PER workgroups per chunk item, each one round of CH_THREADS draws: the
 // searches are chains of dependent loads at scattered addresses, so they are
 // spread over as many compute units as possible.  Two populations of 2e5:
-// 24 us, 32 by halving; 2e4: 5.4 and 6.7.
+// 24 us, 32 by halving; 2e4: 5.4 and 6.7.  They are counted in C, which is
+// clear here: the counts of the last resampling stay in r until the next one
+// has its own.
 __global__ void __launch_bounds__(CH_THREADS) k_mn_draws(const ChunkItem *items, const RunInfo *runs,
                                                           const PopState *st)
 {
@@ -729,7 +725,7 @@ __global__ void __launch_bounds__(CH_THREADS) k_mn_draws(const ChunkItem *items,
     const uint64_t *P = R.P[it.pop];
     const uint64_t *B = R.base64[it.pop];
     const uint32_t c3 = (TAG_MN << 28) | ((uint32_t)it.pop << 24);
-    int32_t *r = R.r[it.pop];
+    int32_t *C = R.C[it.pop];
     __shared__ uint64_t sB[CH];   // the chunk bases
     // largest j with P_j <= t in two levels: the last chunk whose base is
     // <= t (chunk bases staged in LDS), then inside that chunk
@@ -752,11 +748,12 @@ __global__ void __launch_bounds__(CH_THREADS) k_mn_draws(const ChunkItem *items,
         }
         const uint64_t base = staged ? sB[k] : B[k];
         const uint64_t tot = (k + 1 < nch ? (staged ? sB[k + 1] : B[k + 1]) : SX) - base;
-        atomicAdd(&r[k * CH + last_not_above(P + (size_t)k * CH, min(CH, Rp - k * CH), tot, t - base)], 1);
+        atomicAdd(&C[k * CH + last_not_above(P + (size_t)k * CH, min(CH, Rp - k * CH), tot, t - base)], 1);
     }
 }
 
-// Multinomial: chunk-local exclusive prefix of the counts r.
+// Multinomial: the counts r and their chunk-local exclusive prefix C, from the
+// draws counted in C.
 __global__ void __launch_bounds__(CH_THREADS) k_cnt_scan_chunk(const ChunkItem *items, const RunInfo *runs,
                                                                 PopState *st)
 {
@@ -770,9 +767,9 @@ __global__ void __launch_bounds__(CH_THREADS) k_cnt_scan_chunk(const ChunkItem *
     const int j0 = it.chunk * CH;
     if (j0 >= Rp) return;
     const int jb = j0 + threadIdx.x * CH_PER;
-    const int32_t *r = R.r[it.pop];
     int32_t rj[CH_PER], loc[CH_PER];
-    load_block(r, jb, Rp, 0, rj);
+    load_block(R.C[it.pop], jb, Rp, 0, rj);
+    store_block(R.r[it.pop], jb, Rp, rj);
     int32_t sum = 0;
 #pragma unroll
     for (int q = 0; q < CH_PER; ++q) {
@@ -810,7 +807,7 @@ __device__ __forceinline__ void write_children(int32_t *par, int j, int cj, int 
     }
 }
 
-// C_j = base32[chunk] + chunk-local prefix.
+// C_j = base32[chunk] + chunk-local prefix; multinomial draws find C clear again.
 __global__ void __launch_bounds__(CH_THREADS) k_parent(const ChunkItem *items, const RunInfo *runs,
                                                         const PopState *st)
 {
@@ -821,14 +818,17 @@ __global__ void __launch_bounds__(CH_THREADS) k_parent(const ChunkItem *items, c
     const int Rp = S.Rprev;
     const int j0 = it.chunk * CH;
     if (j0 >= Rp) return;
-    const int32_t *C = R.C[it.pop];
+    int32_t *C = R.C[it.pop];
     const int32_t *r = R.r[it.pop];
     const int32_t base = R.base32[it.pop][it.chunk];
+    const bool mn = R.resampling == PA_MULTINOMIAL;
 #pragma unroll
     for (int q = 0; q < CH_PER; ++q) {
         const int j = j0 + q * CH_THREADS + (int)threadIdx.x;
         const bool in = j < Rp;
-        write_children(R.parent[it.pop], j, in ? base + C[j] : 0, in ? r[j] : 0);
+        const int cj = in ? base + C[j] : 0;
+        if (in && mn) C[j] = 0;
+        write_children(R.parent[it.pop], j, cj, in ? r[j] : 0);
     }
 }
 
@@ -3862,10 +3862,9 @@ hipError_t launch_resample(const LaunchCtx &c)
     return hipGetLastError();
 }
 
-
-hipError_t launch_clear_counts(const LaunchCtx &c)
+hipError_t launch_clear_draws(const LaunchCtx &c)
 {
-    k_clear_counts<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs, c.st);
+    k_clear_draws<<<c.n_chunk_items, CH_THREADS, 0, c.stream>>>(c.chunk_items, c.runs);
     return hipGetLastError();
 }
 

@@ -64,7 +64,7 @@ hipError_t launch_sweep_msc(const LaunchCtx &c);
 // c.sweep_cls), and the runs of `wide` one colour at a time.
 hipError_t launch_sweep_bytes(const LaunchCtx &c, const WideRun *wide, int n_wide, int max_N);
 // first: the measurement at i = 0 (the int8 layout has no words yet).
-hipError_t launch_clear_counts(const LaunchCtx &c);   // after a restore between steps (ii) and (iii)
+hipError_t launch_clear_draws(const LaunchCtx &c);   // after a restore
 hipError_t prepare_fused_lds(size_t bytes);
 hipError_t launch_measure(const LaunchCtx &c, bool first);
 hipError_t launch_words(const LaunchCtx &c, int max_N);   // int8 layout: bytes -> words

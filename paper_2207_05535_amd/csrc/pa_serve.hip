@@ -584,7 +584,7 @@ pa_status pa_server_admit(pa_server *s, const pa_run_desc *desc, int32_t *slot)
         if ((st = upload(s, blk + b.o.dos, D.data(), sizeof(uint64_t) * D.size())) != PA_OK) return st;
     }
     bool ok = true;
-    for (int p = 0; p < npop && ok; ++p) ok = launch_fill_u32(blk + b.o.r[p], 0, d.R_cap, s->stream) == hipSuccess;
+    for (int p = 0; p < npop && ok; ++p) ok = launch_fill_u32(blk + b.o.C[p], 0, d.R_cap, s->stream) == hipSuccess;
     if (d.qhist && ok)
         ok = launch_fill_u32(blk + b.o.qh, 0, (size_t)npop * d.K * (N + 1), s->stream) == hipSuccess;
     ok = ok && launch_fill_u32(blk + b.obs, 0, sizeof(pa_obs) / 4 * (size_t)d.K * npop, s->stream) == hipSuccess;

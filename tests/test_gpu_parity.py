@@ -1008,3 +1008,36 @@ def test_contexts_of_different_lds_needs_side_by_side():
             ctx.run(ctx.i + 1, 7)
         assert ctx.obs().tobytes() == want
         ctx.close()
+
+
+@pytest.mark.parametrize("resampling", [W.MULTINOMIAL, W.NEAREST_INT])
+@pytest.mark.parametrize("R", [700, 9000])
+def test_counts_between_reweighting_and_resampling(resampling, R):
+    """Descendant counts are those of the last resampling until the next one:
+    read after step (ii) they still are step i-1's, in the context and in one
+    restored there, in which the run goes on to the same records."""
+    say(f"counts after step (ii) R={R} mode={resampling}")
+    d = W.run_desc(8, W.FM, seed=W.RUN_SEED_BASE + 0x7D00 + R, R=R, theta=1, K=6, beta_f=1.5, resampling=resampling)
+    ctx, other = pa.Context([d], "msc"), pa.Context([d], "msc")
+    whole = pa.Context([d], "msc")
+    whole.run(1, 6)
+    for i in range(1, 4):
+        # after step (i) nothing has been resampled; later, the last step's counts
+        before = ctx.state(0)[3] if i > 1 else np.zeros(R, np.int32)
+        ctx.anneal_step(i)
+        n = min(len(before), len(ctx.state(0)[3]))
+        assert np.array_equal(ctx.state(0)[3][:n], before[:n]), i
+        other.restore(ctx.checkpoint())
+        assert np.array_equal(other.state(0)[3][:n], before[:n]), i
+        ctx.resample(i)
+        assert ctx.state(0)[3].sum() == len(ctx.state(0)[1])
+        ctx.sweep(i)
+        ctx.measure(i)
+    other.resample(3)
+    other.sweep(3)
+    other.measure(3)
+    for c in (ctx, other):
+        c.run(4, 6)
+        assert c.obs().tobytes() == whole.obs().tobytes()
+        c.close()
+    whole.close()
