@@ -169,7 +169,6 @@ struct pa_server {
     bool shaped = false;                // the shape comes from the cache
     std::vector<WideRun> wide;          // int8 layout: runs swept one colour per launch
     int max_N = 0;                      // sites of the largest resident lattice
-    std::map<int, int> resident_groups; // else: L -> the same for the resident runs
     bool failed = false;
     hipError_t last = hipSuccess;
 };
@@ -217,12 +216,88 @@ int serve_mode(const pa_server *s)
     return s->dense | (s->pooled ? 1 << 8 : 0);
 }
 
-int groups_of(const pa_server *s, int L)
+// Sweep list of the resident runs, largest lattice block first, with its LDS;
+// in the int8 layout also the runs swept from memory.  `small`: with as few
+// items as an arena that is nearly full has to hold: the bit-packed layout's
+// shape of 2048 units per workgroup where no cache gives one, no list at all
+// in the int8 layout.  (A shape by the work per SIMD lists up to one item per
+// replica group, 32 bytes each.)  PA_ERR_ARG if a shape does not fit.
+struct ServeSweeps {
+    std::vector<SweepItem> items;
+    std::vector<WideRun> wide;
+    size_t lds = 0;
+    int threads = 512;
+};
+
+pa_status sweep_list(const pa_server *s, bool small, ServeSweeps &out)
 {
-    auto it = s->groups.find(L);
-    if (it != s->groups.end()) return it->second;
-    it = s->resident_groups.find(L);
-    return it == s->resident_groups.end() ? groups_of_2048(L) : it->second;
+    const bool packed = s->repr == PA_MSC64, shaped = packed && s->shaped;
+    std::map<int, int> groups;   // L -> groups per workgroup, where it is not that of 2048 units
+    out = ServeSweeps();
+    if (!shaped && !small) {
+        std::vector<const pa_run_desc *> dp;
+        for (const Slot &sl : s->slots)
+            if (sl.used) dp.push_back(&sl.d);
+        if (!dp.empty()) default_shape(dp.data(), (int)dp.size(), &out.threads, groups);
+    }
+    if (shaped) {
+        out.threads = s->threads;
+        groups = s->groups;
+    }
+    for (int k = 0; k < s->max_slots; ++k) {
+        const Slot &sl = s->slots[k];
+        if (!sl.used) continue;
+        const pa_run_desc &d = sl.d;
+        const int N = d.L * d.L, npop = n_pop_of(d.overlap);
+        const bool ea = d.model == PA_EA_PMJ;
+        const int G = groups.count(d.L) ? groups[d.L] : groups_of_2048(d.L);
+        if (packed) {
+            if ((size_t)G * N > 65535) return PA_ERR_ARG;
+            out.lds = std::max(out.lds, msc_lds_bound(N, G, ea, out.threads / 64));
+        } else {
+            if (d.theta <= 0) continue;
+            if (small || sweeps_wide(d, G, out.threads, s->lds_limit)) {
+                out.wide.push_back({k, d.L, groups_cap_of(d), npop, d.theta, ea ? 1 : 0});
+                continue;
+            }
+            out.lds = std::max(out.lds, msc_stream_lds(N, G, ea, out.threads / 64));
+        }
+        for (int p = 0; p < npop; ++p)
+            for (int g = 0; g < groups_cap_of(d); g += G)
+                out.items.push_back({k, p, g, std::min(G, groups_cap_of(d) - g)});
+    }
+    if (out.lds > (size_t)s->lds_limit) return PA_ERR_ARG;
+    std::stable_sort(out.items.begin(), out.items.end(), [s](const SweepItem &a, const SweepItem &b) {
+        const long wa = (long)a.ngroups * s->slots[a.run].d.L * s->slots[a.run].d.L;
+        const long wb = (long)b.ngroups * s->slots[b.run].d.L * s->slots[b.run].d.L;
+        return wa > wb;
+    });
+    return PA_OK;
+}
+
+size_t list_bytes(const std::vector<SweepItem> &items) { return sizeof(SweepItem) * std::max<size_t>(items.size(), 1); }
+
+// Makes room for blocks of a and b bytes (b may be 0) that the arena does not
+// have by giving up all of the sweep list's region but what its smallest form
+// takes, if that suffices: a request is refused for its own size, not for the
+// shape the others are swept in.
+bool make_room(pa_server *s, size_t a, size_t b)
+{
+    ServeSweeps small;
+    if (!s->sweep_cap || sweep_list(s, true, small) != PA_OK) return false;
+    const size_t keep = list_bytes(small.items);
+    if (keep >= s->sweep_cap) return false;
+    size_t off = 0, at = 0;
+    Arena after = s->arena;
+    after.release(s->sweep_off, s->sweep_cap);
+    if (!after.alloc(keep, &off)) return false;
+    Arena probe = after;
+    if (!probe.alloc(a, &at) || (b && !probe.alloc(b, &at))) return false;
+    s->arena = after;
+    s->sweep_off = off;
+    s->sweep_cap = keep;
+    s->dirty = true;   // what launches next is a new list
+    return true;
 }
 
 // Regrows a work-list region to hold `need` bytes (doubling).  The old
@@ -252,17 +327,8 @@ pa_status rebuild(pa_server *s)
     int hi = 0, npop_ctx = 1;
     bool mn = false, ni = false, wang = false, exact = false, chained = false, ovl = false;
     int fused_max = 0;
-    std::vector<SweepItem> sweep;
-    size_t lds = 0;
-    s->wide.clear();
     s->max_N = 0;
     bool swept = false, unswept = false;
-    if (!s->shaped || s->repr == PA_INT8) {
-        std::vector<const pa_run_desc *> dp;
-        for (const Slot &sl : s->slots)
-            if (sl.used) dp.push_back(&sl.d);
-        if (!dp.empty()) default_shape(dp.data(), (int)dp.size(), &s->threads, s->resident_groups);
-    }
     for (int k = 0; k < s->max_slots; ++k) {
         const Slot &sl = s->slots[k];
         if (!sl.used) continue;
@@ -282,32 +348,7 @@ pa_status rebuild(pa_server *s)
         swept = swept || sl.d.theta > 0;
         unswept = unswept || sl.d.theta <= 0;
         s->max_N = std::max(s->max_N, sl.d.L * sl.d.L);
-        {
-            const int G = s->repr == PA_INT8 ? s->resident_groups.at(sl.d.L) : groups_of(s, sl.d.L);
-            const int N = sl.d.L * sl.d.L;
-            const bool ea = sl.d.model == PA_EA_PMJ;
-            if (s->repr == PA_MSC64) {
-                if ((size_t)G * N > 65535) return PA_ERR_ARG;
-                lds = std::max(lds, msc_lds_bound(N, G, ea, s->threads / 64));
-            } else {
-                if (sl.d.theta <= 0) continue;
-                if (sweeps_wide(sl.d, G, s->threads, s->lds_limit)) {
-                    s->wide.push_back({k, sl.d.L, groups_cap_of(sl.d), npop, sl.d.theta, ea ? 1 : 0});
-                    continue;
-                }
-                lds = std::max(lds, msc_stream_lds(N, G, ea, s->threads / 64));
-            }
-            for (int p = 0; p < npop; ++p)
-                for (int g = 0; g < groups_cap_of(sl.d); g += G)
-                    sweep.push_back({k, p, g, std::min(G, groups_cap_of(sl.d) - g)});
-        }
     }
-    if (lds > (size_t)s->lds_limit) return PA_ERR_ARG;
-    std::stable_sort(sweep.begin(), sweep.end(), [s](const SweepItem &a, const SweepItem &b) {
-        const long wa = (long)a.ngroups * s->slots[a.run].d.L * s->slots[a.run].d.L;
-        const long wb = (long)b.ngroups * s->slots[b.run].d.L * s->slots[b.run].d.L;
-        return wa > wb;
-    });
     // lattice size and model of each slot's run, for the per-class sweep launches
     std::vector<int> run_L(std::max(hi, 1), 0), run_ea(std::max(hi, 1), 0);
     for (int k = 0; k < hi; ++k)
@@ -316,18 +357,27 @@ pa_status rebuild(pa_server *s)
             run_ea[k] = s->slots[k].d.model == PA_EA_PMJ;
         }
     const int mode = s->repr == PA_MSC64 ? serve_mode(s) : 3;   // the knobs are the bit-packed layout's
-    {
+    ServeSweeps list;
+    for (const bool small : {false, true}) {
+        const pa_status ls = sweep_list(s, small, list);
+        if (ls != PA_OK) return ls;
         SweepClass probe[MAX_SWEEP_CLASSES];
         // orders the list by class; a serving mix keeps one launch for its
         // sizes (their classes are too small to fill the chip one by one)
-        if (sweep_classes(sweep, run_L, run_ea, probe, s->threads, mode, false) < 0)
-            return PA_ERR_ARG;
+        if (sweep_classes(list.items, run_L, run_ea, probe, list.threads, mode, false) < 0) return PA_ERR_ARG;
+        if (small && s->sweep_cap) {
+            s->arena.release(s->sweep_off, s->sweep_cap);
+            s->sweep_cap = 0;
+        }
+        if (grow(s, s->items_off, s->items_cap, sizeof(Item) * std::max<size_t>(n_items, 1)) &&
+            grow(s, s->chunks_off, s->chunks_cap, sizeof(ChunkItem) * std::max<size_t>(n_chunks, 1)) &&
+            grow(s, s->meas_off, s->meas_cap, sizeof(SweepItem) * std::max<size_t>(n_meas, 1)) &&
+            grow(s, s->sweep_off, s->sweep_cap, list_bytes(list.items)))   // last: make_room gives it back
+            break;
+        if (small) return PA_ERR_NOMEM;
     }
-    if (!grow(s, s->items_off, s->items_cap, sizeof(Item) * std::max<size_t>(n_items, 1)) ||
-        !grow(s, s->chunks_off, s->chunks_cap, sizeof(ChunkItem) * std::max<size_t>(n_chunks, 1)) ||
-        !grow(s, s->sweep_off, s->sweep_cap, sizeof(SweepItem) * std::max<size_t>(sweep.size(), 1)) ||
-        !grow(s, s->meas_off, s->meas_cap, sizeof(SweepItem) * std::max<size_t>(n_meas, 1)))
-        return PA_ERR_NOMEM;
+    std::vector<SweepItem> &sweep = list.items;
+    s->wide = list.wide;
     size_t ai = 0, ac = 0, am = 0;
     for (int k = 0; k < s->max_slots; ++k) {
         const Slot &sl = s->slots[k];
@@ -376,17 +426,17 @@ pa_status rebuild(pa_server *s)
     c.any_exact_dos = exact;
     c.sweep_items = (const SweepItem *)(s->base + s->sweep_off);
     c.n_sweep_items = (int)sweep.size();
-    c.sweep_threads = s->threads;
+    c.sweep_threads = list.threads;
     c.sweep_dense = mode & 0xFF;
     c.sweep_pooled = mode >> 8;
     c.any_swept = swept;
     c.any_unswept = unswept;
     c.n_sweep_classes = 0;
     if (!sweep.empty()) {
-        if (prepare_msc_lds(lds) != hipSuccess) return sfail(s);
-        const int ncls = sweep_classes(sweep, run_L, run_ea, c.sweep_cls, s->threads, mode, false);
+        if (prepare_msc_lds(list.lds) != hipSuccess) return sfail(s);
+        const int ncls = sweep_classes(sweep, run_L, run_ea, c.sweep_cls, list.threads, mode, false);
         if (ncls < 0) return PA_ERR_ARG;
-        if (!sweep_class_grids(c.sweep_cls, ncls, s->threads, s->repr == PA_MSC64 && s->persistent)) return sfail(s);
+        if (!sweep_class_grids(c.sweep_cls, ncls, list.threads, s->repr == PA_MSC64 && s->persistent)) return sfail(s);
         c.n_sweep_classes = ncls;
         c.n_sweep_items = (int)sweep.size();
     }
@@ -508,6 +558,13 @@ pa_status pa_server_admit(pa_server *s, const pa_run_desc *desc, int32_t *slot)
     Slot &sl = s->slots[k];
     const BlockPlan b = plan_block(d, s->repr);
     size_t off = 0;
+    const size_t tb = t < 0 ? table_bytes(d) : 0;
+    {
+        Arena probe = s->arena;
+        size_t at = 0;
+        const bool fits = probe.alloc(b.bytes, &at) && (!tb || probe.alloc(tb, &at));
+        if (!fits && !make_room(s, b.bytes, tb)) return PA_ERR_NOMEM;
+    }
     if (!s->arena.alloc(b.bytes, &off)) return PA_ERR_NOMEM;
     bool new_table = false;
     if (t < 0) {

@@ -220,3 +220,43 @@ def test_persistent_grid_and_pooled_lists_same_results():
     assert a.stats() == b.stats()
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("repr_", ["msc", "int8"])
+@pytest.mark.parametrize("second", [False, True])
+def test_arena_just_large_enough(repr_, second):
+    """An arena that holds the request and its lists with few sweep items (20
+    of 16 groups each in the bit-packed layout, none in the int8 layout, which
+    then sweeps from memory), but not the 313 items of one group each that the
+    shape by the work per SIMD has; with a second request, one that holds both,
+    where the first one's longer list has taken the second one's place
+    meanwhile.  Both are admitted and run to the records they have alone."""
+    say(f"serving in a tight arena {repr_} second={second}")
+    d = [W.run_desc(16, W.EA_PMJ, seed=W.RUN_SEED_BASE + 0x910 + R, R=R, theta=2, K=6, beta_f=1.0) for R in (20_000, 2000)]
+
+    def lines(n):
+        return (n + 255) & ~255
+    roomy = Server(256 << 20, max_slots=4, repr_=repr_)
+    header = (256 << 20) - roomy.info()["largest_free"]
+    assert roomy.admit(d[0]) is not None
+    roomy.step()
+    used = roomy.info()["bytes_used"]
+    need = used - lines(32 * 313) + lines(32 * (20 if repr_ == "msc" else 1))
+    assert need < used
+    assert roomy.admit(d[1]) is not None
+    block = roomy.info()["bytes_used"] - used
+    roomy.close()
+    # while lists grow the old ones are still there
+    srv = Server(header + need + (block + 9 * 1024 if second else 0), max_slots=4, repr_=repr_)
+    slots = [srv.admit(d[0])]
+    assert slots[0] is not None
+    fin = srv.step()
+    if second:
+        slots.append(srv.admit(d[1]))
+        assert slots[1] is not None
+    for _ in range(d[0]["K"] - 1):
+        fin = fin + srv.step()
+    assert sorted(fin) == sorted(slots)
+    for slot, desc in zip(slots, d):
+        assert_same(srv.read_obs(slot, desc), alone(desc, repr_), slot)
+    srv.close()
