@@ -361,9 +361,8 @@ pa_status pa_get_tuning(pa_ctx *ctx, int32_t L, int32_t *threads, int32_t *group
  * to the remaining schedule) real temperature steps of this context for
  * each candidate launch shape, timing the sweep launches with HIP events:
  * first threads x dense_calls x persistent x pooled with the current groups per L,
- * then groups per workgroup one L at a time (heaviest L first), then, with a
- * persistent grid, 2..4 chunks of sweeps per item.  Every
- * candidate's records and exact work counters must hash to the starting
+ * then groups per workgroup one L at a time (heaviest L first), then 2..4
+ * chunks of sweeps per item on the persistent grid.  Every candidate's records and exact work counters must hash to the starting
  * shape's value; one that differs is rejected (counted in *n_rejected, which
  * is 0 unless a kernel is wrong).  The fastest accepted shape is applied and
  * the context is returned to its starting state, so the tuned run continues
@@ -372,7 +371,8 @@ pa_status pa_get_tuning(pa_ctx *ctx, int32_t L, int32_t *threads, int32_t *group
  * cache_path (host string, may be NULL): JSON file of shapes keyed by
  * (device architecture, representation, L).  If it holds every L of the
  * context, those shapes are applied without a search (*n_tried = 0); after a
- * search the chosen shape is merged into it.  A cache that cannot be written
+ * search the chosen shape is merged into it (with the grid that whole items
+ * did best on, which a server takes).  A cache that cannot be written
  * gives PA_ERR_ARG after the shape has been applied. */
 pa_status pa_autotune(pa_ctx *ctx, int32_t steps, const char *cache_path, int32_t *n_tried,
                       int32_t *n_rejected);

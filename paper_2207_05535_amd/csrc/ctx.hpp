@@ -87,7 +87,8 @@ int groups_of_2048(int L);   // replica groups whose colours hold about 2048 sit
 // Launch shape of the batched sweep for these runs where nobody has chosen
 // one: threads per workgroup and replica groups per workgroup of each L.
 void default_shape(const pa_run_desc *const *runs, int n, int *threads, std::map<int, int> &groups);
-// Batched-sweep shape for lattice size L from an autotuner cache file.
+// Batched-sweep shape of whole items (no chunks of sweeps) for lattice size L
+// from an autotuner cache file.
 bool tuning_from_cache(const char *path, int L, int *threads, int *groups, int *dense, int *persistent,
                        int *pooled);
 

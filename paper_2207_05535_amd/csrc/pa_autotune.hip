@@ -40,6 +40,7 @@ struct CacheEntry {
     int L, threads, groups, dense, persistent, pooled;
     double sweep_us;
     int chunks;
+    int whole_persistent;   // `persistent` for launches of whole items, which the server's are
 };
 
 std::string device_arch()
@@ -64,12 +65,16 @@ std::vector<CacheEntry> read_cache(const char *path)
         e.sweep_us = 0.0;
         e.pooled = 0;
         e.chunks = 1;   // entries written before the chunk knob existed
+        e.whole_persistent = -1;
         const int n = std::sscanf(line,
                                   " {\"arch\": \"%63[^\"]\", \"repr\": \"%15[^\"]\", \"L\": %d, \"threads\": %d, "
                                   "\"groups\": %d, \"dense\": %d, \"persistent\": %d, \"pooled\": %d, "
-                                  "\"sweep_us\": %lf, \"chunks\": %d",
+                                  "\"sweep_us\": %lf, \"chunks\": %d, \"whole_persistent\": %d",
                                   arch, repr, &e.L, &e.threads, &e.groups, &e.dense, &e.persistent, &e.pooled,
-                                  &e.sweep_us, &e.chunks);
+                                  &e.sweep_us, &e.chunks, &e.whole_persistent);
+        // entries written before it was kept: chunks were tried only where
+        // whole items did best on the persistent grid
+        if (e.whole_persistent != 0 && e.whole_persistent != 1) e.whole_persistent = e.persistent;
         if (e.chunks < 1 || e.chunks > MAX_SWEEP_CHUNKS) e.chunks = 1;
         if (n >= 7) {
             e.arch = arch;
@@ -91,9 +96,10 @@ bool write_cache(const char *path, const std::vector<CacheEntry> &entries)
         const CacheEntry &e = entries[k];
         std::fprintf(f,
                      "  {\"arch\": \"%s\", \"repr\": \"%s\", \"L\": %d, \"threads\": %d, \"groups\": %d, "
-                     "\"dense\": %d, \"persistent\": %d, \"pooled\": %d, \"sweep_us\": %.3f, \"chunks\": %d}%s\n",
+                     "\"dense\": %d, \"persistent\": %d, \"pooled\": %d, \"sweep_us\": %.3f, \"chunks\": %d, "
+                     "\"whole_persistent\": %d}%s\n",
                      e.arch.c_str(), e.repr.c_str(), e.L, e.threads, e.groups, e.dense, e.persistent, e.pooled,
-                     e.sweep_us, e.chunks, k + 1 < entries.size() ? "," : "");
+                     e.sweep_us, e.chunks, e.whole_persistent, k + 1 < entries.size() ? "," : "");
     }
     std::fprintf(f, "]}\n");
     const bool ok = std::fclose(f) == 0;
@@ -224,7 +230,7 @@ bool tuning_from_cache(const char *path, int L, int *threads, int *groups, int *
             *threads = e.threads;
             *groups = e.groups;
             *dense = e.dense;
-            *persistent = e.persistent;
+            *persistent = e.whole_persistent;
             *pooled = e.pooled;
             return true;
         }
@@ -348,6 +354,7 @@ extern "C" pa_status pa_autotune(pa_ctx *c, int32_t steps, const char *cache_pat
     // chunks of sweeps on the persistent grid, also where whole items are
     // better off without it (they take effect only where the items outnumber
     // the resident workgroups)
+    const int whole_persistent = best.persistent;
     for (int k = 2; k <= MAX_SWEEP_CHUNKS; ++k) {
         Shape s = best;
         s.persistent = 1;
@@ -366,7 +373,8 @@ extern "C" pa_status pa_autotune(pa_ctx *c, int32_t steps, const char *cache_pat
     if (cache_path) {
         for (int L : Ls) {
             CacheEntry e{arch,        "msc",           L, best.threads, best.groups[L], best.dense, best.persistent,
-                         best.pooled, 1e3 * best_ms / steps, best.chunks};
+                         best.pooled, 1e3 * best_ms / steps, best.chunks,
+                         whole_persistent};
             bool replaced = false;
             for (auto &x : cache)
                 if (x.arch == arch && x.repr == "msc" && x.L == L) {

@@ -260,3 +260,31 @@ def test_arena_just_large_enough(repr_, second):
     for slot, desc in zip(slots, d):
         assert_same(srv.read_obs(slot, desc), alone(desc, repr_), slot)
     srv.close()
+
+
+def test_cache_keeps_the_whole_item_shape(tmp_path):
+    """Chunks of sweeps are tried on the persistent grid also where whole items
+    do better without it; the cache keeps what whole items do best with, which
+    is what a server launches, beside the choice with chunks."""
+    say("cached shape of whole items")
+    cache = str(tmp_path / "tune.json")
+    d = W.run_desc(32, W.EA_PMJ, seed=W.RUN_SEED_BASE + 0x950, disorder_seed=4, R=150_000, theta=3, K=5, beta_f=1.0)
+    ctx = pa.Context([d], "msc")
+    assert ctx.autotune(steps=1, cache_path=cache)["rejected"] == 0
+    assert ctx.tuning(32)["persistent"] in (0, 1)
+    (e,) = json.load(open(cache))["entries"]
+    assert e["whole_persistent"] in (0, 1)
+    assert e["persistent"] == (1 if e["chunks"] > 1 else e["whole_persistent"])
+    ctx.run(1, 5)
+    want = ctx.obs()[0].T
+    ctx.close()
+    for whole in (0, 1):
+        line = dict(e, persistent=1, chunks=2, whole_persistent=whole)
+        with open(cache, "w") as f:
+            f.write('{"pa_tuning_cache": 1, "entries": [\n  ' + json.dumps(line) + "\n]}\n")
+        srv = Server(pa.pa_server_footprint(d, "msc") + (8 << 20), max_slots=1, tuning_cache=cache)
+        slot = srv.admit(d)
+        for _ in range(4):
+            srv.step()
+        assert_same(srv.read_obs(slot, d), np.ascontiguousarray(want), whole)
+        srv.close()
