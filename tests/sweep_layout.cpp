@@ -80,3 +80,5 @@ extern "C" void fused_layout(int R_cap, int64_t *out)
 }
 
 extern "C" int fused_max() { return FUSED_MAX; }
+
+extern "C" int64_t pairing_lds(int R_cap) { return (int64_t)wang_lds_bytes(R_cap); }

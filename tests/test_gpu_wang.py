@@ -253,3 +253,25 @@ def test_pairing_of_tiny_runs_alone(kind):
             paired += 1
     assert paired > len(runs)
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", [W.Q_WANG, W.Q_WANG_RDM])
+def test_pairing_at_the_lds_limit(kind):
+    """The largest population whose pairing fits a workgroup's LDS, and the
+    next one, which is paired in global memory."""
+    say(f"permutation pairing at the LDS limit kind={kind}")
+    runs = [W.run_desc(6, W.EA_PMJ, seed=W.RUN_SEED_BASE + 0x5700 + R, disorder_seed=12, R=R, theta=1, K=5, beta_f=1.0,
+                       resampling=W.MULTINOMIAL, overlap=kind) for R in (20352, 20353)]
+    ctx = pa.Context(runs, "msc")
+    for i in range(5):
+        if i:
+            ctx.step(i)
+        for r, d in enumerate(runs):
+            fam = ctx.state(r, 0)[2]
+            st, pairs = ctx.pairing(r)
+            assert not large_family(fam)
+            pi = oracle.random_permutation(d["seed"], i, 0, len(fam), 0)
+            sigma = oracle.random_permutation(d["seed"], i, 0, len(fam), 1) if kind == W.Q_WANG_RDM else None
+            st_o, want = oracle.wang_repair(fam, pi, sigma)
+            assert st == st_o == 0 and np.array_equal(pairs, want), (r, i)
+    ctx.close()

@@ -20,7 +20,7 @@ def layout(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
                     "-I/opt/rocm/include", "-I" + CSRC, os.path.join(HERE, "sweep_layout.cpp"), "-o", str(out)], check=True)
     lib = C.CDLL(str(out))
-    lib.sweep_lds.restype = lib.wrong_candidates.restype = C.c_int64
+    lib.sweep_lds.restype = lib.wrong_candidates.restype = lib.pairing_lds.restype = C.c_int64
     return lib
 
 
@@ -61,3 +61,9 @@ def test_fused_resampling_layout(layout):
         layout.fused_layout(R, out)
         assert out[1] % 16 == 0 and out[0] <= out[1] < out[2] <= out[3], R
     assert out[3] + 4400 <= LDS
+
+
+def test_largest_population_paired_in_lds(layout):
+    """Runs of up to 20352 replicas leave the pairing kernel the kilobyte it
+    asks for beside its arrays; the next size does not."""
+    assert layout.pairing_lds(20352) + 1024 == LDS < layout.pairing_lds(20353) + 1024
