@@ -61,13 +61,14 @@ void plan_table(Planner &P, int N, const pa_run_desc &d, TableOff &T);
 Layout plan(const pa_run_desc *runs, int n_runs, pa_repr repr);
 void compute_tables(const pa_run_desc &d, int N, std::vector<uint64_t> &X, std::vector<double> &x,
                     std::vector<uint64_t> &T);
+// Whether the populations of this run are resampled by a workgroup each, among
+// n populations of more than alone_any replicas (smaller ones always are).
+inline int alone_any(const pa_run_desc &d) { return d.resampling == PA_MULTINOMIAL ? 6144 : 7168; }
+bool resampled_alone(const pa_run_desc &d, int n);
 // RunInfo of a run whose buffers start at `base` (offsets o) and tables at
 // `tbase` (offsets T); records through obs with the given stride/offset.
-// Whether a population of this run is resampled by one workgroup, in a
-// context of n populations.
-bool resampled_alone(const pa_run_desc &d, int n);
-RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, bool fused, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
-                     pa_obs *obs, int obs_stride, int obs_off);
+RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, bool fused, uint8_t *base, const RunOff &o, uint8_t *tbase,
+                     const TableOff &T, pa_obs *obs, int obs_stride, int obs_off);
 PopState initial_popstate(const pa_run_desc &d);
 // LDS of the permutation pairing in LDS: that of the largest such run that
 // fits, 0 if none does; *large: some run does not.

@@ -842,11 +842,10 @@ __global__ void __launch_bounds__(CH_THREADS) k_parent(const ChunkItem *items, c
 // block's first (offsets are below CH_PER 2^40); a draw whose high bits equal
 // the one found reads the exact prefix.  Bound by the latency of a single
 // workgroup's passes where there are few populations, by LDS reads and the
-// generator where every CU has one.  Draws, scan, checks and parent map: 303
-// -> 58 us for 256 populations of 2e4 (eleven dependent reads of memory per
-// draw before), 16 -> 10 us for one of 1000, 18 -> 18 for one of 8000; one of
-// 2e4 takes 38 chunk by chunk and 58 here, so above 8192 it needs 64
-// populations to pay (32 of 2e4: 61 and 58).
+// generator where every CU has one.  Draws, scan, checks and parent map for
+// 256 populations of 2e4: 58 us, 303 in launches with eleven dependent reads
+// of memory per draw; one of 1000: 10, 16 before.  Where it pays against the
+// present launches: resampled_alone.
 constexpr int FINE_SHIFT = 11;
 static_assert(CH_PER == 8, "40 + 3 bits of offset");
 constexpr int GUIDE_BITS = 11;

@@ -514,18 +514,27 @@ bool dos_thresholds(const pa_run_desc &d, std::vector<uint64_t> &out)
     return true;
 }
 
-// One workgroup per population is a chain of passes on one CU: up to 8192
-// replicas no longer than the launches it replaces (18 us each way at 8000,
-// 10 against 16 at 1000), above that only with enough populations for the
-// CUs (us of step (iii) without the copy, 2e4 replicas, alone / by chunks:
-// 58 / 38 for 16 populations, 58 / 61 for 32, 58 / 303 for 256).
+// One workgroup per population is a chain of passes on one CU, whose length
+// grows with the population; chunk by chunk every pass is a launch over all
+// populations.  So small populations are resampled alone, and larger ones
+// where there are enough of them for the CUs: draws that look for their
+// parents in LDS pay from 32 populations on, the nearest-integer counts, whose
+// chunks run at memory speed, from one population per CU.  Steps of
+// populations of 8 x 8 sites without sweeps, us alone / by chunks: one of 6000
+// 48 / 47 multinomial, 44 / 46 nearest-integer, of 8192 52 / 48 and 48 / 47,
+// of 20000 74 / 49 and 65 / 48; 16 of 20000 86 / 78 and 77 / 59; 32 of 8192
+// 62 / 71 and 58 / 57, of 20000 102 / 109 and 91 / 76; 128 of 10000 118 / 167
+// and 105 / 108, of 20000 194 / 280 and 167 / 158; 256 of 20000 323 / 518 and
+// 273 / 277.
 bool resampled_alone(const pa_run_desc &d, int n)
 {
-    return d.R_cap <= (n >= 64 ? FUSED_MAX : 8192);
+    if (d.R_cap <= alone_any(d)) return true;
+    if (d.resampling == PA_MULTINOMIAL) return n >= 32 && d.R_cap <= FUSED_MAX;
+    return n >= 128 && d.R_cap <= (n >= 256 ? FUSED_MAX : 10240);
 }
 
-RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, bool fused, uint8_t *base, const RunOff &o, uint8_t *tbase, const TableOff &T,
-                     pa_obs *obs, int obs_stride, int obs_off)
+RunInfo make_runinfo(const pa_run_desc &d, pa_repr repr, bool fused, uint8_t *base, const RunOff &o, uint8_t *tbase,
+                     const TableOff &T, pa_obs *obs, int obs_stride, int obs_off)
 {
     RunInfo I;
     std::memset(&I, 0, sizeof(I));
@@ -916,8 +925,8 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
             }
     }
     const Layout &Lo = c->lo;
-    int n_pops = 0;
-    for (int r = 0; r < n_runs; ++r) n_pops += n_pop_of(runs[r].overlap);
+    int n_large = 0;
+    for (int r = 0; r < n_runs; ++r) n_large += runs[r].R_cap > alone_any(runs[r]) ? n_pop_of(runs[r].overlap) : 0;
     c->lc.any_chained = false;
 
     // host images of the device-side records
@@ -939,7 +948,7 @@ pa_status pa_create(const pa_run_desc *runs, int32_t n_runs, pa_repr repr, void 
             if (dos_run[o.table] < 0) dos_run[o.table] = r;
             o.dos = Lo.runs[dos_run[o.table]].dos;
         }
-        const bool fused = resampled_alone(d, n_pops);
+        const bool fused = resampled_alone(d, n_large);
         if (fused) c->lc.fused_max = std::max(c->lc.fused_max, d.R_cap);
         else c->lc.any_chained = true;
         c->hinfo[r] = make_runinfo(d, repr, fused, c->ws, o, c->ws, T, at<pa_obs>(c, Lo.obs), n_runs * Lo.npop_ctx,

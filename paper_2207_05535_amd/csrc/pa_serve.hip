@@ -615,7 +615,8 @@ pa_status pa_server_admit(pa_server *s, const pa_run_desc *desc, int32_t *slot)
             return st;
     }
     const int npop = n_pop_of(d.overlap);
-    const RunInfo I = make_runinfo(sl.d, s->repr, resampled_alone(sl.d, 1), blk, b.o, tbase, T.T, (pa_obs *)(blk + b.obs), npop, 0);
+    const RunInfo I = make_runinfo(sl.d, s->repr, resampled_alone(sl.d, 1), blk, b.o, tbase, T.T,
+                                   (pa_obs *)(blk + b.obs), npop, 0);
     PopState hst[MAX_POP];
     std::memset(hst, 0, sizeof(hst));
     for (int p = 0; p < npop; ++p) hst[p] = initial_popstate(sl.d);

@@ -1041,3 +1041,34 @@ def test_counts_between_reweighting_and_resampling(resampling, R):
         assert c.obs().tobytes() == whole.obs().tobytes()
         c.close()
     whole.close()
+
+
+@pytest.mark.parametrize("resampling,caps", [
+    (W.MULTINOMIAL, [6144, 6145]), (W.NEAREST_INT, [7168, 7169]),
+    # 31 and 32 populations above 6144, and small ones, which do not count
+    (W.MULTINOMIAL, [6145 + 500 * m for m in range(31)] + [500] * 3), (W.MULTINOMIAL, [6145 + 512 * m for m in range(32)]),
+    (W.NEAREST_INT, [10240] * 127), (W.NEAREST_INT, [10240] * 127 + [10241]),
+    (W.NEAREST_INT, [7200] * 254 + [22016, 22017])])
+def test_where_populations_are_resampled_alone(resampling, caps):
+    """On both sides of the line between one workgroup per population and
+    chunks, by capacity and number of populations: the records and states of
+    the first and the last runs are those of the same runs in contexts of
+    their own, which lie on one side."""
+    say(f"resampling rule mode={resampling} {len(caps)} runs of up to {max(caps)}")
+    runs = [W.run_desc(4, W.FM, seed=W.RUN_SEED_BASE + 0x7E00 + m, R=c if resampling == W.MULTINOMIAL else int(0.9 * c),
+                       R_cap=c, theta=1, K=5, beta_f=1.5, resampling=resampling) for m, c in enumerate(caps)]
+    ctx = pa.Context(runs, "msc")
+    ctx.run(1, 5)
+    obs = ctx.obs()
+    for m in {0, 1, len(caps) - 2, len(caps) - 1}:
+        alone = pa.Context([runs[m]], "msc")
+        alone.run(1, 5)
+        assert alone.obs()[0].tobytes() == obs[m].tobytes(), m
+        for a, b in zip(alone.state(0), ctx.state(m)):
+            assert np.array_equal(a, b), m
+        alone.close()
+    m = len(caps) - 1
+    orc = oracle.OracleRun(runs[m]).run_all()
+    assert_obs_equal(obs[m, :1], orc.obs(), f"run {m}")
+    assert_state_equal(ctx, orc, m, f"run {m}")
+    ctx.close()
