@@ -1784,8 +1784,7 @@ __device__ __forceinline__ uint32_t stream_sweeps(const SweepJob &J, uint64_t *l
                 return (uint32_t)(ONE ? J.group0 : J.group0 + (int)((pk >> 12) & 0xFFu));
             };
             using UG = std::integral_constant<bool, ONE>;
-            // one chunk: a unit (site word) per lane.  own: its lattice word (of
-            // the workgroup's, also on lanes with no unit);
+            // one chunk: a unit (site word) per lane.  own: its lattice word;
             // dh, du, dd: offsets of the neighbours beside the word at the
             // same place of the other colour; ug: gs is the same on every lane
             auto chunk = [&](bool in, int own, int dh, int du, int dd, uint32_t n, int gs, auto ug) {
@@ -1805,7 +1804,7 @@ __device__ __forceinline__ uint32_t stream_sweeps(const SweepJob &J, uint64_t *l
                     }
                 }
                 lockstep_calls<decltype(ug)::value>(q, dense, dm, J.Th, n, g, one, und, acc, wcalls);
-                flip_word(&lat[own], acc & ~und);
+                at_unit(in, own, [&](int w) { flip_word(&lat[w], acc & ~und); });
                 stream_push(q, und, one, n | ((uint32_t)dense << 20) | (ONE ? 0u : (uint32_t)gs << 12));
                 stream_rounds<ONE>(q, word, group, wcalls);   // room for the next chunk's entries
             };
@@ -1842,7 +1841,7 @@ __device__ __forceinline__ uint32_t stream_sweeps(const SweepJob &J, uint64_t *l
                 for (int u0 = J.ub; u0 < J.ue; u0 += 64) {
                     const int p = (w.y + colour) & 1;
                     const bool in = u0 + lane < J.ue;
-                    chunk(in, w.word(J, colour, in, lane), w.dh(J, p), w.du(J), w.dd(J),
+                    chunk(in, w.word(J, colour), w.dh(J, p), w.du(J), w.dd(J),
                           2u * (uint32_t)w.k + (uint32_t)p, ONE ? 0 : w.gs, UG{});
                     w.step(J, gq, kr, yr, mr);
                 }
@@ -1913,7 +1912,7 @@ __device__ __forceinline__ void general_item(const SweepItem &item, const RunInf
             UnitWalk w = first;
             for (int u0 = J.ub; u0 < J.ue; u0 += 64) {
                 const bool in = u0 + lane < J.ue;
-                const int p = (w.y + colour) & 1, own = w.word(J, colour, in, lane);
+                const int p = (w.y + colour) & 1, own = w.word(J, colour);
                 const uint32_t n = 2u * (uint32_t)w.k + (uint32_t)p, g = (uint32_t)(J.group0 + w.gs);
                 uint64_t und = 0, one = 0, acc = 0;
                 if (in) {
@@ -1940,7 +1939,7 @@ __device__ __forceinline__ void general_item(const SweepItem &item, const RunInf
                         acc = bop3<LUT_SEL>(was, less, acc);
                     }
                 }
-                flip_word(&lat[own], acc & ~und);
+                at_unit(in, own, [&](int w) { flip_word(&lat[w], acc & ~und); });
                 const uint64_t need = wave_ballot(und != 0);
                 int base_slot = J.ub + cnt;
                 if (pool && need) {

@@ -10,7 +10,7 @@ using namespace pa;
 
 // Walks every wavefront of `threads` over `groups` lattices of side L as the
 // sweep does.  out[0], out[1]: the smallest and the largest lattice word that
-// a lane addresses, with a unit or without; out[2], out[3]: the same for the
+// a lane flips; out[2], out[3]: the same for the
 // neighbours it reads; out[4]: how often the units are visited twice or not
 // at all; out[5]: lanes without a unit.
 extern "C" void sweep_walk(int L, int threads, int groups, int64_t *out)
@@ -30,12 +30,14 @@ extern "C" void sweep_walk(int L, int threads, int groups, int64_t *out)
                 w.start(J, std::min(ub, units - 1) + lane);
                 for (int u0 = ub; u0 < ue; u0 += 64) {
                     const bool in = u0 + lane < ue;
-                    const int own = w.word(J, colour, in, lane), o = own + (colour ? -J.nh : J.nh);
-                    out[0] = std::min<int64_t>(out[0], own);
-                    out[1] = std::max<int64_t>(out[1], own);
+                    const int own = w.word(J, colour), o = own + (colour ? -J.nh : J.nh);
+                    at_unit(in, own, [&](int word) {
+                        out[0] = std::min<int64_t>(out[0], word);
+                        out[1] = std::max<int64_t>(out[1], word);
+                        if (word >= 0 && word < groups * J.N) ++seen[word];
+                    });
                     out[5] += in ? 0 : 1;
                     if (in) {
-                        ++seen[own];
                         for (int d : {0, w.dh(J, (w.y + colour) & 1), w.du(J), w.dd(J)}) {
                             out[2] = std::min<int64_t>(out[2], o + d);
                             out[3] = std::max<int64_t>(out[3], o + d);

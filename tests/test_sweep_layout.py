@@ -26,9 +26,9 @@ def layout(tmp_path_factory):
 
 @pytest.mark.parametrize("threads", [64, 128, 256, 512, 1024])
 def test_sweep_addresses_stay_in_the_lattices(layout, threads):
-    """Every word a lane of the streamed sweep addresses, also one past its
-    wavefront's last unit, lies in the workgroup's lattices, for every lattice
-    size and the numbers of groups that fit; every unit is visited once."""
+    """Every word a lane of the streamed sweep flips or reads lies in the
+    workgroup's lattices, for every lattice size and the numbers of groups that
+    fit; every unit is visited once."""
     idle = 0
     for L in list(range(4, 95, 2)) + [100, 110, 126, 128]:
         for groups in (1, 2, 3, 4, 5, 7, 16, 41, 64, 255, 256):
