@@ -91,7 +91,7 @@ def kernel_source_hash():
     comments and layout removed (an edit of a comment keeps the counters)."""
     import re
     h = hashlib.sha256()
-    for f in ("kernels.hip", "metropolis.hpp", "philox.hpp", "pa_internal.hpp"):
+    for f in ("kernels.hip", "metropolis.hpp", "philox.hpp", "pa_internal.hpp", "unit_walk.hpp"):
         with open(os.path.join(ROOT, "paper_2207_05535_amd", "csrc", f), encoding="utf-8") as fh:
             src = fh.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)

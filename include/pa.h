@@ -360,11 +360,12 @@ pa_status pa_get_tuning(pa_ctx *ctx, int32_t L, int32_t *threads, int32_t *group
  * current state (all steps so far measured) it runs `steps` (1..64, clipped
  * to the remaining schedule) real temperature steps of this context for
  * each candidate launch shape, timing the sweep launches with HIP events:
- * first threads x dense_calls x persistent x pooled with the current groups per L,
- * then groups per workgroup one L at a time (heaviest L first), then 2..4
- * chunks of sweeps per item on the persistent grid.  Every candidate's records and exact work counters must hash to the starting
- * shape's value; one that differs is rejected (counted in *n_rejected, which
- * is 0 unless a kernel is wrong).  The fastest accepted shape is applied and
+ * first threads x dense_calls x persistent x pooled with the current groups
+ * per L, then groups per workgroup one L at a time (heaviest L first), then
+ * 2..4 chunks of sweeps per item on the persistent grid.  Every candidate's
+ * records and exact work counters must hash to the starting shape's value;
+ * one that differs is rejected (counted in *n_rejected, which is 0 unless a
+ * kernel is wrong).  The fastest accepted shape is applied and
  * the context is returned to its starting state, so the tuned run continues
  * exactly as an untuned one would.  Takes a pinned host snapshot of the
  * workspace for the duration of the call.

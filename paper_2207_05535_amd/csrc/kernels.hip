@@ -152,7 +152,7 @@ __device__ __forceinline__ void store_block(T *a, int jb, int end, const T (&v)[
 // Counts this workgroup in once its first thread's stores and atomics have
 // completed; true in the workgroup that comes last of n.  The counter is zero
 // again when it has come (one kernel of a step uses it after the other).  To
-// be called by the whole workgroup; includes a barrier.
+// be called by the whole workgroup; a barrier only for n > 1.
 __device__ __forceinline__ bool last_of(int32_t *done, int n)
 {
     __shared__ int last;
@@ -728,19 +728,19 @@ __global__ void __launch_bounds__(CH_THREADS) k_mn_draws(const ChunkItem *items,
     int32_t *C = R.C[it.pop];
     __shared__ uint64_t sB[CH];   // the chunk bases
     // largest j with P_j <= t in two levels: the last chunk whose base is
-    // <= t (chunk bases staged in LDS), then inside that chunk
+    // <= t (chunk bases staged in LDS), then inside it (last_not_above)
     const int nch = (Rp + CH - 1) / CH;
     const bool staged = nch <= CH;
     if (staged)
         for (int k = threadIdx.x; k < nch; k += CH_THREADS) sB[k] = B[k];
     __syncthreads();
-    // Fixed power-of-two steps: the largest index whose key is <= t,
-    // starting from index 0, whose key is 0.
     const int d = d0 + part * CH_THREADS + (int)threadIdx.x;
     if (d < R.R) {
         const u32x4 o = philox10((uint32_t)d, 0, (uint32_t)S.i, c3, R.key0, R.key1);
         const uint64_t v = (uint64_t)o.x | ((uint64_t)o.y << 32);
-        uint64_t t = umul64hi(v, SX);
+        const uint64_t t = umul64hi(v, SX);
+        // the chunk, by halving in power-of-two steps from the first, whose
+        // base is 0
         int k = 0;
         for (int step = nch > 1 ? 1 << (31 - __builtin_clz(nch - 1)) : 0; step > 0; step >>= 1) {
             const int m = k + step;
@@ -3933,8 +3933,8 @@ size_t msc_lds_bytes(int N, int groups, bool ea, int threads, int mode)
     return msc_lds_need(N, groups, ea, threads / 64, mode);
 }
 
-// The sweep kernel for a launch: one compiled for a single (L, model) when
-// every run of the context has it, else the one that dispatches per item.
+// The sweep kernel for a launch: one compiled for a single (L, model), the one
+// for any size of a model (L = 0), or the one that dispatches per item.
 using SweepKernel = void (*)(const SweepItem *, int, const RunInfo *, const PopState *, int, unsigned long long *,
                              unsigned int *, unsigned int *, SweepList *, int, uint32_t);
 
@@ -3976,7 +3976,8 @@ hipError_t prepare_msc_lds(size_t bytes)
 // One launch per class (sweep_classes below): the kernel compiled for the
 // lattice size and model when every sweeping run shares them; one such
 // kernel per (size, model) when every class is large enough to fill the
-// chip; else the kernel that dispatches per item.  (On the serving mix,
+// chip; else the kernel for any size of the model they share, or the one that
+// dispatches per item.  (On the serving mix,
 // whose per-size launches are too small to fill the chip, launching each
 // size on its own measured 3.03 against 3.54 thousand flips/ns while busy.)
 hipError_t launch_sweep_msc(const LaunchCtx &c)

@@ -57,6 +57,8 @@ struct LaunchCtx {
 
 hipError_t launch_fill_u32(void *p, uint32_t v, size_t n, hipStream_t s);
 hipError_t launch_init(const LaunchCtx &c, const uint64_t *dseed);
+hipError_t launch_clear_draws(const LaunchCtx &c);   // after a restore
+hipError_t prepare_fused_lds(size_t bytes);
 hipError_t launch_anneal(const LaunchCtx &c);
 hipError_t launch_resample(const LaunchCtx &c);
 hipError_t launch_sweep_msc(const LaunchCtx &c);
@@ -64,8 +66,6 @@ hipError_t launch_sweep_msc(const LaunchCtx &c);
 // c.sweep_cls), and the runs of `wide` one colour at a time.
 hipError_t launch_sweep_bytes(const LaunchCtx &c, const WideRun *wide, int n_wide, int max_N);
 // first: the measurement at i = 0 (the int8 layout has no words yet).
-hipError_t launch_clear_draws(const LaunchCtx &c);   // after a restore
-hipError_t prepare_fused_lds(size_t bytes);
 hipError_t launch_measure(const LaunchCtx &c, bool first);
 hipError_t launch_words(const LaunchCtx &c, int max_N);   // int8 layout: bytes -> words
 hipError_t launch_dos_sample(const LaunchCtx &c);   // theta = infinity draws (no-op without such runs)
