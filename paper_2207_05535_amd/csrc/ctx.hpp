@@ -19,10 +19,11 @@ enum Phase { PH_MEASURED = 0, PH_ANNEALED = 1, PH_RESAMPLED = 2, PH_SWEPT = 3 };
 // Offsets of buffers inside a device region (256-byte aligned).
 struct Planner {
     size_t off = 0;
+    static size_t lines(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
     size_t take(size_t bytes)
     {
         const size_t o = off;
-        off += (bytes + 255) & ~(size_t)255;
+        off += lines(bytes);
         return o;
     }
 };

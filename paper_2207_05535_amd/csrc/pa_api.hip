@@ -1391,12 +1391,16 @@ pa_status pa_restore(pa_ctx *c, const void *host_buf, size_t bytes)
     if (c->failed) return PA_ERR_DEVICE;
     CkptHeader h;
     std::memcpy(&h, host_buf, sizeof(h));
+    // the runs' records stand first; one build had them 8 bytes longer
+    const size_t rec = Planner::lines(sizeof(RunInfo) * c->n_runs);
+    const size_t longer = Planner::lines((sizeof(RunInfo) + 8) * c->n_runs) - rec;
+    const size_t skip = h.ws_used == c->lo.total ? 0 : longer;
     if (h.magic != CKPT_MAGIC || h.version != CKPT_VERSION || h.repr != (uint32_t)c->repr ||
-        h.ws_used != c->lo.total || h.n_runs != c->n_runs || h.desc_hash != descs_hash(c) ||
+        h.ws_used != c->lo.total + skip || h.n_runs != c->n_runs || h.desc_hash != descs_hash(c) ||
         bytes < sizeof(h) + h.ws_used)
         return PA_ERR_ARG;
-    PA_HIP(c, hipMemcpyAsync(c->ws, (const uint8_t *)host_buf + sizeof(h), c->lo.total, hipMemcpyHostToDevice,
-                             c->stream));
+    PA_HIP(c, hipMemcpyAsync(c->ws + rec, (const uint8_t *)host_buf + sizeof(h) + rec + skip, c->lo.total - rec,
+                             hipMemcpyHostToDevice, c->stream));
     // device records hold absolute pointers: rewrite them for this workspace
     PA_HIP(c, hipMemcpyAsync((void *)c->lc.runs, c->hinfo.data(), sizeof(RunInfo) * c->n_runs, hipMemcpyHostToDevice,
                              c->stream));

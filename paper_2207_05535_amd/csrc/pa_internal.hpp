@@ -72,9 +72,11 @@ struct RunInfo {
     // record of (population p, temperature i): obs[i * obs_stride + obs_off + p]
     int32_t obs_stride, obs_off;
     int32_t wang_lb;              // permutation pairing: log2 of the bucket capacity
-    int32_t exact_dos;            // 1: theta = infinity (energies drawn; theta is 0 here)
-    int32_t bytes;                // 1: int8 layout
-    int32_t fused;                // 1: resampled by one workgroup per population (k_resample_run)
+    // one word: the workspace's layout, which checkpoints hold, follows from
+    // the size of this record
+    uint32_t exact_dos : 1;       // theta = infinity (energies drawn; theta is 0 here)
+    uint32_t bytes : 1;           // int8 layout
+    uint32_t fused : 1;           // resampled by one workgroup per population (k_resample_run)
     // device pointers into the caller's workspace
     uint8_t *spins[MAX_POP][2];   // int8: [group][site][64] bytes; MSC: [group][site] u64
     int32_t *E[MAX_POP][2];       // energies [R_cap]
@@ -99,6 +101,7 @@ struct RunInfo {
     const uint64_t *tabT;         // [K][2]    Metropolis thresholds for dE = 4, 8
     const double *beta;           // [K]
 };
+static_assert(sizeof(RunInfo) == 400, "checkpoints of earlier builds");
 
 struct PopState {
     int32_t i;        // temperature index of the current population
@@ -115,6 +118,7 @@ struct PopState {
     int32_t EminAcc;
     int32_t done;     // workgroups counted in by the current launch (last_of)
 };
+static_assert(sizeof(PopState) == 176, "checkpoints of earlier builds");
 
 // Work counters of the sweep kernels (exact, for the ALU roofline):
 // word-site updates (64 replicas of one site), Philox calls, attempted flips.

@@ -184,3 +184,12 @@ def test_tuning_calls_validate_before_device():
     assert lib.pa_set_persistent(None, 1) == pa.PA_ERR_ARG
     assert lib.pa_get_tuning(None, 16, None, None, None, None, None) == pa.PA_ERR_ARG
     assert lib.pa_set_pooled(None, 1) == pa.PA_ERR_ARG
+
+
+@pytest.mark.parametrize("n,repr_,overlap,size", [
+    (1, "msc", 0, 38656), (7, "msc", 0, 124672), (7, "int8", 3, 252928), (40, "int8", 0, 1170432), (1000, "msc", 3, 18675456)])
+def test_workspace_layout_is_that_of_saved_checkpoints(n, repr_, overlap, size):
+    """A checkpoint is the workspace's bytes, and callers may size theirs once:
+    the sizes of contexts of few and many runs stay."""
+    runs = [W.run_desc(8, W.FM, seed=m, R=100 + m % 3, theta=3, K=7, overlap=overlap, qhist=m % 2) for m in range(n)]
+    assert _size(runs, repr_) == (0, size)

@@ -1072,3 +1072,33 @@ def test_where_populations_are_resampled_alone(resampling, caps):
     assert_obs_equal(obs[m, :1], orc.obs(), f"run {m}")
     assert_state_equal(ctx, orc, m, f"run {m}")
     ctx.close()
+
+
+@pytest.mark.parametrize("repr_", REPRS)
+def test_restore_of_longer_run_records(repr_):
+    """A checkpoint with run records 8 bytes longer, as one build wrote them,
+    restores like one of the present layout: the records, which hold addresses,
+    are the context's own, what follows them moves up."""
+    say(f"restore of longer run records {repr_}")
+    runs = [W.run_desc(8, W.FM, seed=W.RUN_SEED_BASE + 0x7F00 + m, R=300 + m, theta=1, K=6, beta_f=1.0) for m in range(40)]
+    ctx = pa.Context(runs, repr_)
+    ctx.run(1, 3)
+    ck = ctx.checkpoint()
+    ctx.run(3, 6)
+
+    def lines(n):
+        return (n + 255) & ~255
+    header = len(ck) - pa.pa_workspace_size(runs, repr_)
+    rec, longer = lines(400 * 40), lines(408 * 40) - lines(400 * 40)
+    assert longer > 0
+    old = np.concatenate([ck[:header], np.full(rec + longer, 0xAB, np.uint8), ck[header + rec:]])
+    old[16:24] = np.frombuffer(np.uint64(len(old) - header).tobytes(), np.uint8)   # the workspace's bytes
+    for buf in (ck, old):
+        other = pa.Context(runs, repr_)
+        other.restore(buf)
+        other.run(3, 6)
+        assert other.obs().tobytes() == ctx.obs().tobytes()
+        other.close()
+    with pytest.raises(pa.PAError):                 # cut short
+        ctx.restore(old[:-1])
+    ctx.close()
