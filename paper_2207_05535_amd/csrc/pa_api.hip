@@ -1411,7 +1411,7 @@ pa_status pa_restore(pa_ctx *c, const void *host_buf, size_t bytes)
     // checkpoint time; the launches use the current plan, so its list is
     // written again (the tuning may have changed since)
     const pa_status st = upload_sweep_plan(c);
-    if (st == PA_OK && c->any_multinomial) PA_HIP(c, launch_clear_draws(c->lc));
+    if (st == PA_OK && c->any_multinomial && c->lc.any_chained) PA_HIP(c, launch_clear_draws(c->lc));
     // between a step's sweeps and its measurement the int8 layout's words are
     // read next: a checkpoint that does not hold them has the bytes
     if (st == PA_OK && c->repr == PA_INT8 && c->phase == PH_SWEPT && c->lc.any_swept)
