@@ -72,11 +72,13 @@ struct RunInfo {
     // record of (population p, temperature i): obs[i * obs_stride + obs_off + p]
     int32_t obs_stride, obs_off;
     int32_t wang_lb;              // permutation pairing: log2 of the bucket capacity
-    // one word: the workspace's layout, which checkpoints hold, follows from
-    // the size of this record
-    uint32_t exact_dos : 1;       // theta = infinity (energies drawn; theta is 0 here)
-    uint32_t bytes : 1;           // int8 layout
-    uint32_t fused : 1;           // resampled by one workgroup per population (k_resample_run)
+    // flags in one word: the workspace's layout, which checkpoints hold, follows
+    // from the size of this record.  (Bytes, not bits of it: with the sweep
+    // kernels built from bits a step at L = 64, R = 1e5 took 559 us, not 550.)
+    uint8_t exact_dos;            // 1: theta = infinity (energies drawn; theta is 0 here)
+    uint8_t bytes;                // 1: int8 layout
+    uint8_t fused;                // 1: resampled by one workgroup per population (k_resample_run)
+    uint8_t pad;
     // device pointers into the caller's workspace
     uint8_t *spins[MAX_POP][2];   // int8: [group][site][64] bytes; MSC: [group][site] u64
     int32_t *E[MAX_POP][2];       // energies [R_cap]
