@@ -3021,7 +3021,7 @@ __global__ void __launch_bounds__(WANG_THREADS) k_wang_lds(const RunInfo *runs, 
                 const int end = hi + Rc;   // past every position once
                 int left = __popcll(same), base = 0;
                 while (left > 0 && u < end) {
-                    const int uu = u + lane, m = wang_candidate(uu, end, Rc);
+                    const int uu = u + lane, m = wang_candidate(uu, Rc);
                     const int fm = Lfpi[m];
                     const bool ok = uu < end && Lfam[m] != f && fm != f;
                     const uint64_t v = __ballot(ok);

@@ -250,11 +250,11 @@ __host__ __device__ inline size_t wang_lds_bytes(int R_cap)
     return R_cap > 65535 ? (size_t)1 << 30 : (a > b ? a : b);
 }
 // Position of the repair's candidate uu, counted on past the population's end
-// (Rc replicas; the search ends before `end` <= 2 Rc).  Lanes past the search's
-// end read position 0, which they do not use.
-__host__ __device__ inline int wang_candidate(int uu, int end, int Rc)
+// (Rc replicas).  The search ends before 2 Rc; lanes beyond that read position 0,
+// which they do not use.
+__host__ __device__ inline int wang_candidate(int uu, int Rc)
 {
-    return uu < end ? (uu >= Rc ? uu - Rc : uu) : 0;
+    return uu >= 2 * Rc ? 0 : (uu >= Rc ? uu - Rc : uu);
 }
 struct WangBufs {
     int32_t *pi, *sigma, *fampi, *members, *list, *cnt, *start, *hdr;

@@ -64,7 +64,7 @@ extern "C" int64_t wrong_candidates(int Rc)
     for (int hi = 1; hi <= Rc; ++hi)
         for (int u = hi; u < hi + Rc; ++u)
             for (int lane = 0; lane < 64; ++lane) {
-                const int m = wang_candidate(u + lane, hi + Rc, Rc);
+                const int m = wang_candidate(u + lane, Rc);
                 wrong += m < 0 || m >= Rc || (u + lane < hi + Rc && m != (u + lane) % Rc);
             }
     return wrong;
